@@ -147,8 +147,8 @@ int launch_fill_i32(int32_t *p, int64_t count, int32_t value, hipStream_t s);
 int launch_scan_i32_to_i32(const int32_t *in, int32_t *out, int64_t m, int64_t *bsum, hipStream_t s);
 // out[c] = sum over nb partial rows of part[b*8 + c], fixed order; then the
 // combination selected by `mode` (see md_reduce.hip).
-int launch_reduce_partials(const double *part1, int64_t nb1, const double *part2, int64_t nb2,
-                           double *out, int mode, double a0, double a1, hipStream_t s);
+int launch_reduce_partials(double *part1, int64_t nb1, double *part2, int64_t nb2, double *out, int mode, double a0,
+                           hipStream_t s);
 
 enum ReduceMode { kReduceLJ = 0, kReduceEAM = 1, kReduceKE = 2 };
 

@@ -654,7 +654,7 @@ int forces_lj_part(const md_box_t *box, int64_t n, const double *x, const uint32
         }
         MD_HIP_TRY(hipGetLastError());
     }
-    if (energy) return launch_reduce_partials(part, gb, nullptr, 0, ev, kReduceLJ, phi_rc, 0.0, s);
+    if (energy) return launch_reduce_partials(part, gb, nullptr, 0, ev, kReduceLJ, phi_rc, s);
     return MD_OK;
 }
 
@@ -705,7 +705,7 @@ static int forces_two_pass(const md_box_t *box, int64_t n, uint32_t *xs, const L
                                          whole(n));
         MD_HIP_TRY(hipGetLastError());
     }
-    if (energy) return launch_reduce_partials(part1, gb, part2, gb, ev, kReduceEAM, 0.0, 0.0, s);
+    if (energy) return launch_reduce_partials(part1, gb, part2, gb, ev, kReduceEAM, 0.0, s);
     return MD_OK;
 }
 

@@ -802,7 +802,7 @@ int dd_forces(md_dd_t *dd, double *ev, int32_t flags, void *stream, void *comm, 
         if (fl & MD_ENERGY) {
             const double s2 = dd->lj.sigma * dd->lj.sigma / (dd->lj.rc * dd->lj.rc), s6 = s2 * s2 * s2;
             return launch_reduce_partials(part1, rows1, nullptr, 0, ev, kReduceLJ, 4.0 * dd->lj.eps * (s6 * s6 - s6),
-                                          0.0, s);
+                                          s);
         }
         return MD_OK;
     }
@@ -823,7 +823,7 @@ int dd_forces(md_dd_t *dd, double *ev, int32_t flags, void *stream, void *comm, 
     if (int rc = phase(2, true)) return rc;
     MD_HIP_TRY(hipStreamWaitEvent(s, eF, 0));
     if (int rc = phase(2, false)) return rc;
-    if (fl & MD_ENERGY) return launch_reduce_partials(part1, rows1, part2, rows2, ev, kReduceEAM, 0.0, 0.0, s);
+    if (fl & MD_ENERGY) return launch_reduce_partials(part1, rows1, part2, rows2, ev, kReduceEAM, 0.0, s);
     return MD_OK;
 }
 

@@ -146,7 +146,7 @@ int integrate(int32_t phase, const md_box_t *box, int64_t n, double *x, double *
         }
         MD_HIP_TRY(hipGetLastError());
     }
-    if (ke) return launch_reduce_partials(part, n > 0 ? gb : 0, nullptr, 0, ke, kReduceKE, mass, 0.0, s);
+    if (ke) return launch_reduce_partials(part, n > 0 ? gb : 0, nullptr, 0, ke, kReduceKE, mass, s);
     return MD_OK;
 }
 

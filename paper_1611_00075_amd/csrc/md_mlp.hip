@@ -940,7 +940,7 @@ int forces_mlp(const md_box_t *box, int64_t n, const uint32_t *xs, int32_t cap, 
                                d4, f, part2);
         MD_HIP_TRY(hipGetLastError());
     }
-    if (energy) return launch_reduce_partials(part1, g1, part2, g2, ev, kReduceEAM, 0.0, 0.0, s);
+    if (energy) return launch_reduce_partials(part1, g1, part2, g2, ev, kReduceEAM, 0.0, s);
     return MD_OK;
 }
 

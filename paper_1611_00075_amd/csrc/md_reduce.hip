@@ -120,22 +120,41 @@ int launch_scan_i32_to_i32(const int32_t *in, int32_t *out, int64_t m, int64_t *
     return scan_impl<int32_t>(in, out, m, bsum, s);
 }
 
-// Fixed-order reduction of [nb][8] partial rows: thread t sums rows
-// t, t + kBlock, ... in order, then a fixed tree combines the threads.
-__device__ void reduce_rows(const double *part, int64_t nb, double (&acc)[8], double *lds)
+// Fixed-order sums of [rows][8] partials, `stride` rows apart.  Thread t adds
+// column t % 8 of rows t / 8, t / 8 + T / 8, ... (a wavefront reads 8 whole
+// rows at a time), then a fixed tree combines the T / 8 row classes; the
+// totals end in lds[0 .. 7].
+template <int T>
+__device__ __forceinline__ void reduce_rows(const double *part, int64_t rows, int64_t stride, double *lds /* T / 8 */)
 {
-    for (int c = 0; c < 8; ++c) acc[c] = 0.0;
-    for (int64_t b = threadIdx.x; b < nb; b += kBlock)
-        for (int c = 0; c < 8; ++c) acc[c] += part[b * 8 + c];
-    for (int c = 0; c < 8; ++c) lds[c * kBlock + threadIdx.x] = acc[c];
+    const int col = threadIdx.x % 8, lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    double s = 0.0;
+#pragma unroll 8
+    for (int64_t r = threadIdx.x / 8; r < rows; r += T / 8) s += part[r * stride * 8 + col];
+#pragma unroll
+    for (int o = 8; o < kWave; o <<= 1) s += __shfl_xor(s, o, kWave);
+    if (lane < 8) lds[wave * 8 + col] = s;
     __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w)
-            for (int c = 0; c < 8; ++c) lds[c * kBlock + threadIdx.x] += lds[c * kBlock + threadIdx.x + w];
-        __syncthreads();
+    if (threadIdx.x < 8) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < T / kWave; ++w) t += lds[w * 8 + col];
+        lds[col] = t;
     }
-    for (int c = 0; c < 8; ++c) acc[c] = lds[c * kBlock];
     __syncthreads();
+}
+
+// Rows [b C, (b + 1) C) of part1 (blockIdx.y = 0) or part2 (1) summed into
+// row b C, in place: the block has read its rows before it writes.
+__global__ __launch_bounds__(kBlock) void k_reduce_chunks(double *part1, int64_t nb1, double *part2, int64_t nb2,
+                                                          int64_t C)
+{
+    __shared__ double lds[kBlock / 8];
+    double *part = blockIdx.y ? part2 : part1;
+    const int64_t r0 = int64_t(blockIdx.x) * C, left = (blockIdx.y ? nb2 : nb1) - r0;
+    if (left <= 0) return;
+    reduce_rows<kBlock>(part + r0 * 8, left < C ? left : C, 1, lds);
+    if (threadIdx.x < 8) part[r0 * 8 + threadIdx.x] = lds[threadIdx.x];
 }
 
 // mode kReduceLJ : rows = [sum e, pair count, w0..w5] over a full list (every
@@ -143,14 +162,21 @@ __device__ void reduce_rows(const double *part, int64_t nb, double (&acc)[8], do
 // mode kReduceEAM: part1 rows = [E_embed, ...], part2 rows = [sum V, 0, w0..w5]
 //                  out = [E_embed + V/2, E_embed, w/2]
 // mode kReduceKE : rows = [sum v^2, ...]; out[0] = a0 * sum / 2 (a0 = mass)
-__global__ __launch_bounds__(kBlock) void k_reduce_partials(const double *part1, int64_t nb1, const double *part2,
-                                                            int64_t nb2, double *out, int mode, double a0, double a1)
+constexpr int kReduceBlock = 1024;
+// Rows (every C-th of nb) that one block sums itself: 2,048 rows are 16 loads
+// per thread, about one extra launch's time.
+constexpr int64_t kReduceDirect = 2048;
+constexpr int64_t kReduceBlocks = 1024;   // chunks at most above that
+
+__global__ __launch_bounds__(kReduceBlock) void k_reduce_partials(const double *part1, int64_t rows1,
+                                                                  const double *part2, int64_t rows2, int64_t stride,
+                                                                  double *out, int mode, double a0)
 {
-    __shared__ double lds[8 * kBlock];
-    double r1[8], r2[8];
-    reduce_rows(part1, nb1, r1, lds);
-    if (part2) reduce_rows(part2, nb2, r2, lds);
+    __shared__ double lds1[kReduceBlock / 8], lds2[kReduceBlock / 8];
+    reduce_rows<kReduceBlock>(part1, rows1, stride, lds1);
+    if (part2) reduce_rows<kReduceBlock>(part2, rows2, stride, lds2);
     if (threadIdx.x != 0) return;
+    const double *r1 = lds1, *r2 = lds2;
     if (mode == kReduceLJ) {
         out[0] = 0.5 * r1[0];
         out[1] = 0.5 * r1[0] - 0.5 * r1[1] * a0;
@@ -162,13 +188,25 @@ __global__ __launch_bounds__(kBlock) void k_reduce_partials(const double *part1,
     } else {
         out[0] = 0.5 * a0 * r1[0];
     }
-    (void)a1;
 }
 
-int launch_reduce_partials(const double *part1, int64_t nb1, const double *part2, int64_t nb2, double *out, int mode,
-                           double a0, double a1, hipStream_t s)
+// One block over all rows when they are few; otherwise chunks of C rows are
+// summed first, on all CUs (the partials of 4 M atoms are 2 x 125,000 rows,
+// 16 MB; half a million copper atoms: one block over 2 x 15,625 rows took
+// 48 us of the 163 us of an energy evaluation, two launches take 9.4 of 120).
+int launch_reduce_partials(double *part1, int64_t nb1, double *part2, int64_t nb2, double *out, int mode, double a0,
+                           hipStream_t s)
 {
-    hipLaunchKernelGGL(k_reduce_partials, dim3(1), dim3(kBlock), 0, s, part1, nb1, part2, nb2, out, mode, a0, a1);
+    const int64_t nb = nb1 > nb2 ? nb1 : nb2;
+    int64_t C = 1;
+    if (nb > kReduceDirect) {
+        C = (nb + kReduceBlocks - 1) / kReduceBlocks;
+        if (C < 64) C = 64;
+        hipLaunchKernelGGL(k_reduce_chunks, dim3(uint32_t((nb + C - 1) / C), part2 ? 2 : 1), dim3(kBlock), 0, s, part1,
+                           nb1, part2, nb2, C);
+    }
+    hipLaunchKernelGGL(k_reduce_partials, dim3(1), dim3(kReduceBlock), 0, s, part1, (nb1 + C - 1) / C, part2,
+                       (nb2 + C - 1) / C, C, out, mode, a0);
     MD_HIP_TRY(hipGetLastError());
     return MD_OK;
 }

@@ -395,7 +395,7 @@ int forces_tab(const md_box_t *box, int64_t n, uint32_t *xs, int32_t cap, const 
         else rc_ = energy ? (comp ? go(F{}, T{}, T{}) : go(F{}, T{}, F{})) : (comp ? go(F{}, F{}, T{}) : go(F{}, F{}, F{}));
         if (rc_ != MD_OK) return rc_;
     }
-    if (energy) return launch_reduce_partials(part1, g1, part2, g2, ev, kReduceEAM, 0.0, 0.0, s);
+    if (energy) return launch_reduce_partials(part1, g1, part2, g2, ev, kReduceEAM, 0.0, s);
     return MD_OK;
 }
 
