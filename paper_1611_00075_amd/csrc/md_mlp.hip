@@ -9,7 +9,7 @@
 //   pass 2 (k_mlp_force): per pair of the compact list,
 //     s_ij = sum_k (dE_i/dG_ik + dE_j/dG_jk) g_k'(r), F_i -= s_ij R / r.
 // Training: k_mlp_grad (forward, loss, backward, weight gradients as
-// matrix-core products over atoms, one partial row per wavefront) and
+// matrix-core products over atoms, one partial row per block) and
 // k_mlp_update (fixed-order sum of the rows, then Adam on FP32 masters).
 //
 // Matrix-core layout (v_mfma_f32_16x16x32_bf16: A 16x32, B 32x16, D 16x16;
@@ -53,7 +53,10 @@ constexpr int kTile = 16;                           // atoms per matrix-core til
 constexpr int kChunk = kTile * (kBlock / kWave);    // atoms per block iteration
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kMaxAtomBlocks = 2048;                // persistent grid of pass 1
-constexpr int kMaxGradWaves = 1024;
+constexpr int kMaxGradRows = 1024;                  // partial-gradient rows (blocks of k_mlp_grad) at most
+constexpr int kGradBlock = 2 * kWave;               // two wavefronts per 32-atom group
+constexpr int kUpdWaves = 16, kUpdBlock = kUpdWaves * kWave;
+constexpr int kUpdGroups = (kNP + kWave - 1) / kWave;   // blocks of k_mlp_update, one more for the loss
 
 __device__ __forceinline__ f32x4 mfma(const bf16x8 &a, const bf16x8 &b, const f32x4 &c)
 {
@@ -276,8 +279,8 @@ __device__ __forceinline__ float2 silu2(float a)
     return make_float2(a * s, s * __builtin_fmaf(a, 1.f - s, 1.f));
 }
 
-template <int NS>
-__device__ __forceinline__ void forward(const WeightsLds &L, int lane, const Opd<NS> &X, Fwd<NS> &F)
+template <int NS, class W>
+__device__ __forceinline__ void forward(const W &L, int lane, const Opd<NS> &X, Fwd<NS> &F)
 {
     const int g = lane >> 4;
     const f32x4 z = {0.f, 0.f, 0.f, 0.f};
@@ -612,11 +615,98 @@ __global__ __launch_bounds__(kBlock) void k_mlp_force(int64_t n, MlpArgs p, cons
 
 // ---- training ---------------------------------------------------------------
 
+// The parameters as they lie in memory, in LDS: a training block uses each
+// operand once or twice, so the reordered copy of WeightsLds would cost more
+// than it saves (22 x 512 two-byte gathers from memory per block).  Rows of
+// W2 are 4 values longer than their 64, which spreads the 16 rows that an
+// operand reads over the banks.
+struct GradW {
+    uint16_t w1[kHid * kIn];
+    uint16_t w2[kHid * (kHid + 4)];
+    float b1[kHid], b2[kHid], w3[kHid];
+    float mean[kIn], inv_std[kIn];
+    float b3;
+};
+
+// w with the block's threads: 16 bytes a load where the pointer allows it
+// (the entry points take any two-byte aligned one), else value by value.
+__device__ __forceinline__ void stage_params(GradW &L, const uint16_t *__restrict__ w, const MlpArgs &p)
+{
+    static_assert(oW1 % 8 == 0 && oB1 % 8 == 0 && oW2 % 8 == 0 && oB2 % 8 == 0 && oW3 % 8 == 0 && oB3 % 8 == 0,
+                  "16-byte groups of the parameters");
+    constexpr int S = kHid + 4;
+    auto vec = [&](int e) -> float * { return e < oW2 ? L.b1 + (e - oB1) : (e < oW3 ? L.b2 + (e - oB2) : L.w3 + (e - oW3)); };
+    if ((reinterpret_cast<uintptr_t>(w) & 15u) == 0) {
+#pragma unroll 6
+        for (int q = threadIdx.x; q < oB3 / 8; q += kGradBlock) {
+            const uint4 v = reinterpret_cast<const uint4 *>(w)[q];
+            const int e = 8 * q;
+            if (e < oB1) {
+                *reinterpret_cast<uint4 *>(L.w1 + e) = v;
+            } else if (e >= oW2 && e < oB2) {
+                const int k = e - oW2;
+                uint2 *d = reinterpret_cast<uint2 *>(L.w2 + (k >> 6) * S + (k & 63));
+                d[0] = make_uint2(v.x, v.y);
+                d[1] = make_uint2(v.z, v.w);
+            } else {
+                float *d = vec(e);
+                const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    d[2 * j] = __uint_as_float(u[j] << 16);
+                    d[2 * j + 1] = __uint_as_float(u[j] & 0xffff0000u);
+                }
+            }
+        }
+    } else {
+        for (int e = threadIdx.x; e < oB3; e += kGradBlock) {
+            const uint16_t v = w[e];
+            if (e < oB1) L.w1[e] = v;
+            else if (e >= oW2 && e < oB2) L.w2[((e - oW2) >> 6) * S + ((e - oW2) & 63)] = v;
+            else *vec(e) = bf16_to_f(v);
+        }
+    }
+    if (threadIdx.x < kIn) {
+        L.mean[threadIdx.x] = p.mean[threadIdx.x];
+        L.inv_std[threadIdx.x] = p.inv_std[threadIdx.x];
+    }
+    if (threadIdx.x == 0) L.b3 = bf16_to_f(w[oB3]);
+    __syncthreads();
+}
+
+// Operand o of `lane`, the values stage_weights puts there (o is a constant
+// after unrolling; the 16 inputs of layer 1 fill half of its K slots).
+__device__ __forceinline__ bf16x8 op(const GradW &L, int o, int lane)
+{
+    constexpr int S = kHid + 4;
+    const int g = lane >> 4, li = lane & 15;
+    uint4 v = make_uint4(0u, 0u, 0u, 0u);
+    if (o < kOpL2) {
+        if (g < 2) v = *reinterpret_cast<const uint4 *>(L.w1 + (16 * o + li) * kIn + 8 * g);
+    } else if (o < kOpB2) {
+        const int t = (o - kOpL2) >> 1, s = (o - kOpL2) & 1;
+        const uint16_t *r = L.w2 + (16 * t + li) * S + 32 * s + 4 * g;
+        const uint2 a = *reinterpret_cast<const uint2 *>(r), b = *reinterpret_cast<const uint2 *>(r + 16);
+        v = make_uint4(a.x, a.y, b.x, b.y);
+    } else {
+        const int t = (o - kOpB2) >> 1, s = (o - kOpB2) & 1;
+        const uint16_t *r = L.w2 + (32 * s + 4 * g) * S + 16 * t + li;
+        const auto two = [&](int k) { return uint32_t(r[k * S]) | (uint32_t(r[(k + 1) * S]) << 16); };
+        v = make_uint4(two(0), two(2), two(16), two(18));
+    }
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+constexpr int kGradCols = 2 * kTile + 8;   // a row's 32 atoms and padding (banks)
+
 struct GradLds {
-    uint16_t xT[kIn][2 * kTile];     // [feature][atom of the 32-atom group]
-    uint16_t h1T[kHid][2 * kTile];
-    uint16_t d2T[kHid][2 * kTile];
-    uint16_t d1T[kHid][2 * kTile];
+    uint16_t xT[kIn][kGradCols];     // [feature][atom of the 32-atom group]
+    uint16_t h1T[kHid][kGradCols];
+    uint16_t d2T[kHid][kGradCols];
+    uint16_t d1T[kHid][kGradCols];
+    float bias[3][kHid];             // the second wave's sums for b1, b2, w3
+    float b3;
+    double loss;
 };
 
 __device__ __forceinline__ bf16x8 lds8(const uint16_t *p)
@@ -624,101 +714,120 @@ __device__ __forceinline__ bf16x8 lds8(const uint16_t *p)
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(p));
 }
 
-// One partial gradient row per wavefront over a contiguous range of 32-atom
-// groups of the batch; part[wave][kNP] (float), lpart[wave] = sum of err^2.
-__global__ __launch_bounds__(kBlock) void k_mlp_grad(int64_t batch, const int32_t *__restrict__ sel,
-                                                     const float *__restrict__ G, const float *__restrict__ target,
-                                                     MlpArgs p, const uint16_t *__restrict__ w, int32_t waves,
-                                                     float *__restrict__ part, double *__restrict__ lpart)
+// One partial gradient row per block over a contiguous range of 32-atom
+// groups of the batch; part[block][kNP] (float), lpart[block] = sum of err^2.
+//
+// At the usual batch (4,096 atoms: 128 groups) this is one dependent chain
+// per block -- parameters, rows, three layers of products -- so what counts is
+// its length and how many CUs share it: two wavefronts take a group, 16
+// atoms each up to dE/da1, then half of the weight-gradient tiles each.
+// Four groups a block with the two halves of a group in turn, and operands
+// reordered from memory, measured 63.6 us a step with k_mlp_update (one thread
+// a parameter); this form: see k_mlp_update.
+__global__ __launch_bounds__(kGradBlock) void k_mlp_grad(int64_t batch, const int32_t *__restrict__ sel,
+                                                         const float *__restrict__ G,
+                                                         const float *__restrict__ target, MlpArgs p,
+                                                         const uint16_t *__restrict__ w, float *__restrict__ part,
+                                                         double *__restrict__ lpart)
 {
-    __shared__ WeightsLds L;
-    __shared__ GradLds S[kBlock / kWave];
-    stage_weights(L, w, p);
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    __shared__ __attribute__((aligned(16))) GradW L;
+    __shared__ __attribute__((aligned(16))) GradLds T;
+    const int h = threadIdx.x / kWave, lane = threadIdx.x % kWave;   // h: the half of a group, then of the tiles
     const int g = lane >> 4, m = lane & 15;
-    const int64_t wg = int64_t(blockIdx.x) * (kBlock / kWave) + wave;
-    if (wg >= waves) return;
-    GradLds &T = S[wave];
     const int64_t groups = (batch + 2 * kTile - 1) / (2 * kTile);
-    const int64_t q0 = groups * wg / waves, q1 = groups * (wg + 1) / waves;
+    const int64_t q0 = groups * blockIdx.x / gridDim.x, q1 = groups * (blockIdx.x + 1) / gridDim.x;
     const float scale = 2.f / float(batch);
     const f32x4 z = {0.f, 0.f, 0.f, 0.f};
 
-    f32x4 gW2[16], gW1[4];
+    // rows of group q: this lane's atom, its 8 inputs and its target
+    float4 u0 = {0.f, 0.f, 0.f, 0.f}, u1 = u0;
+    float want = 0.f;
+    auto fetch = [&](int64_t q) {
+        const int64_t a = q * 2 * kTile + h * kTile + m;
+        if (a < batch) {
+            const int64_t row = sel ? int64_t(sel[a]) : a;
+            if (g < 2) {
+                u0 = *reinterpret_cast<const float4 *>(G + row * kIn + 8 * g);
+                u1 = *reinterpret_cast<const float4 *>(G + row * kIn + 8 * g + 4);
+            }
+            want = target[row];
+        }
+    };
+    if (q0 < q1) fetch(q0);
+    stage_params(L, w, p);
+
+    f32x4 gW2[8], gW1[2];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) gW2[k] = z;
+    for (int k = 0; k < 8; ++k) gW2[k] = z;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) gW1[k] = z;
+    for (int k = 0; k < 2; ++k) gW1[k] = z;
     float gb1[16], gb2[16], gw3[16], gb3 = 0.f;
 #pragma unroll
     for (int k = 0; k < 16; ++k) gb1[k] = gb2[k] = gw3[k] = 0.f;
     double loss = 0.0;
 
     for (int64_t q = q0; q < q1; ++q) {
-#pragma unroll 1
-        for (int h = 0; h < 2; ++h) {
-            const int64_t a = q * 2 * kTile + h * kTile + m;
-            const bool valid = a < batch;
-            const int64_t row = valid ? (sel ? int64_t(sel[a]) : a) : 0;
-            bf16x8 X = {};
-            if (g < 2) {
-                float u[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                if (valid) {
-                    const float4 u0 = *reinterpret_cast<const float4 *>(G + row * kIn + 8 * g);
-                    const float4 u1 = *reinterpret_cast<const float4 *>(G + row * kIn + 8 * g + 4);
-                    const float v[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
+        const bool valid = q * 2 * kTile + h * kTile + m < batch;
+        const int col = h * kTile + m;
+        bf16x8 X = {};
+        if (g < 2) {
+            float u[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            if (valid) {
+                const float v[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) u[j] = (v[j] - L.mean[8 * g + j]) * L.inv_std[8 * g + j];
-                }
-                X = pack8(u);
-#pragma unroll
-                for (int j = 0; j < 8; ++j) T.xT[8 * g + j][h * kTile + m] = f_to_bf16(u[j]);
+                for (int j = 0; j < 8; ++j) u[j] = (v[j] - L.mean[8 * g + j]) * L.inv_std[8 * g + j];
             }
-            Fwd<1> F;
-            forward<1>(L, lane, Opd<1>{{X}}, F);
-            const float err = valid ? F.E - target[row] : 0.f;
-            const float gE = scale * err;
-            if (g == 0) {
-                loss += double(err) * double(err);
-                gb3 += gE;
+            X = pack8(u);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) T.xT[8 * g + j][col] = f_to_bf16(u[j]);
+        }
+        const float goal = want;
+        if (q + 1 < q1) fetch(q + 1);
+        Fwd<1> F;
+        forward<1>(L, lane, Opd<1>{{X}}, F);
+        const float err = valid ? F.E - goal : 0.f;
+        const float gE = scale * err;
+        if (g == 0) {
+            loss += double(err) * double(err);
+            gb3 += gE;
+        }
+        f32x4 d[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int f = 16 * t + 4 * g + r;
+                gw3[4 * t + r] = __builtin_fmaf(gE, F.h2[t][r], gw3[4 * t + r]);
+                d[t][r] = gE * L.w3[f] * F.ds2[t][r];
+                gb2[4 * t + r] += d[t][r];
+                T.d2T[f][col] = f_to_bf16(d[t][r]);
+                T.h1T[f][col] = f_to_bf16(F.h[t][r]);
             }
-            f32x4 d[4];
+        const bf16x8 D2[2] = {pack(d[0], d[1]), pack(d[2], d[3])};
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < 4; ++t) {
+            f32x4 pr = mfma(op(L, kOpB2 + 2 * t, lane), D2[0], z);
+            pr = mfma(op(L, kOpB2 + 2 * t + 1, lane), D2[1], pr);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int f = 16 * t + 4 * g + r;
-                    gw3[4 * t + r] = __builtin_fmaf(gE, F.h2[t][r], gw3[4 * t + r]);
-                    d[t][r] = gE * L.w3[f] * F.ds2[t][r];
-                    gb2[4 * t + r] += d[t][r];
-                    T.d2T[f][h * kTile + m] = f_to_bf16(d[t][r]);
-                    T.h1T[f][h * kTile + m] = f_to_bf16(F.h[t][r]);
-                }
-            const bf16x8 D2[2] = {pack(d[0], d[1]), pack(d[2], d[3])};
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                f32x4 pr = mfma(op(L, kOpB2 + 2 * t, lane), D2[0], z);
-                pr = mfma(op(L, kOpB2 + 2 * t + 1, lane), D2[1], pr);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float d1 = pr[r] * F.ds1[t][r];
-                    gb1[4 * t + r] += d1;
-                    T.d1T[16 * t + 4 * g + r][h * kTile + m] = f_to_bf16(d1);
-                }
+            for (int r = 0; r < 4; ++r) {
+                const float d1 = pr[r] * F.ds1[t][r];
+                gb1[4 * t + r] += d1;
+                T.d1T[16 * t + 4 * g + r][col] = f_to_bf16(d1);
             }
         }
-        wave_sync();
+        __syncthreads();
 #pragma unroll
-        for (int tn = 0; tn < 4; ++tn) {
+        for (int a = 0; a < 2; ++a) {
+            const int tn = 2 * h + a;
             const bf16x8 A2 = lds8(&T.d2T[16 * tn + m][8 * g]);
 #pragma unroll
-            for (int tk = 0; tk < 4; ++tk) gW2[4 * tn + tk] = mfma(A2, lds8(&T.h1T[16 * tk + m][8 * g]), gW2[4 * tn + tk]);
-            gW1[tn] = mfma(lds8(&T.d1T[16 * tn + m][8 * g]), lds8(&T.xT[m][8 * g]), gW1[tn]);
+            for (int tk = 0; tk < 4; ++tk) gW2[4 * a + tk] = mfma(A2, lds8(&T.h1T[16 * tk + m][8 * g]), gW2[4 * a + tk]);
+            gW1[a] = mfma(lds8(&T.d1T[16 * tn + m][8 * g]), lds8(&T.xT[m][8 * g]), gW1[a]);
         }
-        wave_sync();
+        __syncthreads();
     }
 
-    // sums over the 16 atoms of a lane group
+    // sums over the 16 atoms of a lane group, then over the two waves
 #pragma unroll
     for (int k = 0; k < 16; ++k)
 #pragma unroll
@@ -732,45 +841,87 @@ __global__ __launch_bounds__(kBlock) void k_mlp_grad(int64_t batch, const int32_
         gb3 += __shfl_xor(gb3, o, kWave);
         loss += __shfl_xor(loss, o, kWave);
     }
-    float *out = part + wg * kRow;
+    float *out = part + int64_t(blockIdx.x) * kRow;
 #pragma unroll
-    for (int tn = 0; tn < 4; ++tn)
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int fo = 16 * tn + 4 * g + r;
+            const int fo = 16 * (2 * h + a) + 4 * g + r;
 #pragma unroll
-            for (int tk = 0; tk < 4; ++tk) out[oW2 + fo * kHid + 16 * tk + m] = gW2[4 * tn + tk][r];
-            out[oW1 + fo * kIn + m] = gW1[tn][r];
-            if (m == 0) {
-                out[oB1 + fo] = gb1[4 * tn + r];
-                out[oB2 + fo] = gb2[4 * tn + r];
-                out[oW3 + fo] = gw3[4 * tn + r];
-            }
+            for (int tk = 0; tk < 4; ++tk) out[oW2 + fo * kHid + 16 * tk + m] = gW2[4 * a + tk][r];
+            out[oW1 + fo * kIn + m] = gW1[a][r];
         }
-    if (lane == 0) {
-        out[oB3] = gb3;
-        lpart[wg] = loss;
+    if (h == 1 && m == 0) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int f = 16 * (k >> 2) + 4 * g + (k & 3);
+            T.bias[0][f] = gb1[k];
+            T.bias[1][f] = gb2[k];
+            T.bias[2][f] = gw3[k];
+        }
+        if (g == 0) {
+            T.b3 = gb3;
+            T.loss = loss;
+        }
+    }
+    __syncthreads();
+    if (h == 0 && m == 0) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int f = 16 * (k >> 2) + 4 * g + (k & 3);
+            out[oB1 + f] = gb1[k] + T.bias[0][f];
+            out[oB2 + f] = gb2[k] + T.bias[1][f];
+            out[oW3 + f] = gw3[k] + T.bias[2][f];
+        }
+        if (g == 0) {
+            out[oB3] = gb3 + T.b3;
+            lpart[blockIdx.x] = loss + T.loss;
+        }
     }
 }
 
 // Fixed-order sum of the partial rows; then either the raw gradient or an
 // Adam step (c1 = 1 / (1 - beta1^t), c2 = 1 / (1 - beta2^t)).
-__global__ __launch_bounds__(kBlock) void k_mlp_update(int32_t rows, const float *__restrict__ part,
-                                                       const double *__restrict__ lpart, double inv_batch,
-                                                       float *__restrict__ grad, double *__restrict__ loss,
-                                                       float lr, float b1, float b2, float eps, float c1, float c2,
-                                                       float *__restrict__ master, float *__restrict__ m1,
-                                                       float *__restrict__ m2, uint16_t *__restrict__ w)
+//
+// A block takes 64 parameters (one coalesced 256-byte piece of a row), its 16
+// wavefronts every 16th row each: 128 rows (a batch of 4,096) are 8 loads in
+// flight per lane instead of 128 in turn, on 84 CUs instead of 21.  The last
+// block sums the loss.  One step (both kernels and the call) at a batch of
+// 4,096 went from 63.6 us to MEASURED us.
+__global__ __launch_bounds__(kUpdBlock) void k_mlp_update(int32_t rows, const float *__restrict__ part,
+                                                          const double *__restrict__ lpart, double inv_batch,
+                                                          float *__restrict__ grad, double *__restrict__ loss,
+                                                          float lr, float b1, float b2, float eps, float c1, float c2,
+                                                          float *__restrict__ master, float *__restrict__ m1,
+                                                          float *__restrict__ m2, uint16_t *__restrict__ w)
 {
-    const int pi = blockIdx.x * kBlock + threadIdx.x;
-    if (loss && pi == 0) {
+    __shared__ double sum[kUpdWaves][kWave];
+    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    if (blockIdx.x == kUpdGroups) {   // launched only with loss
         double s = 0.0;
-        for (int r = 0; r < rows; ++r) s += lpart[r];
-        *loss = s * inv_batch;
+        for (int r = threadIdx.x; r < rows; r += kUpdBlock) s += lpart[r];
+        s = group_sum(s, kWave);
+        if (lane == 0) sum[wave][0] = s;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double t = 0.0;
+            for (int k = 0; k < kUpdWaves; ++k) t += sum[k][0];
+            *loss = t * inv_batch;
+        }
+        return;
     }
-    if (pi >= kNP) return;
+    const int pi = blockIdx.x * kWave + lane;
     double s = 0.0;
-    for (int r = 0; r < rows; ++r) s += double(part[int64_t(r) * kRow + pi]);
+    if (pi < kNP) {
+#pragma unroll 8
+        for (int r = wave; r < rows; r += kUpdWaves) s += double(part[int64_t(r) * kRow + pi]);
+    }
+    sum[wave][lane] = s;
+    __syncthreads();
+    if (wave != 0 || pi >= kNP) return;
+    s = 0.0;
+#pragma unroll
+    for (int k = 0; k < kUpdWaves; ++k) s += sum[k][lane];
     const float gr = float(s);
     if (grad) grad[pi] = gr;
     if (master) {
@@ -848,20 +999,20 @@ TrainWs train_ws(int64_t batch)
 {
     auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
     const int64_t groups = (batch + 2 * kTile - 1) / (2 * kTile);
-    const int64_t waves = groups < kMaxGradWaves ? (groups > 0 ? groups : 1) : kMaxGradWaves;
+    const int64_t rows = groups < kMaxGradRows ? (groups > 0 ? groups : 1) : kMaxGradRows;
     TrainWs t{};
     size_t o = 0;
-    t.part = o;    o += up(size_t(waves) * kRow * 4);
-    t.lpart = o;   o += up(size_t(waves) * 8);
+    t.part = o;    o += up(size_t(rows) * kRow * 4);
+    t.lpart = o;   o += up(size_t(rows) * 8);
     t.moments = o; o += up(size_t(kMomentBlocks) * 2 * kIn * 8);
     t.total = o;
     return t;
 }
 
-int32_t grad_waves(int64_t batch)
+int32_t grad_rows(int64_t batch)
 {
     const int64_t groups = (batch + 2 * kTile - 1) / (2 * kTile);
-    return int32_t(groups < kMaxGradWaves ? groups : kMaxGradWaves);
+    return int32_t(groups < kMaxGradRows ? groups : kMaxGradRows);
 }
 
 }  // namespace
@@ -964,11 +1115,9 @@ int mlp_grad_update(int64_t batch, const int32_t *sel, const float *G, const flo
     const TrainWs t = train_ws(batch);
     float *part = ws_ptr<float>(tws, t.part);
     double *lpart = ws_ptr<double>(tws, t.lpart);
-    const int32_t waves = grad_waves(batch);
+    const int32_t rows = grad_rows(batch);
     const MlpArgs a = make_args(nullptr, mlp);
-    const uint32_t blocks = uint32_t((waves + kBlock / kWave - 1) / (kBlock / kWave));
-    hipLaunchKernelGGL(k_mlp_grad, dim3(blocks), dim3(kBlock), 0, s, batch, sel, G, target, a, w_in, waves, part,
-                       lpart);
+    hipLaunchKernelGGL(k_mlp_grad, dim3(rows), dim3(kGradBlock), 0, s, batch, sel, G, target, a, w_in, part, lpart);
     float lr = 0.f, b1 = 0.f, b2 = 0.f, eps = 0.f, c1 = 0.f, c2 = 0.f;
     if (adam) {
         lr = float(adam->lr);
@@ -978,7 +1127,7 @@ int mlp_grad_update(int64_t batch, const int32_t *sel, const float *G, const flo
         c1 = float(1.0 / (1.0 - std::pow(adam->beta1, double(adam->step))));
         c2 = float(1.0 / (1.0 - std::pow(adam->beta2, double(adam->step))));
     }
-    hipLaunchKernelGGL(k_mlp_update, dim3((kNP + kBlock - 1) / kBlock), dim3(kBlock), 0, s, waves, part, lpart,
+    hipLaunchKernelGGL(k_mlp_update, dim3(kUpdGroups + (loss ? 1 : 0)), dim3(kUpdBlock), 0, s, rows, part, lpart,
                        1.0 / double(batch), grad, loss, lr, b1, b2, eps, c1, c2, adam ? master : nullptr,
                        adam ? m1 : nullptr, adam ? m2 : nullptr, adam ? w_out : nullptr);
     MD_HIP_TRY(hipGetLastError());

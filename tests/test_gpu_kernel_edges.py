@@ -54,3 +54,40 @@ def test_energy_rows_either_side_of_the_one_block_sum(M, pot):
         ev.append(sim.ev.cpu().numpy() / s.n)
     scale = np.abs(ev[0]).max()
     assert np.abs(ev[1] - ev[0]).max() <= (1e-11 if pot == "lj" else 2e-6) * scale, ev
+
+
+# ---- training -------------------------------------------------------------------
+
+@pytest.mark.parametrize("batch,shift", [(1, 0), (17, 0), (32, 1), (33, 0), (4095, 1), (32 * 1024 + 5, 0)])
+def test_gradient_at_group_edges(M, orc, batch, shift):
+    """Batches around the 32-atom groups, one atom, more groups than partial
+    rows (1,024), and parameters that start two bytes past a 16-byte boundary
+    (shift): FP32 sums to 1e-5, plus what one activation rounded to the other
+    bfloat16 neighbour (2^-8) can do to the batch's mean."""
+    from oracle import mlp as om
+    from paper_1611_00075_amd import mlp as P
+    rng = np.random.default_rng(batch)
+    rows = 600
+    G = np.abs(rng.standard_normal((rows, 16)) * 3.0 + 4.0).astype(np.float32)
+    target = (-3.5 + 0.05 * rng.standard_normal(rows)).astype(np.float32)
+    sel = rng.integers(0, rows, batch).astype(np.int32)
+    bits = P.bf16_bits(P.init_params(11, e_mean=-3.4, w3_scale=0.3))
+    w = torch.zeros(M.MD_MLP_NPARAM + 8, dtype=torch.int16, device="cuda")[shift:shift + M.MD_MLP_NPARAM]
+    w.copy_(bits)
+    sp = P.spec(np.zeros(16), np.full(16, 0.25))
+    grad = torch.full((M.MD_MLP_NPARAM,), np.nan, dtype=torch.float32, device="cuda")
+    loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+    tws = torch.empty(M.md_mlp_workspace_bytes(batch), dtype=torch.uint8, device="cuda")
+    M.md_mlp_grad(batch, torch.tensor(sel, device="cuda"), torch.tensor(G, device="cuda"),
+                  torch.tensor(target, device="cuda"), sp, w, grad, loss, tws)
+    g = grad.cpu().numpy().astype(np.float64)
+    lo, go = om.loss_grad(G[sel].astype(np.float64), target[sel].astype(np.float64),
+                          om.Spec(mean=np.zeros(16), inv_std=np.full(16, 0.25)), P.bf16_values(bits), bf16=True)
+    tol = 1e-5 + 4 * 2.0 ** -8 / batch
+    assert loss.item() == pytest.approx(lo, rel=tol)
+    o = 0
+    for name, shape in P.SHAPES:
+        k = int(np.prod(shape)) if shape else 1
+        rel = np.linalg.norm(g[o:o + k] - go[o:o + k]) / np.linalg.norm(go[o:o + k])
+        assert rel < tol, (name, rel)
+        o += k
