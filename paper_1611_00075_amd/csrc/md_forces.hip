@@ -136,7 +136,12 @@ __device__ __forceinline__ double minimg64(double d, double L, double hL)
     return d;
 }
 
-template <int TPA, bool ENERGY>
+// U entries and then their U positions are loaded before any is used: one
+// entry at a time, a row of 70 was nine pairs of dependent loads per lane, and
+// at 4,000 atoms (500 waves, half of one per SIMD) their latency was the
+// launch: 11.4 us; five at a time 7.8 us.  Same pairs in the same order: the sums
+// are bit for bit the same.
+template <int TPA, int U, bool ENERGY>
 __global__ __launch_bounds__(kBlock) void k_lj64(int64_t n, const double *__restrict__ x,
                                                  int32_t cap, const int32_t *__restrict__ idx,
                                                  const int32_t *__restrict__ count, LJ64 p, double *__restrict__ f,
@@ -154,25 +159,35 @@ __global__ __launch_bounds__(kBlock) void k_lj64(int64_t n, const double *__rest
         const double xi = x[i], yi = x[n + i], zi = x[2 * n + i];
         const int32_t cnt = min(count[i], cap);
         const int32_t *row = ell_row(idx, i, cap);
-        for (int32_t k = sub; k < cnt; k += TPA) {
-            const int64_t j = row[ell_pos(k)];
-            // displacement i -> j as in the plain definition, then R = -d
-            const double dx = minimg64(x[j] - xi, p.L[0], p.hL[0]);
-            const double dy = minimg64(x[n + j] - yi, p.L[1], p.hL[1]);
-            const double dz = minimg64(x[2 * n + j] - zi, p.L[2], p.hL[2]);
-            const double r2 = (dx * dx + dy * dy) + dz * dz;
-            if (r2 < p.rc2) {
-                const double s2 = p.sig2 / r2;
-                const double s6 = s2 * s2 * s2;
-                const double fs = p.eps24 * (2.0 * s6 * s6 - s6) / r2;
-                fx -= fs * dx;
-                fy -= fs * dy;
-                fz -= fs * dz;
-                if (ENERGY) {
-                    e += p.eps4 * (s6 * s6 - s6);
-                    np += 1.0;
-                    w[0] += fs * dx * dx; w[1] += fs * dy * dy; w[2] += fs * dz * dz;
-                    w[3] += fs * dx * dy; w[4] += fs * dx * dz; w[5] += fs * dy * dz;
+        for (int32_t k0 = sub; k0 < cnt; k0 += U * TPA) {
+            int64_t j[U];
+            double xj[U][3];
+#pragma unroll
+            for (int u = 0; u < U; ++u) j[u] = k0 + u * TPA < cnt ? row[ell_pos(k0 + u * TPA)] : i;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int a = 0; a < 3; ++a) xj[u][a] = x[a * n + j[u]];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                // displacement i -> j as in the plain definition, then R = -d
+                const double dx = minimg64(xj[u][0] - xi, p.L[0], p.hL[0]);
+                const double dy = minimg64(xj[u][1] - yi, p.L[1], p.hL[1]);
+                const double dz = minimg64(xj[u][2] - zi, p.L[2], p.hL[2]);
+                const double r2 = (dx * dx + dy * dy) + dz * dz;
+                if (r2 < p.rc2 && k0 + u * TPA < cnt) {
+                    const double s2 = p.sig2 / r2;
+                    const double s6 = s2 * s2 * s2;
+                    const double fs = p.eps24 * (2.0 * s6 * s6 - s6) / r2;
+                    fx -= fs * dx;
+                    fy -= fs * dy;
+                    fz -= fs * dz;
+                    if (ENERGY) {
+                        e += p.eps4 * (s6 * s6 - s6);
+                        np += 1.0;
+                        w[0] += fs * dx * dx; w[1] += fs * dy * dy; w[2] += fs * dz * dz;
+                        w[3] += fs * dx * dy; w[4] += fs * dx * dz; w[5] += fs * dy * dz;
+                    }
                 }
             }
         }
@@ -546,6 +561,7 @@ __global__ __launch_bounds__(kBlock) void k_eam_force(int64_t n, const uint4 *__
 // ---------------------------------------------------------------------------
 constexpr int kTPA = kSlice;   // lanes per atom of the FP32 kernels
 constexpr int kUnroll = 4;     // row entries per lane per batch (embedded-atom passes)
+constexpr int kUnroll64 = 5;   // FP64 LJ: rows of ~70 entries take two batches
 constexpr int kUnrollLJ = 6;   // LJ: rows of ~70 entries take two batches (measured best of 2-12)
 
 static uint32_t blocks_for(int64_t n, int tpa) { return uint32_t((n * tpa + kBlock - 1) / kBlock); }
@@ -636,10 +652,10 @@ int forces_lj_part(const md_box_t *box, int64_t n, const double *x, const uint32
             p.gate = gate;
             double *fd = static_cast<double *>(f);
             if (energy)
-                hipLaunchKernelGGL((k_lj64<kTPA, true>), dim3(gb), dim3(kBlock), 0, s, n, x, cap, idx, cnt, p, fd,
+                hipLaunchKernelGGL((k_lj64<kTPA, kUnroll64, true>), dim3(gb), dim3(kBlock), 0, s, n, x, cap, idx, cnt, p, fd,
                                    part);
             else
-                hipLaunchKernelGGL((k_lj64<kTPA, false>), dim3(gb), dim3(kBlock), 0, s, n, x, cap, idx, cnt, p, fd,
+                hipLaunchKernelGGL((k_lj64<kTPA, kUnroll64, false>), dim3(gb), dim3(kBlock), 0, s, n, x, cap, idx, cnt, p, fd,
                                    part);
         } else {
             const bool cubic = is_cubic(box);

@@ -91,3 +91,23 @@ def test_gradient_at_group_edges(M, orc, batch, shift):
         rel = np.linalg.norm(g[o:o + k] - go[o:o + k]) / np.linalg.norm(go[o:o + k])
         assert rel < tol, (name, rel)
         o += k
+
+
+# ---- FP64 Lennard-Jones ------------------------------------------------------------
+
+def test_fp64_lj_rows_of_every_length(M, orc):
+    """Rows of 0 to about 100 entries through the batched FP64 walk, to the
+    1e-12 of the FP64 path."""
+    from test_gpu_parity import _gpu_lists
+    x, L = inputs.graded(14, inputs.fcc_lattice_constant(1.2), 0.03, seed=72)
+    x = orc.wrap(x, L)
+    n = len(x)
+    _, st = _gpu_lists(M, x, L, 2.8)
+    f = torch.full((3, n), np.nan, dtype=torch.float64, device="cuda")
+    M.md_forces_lj(L, n, st["x"], None, st["cap"], st["idx"], st["cnt"], (1.0, 1.0, 2.5), f, None, M.MD_PAIR_FP64,
+                   st["ws"])
+    fg = np.empty((n, 3))
+    fg[st["perm"].cpu().numpy()[:n]] = f.cpu().numpy().T
+    oc, ic = orc.neighbors_cells(x, L, 2.8)
+    fo, _ = orc.forces_lj(x, L, oc, ic, rc=2.5)
+    assert np.linalg.norm(fg - fo) <= 1e-12 * np.linalg.norm(fo)
