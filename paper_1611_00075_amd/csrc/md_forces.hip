@@ -226,7 +226,7 @@ struct FS32 {
     Gate gate;
     static constexpr int kRhoWords = 3;   // words of a neighbour's scaled coordinates pass 1 reads
     static constexpr bool kSplit = true;  // row walk: full batches, then one masked tail batch
-    static constexpr int kRhoUnroll = 4;  // row entries per lane per batch in pass 1 (measured)
+    static constexpr int kRhoUnroll = 4, kForceUnroll = 4;  // row entries per lane per batch of the passes (measured)
 };
 
 // Second-moment tight-binding form: psi = exp2(cq - kq r) S(r),
@@ -243,7 +243,9 @@ struct TB32 {
     Gate gate;
     static constexpr int kRhoWords = 3;
     static constexpr bool kSplit = true;
-    static constexpr int kRhoUnroll = 6;  // exponentials per pair: deeper batches pay (measured)
+    // exponentials per pair: deeper batches pay (force pass of 500,000 Cu atoms
+    // with 4: both passes 96.3 us, with 6: 94.7)
+    static constexpr int kRhoUnroll = 6, kForceUnroll = 6;
 };
 
 // Two elements: the tight-binding constants per pair kind k = t_i + t_j
@@ -266,7 +268,7 @@ struct TBM32 {
     // whole batches without selects, slots past the row end masked in the
     // pair term: the longer pair terms favour fewer selects over fewer slots
     static constexpr bool kSplit = false;
-    static constexpr int kRhoUnroll = 6;
+    static constexpr int kRhoUnroll = 6, kForceUnroll = 4;
 };
 
 // ---- pair terms of the forms ------------------------------------------------
@@ -560,7 +562,6 @@ __global__ __launch_bounds__(kBlock) void k_eam_force(int64_t n, const uint4 *__
 // launchers
 // ---------------------------------------------------------------------------
 constexpr int kTPA = kSlice;   // lanes per atom of the FP32 kernels
-constexpr int kUnroll = 4;     // row entries per lane per batch (embedded-atom passes)
 constexpr int kUnroll64 = 5;   // FP64 LJ: rows of ~70 entries take two batches
 constexpr int kUnrollLJ = 6;   // LJ: rows of ~70 entries take two batches (measured best of 2-12)
 
@@ -683,7 +684,7 @@ static void launch_eam(int passes, uint32_t gb, hipStream_t s, int64_t n, uint4 
         hipLaunchKernelGGL((k_eam_rho<P, TPA, P::kRhoUnroll, CUBIC, E, C>), dim3(gb), dim3(kBlock), 0, s, n, q, l.cap,
                            l.idx, l.cnt, p, rho, fprime, part1, sp, tab);
     if (passes & 2)
-        hipLaunchKernelGGL((k_eam_force<P, TPA, kUnroll, CUBIC, E, C>), dim3(gb), dim3(kBlock), 0, s, n, q, l.cap,
+        hipLaunchKernelGGL((k_eam_force<P, TPA, P::kForceUnroll, CUBIC, E, C>), dim3(gb), dim3(kBlock), 0, s, n, q, l.cap,
                            l.idx, l.cnt, p, rho, f, ea, part2, sp, tab);
 }
 

@@ -122,17 +122,29 @@ __device__ __forceinline__ void walk_buf(const __amdgpu_buffer_rsrc_t &xs_r, con
 }
 
 // Row walk in two parts.  Full batches: while all U entries t + 8 u of the
-// lane are inside the row, U indices then U positions are loaded with no
-// per-slot selects and body(pj, t, Masked<false>) gets U positions, all of
-// them real neighbours.  Tail (1 to U - 1 entries left): one batch of
-// U - 1 slots, body(pj, t, Masked<true>) with pj of length U - 1; the loads
-// of slots past the end are switched off in the execution mask (zeros in
-// pj).  A lane given an out-of-range offset instead still passes through
-// the gather's address processing and issue: masking took the LJ kernel
-// from 0.130 to 0.1255 ms.  A lane thus evaluates fewer slots than
-// U * ceil(cnt / 8U) and makes no selects in its full batches.  (What
-// bounds the pair kernels is the list stream, 4 bytes per entry read once,
-// together with the pair arithmetic; the position gathers add little.)
+// lane are inside the row, body(pj, t, Masked<false>) gets U positions, all
+// of them real neighbours, with no per-slot selects.  Tail (1 to U - 1
+// entries left): one batch of U - 1 slots, body(pj, t, Masked<true>) with pj
+// of length U - 1 and zeros in the slots past the end.  A lane thus evaluates
+// fewer slots than U * ceil(cnt / 8U).
+//
+// Order of the loads: a batch's positions, then the next batch's list
+// entries, then the arithmetic.  Loads return in the order of their issue, so
+// with the entries (a miss to HBM) behind the positions (cache hits) the
+// arithmetic waits for the positions alone and the entries travel meanwhile;
+// entries first makes every batch wait for HBM, and entries only after the
+// arithmetic leaves the list stream idle during it.  sched_barrier holds the
+// compiler to this order.  Entries after the arithmetic against this order:
+// LJ, 1.23 M atoms with voids, 114.3 -> 111.3 us; FS, 4 M Cu, both passes
+// 602 -> 587 us; tabulated, 1 M Cu, 173.3 -> 166.5 us; same bits.
+//
+// Loads past the row's end are switched off in the execution mask: given an
+// out-of-range offset instead, a lane still passes through the gather's
+// address processing and issue (LJ 117 us).  (What bounds the pair kernels is
+// the list stream, 4 bytes per entry read once, together with the pair
+// arithmetic; entries in 16-byte loads, four consecutive ones per lane, ran
+// LJ at 122-129 us: the lanes of a gather then spread over 32 entries of a
+// row instead of 8 adjacent ones.)
 template <int U, int WORDS, typename Body>
 __device__ __forceinline__ void walk_split(const __amdgpu_buffer_rsrc_t &xs_r, const __amdgpu_buffer_rsrc_t &row_r,
                                            int32_t cnt, int sub, Body &&body)
@@ -149,30 +161,34 @@ __device__ __forceinline__ void walk_split(const __amdgpu_buffer_rsrc_t &xs_r, c
     };
     uint32_t off = (threadIdx.x % kWave) * 4u;
     int32_t t = sub;
-    for (; t + (U - 1) * kSlice < cnt; t += U * kSlice, off += U * 256u) {
-        uint32_t j[U];
+    uint32_t j[U];   // entries of the batch at t (zeros past the row's end)
+    auto entries = [&]() {
 #pragma unroll
-        for (int u = 0; u < U; ++u) j[u] = __builtin_amdgcn_raw_buffer_load_b32(row_r, off + u * 256u, 0, 0);
+        for (int u = 0; u < U; ++u) {
+            j[u] = 0u;
+            if (t + u * kSlice < cnt) j[u] = __builtin_amdgcn_raw_buffer_load_b32(row_r, off + u * 256u, 0, 0);
+        }
+    };
+    entries();
+    while (t + (U - 1) * kSlice < cnt) {
         uint4 pj[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) pj[u] = pos(j[u] << 4);
-        body(pj, t, Masked<false>{});
+        const int32_t t0 = t;
+        t += U * kSlice;
+        off += U * 256u;
+        __builtin_amdgcn_sched_barrier(0);
+        entries();
+        __builtin_amdgcn_sched_barrier(0);
+        body(pj, t0, Masked<false>{});
     }
     if (t < cnt) {
         constexpr int V = U - 1;
-        bool ok[V];
-        uint32_t j[V];
-#pragma unroll
-        for (int u = 0; u < V; ++u) {
-            ok[u] = t + u * kSlice < cnt;
-            j[u] = 0u;
-            if (ok[u]) j[u] = __builtin_amdgcn_raw_buffer_load_b32(row_r, off + u * 256u, 0, 0);
-        }
         uint4 pj[V];
 #pragma unroll
         for (int u = 0; u < V; ++u) {
             pj[u] = make_uint4(0u, 0u, 0u, 0u);
-            if (ok[u]) pj[u] = pos(j[u] << 4);
+            if (t + u * kSlice < cnt) pj[u] = pos(j[u] << 4);
         }
         body(pj, t, Masked<true>{});
     }
