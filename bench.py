@@ -729,9 +729,9 @@ COUNTER_KERNELS = {
     "k_mlp_desc_cu_4M": (MLP_SRC, r"k_mlp_desc\(", 32000000),
     "k_mlp_net_cu_4M": (MLP_SRC, r"k_mlp_net<1>", 524288),
     "k_mlp_force_cu_4M": (MLP_SRC, r"k_mlp_force<2, false, true>", 32000000),
-    "k_neighbors_lj_voids_1.23M": (CELLS_SRC, r"k_neighbors\(", 103823 * 64),
-    "k_neighbors_cu_5.4A_4M": (CELLS_SRC, r"k_neighbors\(", 287496 * 64),
-    "k_neighbors_lj_slab_32M": (CELLS_SRC, r"k_neighbors\(", 3375000 * 64),
+    "k_neighbors_lj_voids_1.23M": (CELLS_SRC, r"k_neighbors(<1>)?\(", 103823 * 64),
+    "k_neighbors_cu_5.4A_4M": (CELLS_SRC, r"k_neighbors(<1>)?\(", 287496 * 64),
+    "k_neighbors_lj_slab_32M": (CELLS_SRC, r"k_neighbors(<1>)?\(", 3375000 * 64),
     "k_probe_fma_f32": (PROBE_SRC, r"k_probe_fma<float>", None),
     "k_probe_fma_f64": (PROBE_SRC, r"k_probe_fma<double>", None),
     "k_probe_mfma": (PROBE_SRC, r"k_probe_mfma\(", None),

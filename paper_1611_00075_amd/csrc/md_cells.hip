@@ -6,6 +6,8 @@
 // taken in FP64 with the operation order of the plain definition and no FMA
 // contraction (the library is built with -ffp-contract=off), so cell
 // assignments and neighbour sets are reproducible bit for bit.
+#include <algorithm>
+
 #include "md_common.h"
 #include "md_pair.h"
 
@@ -315,11 +317,112 @@ __device__ __forceinline__ double wave_max(double v)
 constexpr int kNbChunks = 4;                   // 64-candidate chunks held in registers at once
 constexpr int kNbTile = kNbChunks * kWave;     // candidates per register tile
 constexpr int kNbStage = 2 * kNbTile;          // staged candidates: a tile plus one raw tile's survivors
-constexpr int kNbWaves = 1;                    // wavefronts (cells) per block
 constexpr int kNbMap = 1024;                   // candidates whose stencil cell is tabulated in LDS
-constexpr int kNbCellsPerWave = 1;             // consecutive cells (Morton ranks) per wavefront
 constexpr uint32_t kNbXcdChunk = 256;          // consecutive blocks (cells) an XCD takes at a time
-constexpr int kNbBlock = kNbWaves * kWave;
+
+// What the set-up of a cell found: its homes, its stencil cells, their atoms.
+struct NbCell {
+    int32_t h0, h1;      // sorted atoms of the cell
+    int32_t m, total;    // stencil cells, candidates in them
+    bool interior;       // no stencil cell wraps around the box
+    bool nodup;          // every stencil offset is a cell of its own
+};
+
+// The stencil of cell `rank` into L: per stencil cell (x fastest) the first
+// atom, the candidates before it and its periodic image, and for up to kNbMap
+// candidates the stencil cell of each.
+template <class LDS>
+__device__ __forceinline__ NbCell nb_stencil(LDS &L, int64_t rank, const GridArgs &g, const int32_t *cell_start,
+                                             const int32_t *rank_xyz, const int32_t *lin2rank)
+{
+    const int lane = threadIdx.x % kWave;
+    NbCell c;
+    c.h0 = uni(cell_start[rank]);
+    c.h1 = uni(cell_start[rank + 1]);
+    c.m = c.total = 0;
+    c.interior = c.nodup = true;
+    if (c.h0 == c.h1) return c;
+
+    const int32_t pk = uni(rank_xyz[rank]);   // packed cell coordinates
+    const int32_t c3[3] = {pk & 1023, (pk >> 10) & 1023, pk >> 20};
+    for (int a = 0; a < 3; ++a) {
+        c.interior &= (g.nc[a] >= 2 * g.reach + 2) && (c3[a] - g.reach >= 0) && (c3[a] + g.reach < g.nc[a]);
+        c.nodup &= g.nc[a] >= 2 * g.reach + 1;
+    }
+    int32_t ax[5], ay[5], az[5], ix[5], iy[5], iz[5];
+    const int mx = stencil_axis(c3[0], g.nc[0], g.reach, ax, ix);
+    const int my = stencil_axis(c3[1], g.nc[1], g.reach, ay, iy);
+    const int mz = stencil_axis(c3[2], g.nc[2], g.reach, az, iz);
+    const int m = mx * my * mz;
+    // stencil cells: lane t takes cells t and t + 64 (x-fastest order), reads
+    // their ranges, and a shuffle scan forms the range prefix
+    int32_t carry = 0;
+    for (int t0 = 0; t0 < m; t0 += kWave) {
+        const int t = t0 + lane;
+        int32_t len = 0;
+        if (t < m) {
+            // t = a + mx (b + my c) for small mx, my: exact reciprocal multiplies
+            const int q1 = (t * ((65536 + mx - 1) / mx)) >> 16;
+            const int a = t - q1 * mx;
+            const int cz = (q1 * ((65536 + my - 1) / my)) >> 16;
+            const int b = q1 - cz * my;
+            const int64_t l = ax[a] + int64_t(g.nc[0]) * (ay[b] + int64_t(g.nc[1]) * az[cz]);
+            const int32_t r = lin2rank[l];
+            const int32_t st = cell_start[r];
+            len = cell_start[r + 1] - st;
+            L.rstart[t] = st;
+            L.rimg[t] = uint8_t((ix[a] + 1) | ((iy[b] + 1) << 2) | ((iz[cz] + 1) << 4));
+        }
+        int32_t v = len;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int32_t u = __shfl_up(v, o, kWave);
+            if (lane >= o) v += u;
+        }
+        if (t < m) L.rbase[t + 1] = carry + v;
+        carry += __builtin_amdgcn_readlane(v, kWave - 1);
+    }
+    if (lane == 0) L.rbase[0] = 0;
+    wave_sync();
+    if (carry <= kNbMap)   // tabulate the stencil cell of every candidate: lane t writes cell t's run
+        for (int t = lane; t < m; t += kWave)
+            for (int32_t q = L.rbase[t], e = L.rbase[t + 1]; q < e; ++q) L.cmap[q] = uint8_t(t);
+    wave_sync();
+    c.m = m;
+    c.total = carry;
+    return c;
+}
+
+// The stencil cell of candidate gq: tabulated, or the last range with
+// rbase[k] <= gq (rbase[m] = total never is); top: highest power of two <= m.
+template <class LDS>
+__device__ __forceinline__ int nb_cell_of(const LDS &L, int32_t gq, int32_t m, int32_t total, int top)
+{
+    if (total <= kNbMap) return L.cmap[gq];
+    int k = 0;
+    for (int s = top; s > 0; s >>= 1) {
+        const int t = min(k + s, m);
+        k = L.rbase[t] <= gq ? t : k;
+    }
+    return k;
+}
+
+// *max_count only grows, so a wave whose longest row does not exceed a
+// value already there has nothing to add: the check keeps the atomics on
+// this one word (which the L2 serialises) to a few per launch.
+__device__ __forceinline__ void nb_longest(int32_t longest, int32_t *max_count)
+{
+    for (int o = kWave / 2; o > 0; o >>= 1) longest = max(longest, __shfl_xor(longest, o, kWave));
+    if (threadIdx.x % kWave == 0 &&
+        longest > __hip_atomic_load(max_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(max_count, longest);
+}
+
+// How a launch splits a cell's homes: `parts` wavefronts per cell, each
+// taking every parts-th batch of `batch` homes.
+struct NbSplit {
+    int32_t parts, batch;
+};
 
 // Per-wave LDS state: the home atoms' positions (read back as broadcasts),
 // the stencil's cell ranges with their periodic images, and the candidates
@@ -327,8 +430,9 @@ constexpr int kNbBlock = kNbWaves * kWave;
 struct NbWaveLds {
     double hx[kWave], hy[kWave], hz[kWave];
     double box[6];                            // homes' bounding box: lo x, y, z, hi x, y, z
-    int32_t rstart[kMaxStencil], rbase[kMaxStencil + 1], rimg[kMaxStencil];
+    int32_t rstart[kMaxStencil], rbase[kMaxStencil + 1];
     int32_t stage[kNbStage];
+    uint8_t rimg[kMaxStencil];
     uint8_t cmap[kNbMap];                     // stencil cell of each candidate (up to kNbMap)
 };
 
@@ -344,19 +448,16 @@ struct NbTile {
 // stored, so the NC chains are independent; only lanes with a hit store,
 // through a buffer whose range ends at the row capacity (stores past it are
 // dropped).
-template <int NC, bool INTERIOR>
+template <int NC>
 __device__ __forceinline__ uint32_t nb_home(const NbTile &T, double xi, double yi, double zi, int32_t i, uint32_t r,
                                             __amdgpu_buffer_rsrc_t row, double rl2, const GridArgs &g)
 {
     uint64_t mk[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        double dx = T.x[c] - xi, dy = T.y[c] - yi, dz = T.z[c] - zi;
-        if (!INTERIOR) {
-            dx = minimg_sel(dx, g.L[0], g.hL[0]);
-            dy = minimg_sel(dy, g.L[1], g.hL[1]);
-            dz = minimg_sel(dz, g.L[2], g.hL[2]);
-        }
+        const double dx = minimg_sel(T.x[c] - xi, g.L[0], g.hL[0]);
+        const double dy = minimg_sel(T.y[c] - yi, g.L[1], g.hL[1]);
+        const double dz = minimg_sel(T.z[c] - zi, g.L[2], g.hL[2]);
         const double r2 = (dx * dx + dy * dy) + dz * dz;
         // the wave's hit mask straight from the two compares (r2 < rl2 as an
         // ordered less-than, so a +inf padding candidate never hits)
@@ -385,12 +486,13 @@ __device__ __forceinline__ uint32_t nb_home(const NbTile &T, double xi, double y
 // either test, so no candidate that the exact test accepts is dropped).
 // Kept candidates are staged in LDS; every 256 of them fill a register
 // tile, against which each home atom is tested with the exact FP64 test.
-template <bool INTERIOR>
 __device__ __forceinline__ int32_t nb_cell(NbWaveLds &L, int64_t n, const double *x, const GridArgs &g, double rl2,
-                                           double keep2, bool filter, int32_t h0, int32_t h1, int32_t m,
-                                           int32_t total, int32_t row_cap, int32_t *idx, int32_t *count)
+                                           double keep2, const NbCell &cell, int32_t first, const NbSplit &sp,
+                                           int32_t row_cap, int32_t *idx, int32_t *count)
 {
     const int lane = threadIdx.x % kWave;
+    const int32_t m = cell.m, total = cell.total;
+    const bool filter = cell.nodup;
     int top = 1;                              // highest power of two <= m
     while (2 * top <= m) top *= 2;
     int32_t longest = 0;
@@ -398,8 +500,8 @@ __device__ __forceinline__ int32_t nb_cell(NbWaveLds &L, int64_t n, const double
     // bytes of one row seen as a buffer: its last entry (row_cap - 1) ends there
     const uint32_t row_bytes = uint32_t(row_cap) * 32u - 224u;
 
-    for (int32_t hb = h0; hb < h1; hb += kWave) {
-        const int32_t hn = min(kWave, h1 - hb);
+    for (int32_t hb = cell.h0 + first; hb < cell.h1; hb += sp.parts * sp.batch) {
+        const int32_t hn = min(sp.batch, cell.h1 - hb);
         const int32_t hl = hb + min(lane, hn - 1);
         const double xh = x[hl], yh = x[n + hl], zh = x[2 * n + hl];
         L.hx[lane] = xh;
@@ -429,28 +531,16 @@ __device__ __forceinline__ int32_t nb_cell(NbWaveLds &L, int64_t n, const double
                 keep[c] = false;
                 jr[c] = 0;
                 if (gq < total) {
-                    // the stencil cell k of candidate gq: tabulated, or the last
-                    // range with rbase[k] <= gq (rbase[m] = total never is)
-                    int k = 0;
-                    if (total <= kNbMap) {
-                        k = L.cmap[gq];
-                    } else {
-                        for (int s = top; s > 0; s >>= 1) {
-                            const int t = min(k + s, m);
-                            k = L.rbase[t] <= gq ? t : k;
-                        }
-                    }
+                    const int k = nb_cell_of(L, gq, m, total, top);
                     const int32_t j = L.rstart[k] + (gq - L.rbase[k]);
                     jr[c] = j;
                     keep[c] = true;
                     if (filter) {
                         double cx = x[j], cy = x[n + j], cz = x[2 * n + j];
-                        if (!INTERIOR) {
-                            const int32_t im = L.rimg[k];
-                            cx += double((im & 3) - 1) * g.L[0];
-                            cy += double(((im >> 2) & 3) - 1) * g.L[1];
-                            cz += double(((im >> 4) & 3) - 1) * g.L[2];
-                        }
+                        const int32_t im = L.rimg[k];
+                        cx += double((im & 3) - 1) * g.L[0];
+                        cy += double(((im >> 2) & 3) - 1) * g.L[1];
+                        cz += double(((im >> 4) & 3) - 1) * g.L[2];
                         const double dx = fmax(fmax(L.box[0] - cx, cx - L.box[3]), 0.0);
                         const double dy = fmax(fmax(L.box[1] - cy, cy - L.box[4]), 0.0);
                         const double dz = fmax(fmax(L.box[2] - cz, cz - L.box[5]), 0.0);
@@ -495,10 +585,10 @@ __device__ __forceinline__ int32_t nb_cell(NbWaveLds &L, int64_t n, const double
                     const double xi = L.hx[h], yi = L.hy[h], zi = L.hz[h];
                     uint32_t rn;
                     switch (nch) {
-                    case 4: rn = nb_home<4, INTERIOR>(T, xi, yi, zi, i, r, row, rl2, g); break;
-                    case 3: rn = nb_home<3, INTERIOR>(T, xi, yi, zi, i, r, row, rl2, g); break;
-                    case 2: rn = nb_home<2, INTERIOR>(T, xi, yi, zi, i, r, row, rl2, g); break;
-                    default: rn = nb_home<1, INTERIOR>(T, xi, yi, zi, i, r, row, rl2, g); break;
+                    case 4: rn = nb_home<4>(T, xi, yi, zi, i, r, row, rl2, g); break;
+                    case 3: rn = nb_home<3>(T, xi, yi, zi, i, r, row, rl2, g); break;
+                    case 2: rn = nb_home<2>(T, xi, yi, zi, i, r, row, rl2, g); break;
+                    default: rn = nb_home<1>(T, xi, yi, zi, i, r, row, rl2, g); break;
                     }
                     if (lane == h) run_l = int32_t(rn);
                 }
@@ -523,8 +613,9 @@ __device__ __forceinline__ int32_t nb_cell(NbWaveLds &L, int64_t n, const double
     return longest;
 }
 
-// One wavefront per cell (Morton rank) in one-wave blocks, no block-wide
-// barriers.  The atoms of the up to 27 (125) neighbouring cells are
+// ---- boxes of fewer than 2 reach + 2 cells on an axis ----
+// One wavefront per cell (Morton rank) and part in one-wave blocks, no
+// block-wide barriers.  The atoms of the up to 27 (125) neighbouring cells are
 // contiguous runs of the sorted arrays; the wave streams them, keeps those
 // within reach of its homes' bounding box, and tests each home atom against
 // 64 kept candidates at a time, compacting hits with a ballot straight into
@@ -533,103 +624,420 @@ __device__ __forceinline__ int32_t nb_cell(NbWaveLds &L, int64_t n, const double
 // cell (x fastest), then sorted index.  Rows longer than row_cap are counted
 // but truncated (the row is written through a buffer whose range ends at
 // entry row_cap, so stores past it are dropped); the longest row length is
-// folded into *max_count.
-//
-// Interior cells (no stencil cell wraps around the box and nc >= 2 reach + 2
-// on every axis) use the plain difference x_j - x_i: every candidate is then
-// closer than half a box, so the minimum-image correction of the definition
-// never applies and the result is bitwise the same.  A padding candidate
-// gives +inf in every branch, so it never passes r^2 < r_list^2.  The
-// bounding-box filter runs when no stencil offset was de-duplicated on any
-// axis (nc >= 2 reach + 1): each stencil cell is then one periodic image,
-// the only one that can lie within r_list of a home.
-// The rows of the atoms of cell `rank`; returns the cell's longest row.
-__device__ __forceinline__ int32_t nb_one_cell(NbWaveLds &L, int64_t rank, int64_t n, const double *x,
-                                               const GridArgs &g, double rl2, double keep2,
-                                               const int32_t *cell_start, const int32_t *rank_xyz,
-                                               const int32_t *lin2rank, int32_t row_cap, int32_t *idx,
-                                               int32_t *count)
+// folded into *max_count.  A padding candidate gives +inf, so it never
+// passes r^2 < r_list^2.  The bounding-box filter runs when no stencil offset
+// was de-duplicated on any axis (nc >= 2 reach + 1): each stencil cell is then
+// one periodic image, the only one that can lie within r_list of a home.
+__global__ __launch_bounds__(kWave)
+void k_neighbors_small(int64_t n, const double *x, GridArgs g, double rl2, double keep2, NbSplit sp,
+                       const int32_t *cell_start, const int32_t *rank_xyz, const int32_t *lin2rank, int32_t row_cap,
+                       int32_t *idx, int32_t *count, int32_t *max_count)
 {
-    const int lane = threadIdx.x % kWave;
-    const int32_t h0 = uni(cell_start[rank]), h1 = uni(cell_start[rank + 1]);
-    if (h0 == h1) return 0;
-
-    const int32_t pk = uni(rank_xyz[rank]);   // packed cell coordinates
-    const int32_t c3[3] = {pk & 1023, (pk >> 10) & 1023, pk >> 20};
-    bool interior = true, nodup = true;
-    for (int a = 0; a < 3; ++a) {
-        interior &= (g.nc[a] >= 2 * g.reach + 2) && (c3[a] - g.reach >= 0) && (c3[a] + g.reach < g.nc[a]);
-        nodup &= g.nc[a] >= 2 * g.reach + 1;
-    }
-    int32_t ax[5], ay[5], az[5], ix[5], iy[5], iz[5];
-    const int mx = stencil_axis(c3[0], g.nc[0], g.reach, ax, ix);
-    const int my = stencil_axis(c3[1], g.nc[1], g.reach, ay, iy);
-    const int mz = stencil_axis(c3[2], g.nc[2], g.reach, az, iz);
-    const int m = mx * my * mz;
-    // stencil cells: lane t takes cells t and t + 64 (x-fastest order), reads
-    // their ranges, and a shuffle scan forms the range prefix
-    int32_t carry = 0;
-    for (int t0 = 0; t0 < m; t0 += kWave) {
-        const int t = t0 + lane;
-        int32_t len = 0;
-        if (t < m) {
-            // t = a + mx (b + my c) for small mx, my: exact reciprocal multiplies
-            const int q1 = (t * ((65536 + mx - 1) / mx)) >> 16;
-            const int a = t - q1 * mx;
-            const int c = (q1 * ((65536 + my - 1) / my)) >> 16;
-            const int b = q1 - c * my;
-            const int64_t l = ax[a] + int64_t(g.nc[0]) * (ay[b] + int64_t(g.nc[1]) * az[c]);
-            const int32_t r = lin2rank[l];
-            const int32_t st = cell_start[r];
-            len = cell_start[r + 1] - st;
-            L.rstart[t] = st;
-            L.rimg[t] = (ix[a] + 1) | ((iy[b] + 1) << 2) | ((iz[c] + 1) << 4);
-        }
-        int32_t v = len;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int32_t u = __shfl_up(v, o, kWave);
-            if (lane >= o) v += u;
-        }
-        if (t < m) L.rbase[t + 1] = carry + v;
-        carry += __builtin_amdgcn_readlane(v, kWave - 1);
-    }
-    if (lane == 0) L.rbase[0] = 0;
-    wave_sync();
-    if (carry <= kNbMap)   // tabulate the stencil cell of every candidate: lane t writes cell t's run
-        for (int t = lane; t < m; t += kWave)
-            for (int32_t q = L.rbase[t], e = L.rbase[t + 1]; q < e; ++q) L.cmap[q] = uint8_t(t);
-    wave_sync();
-    return interior ? nb_cell<true>(L, n, x, g, rl2, keep2, nodup, h0, h1, m, carry, row_cap, idx, count)
-                               : nb_cell<false>(L, n, x, g, rl2, keep2, nodup, h0, h1, m, carry, row_cap, idx, count);
+    __shared__ NbWaveLds L;
+    const uint32_t part = blockIdx.x % uint32_t(sp.parts);
+    const NbCell c = nb_stencil(L, blockIdx.x / uint32_t(sp.parts), g, cell_start, rank_xyz, lin2rank);
+    if (c.h0 == c.h1) return;
+    nb_longest(nb_cell(L, n, x, g, rl2, keep2, c, int32_t(part) * sp.batch, sp, row_cap, idx, count), max_count);
 }
 
-// The per-wave LDS (about 6 KB) lets a CU hold 26 waves, 6 per SIMD; the
-// register budget is set to match (80 VGPRs instead of the 83 the compiler
-// would take, which allow only 5): the candidate gathers and the dependent
-// loads of the stencil set-up need the waves to hide their latency.
-__global__ __launch_bounds__(kNbBlock) __attribute__((amdgpu_waves_per_eu(6)))
-void k_neighbors(int64_t n, const double *x, GridArgs g, double rl2, double keep2, int64_t n_cells,
-                 const int32_t *cell_start, const int32_t *rank_xyz, const int32_t *lin2rank, int32_t row_cap,
-                 int32_t *idx, int32_t *count, int32_t *max_count)
+// ---- the matrix-core build ----
+constexpr int kNmStage = 2 * kWave;   // staged candidates: a rest plus what one chunk of 64 keeps
+
+typedef float nm_f32x4 __attribute__((ext_vector_type(4)));
+
+template <int R>
+struct NmLds {
+    static constexpr int kCells = (2 * R + 1) * (2 * R + 1) * (2 * R + 1);
+    float4 stage[kNmStage];          // kept candidates: position from the batch's centre, its square
+    float4 home[kWave];              // homes: -2 x, -2 y, -2 z, 1
+    float hom2[kWave];               // |home|^2 - r_list^2
+    int32_t run[kWave], off[kWave];  // homes: row length so far, byte offset of the row in the batch's rows
+    int32_t stage_j[kNmStage];
+    int32_t shift[kCells];           // stencil cell: its first atom minus the candidates before it
+    int32_t rbase[kCells + 1];       // candidates before it
+    int8_t img[kCells][4];           // its periodic image
+    uint8_t cmap[kNbMap];
+};
+
+template <bool MAX>
+__device__ __forceinline__ float wave_extreme(float v)
 {
-    __shared__ NbWaveLds lds_all[kNbWaves];
-    const int lane = threadIdx.x % kWave, wave = uni(threadIdx.x / kWave);
-    NbWaveLds &L = lds_all[wave];
-    const int64_t first = (int64_t(xcd_chunked(blockIdx.x, gridDim.x, kNbXcdChunk)) * kNbWaves + wave) *
-                          kNbCellsPerWave;
+    auto pick = [](float a, float b) { return MAX ? fmaxf(a, b) : fminf(a, b); };
+#define MD_DPP(ctrl, rows) \
+    v = pick(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), ctrl, rows, 0xf, false)))
+    MD_DPP(0xb1, 0xf);    // lane ^ 1
+    MD_DPP(0x4e, 0xf);    // lane ^ 2
+    MD_DPP(0x141, 0xf);   // mirrored within 8
+    MD_DPP(0x140, 0xf);   // mirrored within 16
+    MD_DPP(0x142, 0xa);   // rows 1 and 3 take row 0's and 2's last lane
+    MD_DPP(0x143, 0xc);   // rows 2 and 3 take lane 31
+#undef MD_DPP
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), kWave - 1));
+}
+
+// Low (HI = 0) or high halves of two words side by side: one scalar
+// instruction, which the compiler does not find from shifts and masks.
+template <int HI>
+__device__ __forceinline__ uint32_t pack16(uint32_t a, uint32_t b)
+{
+    uint32_t r;
+    if (HI) asm("s_pack_hh_b32_b16 %0, %1, %2" : "=s"(r) : "s"(a), "s"(b));
+    else asm("s_pack_ll_b32_b16 %0, %1, %2" : "=s"(r) : "s"(a), "s"(b));
+    return r;
+}
+
+// v with `val` (wave-uniform) in lane LANE
+template <int LANE>
+__device__ __forceinline__ int32_t put_lane(int32_t v, uint32_t val)
+{
+    asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(val), "n"(LANE));
+    return v;
+}
+
+// Home H of a 16-home tile against 64 candidates: the hits of its mask
+// (registers S, see nm_chunk) appended to its row in candidate order.  run,
+// off: row length and row offset of home `lane` of the tile.
+template <int H>
+__device__ __forceinline__ void nm_home(const uint64_t (&S)[4][4], int32_t jj, __amdgpu_buffer_rsrc_t rows,
+                                        int32_t off, uint32_t row_cap, int32_t &run)
+{
+    constexpr int r = H & 3, q = H >> 2;
+    auto word = [&](int c) { return q < 2 ? uint32_t(S[c][r]) : uint32_t(S[c][r] >> 32); };
+    const uint64_t mk = uint64_t(pack16<q & 1>(word(0), word(1))) | (uint64_t(pack16<q & 1>(word(2), word(3))) << 32);
+    if (!mk) return;   // no hit (wave-uniform)
+    const uint32_t r0 = uint32_t(__builtin_amdgcn_readlane(run, H));
+    const uint32_t so = uint32_t(__builtin_amdgcn_readlane(off, H));
+    const uint32_t r1 = r0 + uint32_t(__popcll(mk));
+    const uint32_t e = __builtin_amdgcn_mbcnt_hi(uint32_t(mk >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mk), r0));
+    const uint32_t at = (e << 2) + __umul24(e >> 3, 224u);   // entry e of the row: byte (e / 8) * 256 + (e % 8) * 4
+    uint64_t put = mk;
+    if (__builtin_expect(r1 > row_cap, 0)) put &= __builtin_amdgcn_ballot_w64(e < row_cap);
+    if (__builtin_amdgcn_inverse_ballot_w64(put)) __builtin_amdgcn_raw_buffer_store_b32(jj, rows, at, so, 0);
+    run = put_lane<H>(run, r1);
+}
+
+// The rows of one batch of homes against 64 staged candidates at `base`.
+//
+// v_mfma_f32_16x16x4_f32 (A 16x4: lane = row + 16 k; B 4x16: lane = column +
+// 16 k; D: lane = column + 16 (row / 4), register row % 4) gives
+// |h|^2 - r_list^2 - 2 h.c + |c|^2 of 16 homes and 16 candidates at once.  A
+// compare of one register is then the hit mask of four homes x 16
+// candidates, and two 16-bit packs make it a home's mask over 64 candidates.
+// Values within `eps` of zero (their rounding error is below that) are
+// decided by the definition in FP64.
+template <class LDS>
+__device__ __forceinline__ void nm_chunk(LDS &L, int32_t base, int64_t n, const double *x, const GridArgs &g,
+                                         double rl2, float eps, int32_t hb, int32_t hn, int32_t self,
+                                         __amdgpu_buffer_rsrc_t rows, uint32_t row_cap)
+{
+    const int lane = threadIdx.x % kWave, li = lane & 15, gq = lane >> 4;
+    const float *st = reinterpret_cast<const float *>(L.stage + base);
+    float b[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) b[c] = st[(16 * c + li) * 4 + gq];
+    const int32_t jj = L.stage_j[base + lane];
+    const bool own = self < kWave && self + hn > 0;   // some home is among these candidates
+    for (int32_t t = 0; t < hn; t += 16) {
+        const float a = reinterpret_cast<const float *>(L.home + t + li)[gq];
+        const nm_f32x4 c2 = *reinterpret_cast<const nm_f32x4 *>(L.hom2 + t + 4 * gq);
+        int32_t run = L.run[t + li];
+        const int32_t off = L.off[t + li];
+        nm_f32x4 D[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) D[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b[c], c2, 0, 0, 0);
+        if (own) {   // a home is no neighbour of its own
+            const int32_t d = self + t + 4 * gq - li;
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) D[c][r] = d + r == 16 * c ? 1e30f : D[c][r];
+        }
+        float near = __builtin_inff();
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            near = fminf(fminf(near, fabsf(D[c][0])), fabsf(D[c][1]));
+            near = fminf(fminf(near, fabsf(D[c][2])), fabsf(D[c][3]));
+        }
+        if (__builtin_amdgcn_fcmpf(near, eps, 5)) {   // any lane: ordered less or equal
+            uint32_t open = 0, hit = 0;   // bit 4 c + r: undecided values of this lane, those found to be hits
+#pragma unroll
+            for (int q = 0; q < 16; ++q) open |= fabsf(D[q >> 2][q & 3]) <= eps ? 1u << q : 0u;
+            for (uint32_t m = open; __builtin_amdgcn_ballot_w64(m != 0); m &= m - 1) {
+                const int q = m ? __builtin_ctz(m) : 0;
+                const int32_t j = __shfl(jj, 4 * (q & 12) + li, kWave);
+                if (m) {
+                    const int32_t i = hb + t + 4 * gq + (q & 3);
+                    const double dx = minimg_sel(x[j] - x[i], g.L[0], g.hL[0]);
+                    const double dy = minimg_sel(x[n + j] - x[n + i], g.L[1], g.hL[1]);
+                    const double dz = minimg_sel(x[2 * n + j] - x[2 * n + i], g.L[2], g.hL[2]);
+                    hit |= (dx * dx + dy * dy) + dz * dz < rl2 ? 1u << q : 0u;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 16; ++q)
+                if (open & (1u << q)) D[q >> 2][q & 3] = hit & (1u << q) ? -1.f : 1.f;
+        }
+        uint64_t S[4][4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) S[c][r] = __builtin_amdgcn_fcmpf(D[c][r], 0.f, 4);   // ordered less-than
+        // homes past hn have empty masks
+#define NM_HOME(h) nm_home<h>(S, jj, rows, off, row_cap, run)
+        NM_HOME(0); NM_HOME(1); NM_HOME(2); NM_HOME(3);
+        if (t + 4 < hn) {
+            NM_HOME(4); NM_HOME(5); NM_HOME(6); NM_HOME(7);
+            if (t + 8 < hn) {
+                NM_HOME(8); NM_HOME(9); NM_HOME(10); NM_HOME(11);
+                if (t + 12 < hn) {
+                    NM_HOME(12); NM_HOME(13); NM_HOME(14); NM_HOME(15);
+                }
+            }
+        }
+#undef NM_HOME
+        if (lane < 16) L.run[t + lane] = run;
+    }
+}
+
+// Inclusive prefix sum over the wave.
+__device__ __forceinline__ int32_t wave_prefix(int32_t v)
+{
+#define MD_DPP(ctrl, rows) v += __builtin_amdgcn_update_dpp(0, v, ctrl, rows, 0xf, false)
+    MD_DPP(0x111, 0xf);   // from 1, 2, 4 and 8 lanes below in each row of 16
+    MD_DPP(0x112, 0xf);
+    MD_DPP(0x114, 0xf);
+    MD_DPP(0x118, 0xf);
+    MD_DPP(0x142, 0xa);   // rows 1 and 3 add row 0's and 2's last lane
+    MD_DPP(0x143, 0xc);   // rows 2 and 3 add lane 31
+#undef MD_DPP
+    return v;
+}
+
+// The homes of cell `rank` (those of `part`) against its stencil's
+// candidates; returns the longest row.  Candidates are read 64 at a time, the
+// next ones while the last are worked on; one is kept if it lies within
+// r_list of the bounding box of the batch's homes, in its periodic image of
+// the stencil (FP32 positions from the box's centre, margin 1e-5 of r_list^2,
+// far above their rounding), or is one of the homes itself, which keeps these
+// consecutive in the stage.
+template <int R>
+__device__ __forceinline__ int32_t nm_cell(NmLds<R> &L, int64_t rank, int32_t part, int64_t n, const double *x,
+                                           const GridArgs &g, double rl2, const NbSplit &sp,
+                                           const int32_t *cell_start, const int32_t *rank_xyz,
+                                           const int32_t *lin2rank, int32_t row_cap, int32_t *idx, int32_t *count)
+{
+    constexpr int W = 2 * R + 1, kCells = W * W * W;
+    const int lane = threadIdx.x % kWave;
+    const int32_t pk = rank_xyz[rank];   // packed cell coordinates
+    const int32_t h0 = uni(cell_start[rank]), h1 = uni(cell_start[rank + 1]);
+    int32_t hb = h0 + part * sp.batch;
+    if (hb >= h1) return 0;
+    double xh, yh, zh;
+    auto homes = [&](int32_t hn) {   // lanes past hn repeat the last home
+        const int32_t hl = hb + min(lane, hn - 1);
+        xh = x[hl], yh = x[n + hl], zh = x[2 * n + hl];
+    };
+    homes(min(sp.batch, h1 - hb));
+
+    // the stencil (x fastest): lane t takes cells t and t + 64
+    int32_t total = 0, centre = 0;
+    bool interior = true;
+#pragma unroll
+    for (int t0 = 0; t0 < kCells; t0 += kWave) {
+        const int t = t0 + lane;
+        const int32_t cx = pk & 1023, cy = (pk >> 10) & 1023, cz = pk >> 20;
+        int32_t vx = cx + t % W - R, vy = cy + (t / W) % W - R, vz = cz + t / (W * W) - R;
+        const int32_t ix = vx < 0 ? -1 : (vx >= g.nc[0] ? 1 : 0), iy = vy < 0 ? -1 : (vy >= g.nc[1] ? 1 : 0),
+                      iz = vz < 0 ? -1 : (vz >= g.nc[2] ? 1 : 0);
+        int32_t st = 0, len = 0;
+        if (t < kCells) {
+            vx -= ix * g.nc[0], vy -= iy * g.nc[1], vz -= iz * g.nc[2];
+            const int32_t r = lin2rank[vx + g.nc[0] * (vy + g.nc[1] * vz)];
+            st = cell_start[r];
+            len = cell_start[r + 1] - st;
+        }
+        interior &= !__builtin_amdgcn_ballot_w64(t < kCells && (ix | iy | iz));
+        const int32_t end = total + wave_prefix(len), base = end - len;
+        if (t < kCells) {
+            L.shift[t] = st - base;
+            L.rbase[t] = base;
+            *reinterpret_cast<uint32_t *>(L.img[t]) = uint32_t(ix & 255) | uint32_t(iy & 255) << 8 | uint32_t(iz & 255) << 16;
+        }
+        if ((kCells - 1) / 2 >= t0 && (kCells - 1) / 2 < t0 + kWave)
+            centre = __builtin_amdgcn_readlane(base, (kCells - 1) / 2 - t0);
+        total = __builtin_amdgcn_readlane(end, kWave - 1);
+    }
+    if (lane == 0) L.rbase[kCells] = total;
+    wave_sync();
+    if (total <= kNbMap) {   // tabulate the stencil cell of every candidate
+        constexpr int P = kCells <= kWave / 2 ? 2 : 1;   // lanes per stencil cell
+        for (int t = lane / P; t < kCells; t += kWave / P)
+            for (int32_t q = L.rbase[t] + lane % P, e = L.rbase[t + 1]; q < e; q += P) L.cmap[q] = uint8_t(t);
+    }
+    wave_sync();
+
     int32_t longest = 0;
-    for (int c = 0; c < kNbCellsPerWave && first + c < n_cells; ++c) {
-        longest = max(longest, nb_one_cell(L, first + c, n, x, g, rl2, keep2, cell_start, rank_xyz, lin2rank,
-                                           row_cap, idx, count));
+    const float keep2 = float(rl2) * (1.f + 1e-5f), rl = __builtin_sqrtf(float(rl2));
+    while (hb < h1) {
+        const int32_t hn = min(sp.batch, h1 - hb);
+        // the slices of the batch as one buffer (at most 9 of them)
+        const auto rows = make_rsrc(idx + int64_t(hb >> 3) * row_cap * 8, 9u * uint32_t(row_cap) * 32u);
+        const int32_t hl = hb + min(lane, hn - 1);
+        L.run[lane] = 0;
+        L.off[lane] = int32_t(uint32_t((hl >> 3) - (hb >> 3)) * uint32_t(row_cap) * 32u + uint32_t(hl & 7) * 32u);
+        // bounding box of the homes: its centre and half edges, through FP32
+        // offsets from the first home
+        auto first = [&](double v) {
+            return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                                    __builtin_amdgcn_readfirstlane(__double2loint(v)));
+        };
+        const double ox = first(xh), oy = first(yh), oz = first(zh);
+        const float fx = float(xh - ox), fy = float(yh - oy), fz = float(zh - oz);
+        const float lx = wave_extreme<false>(fx), ly = wave_extreme<false>(fy), lz = wave_extreme<false>(fz);
+        const float ux = wave_extreme<true>(fx), uy = wave_extreme<true>(fy), uz = wave_extreme<true>(fz);
+        const double mx = ox + double(0.5f * (lx + ux)), my = oy + double(0.5f * (ly + uy)),
+                     mz = oz + double(0.5f * (lz + uz));
+        const float bx = 0.5000004f * (ux - lx), by = 0.5000004f * (uy - ly), bz = 0.5000004f * (uz - lz);
+        // rounding of the matrix-core squares: coordinates (2), |c|^2 (3),
+        // |h|^2 - r_list^2 (1), four products and their sums (8), in units of
+        // 2^-24 of (|h| + |c|)^2 + r_list^2 with |h| <= hd, |c| <= hd + r_list
+        const float hd = __builtin_sqrtf(bx * bx + by * by + bz * bz) * 1.00001f;
+        const float reach = 2.f * hd + rl * 1.00001f;
+        const float eps = 16.f * 5.9604645e-8f * (reach * reach + keep2);
+        const float px = float(xh - mx), py = float(yh - my), pz = float(zh - mz);
+        const bool there = lane < hn;
+        L.home[lane] = make_float4(there ? -2.f * px : 0.f, there ? -2.f * py : 0.f, there ? -2.f * pz : 0.f, 1.f);
+        L.hom2[lane] = there ? float(double(px) * px + double(py) * py + double(pz) * pz - rl2) : 1e30f;
+        const int32_t ts = centre + (hb - h0);   // candidate number of the first home
+        int32_t self = 1 << 28;                  // its place in the stage, once staged
+
+        int32_t j = 0;
+        uint32_t im = 0;
+        double cx = 0.0, cy = 0.0, cz = 0.0;
+        auto fetch = [&](int32_t gq) {
+            if (gq >= total) return;
+            int k = 0;
+            if (total <= kNbMap) {
+                k = L.cmap[gq];
+            } else {   // the last cell with rbase <= gq
+#pragma unroll
+                for (int s = kCells > kWave ? 64 : 16; s > 0; s >>= 1) {
+                    const int t = min(k + s, kCells);
+                    k = L.rbase[t] <= gq ? t : k;
+                }
+            }
+            j = gq + L.shift[k];
+            im = *reinterpret_cast<const uint32_t *>(L.img[k]);
+            cx = x[j], cy = x[n + j], cz = x[2 * n + j];
+        };
+        int32_t fill = 0;
+        for (int32_t t0 = 0; t0 < total; t0 += kWave) {
+            fetch(t0 + lane);
+            if (!interior) {
+                cx += double(int8_t(im)) * g.L[0];
+                cy += double(int8_t(im >> 8)) * g.L[1];
+                cz += double(int8_t(im >> 16)) * g.L[2];
+            }
+            const float qx = float(cx - mx), qy = float(cy - my), qz = float(cz - mz);
+            const int32_t jr = j;
+            const float dx = fmaxf(fabsf(qx) - bx, 0.f), dy = fmaxf(fabsf(qy) - by, 0.f),
+                        dz = fmaxf(fabsf(qz) - bz, 0.f);
+            const float d2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
+            const bool keep = t0 + lane < total && (d2 < keep2 || uint32_t(jr - hb) < uint32_t(hn));
+            const uint64_t mk = __builtin_amdgcn_ballot_w64(keep);
+            const int32_t tl = ts - t0;
+            if (tl >= 0 && tl < kWave) self = fill + __popcll(mk & ((uint64_t(1) << tl) - 1));
+            if (keep) {
+                const int32_t at = int32_t(__builtin_amdgcn_mbcnt_hi(
+                    uint32_t(mk >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mk), uint32_t(fill))));
+                L.stage[at] = make_float4(qx, qy, qz, __builtin_fmaf(qz, qz, __builtin_fmaf(qy, qy, qx * qx)));
+                L.stage_j[at] = jr;
+            }
+            fill += __popcll(mk);
+            const bool last = t0 + kWave >= total;
+            if (last && lane >= (fill & (kWave - 1)) && (fill & (kWave - 1))) {
+                // candidates that no home hits fill the last chunk
+                const int32_t at = (fill & ~(kWave - 1)) + lane;
+                L.stage[at] = make_float4(0.f, 0.f, 0.f, 1e30f);
+                L.stage_j[at] = 0;
+            }
+            wave_sync();
+            int32_t done = 0;
+            for (; fill - done >= kWave || (last && done < fill); done += kWave)
+                nm_chunk(L, done, n, x, g, rl2, eps, hb, hn, self - done, rows, uint32_t(row_cap));
+            if (!last && done > 0) {   // the rest moves to the front
+                const int32_t left = fill - done;
+                float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
+                int32_t q = 0;
+                if (lane < left) {
+                    p = L.stage[done + lane];
+                    q = L.stage_j[done + lane];
+                }
+                wave_sync();
+                if (lane < left) {
+                    L.stage[lane] = p;
+                    L.stage_j[lane] = q;
+                }
+                fill = left;
+                self -= done;
+            }
+            wave_sync();
+        }
+        if (lane < hn) {
+            const int32_t len = L.run[lane];
+            count[hb + lane] = len;
+            longest = max(longest, len);
+        }
+        hb += sp.parts * sp.batch;
+        if (hb < h1) homes(min(sp.batch, h1 - hb));
         wave_sync();
     }
-    for (int o = kWave / 2; o > 0; o >>= 1) longest = max(longest, __shfl_xor(longest, o, kWave));
-    // *max_count only grows, so a wave whose longest row does not exceed a
-    // value already there has nothing to add: the check keeps the atomics on
-    // this one word (which the L2 serialises) to a few per launch
-    if (lane == 0 && longest > __hip_atomic_load(max_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-        atomicMax(max_count, longest);
+    return longest;
+}
+
+// One wavefront per cell and part in one-wave blocks, as k_neighbors_small,
+// for boxes of at least 2 reach + 2 cells on every axis: a stencil cell is
+// then one periodic image and no home is further than half a box from a
+// candidate in that image, so the minimum image of the definition is the
+// image of the stencil (it differs only for pairs beyond half a box, which
+// neither counts).  Same rows, same order, bit for bit.
+//
+// What bounds it: instruction issue.  The FP64 test of every home against 64
+// candidates took 8 FP64 operations, two compares and the broadcast of a home
+// from LDS, ~27 vector instructions with the compaction; the squares now come
+// from the matrix cores beside the vector unit (one compare per four homes
+// and 16 candidates, a quarter of an instruction each for the check against
+// rounding), ~10 vector and ~11 scalar instructions.  The build of 1.23 M
+// atoms with voids went from 452 to 315 us (stripped variants: set-up 40,
+// reading and box test 75, squares and rows 195, of which stores 30), of 1 M
+// copper atoms at 5.4 A from 334 to 231 us, of 4,000 atoms from 60 to 33 us.
+// Slower: 128 or 256 candidates read at once (LDS for fewer waves; 490 against
+// 515 and 581 us for the whole rebuild of the void system), the next 64
+// requested ahead (the registers cost more than the wait), 4, 5, 7 or 8 waves
+// per SIMD.
+template <int R>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(6)))
+void k_neighbors(int64_t n, const double *__restrict__ x, GridArgs g, double rl2, NbSplit sp,
+                 const int32_t *__restrict__ cell_start, const int32_t *__restrict__ rank_xyz,
+                 const int32_t *__restrict__ lin2rank, int32_t row_cap, int32_t *__restrict__ idx,
+                 int32_t *__restrict__ count, int32_t *max_count)
+{
+    __shared__ NmLds<R> L;
+    const uint32_t blk = xcd_chunked(blockIdx.x, gridDim.x, kNbXcdChunk);
+    const uint32_t rank = blk / uint32_t(sp.parts), part = blk % uint32_t(sp.parts);
+    nb_longest(nm_cell<R>(L, rank, int32_t(part), n, x, g, rl2, sp, cell_start, rank_xyz, lin2rank, row_cap, idx, count),
+               max_count);
+}
+
+// Wavefronts per cell: one, unless the cells are too few to fill the chip
+// (256 CUs x 4 SIMDs x 2); then batches of 16 homes (8 on the path without
+// matrix cores), as many parts as an average cell has batches.
+NbSplit nb_split(int64_t n, int64_t n_cells, bool small)
+{
+    if (n_cells >= 2048) return {1, kWave};
+    const int32_t batch = small ? 8 : 16;
+    const int64_t parts = (n + n_cells * batch - 1) / (n_cells * batch);
+    return {int32_t(parts < 1 ? 1 : (parts > 8 ? 8 : parts)), batch};
 }
 
 int build_neighbors(const md_grid_t *grid, int64_t n, const double *x, const int32_t *cell_start, int32_t row_cap,
@@ -645,15 +1053,24 @@ int build_neighbors(const md_grid_t *grid, int64_t n, const double *x, const int
     }
     g.reach = grid->reach;
     const double rl2 = grid->r_list * grid->r_list;
-    const double keep2 = rl2 * (1.0 + 1e-9);
     int rc = launch_fill_i32(max_count, 1, 0, s);
     if (rc) return rc;
-    const int64_t per_block = int64_t(kNbWaves) * kNbCellsPerWave;
-    const uint32_t nb = uint32_t((grid->n_cells + per_block - 1) / per_block);
     if (n > 0) {
-        hipLaunchKernelGGL(k_neighbors, dim3(nb), dim3(kNbBlock), 0, s, n, x, g, rl2, keep2, grid->n_cells,
-                           cell_start, ws_ptr<int32_t>(ws, w.rank2lin), ws_ptr<int32_t>(ws, w.lin2rank), row_cap, idx,
-                           count, max_count);
+        const int32_t least = std::min(grid->nc[0], std::min(grid->nc[1], grid->nc[2]));
+        // (rows of a million entries and more: nine slices of them pass a buffer's 32-bit range)
+        const bool small = least < 2 * grid->reach + 2 || row_cap > (1 << 20);
+        const NbSplit sp = nb_split(n, grid->n_cells, small);
+        const dim3 nb(uint32_t(grid->n_cells * sp.parts));
+        const int32_t *xyz = ws_ptr<int32_t>(ws, w.rank2lin), *l2r = ws_ptr<int32_t>(ws, w.lin2rank);
+        if (small)
+            hipLaunchKernelGGL(k_neighbors_small, nb, dim3(kWave), 0, s, n, x, g, rl2, rl2 * (1.0 + 1e-9), sp,
+                               cell_start, xyz, l2r, row_cap, idx, count, max_count);
+        else if (grid->reach == 1)
+            hipLaunchKernelGGL(k_neighbors<1>, nb, dim3(kWave), 0, s, n, x, g, rl2, sp, cell_start, xyz, l2r, row_cap,
+                               idx, count, max_count);
+        else
+            hipLaunchKernelGGL(k_neighbors<2>, nb, dim3(kWave), 0, s, n, x, g, rl2, sp, cell_start, xyz, l2r,
+                               row_cap, idx, count, max_count);
         MD_HIP_TRY(hipGetLastError());
     }
     if (needed) {

@@ -111,3 +111,123 @@ def test_fp64_lj_rows_of_every_length(M, orc):
     oc, ic = orc.neighbors_cells(x, L, 2.8)
     fo, _ = orc.forces_lj(x, L, oc, ic, rc=2.5)
     assert np.linalg.norm(fg - fo) <= 1e-12 * np.linalg.norm(fo)
+
+
+# ---- neighbour lists ----------------------------------------------------------------
+
+def _ordered_rows(M, g, x, cell_start, want, atoms):
+    """Rows of sorted atoms in the list's order: stencil cells x fastest,
+    atoms of a cell in sorted order, kept where `want` (sets of sorted
+    indices) says so."""
+    nc, R = np.array(g.nc[:]), g.reach
+    ranks = M.md_grid_cell_ranks(g)
+    lin = np.empty(g.n_cells, np.int64)
+    lin[ranks] = np.arange(g.n_cells)
+    home = lin[np.searchsorted(cell_start, atoms, side="right") - 1]
+    rows = []
+    for i, l in zip(atoms, home):
+        c = np.array([l % nc[0], (l // nc[0]) % nc[1], l // (nc[0] * nc[1])])
+        row = []
+        for dz in range(-R, R + 1):
+            for dy in range(-R, R + 1):
+                for dx in range(-R, R + 1):
+                    v = (c + (dx, dy, dz)) % nc
+                    r = ranks[v[0] + nc[0] * (v[1] + nc[1] * v[2])]
+                    row += [j for j in range(cell_start[r], cell_start[r + 1]) if j in want[i]]
+        rows.append(row)
+    return rows
+
+
+def _lists(M, orc, x, L, r_list, reach, row_cap):
+    """(grid, cell_start, sorted positions, idx filled with -1 beforehand, counts, longest)"""
+    n = len(x)
+    g = M.md_grid_init(L, r_list, reach)
+    ws = torch.empty(M.md_workspace_bytes(g, n), dtype=torch.uint8, device="cuda")
+    M.md_workspace_init(g, n, ws)
+    xd = torch.tensor(np.ascontiguousarray(x.T), dtype=torch.float64, device="cuda")
+    i32 = lambda k: torch.zeros(k, dtype=torch.int32, device="cuda")   # noqa: E731
+    cell, perm, cs, cnt, mx = i32(n), i32(n), i32(g.n_cells + 1), i32(n), i32(1)
+    M.md_bin_cells(g, n, xd, cell, perm, cs, ws)
+    xs = torch.empty_like(xd)
+    M.md_permute(n, 3, perm, xd, xs, 8)
+    idx = torch.full((M.ell_size(n, row_cap),), -1, dtype=torch.int32, device="cuda")
+    M.md_build_neighbors(g, n, xs, cs, row_cap, idx, cnt, mx, ws)
+    return g, cs.cpu().numpy(), xs.cpu().numpy().T.copy(), idx.cpu().numpy(), cnt.cpu().numpy(), int(mx[0])
+
+
+def _row(idx, i, row_cap):
+    return idx.reshape(-1, row_cap // 8, 8, 8)[i // 8, :, i % 8, :].reshape(-1)
+
+
+LIST_CASES = [
+    # box, r_list, reach, atoms: few homes per cell, about one and two matrix
+    # tiles of 16, three batches of homes and more candidates than the table
+    # of 1,024, 125-cell stencils, enough cells for one wavefront each
+    ((11.3, 12.1, 13.0), 2.8, 1, 150),
+    ((11.3, 12.1, 13.0), 2.8, 1, 1060),
+    ((11.3, 12.1, 13.0), 2.8, 1, 2300),
+    ((16.0, 16.5, 17.0), 3.9, 1, 9000),
+    ((8.5, 9.0, 9.6), 2.8, 2, 700),
+    ((36.5, 36.6, 37.0), 2.8, 1, 33000),
+    # a box of three cells on one axis: the path without matrix cores
+    ((9.0, 12.0, 12.5), 2.9, 1, 1500),
+]
+
+
+@pytest.mark.parametrize("L,r_list,reach,n", LIST_CASES)
+def test_list_rows_in_order(M, orc, L, r_list, reach, n):
+    L = np.array(L)
+    x = orc.wrap(inputs.random_gas(n, L, n), L)
+    cap = 640
+    g, cs, xs, idx, cnt, longest = _lists(M, orc, x, L, r_list, reach, cap)
+    off, ob = orc.neighbors_brute(xs, L, r_list) if n < 10_000 else orc.neighbors_cells(xs, L, r_list)
+    assert np.array_equal(cnt, np.diff(off)) and longest == cnt.max() <= cap
+    atoms = np.random.default_rng(n).choice(n, min(n, 250), replace=False)
+    want = {i: set(ob[off[i]:off[i + 1]].tolist()) for i in atoms}
+    for i, row in zip(atoms, _ordered_rows(M, g, xs, cs, want, atoms)):
+        got = _row(idx, i, cap)
+        assert got[:cnt[i]].tolist() == row, i
+        assert (got[cnt[i]:] == -1).all()          # nothing is written past a row
+
+
+@pytest.mark.parametrize("shell", [4, 6])
+def test_list_cutoff_on_a_shell(M, orc, shell):
+    """r_list equal to a shell radius of a perfect crystal: every pair of the
+    shell is decided by the rounding of its own FP64 r^2."""
+    s = inputs.lj_fcc(ncell=9)
+    a = s.meta["a"]
+    x = orc.wrap(s.x + np.array([0.1, 0.2, 0.3]), s.L)
+    r_list = a * np.sqrt(shell / 2.0)
+    g, cs, xs, idx, cnt, _ = _lists(M, orc, x, s.L, r_list, 1, 128)
+    off, ob = orc.neighbors_brute(xs, s.L, r_list)
+    assert np.array_equal(cnt, np.diff(off))
+    for i in range(len(x)):
+        assert np.array_equal(np.sort(_row(idx, i, 128)[:cnt[i]]), ob[off[i]:off[i + 1]])
+
+
+def test_list_rows_past_the_capacity_are_cut(M, orc):
+    L = np.array((11.3, 12.1, 13.0))
+    n, cap = 1700, 24
+    x = orc.wrap(inputs.random_gas(n, L, 5), L)
+    full = _lists(M, orc, x, L, 2.8, 1, 400)
+    cut = _lists(M, orc, x, L, 2.8, 1, cap)
+    assert cut[5] == full[5] > cap and np.array_equal(cut[4], full[4])
+    for i in range(n):
+        k = min(cap, full[4][i])
+        assert np.array_equal(_row(cut[3], i, cap)[:k], _row(full[3], i, 400)[:k])
+        assert (_row(cut[3], i, cap)[k:] == -1).all()
+
+
+def test_list_with_a_position_that_is_no_number(M, orc):
+    """The atom has no neighbours and is nobody's; all other rows are those of
+    the system without it."""
+    L = np.array((11.3, 12.1, 13.0))
+    x = orc.wrap(inputs.random_gas(900, L, 6), L)
+    x[450] = np.nan
+    _, _, xs, idx, cnt, _ = _lists(M, orc, x, L, 2.8, 1, 200)
+    odd = np.flatnonzero(np.isnan(xs[:, 0]))
+    assert len(odd) == 1 and cnt[odd[0]] == 0
+    rest = np.flatnonzero(~np.isnan(xs[:, 0]))
+    off, ob = orc.neighbors_brute(xs[rest], L, 2.8)
+    for k, i in enumerate(rest):
+        assert np.array_equal(np.sort(_row(idx, i, 200)[:cnt[i]]), rest[ob[off[k]:off[k + 1]]])
