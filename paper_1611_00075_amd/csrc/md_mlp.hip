@@ -52,6 +52,7 @@ constexpr int kOpL1 = 0, kOpL2 = 4, kOpB2 = 12, kOpB1 = 20, kOps = 22;
 constexpr int kTile = 16;                           // atoms per matrix-core tile
 constexpr int kChunk = kTile * (kBlock / kWave);    // atoms per block iteration
 constexpr float kLog2e = 1.4426950408889634f;
+constexpr int kDescUnroll = 5;   // row entries per lane per batch of the descriptor pass
 constexpr int kMaxAtomBlocks = 2048;                // persistent grid of pass 1
 constexpr int kMaxGradRows = 1024;                  // partial-gradient rows (blocks of k_mlp_grad) at most
 constexpr int kGradBlock = 2 * kWave;               // two wavefronts per 32-atom group
@@ -343,25 +344,42 @@ __device__ __forceinline__ f32x4 backward_input(const WeightsLds &L, int lane, c
 
 // Descriptor sums of one atom (unreduced over its 8 lanes), in two phases.
 // (1) The 8 lanes sweep the row; the distances of the pairs within rc are
-// packed into the atom's LDS segment `seg` and, if orow is not NULL, their
-// indices into the atom's compact row (the list pass 2 walks).  (2) The
-// Gaussians of the packed pairs, 8 at a time, so no lane computes a pair
-// beyond rc.  Returns the number of pairs within rc (in all 8 lanes).  All
-// lanes of the wave call it (cnt = 0 for atoms past the end).
-template <int U>
-__device__ __forceinline__ int32_t descriptor(const MlpArgs &p, const uint4 *__restrict__ xs,
-                                              const int32_t *__restrict__ row, int32_t cnt, const uint4 &pi,
-                                              int sub, int lane, float *seg, int32_t *__restrict__ orow,
+// packed into the atom's LDS segment `seg` and, with LIST, their indices into
+// the atom's compact row (the list pass 2 walks).  (2) The Gaussians of the
+// packed pairs, 8 at a time, so no lane computes a pair beyond rc.  Returns
+// the number of pairs within rc (in all 8 lanes).  All lanes of the wave call
+// it (cnt = 0 for atoms past the end).
+//
+// Both row walks go through buffers with 32-bit offsets (entry sub + 8 q of
+// the lane's atom at byte 256 q + 4 lane of its slice's block); a batch's
+// positions are requested before the next batch's entries (see walk_split).
+template <int U, bool LIST>
+__device__ __forceinline__ int32_t descriptor(const MlpArgs &p, const SliceBufs &b, __amdgpu_buffer_rsrc_t orow,
+                                              int32_t cnt, const uint4 &pi, int sub, int lane, float *seg,
                                               float (&G)[kIn])
 {
+    constexpr uint32_t kOut = 0xfffffff0u;   // beyond any buffer here: no memory traffic, zeros
     int32_t base = 0;
+    uint32_t j[U];
+    auto entries = [&](int32_t t0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            j[u] = __builtin_amdgcn_raw_buffer_load_b32(
+                b.row, t0 + u * kSlice + sub < cnt ? uint32_t(t0) * 32u + u * 256u + uint32_t(lane) * 4u : kOut, 0, 0);
+    };
+    entries(0);
     for (int32_t t0 = 0; t0 < cnt; t0 += U * kSlice) {
-        int32_t j[U];
         uint4 pj[U];
+        uint32_t jc[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) j[u] = row[ell_pos(min(t0 + u * kSlice + sub, cnt - 1))];
-#pragma unroll
-        for (int u = 0; u < U; ++u) pj[u] = xs[j[u]];
+        for (int u = 0; u < U; ++u) {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b96(b.xs, j[u] << 4, 0, 0);
+            pj[u] = make_uint4(v[0], v[1], v[2], 0u);
+            jc[u] = j[u];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        entries(t0 + U * kSlice);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             float dx, dy, dz;
@@ -374,7 +392,10 @@ __device__ __forceinline__ int32_t descriptor(const MlpArgs &p, const uint4 *__r
             const int32_t pos = base + __popc(gm & ((1u << sub) - 1u));
             if (__builtin_amdgcn_inverse_ballot_w64(inm)) {
                 seg[pos] = __builtin_amdgcn_sqrtf(r2);
-                if (orow) orow[ell_pos(pos)] = j[u];
+                if (LIST)
+                    __builtin_amdgcn_raw_buffer_store_b32(
+                        jc[u], orow, uint32_t(pos >> 3) * 256u + uint32_t(pos & 7) * 4u + uint32_t(lane >> 3) * 32u, 0,
+                        0);
             }
             base += __popc(gm);
         }
@@ -417,8 +438,9 @@ __device__ __forceinline__ void reduce_scatter8(float (&G)[kIn], int sub, float 
 }
 
 // Pass 1a: raw descriptors G[n][16] of one slice of 8 atoms per wavefront
-// (8 lanes per atom) and, if idx_in is not NULL, the compact list of the
-// pairs within rc.  Dynamic LDS: cap floats per atom of the block.
+// (8 lanes per atom) and, with LIST, the compact list of the pairs within rc.
+// Dynamic LDS: cap floats per atom of the block.
+template <bool LIST>
 __global__ __launch_bounds__(kBlock) void k_mlp_desc(int64_t n, MlpArgs p, const uint4 *__restrict__ xs, int32_t cap,
                                                      const int32_t *__restrict__ idx,
                                                      const int32_t *__restrict__ count, float *__restrict__ G,
@@ -437,9 +459,11 @@ __global__ __launch_bounds__(kBlock) void k_mlp_desc(int64_t n, MlpArgs p, const
     const int32_t cnt = live ? min(count[i], cap) : 0;
     const uint4 pi = live ? xs[i] : make_uint4(0, 0, 0, 0);
     float *seg = seg_lds + (threadIdx.x / kSlice) * cap;
-    const int32_t nin = descriptor<6>(p, xs, live ? ell_row(idx, i, cap) : idx, cnt, pi, sub, lane, seg,
-                                      idx_in && live ? idx_in + (ell_row(idx_in, i, cap) - idx_in) : nullptr, g);
-    if (cnt_in && live && sub == 0) cnt_in[i] = nin;
+    const SliceBufs b = slice_bufs(xs, n, idx, cap, blk);
+    const int32_t nin =
+        descriptor<kDescUnroll, LIST>(p, b, LIST ? slice_bufs(xs, n, idx_in, cap, blk).row : b.row, cnt, pi, sub, lane,
+                                      seg, g);
+    if (LIST && live && sub == 0) cnt_in[i] = nin;
     float v0, v1;
     reduce_scatter8(g, sub, v0, v1);
     if (live) *reinterpret_cast<float2 *>(G + i * kIn + 2 * sub) = make_float2(v0, v1);
@@ -1024,7 +1048,7 @@ int mlp_descriptors(const md_box_t *box, int64_t n, const uint32_t *xs, int32_t 
 {
     if (n == 0) return MD_OK;
     const MlpArgs a = make_args(box, mlp);
-    hipLaunchKernelGGL(k_mlp_desc, dim3(slice_blocks(n)), dim3(kBlock), seg_bytes(cap), s, n, a,
+    hipLaunchKernelGGL(k_mlp_desc<false>, dim3(slice_blocks(n)), dim3(kBlock), seg_bytes(cap), s, n, a,
                        reinterpret_cast<const uint4 *>(xs), cap, idx, count, G, nullptr, nullptr);
     MD_HIP_TRY(hipGetLastError());
     return MD_OK;
@@ -1063,7 +1087,7 @@ int forces_mlp(const md_box_t *box, int64_t n, const uint32_t *xs, int32_t cap, 
         if (!reuse) {
             // pass 1a: descriptors into the dEdG buffer and the compact list;
             // pass 1b: the network overwrites each row with dE/dG in place
-            hipLaunchKernelGGL(k_mlp_desc, dim3(g2), dim3(kBlock), seg_bytes(cap), s, n, a, q, cap, idx, count,
+            hipLaunchKernelGGL(k_mlp_desc<true>, dim3(g2), dim3(kBlock), seg_bytes(cap), s, n, a, q, cap, idx, count,
                                dEdG, idx_in, cnt_in);
             if (mlp->activations == MD_MLP_ACT_FP32)
                 hipLaunchKernelGGL(k_mlp_net<3>, dim3(g1), dim3(kBlock), 0, s, n, a, dEdG, w, e_atom, dEdG,
