@@ -32,6 +32,7 @@
 // cos^2(pi r / 2 rc), with cos and sin from their Taylor series on
 // [0, pi/2] (truncation below 1e-8).
 #include <cmath>
+#include <type_traits>
 
 #include "md_pair.h"
 
@@ -52,6 +53,7 @@ constexpr int kOpL1 = 0, kOpL2 = 4, kOpB2 = 12, kOpB1 = 20, kOps = 22;
 constexpr int kTile = 16;                           // atoms per matrix-core tile
 constexpr int kChunk = kTile * (kBlock / kWave);    // atoms per block iteration
 constexpr float kLog2e = 1.4426950408889634f;
+constexpr int kForceUnroll = 1;   // pairs per lane per batch of the pair pass
 constexpr int kDescUnroll = 5;   // row entries per lane per batch of the descriptor pass
 constexpr int kMaxAtomBlocks = 2048;                // persistent grid of pass 1
 constexpr int kMaxGradRows = 1024;                  // partial-gradient rows (blocks of k_mlp_grad) at most
@@ -150,6 +152,7 @@ struct MlpArgs {
     float ka;               // log2(e) / (2 w^2)
     float alpha;            // log2(e) dmu / w^2
     float q[8];             // exp(-(m + 1/2) dmu^2 / w^2)
+    float Q[9];             // exp(-m^2 dmu^2 / 2 w^2)
     float phi;              // pi / (2 rc)
     float iw2, cw;          // 1 / w^2, dmu / w^2
     float mean[kIn], inv_std[kIn];
@@ -171,6 +174,7 @@ MlpArgs make_args(const md_box_t *box, const md_mlp_t *m)
     a.ka = float(l2e / (2.0 * w2));
     a.alpha = float(l2e * m->dmu / w2);
     for (int k = 0; k < 8; ++k) a.q[k] = float(std::exp(-(k + 0.5) * m->dmu * m->dmu / w2));
+    for (int k = 0; k < 9; ++k) a.Q[k] = float(std::exp(-0.5 * k * k * m->dmu * m->dmu / w2));
     a.phi = float(3.14159265358979323846 / (2.0 * m->rc));
     a.iw2 = float(1.0 / w2);
     a.cw = float(m->dmu / w2);
@@ -544,7 +548,65 @@ void k_mlp_net(int64_t n, MlpArgs p, const float *Gin, const uint16_t *__restric
 
 // ---- pass 2: forces ---------------------------------------------------------
 
-template <int U, bool ENERGY, bool COMP>
+// S0 = sum_k c_k e_k and S1 = sum_k (k - 8) c_k e_k over the 16 Gaussians of a
+// pair, c_k = dE_i/dG_ik + dE_j/dG_jk, t = r - c8.  With u = exp(t dmu / w^2),
+// e_{8+m} = e_8 u^m Q_m and e_{8-m} = e_8 u^-m Q_m, Q_m = exp(-m^2 dmu^2 / 2w^2):
+// with Q folded into the coefficients (di holds c's first term times Q) both
+// sums are polynomials in u and in 1/u, taken with their derivatives by
+// Horner's rule: 16 + 30 operations where forming the Gaussians and both
+// sums took 94.
+__device__ __forceinline__ void basis_sums_folded(const MlpArgs &p, float t, const float (&di)[kIn],
+                                                  const float (&dj)[kIn], float &S0, float &S1)
+{
+    const float e8 = __builtin_amdgcn_exp2f(-p.ka * t * t);
+    const float up = __builtin_amdgcn_exp2f(p.alpha * t), dn = __builtin_amdgcn_exp2f(-p.alpha * t);
+    float c[kIn];
+#pragma unroll
+    for (int k = 0; k < kIn; ++k) c[k] = __builtin_fmaf(dj[k], p.Q[k < 8 ? 8 - k : k - 8], di[k]);
+    // A(u) = sum_{m=0..7} c_{8+m} u^m and A'(u)
+    float A = c[15], dA = 0.f;
+#pragma unroll
+    for (int m = 6; m >= 0; --m) {
+        dA = m == 6 ? A : __builtin_fmaf(dA, up, A);
+        A = __builtin_fmaf(A, up, c[8 + m]);
+    }
+    // v C(v) = sum_{m=1..8} c_{8-m} v^m, v = 1/u, and C'(v)
+    float C = c[0], dC = 0.f;
+#pragma unroll
+    for (int m = 7; m >= 1; --m) {
+        dC = m == 7 ? C : __builtin_fmaf(dC, dn, C);
+        C = __builtin_fmaf(C, dn, c[8 - m]);
+    }
+    S0 = e8 * __builtin_fmaf(C, dn, A);
+    S1 = e8 * __builtin_fmaf(up, dA, -dn * __builtin_fmaf(dn, dC, C));
+}
+
+// The same sums from the Gaussians themselves (di: c's first term): for
+// spacings so wide against the width that Q_8 leaves the FP32 range.
+__device__ __forceinline__ void basis_sums(const MlpArgs &p, float t, const float (&di)[kIn], const float (&dj)[kIn],
+                                           float &S0, float &S1)
+{
+    float e[kIn];
+    gaussians(p, t, e);
+    S0 = S1 = 0.f;
+#pragma unroll
+    for (int k = 0; k < kIn; ++k) {
+        const float qk = (di[k] + dj[k]) * e[k];
+        S0 += qk;
+        S1 = __builtin_fmaf(float(k - 8), qk, S1);
+    }
+}
+
+// A row of dE/dG is 64 bytes.  Gathered by its own lane (four 16-byte loads,
+// every lane in a line of its own) a pair's row passes the texture addresser
+// four times.  Here the four lanes of a quad take the four quarters of one
+// row, straight into LDS (16 rows a load, a 64-byte line each), and each lane
+// then reads its own row back; the quarters of row r lie permuted by r / 2,
+// so that 8 lanes reading the same quarter touch all 32 banks.  With the folded
+// sums 1 M copper atoms (43 M pairs) went from 285 to 262 us (one pair a lane
+// at a time; two 268, three 318); the vector unit and the addressers are then
+// both busy 87 % of the time.
+template <int U, bool FOLD, bool ENERGY, bool COMP>
 __global__ __launch_bounds__(kBlock) void k_mlp_force(int64_t n, MlpArgs p, const uint4 *__restrict__ xs,
                                                       int32_t cap, const int32_t *__restrict__ idx,
                                                       const int32_t *__restrict__ count,
@@ -552,78 +614,98 @@ __global__ __launch_bounds__(kBlock) void k_mlp_force(int64_t n, MlpArgs p, cons
                                                       double *__restrict__ part)
 {
     if (gated(p.gate)) return;
+    __shared__ float4 stage[kBlock / kWave][U][4 * kWave];
     const uint32_t blk = xcd_block(blockIdx.x, gridDim.x);
     const SliceLane sl = slice_lane(blk);
     const int64_t i = sl.i;
-    const int sub = sl.sub;
+    const int sub = sl.sub, lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    float4 (&rows)[U][4 * kWave] = stage[wave];
+
+    const bool live = i < n;
+    const int64_t self = live ? i : 0;
+    const uint4 pi = xs[self];
+    float di[kIn];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float4 v = dEdG[self * 4 + q];
+        di[4 * q] = v.x;
+        di[4 * q + 1] = v.y;
+        di[4 * q + 2] = v.z;
+        di[4 * q + 3] = v.w;
+    }
+    if (FOLD)
+#pragma unroll
+        for (int k = 0; k < kIn; ++k) di[k] *= p.Q[k < 8 ? 8 - k : k - 8];
+    const int32_t cnt = live ? min(count[i], cap) : 0;
+    // rows are fetched by quads, so the wave walks its longest row; the slots
+    // past a lane's own row fetch its own atom and are masked
+    int32_t most = cnt;
+#pragma unroll
+    for (int o = kSlice; o < kWave; o <<= 1) most = max(most, __shfl_xor(most, o, kWave));
+    most = __builtin_amdgcn_readfirstlane(most);
+    const int32_t *row = live ? ell_row(idx, i, cap) : idx;
 
     float fx = 0.f, fy = 0.f, fz = 0.f, cx = 0.f, cy = 0.f, cz = 0.f;
     double w[6] = {0, 0, 0, 0, 0, 0};
-    if (i < n) {
-        const uint4 pi = xs[i];
-        float di[kIn];
+    for (int32_t t0 = 0; t0 < most; t0 += U * kSlice) {
+        int32_t j[U];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float4 v = dEdG[i * 4 + q];
-            di[4 * q] = v.x;
-            di[4 * q + 1] = v.y;
-            di[4 * q + 2] = v.z;
-            di[4 * q + 3] = v.w;
-        }
-        const int32_t cnt = min(count[i], cap);
-        const int32_t *row = ell_row(idx, i, cap);
-        for (int32_t t0 = sub; t0 < cnt; t0 += U * kSlice) {
-            int32_t j[U];
+        for (int u = 0; u < U; ++u)
+            j[u] = t0 + u * kSlice + sub < cnt ? row[ell_pos(t0 + u * kSlice + sub)] : int32_t(self);
+        uint4 pj[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) j[u] = row[ell_pos(min(t0 + u * kSlice, cnt - 1))];
-            uint4 pj[U];
-            float4 dj[U][4];
+        for (int u = 0; u < U; ++u) pj[u] = xs[j[u]];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                pj[u] = xs[j[u]];
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) dj[u][q] = dEdG[int64_t(j[u]) * 4 + q];
+            for (int q = 0; q < 4; ++q) {
+                const int r = 16 * q + lane / 4;   // the row (lane) this quad fetches
+                const int64_t jr = __shfl(j[u], r, kWave);
+                __builtin_amdgcn_global_load_lds(
+                    (const __attribute__((address_space(1))) void *)(dEdG + jr * 4 + ((lane & 3) ^ ((r >> 1) & 3))),
+                    (__attribute__((address_space(3))) void *)(&rows[u][q * kWave]), 16, 0, 0);
             }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                float dx, dy, dz;
-                disp<false>(pi, pj[u], p.ax, p.ay, p.az, dx, dy, dz);
-                const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
-                const bool in = t0 + u * kSlice < cnt && r2 < p.rc2;
-                const float ir = __builtin_amdgcn_rsqf(r2);   // 1/r, and r = r2 / r
-                const float r = r2 * ir;
-                const float t = r - p.c8;
-                float e[kIn];
-                gaussians(p, t, e);
-                const float ph = p.phi * r, zz = ph * ph;
-                const float c = cos_z(zz), s = sin_z(ph, zz);
-                const float fc = c * c, dfc = -2.f * p.phi * s * c;
-                const float dju[kIn] = {dj[u][0].x, dj[u][0].y, dj[u][0].z, dj[u][0].w,
-                                        dj[u][1].x, dj[u][1].y, dj[u][1].z, dj[u][1].w,
-                                        dj[u][2].x, dj[u][2].y, dj[u][2].z, dj[u][2].w,
-                                        dj[u][3].x, dj[u][3].y, dj[u][3].z, dj[u][3].w};
-                // s_ij = sum_k c_k e_k (dfc - fc (t - (k - 8) dmu) / w^2)
-                float S0 = 0.f, S1 = 0.f;
+        for (int u = 0; u < U; ++u) {
+            float dj[kIn];
 #pragma unroll
-                for (int k = 0; k < kIn; ++k) {
-                    const float qk = (di[k] + dju[k]) * e[k];
-                    S0 += qk;
-                    S1 = __builtin_fmaf(float(k - 8), qk, S1);
-                }
-                const float sij = __builtin_fmaf(-fc * t, p.iw2, dfc) * S0 + fc * p.cw * S1;
-                const float gs = in ? -sij * ir : 0.f;
-                acc_add<COMP>(fx, cx, gs, dx);
-                acc_add<COMP>(fy, cy, gs, dy);
-                acc_add<COMP>(fz, cz, gs, dz);
-                if (ENERGY && in) {
-                    w[0] += double(gs * dx * dx); w[1] += double(gs * dy * dy); w[2] += double(gs * dz * dz);
-                    w[3] += double(gs * dx * dy); w[4] += double(gs * dx * dz); w[5] += double(gs * dy * dz);
-                }
+            for (int q = 0; q < 4; ++q) {
+                const float4 v = rows[u][lane * 4 + (q ^ ((lane >> 1) & 3))];
+                dj[4 * q] = v.x;
+                dj[4 * q + 1] = v.y;
+                dj[4 * q + 2] = v.z;
+                dj[4 * q + 3] = v.w;
+            }
+            float dx, dy, dz;
+            disp<false>(pi, pj[u], p.ax, p.ay, p.az, dx, dy, dz);
+            const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
+            const bool in = t0 + u * kSlice + sub < cnt && r2 < p.rc2;
+            const float ir = __builtin_amdgcn_rsqf(r2);   // 1/r, and r = r2 / r
+            const float r = r2 * ir;
+            const float t = r - p.c8;
+            const float ph = p.phi * r, zz = ph * ph;
+            const float c = cos_z(zz), s = sin_z(ph, zz);
+            const float fc = c * c, dfc = -2.f * p.phi * s * c;
+            // s_ij = sum_k c_k e_k (dfc - fc (t - (k - 8) dmu) / w^2)
+            float S0, S1;
+            if (FOLD) basis_sums_folded(p, t, di, dj, S0, S1);
+            else basis_sums(p, t, di, dj, S0, S1);
+            const float sij = __builtin_fmaf(-fc * t, p.iw2, dfc) * S0 + fc * p.cw * S1;
+            const float gs = in ? -sij * ir : 0.f;
+            acc_add<COMP>(fx, cx, gs, dx);
+            acc_add<COMP>(fy, cy, gs, dy);
+            acc_add<COMP>(fz, cz, gs, dz);
+            if (ENERGY && in) {
+                w[0] += double(gs * dx * dx); w[1] += double(gs * dy * dy); w[2] += double(gs * dz * dz);
+                w[3] += double(gs * dx * dy); w[4] += double(gs * dx * dz); w[5] += double(gs * dy * dz);
             }
         }
+        asm volatile("" ::: "memory");   // this batch's rows are read before the next ones arrive
     }
     const double gx = combine(fx, cx), gy = combine(fy, cy), gz = combine(fz, cz);
-    if (sub == 0 && i < n) {
+    if (sub == 0 && live) {
         f[i] = float(gx);
         f[n + i] = float(gy);
         f[2 * n + i] = float(gz);
@@ -1101,18 +1183,20 @@ int forces_mlp(const md_box_t *box, int64_t n, const uint32_t *xs, int32_t cap, 
         // dE/dG is given)
         const int32_t *pidx = reuse ? idx : idx_in;
         const int32_t *pcnt = reuse ? count : cnt_in;
-        if (energy && comp)
-            hipLaunchKernelGGL((k_mlp_force<2, true, true>), dim3(g2), dim3(kBlock), 0, s, n, a, q, cap, pidx, pcnt,
-                               d4, f, part2);
-        else if (energy)
-            hipLaunchKernelGGL((k_mlp_force<2, true, false>), dim3(g2), dim3(kBlock), 0, s, n, a, q, cap, pidx, pcnt,
-                               d4, f, part2);
-        else if (comp)
-            hipLaunchKernelGGL((k_mlp_force<2, false, true>), dim3(g2), dim3(kBlock), 0, s, n, a, q, cap, pidx, pcnt,
-                               d4, f, part2);
-        else
-            hipLaunchKernelGGL((k_mlp_force<2, false, false>), dim3(g2), dim3(kBlock), 0, s, n, a, q, cap, pidx, pcnt,
-                               d4, f, part2);
+        auto force = [&](auto fold, auto en, auto co) {
+            hipLaunchKernelGGL((k_mlp_force<kForceUnroll, decltype(fold)::value, decltype(en)::value, decltype(co)::value>),
+                               dim3(g2), dim3(kBlock), 0, s, n, a, q, cap, pidx, pcnt, d4, f, part2);
+        };
+        using T = std::true_type;
+        using F = std::false_type;
+        // Folded sums where Q_8 = exp(-32 (dmu / w)^2) is above 1e-28 (the
+        // default spacing, dmu = w: 1.3e-14), so that the coefficients keep
+        // the FP32 range; plain ones for wider spacings, and with MD_ENERGY,
+        // whose FP64 virial then has the value it always had (the two differ
+        // in the last bits of a pair's force factor).
+        if (energy) comp ? force(F{}, T{}, T{}) : force(F{}, T{}, F{});
+        else if (a.Q[8] > 1e-28f) comp ? force(T{}, F{}, T{}) : force(T{}, F{}, F{});
+        else comp ? force(F{}, F{}, T{}) : force(F{}, F{}, F{});
         MD_HIP_TRY(hipGetLastError());
     }
     if (energy) return launch_reduce_partials(part1, g1, part2, g2, ev, kReduceEAM, 0.0, s);

@@ -231,3 +231,34 @@ def test_list_with_a_position_that_is_no_number(M, orc):
     off, ob = orc.neighbors_brute(xs[rest], L, 2.8)
     for k, i in enumerate(rest):
         assert np.array_equal(np.sort(_row(idx, i, 200)[:cnt[i]]), rest[ob[off[k]:off[k + 1]]])
+
+
+# ---- learned potential ----------------------------------------------------------------
+
+@pytest.mark.parametrize("dmu,width", [(0.2, 0.2), (0.3, 0.16)])
+def test_learned_pair_pass_over_ragged_rows(M, orc, dmu, width):
+    """Rows of every length (0 to 60 in range) in one slice, and Gaussian
+    spacings on both sides of the rule that folds them into polynomials
+    (exp(-32 (dmu / width)^2) above 1e-28: ratios 1 and 1.9).  FP32 pair
+    terms from the same dE/dG: 1e-5 normwise."""
+    from oracle import mlp as om
+    from paper_1611_00075_amd import mlp as P
+    from paper_1611_00075_amd.sim import Simulation
+    x, L = inputs.graded(12, 3.5, 0.08, seed=31, n_gas=40, gas_sep=2.2)
+    x = orc.wrap(x, L)
+    n = len(x)
+    spec = dict(rc=5.0, mu0=1.4, dmu=dmu, width=width)
+    sim = Simulation(L, x, np.zeros_like(x), potential="mlp", mlp=M.mlp_spec(*spec.values()),
+                     mlp_w=P.bf16_bits(P.init_params(5)).cuda(), skin=1.0, dt=1.0)
+    ids = sim.ids.cpu().numpy()
+    D = np.random.default_rng(3).standard_normal((n, 16)).astype(np.float32)
+    sim.dEdG[:n] = torch.tensor(D[ids], device="cuda")
+    f = torch.full((3, n), np.nan, dtype=torch.float32, device="cuda")
+    M.md_forces_mlp(L, n, sim.xs, sim.row_cap, sim.idx, sim.count, sim.mlp, None, sim.dEdG, None, None, None, f, None,
+                    M.MD_MLP_REUSE, sim.ws)
+    off, idx = orc.neighbors_brute(x, L, 5.0)
+    assert np.diff(off).min() <= 2 and np.diff(off).max() >= 45
+    fo, _ = om.forces(x, L, off, idx, om.Spec(**spec), D.astype(np.float64))
+    fg = np.empty((n, 3))
+    fg[ids] = f.cpu().numpy().T
+    assert np.linalg.norm(fg - fo) <= 1e-5 * np.linalg.norm(fo)
