@@ -55,7 +55,7 @@ constexpr int kChunk = kTile * (kBlock / kWave);    // atoms per block iteration
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kForceUnroll = 1;   // pairs per lane per batch of the pair pass
 constexpr int kDescUnroll = 5;   // row entries per lane per batch of the descriptor pass
-constexpr int kMaxAtomBlocks = 2048;                // persistent grid of pass 1
+constexpr int kMaxAtomBlocks = 512;                // persistent grid of pass 1
 constexpr int kMaxGradRows = 1024;                  // partial-gradient rows (blocks of k_mlp_grad) at most
 constexpr int kGradBlock = 2 * kWave;               // two wavefronts per 32-atom group
 constexpr int kUpdWaves = 16, kUpdBlock = kUpdWaves * kWave;
@@ -224,6 +224,90 @@ __device__ __forceinline__ float sin_z(float ph, float z)
 
 // ---- weights in LDS -------------------------------------------------------
 
+// The parameters as they lie in memory, in LDS.  Rows of W2 are 4 values longer
+// than their 64, which spreads the 16 rows that an operand reads over the
+// banks.  A training block uses each operand once or twice and takes it from
+// here; the network pass reorders them once per block (WeightsLds).
+struct ParamsLds {
+    uint16_t w1[kHid * kIn];
+    uint16_t w2[kHid * (kHid + 4)];
+    float b1[kHid], b2[kHid], w3[kHid];
+    float mean[kIn], inv_std[kIn];
+    float b3;
+};
+
+// w with the block's threads: 16 bytes a load where the pointer allows it
+// (the entry points take any two-byte aligned one), else value by value.
+template <int BLOCK>
+__device__ __forceinline__ void stage_params(ParamsLds &L, const uint16_t *__restrict__ w, const MlpArgs &p)
+{
+    static_assert(oW1 % 8 == 0 && oB1 % 8 == 0 && oW2 % 8 == 0 && oB2 % 8 == 0 && oW3 % 8 == 0 && oB3 % 8 == 0,
+                  "16-byte groups of the parameters");
+    constexpr int S = kHid + 4;
+    auto vec = [&](int e) -> float * { return e < oW2 ? L.b1 + (e - oB1) : (e < oW3 ? L.b2 + (e - oB2) : L.w3 + (e - oW3)); };
+    if ((reinterpret_cast<uintptr_t>(w) & 15u) == 0) {
+#pragma unroll 6
+        for (int q = threadIdx.x; q < oB3 / 8; q += BLOCK) {
+            const uint4 v = reinterpret_cast<const uint4 *>(w)[q];
+            const int e = 8 * q;
+            if (e < oB1) {
+                *reinterpret_cast<uint4 *>(L.w1 + e) = v;
+            } else if (e >= oW2 && e < oB2) {
+                const int k = e - oW2;
+                uint2 *d = reinterpret_cast<uint2 *>(L.w2 + (k >> 6) * S + (k & 63));
+                d[0] = make_uint2(v.x, v.y);
+                d[1] = make_uint2(v.z, v.w);
+            } else {
+                float *d = vec(e);
+                const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    d[2 * j] = __uint_as_float(u[j] << 16);
+                    d[2 * j + 1] = __uint_as_float(u[j] & 0xffff0000u);
+                }
+            }
+        }
+    } else {
+        for (int e = threadIdx.x; e < oB3; e += BLOCK) {
+            const uint16_t v = w[e];
+            if (e < oB1) L.w1[e] = v;
+            else if (e >= oW2 && e < oB2) L.w2[((e - oW2) >> 6) * S + ((e - oW2) & 63)] = v;
+            else *vec(e) = bf16_to_f(v);
+        }
+    }
+    if (threadIdx.x < kIn) {
+        L.mean[threadIdx.x] = p.mean[threadIdx.x];
+        L.inv_std[threadIdx.x] = p.inv_std[threadIdx.x];
+    }
+    if (threadIdx.x == 0) L.b3 = bf16_to_f(w[oB3]);
+    __syncthreads();
+}
+
+// Operand o of `lane` (o is wave-uniform; the 16 inputs of layer 1 fill half of
+// its K slots).
+__device__ __forceinline__ bf16x8 op(const ParamsLds &L, int o, int lane)
+{
+    constexpr int S = kHid + 4;
+    const int g = lane >> 4, li = lane & 15;
+    uint4 v = make_uint4(0u, 0u, 0u, 0u);
+    if (o < kOpL2) {
+        if (g < 2) v = *reinterpret_cast<const uint4 *>(L.w1 + (16 * o + li) * kIn + 8 * g);
+    } else if (o < kOpB2) {
+        const int t = (o - kOpL2) >> 1, s = (o - kOpL2) & 1;
+        const uint16_t *r = L.w2 + (16 * t + li) * S + 32 * s + 4 * g;
+        const uint2 a = *reinterpret_cast<const uint2 *>(r), b = *reinterpret_cast<const uint2 *>(r + 16);
+        v = make_uint4(a.x, a.y, b.x, b.y);
+    } else {   // transposed: eight inputs (features of the layer's output) from as many rows
+        const bool second = o < kOpB1;
+        const int t = second ? (o - kOpB2) >> 1 : 0, s = second ? (o - kOpB2) & 1 : o - kOpB1;
+        const int stride = second ? S : kIn;
+        const uint16_t *r = (second ? L.w2 : L.w1) + (32 * s + 4 * g) * stride + 16 * t + li;
+        const auto two = [&](int k) { return uint32_t(r[k * stride]) | (uint32_t(r[(k + 1) * stride]) << 16); };
+        v = make_uint4(two(0), two(2), two(16), two(18));
+    }
+    return __builtin_bit_cast(bf16x8, v);
+}
+
 struct WeightsLds {
     uint16_t ops[kOps][kWave][8];
     float b1[kHid], b2[kHid], w3[kHid];
@@ -231,34 +315,27 @@ struct WeightsLds {
     float b3;
 };
 
-__device__ void stage_weights(WeightsLds &L, const uint16_t *__restrict__ w, const MlpArgs &p)
+// The operands in order, from the parameters in LDS.  (Gathered from memory,
+// 22 x 512 two-byte loads a block, they took as long as several tiles: 1 M
+// atoms 152 us, now 94.)
+template <int BLOCK>
+__device__ __forceinline__ void stage_weights(WeightsLds &L, ParamsLds &P, const uint16_t *__restrict__ w,
+                                              const MlpArgs &p)
 {
-    for (int e = threadIdx.x; e < kOps * kWave * 8; e += blockDim.x) {
-        const int o = e >> 9, lane = (e >> 3) & (kWave - 1), j = e & 7, g = lane >> 4, li = lane & 15;
-        uint16_t v = 0;
-        if (o < kOpL2) {
-            if (g < 2) v = w[oW1 + (16 * o + li) * kIn + 8 * g + j];
-        } else if (o < kOpB2) {
-            const int t = (o - kOpL2) >> 1, s = (o - kOpL2) & 1;
-            v = w[oW2 + (16 * t + li) * kHid + kslot(s, g, j)];
-        } else if (o < kOpB1) {
-            const int t = (o - kOpB2) >> 1, s = (o - kOpB2) & 1;
-            v = w[oW2 + kslot(s, g, j) * kHid + 16 * t + li];
-        } else {
-            v = w[oW1 + kslot(o - kOpB1, g, j) * kIn + li];
-        }
-        L.ops[o][lane][j] = v;
-    }
-    for (int e = threadIdx.x; e < kHid; e += blockDim.x) {
-        L.b1[e] = bf16_to_f(w[oB1 + e]);
-        L.b2[e] = bf16_to_f(w[oB2 + e]);
-        L.w3[e] = bf16_to_f(w[oW3 + e]);
+    stage_params<BLOCK>(P, w, p);
+    const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    for (int o = wave; o < kOps; o += BLOCK / kWave)
+        *reinterpret_cast<uint4 *>(L.ops[o][lane]) = __builtin_bit_cast(uint4, op(P, o, lane));
+    for (int e = threadIdx.x; e < kHid; e += BLOCK) {
+        L.b1[e] = P.b1[e];
+        L.b2[e] = P.b2[e];
+        L.w3[e] = P.w3[e];
     }
     if (threadIdx.x < kIn) {
         L.mean[threadIdx.x] = p.mean[threadIdx.x];
         L.inv_std[threadIdx.x] = p.inv_std[threadIdx.x];
     }
-    if (threadIdx.x == 0) L.b3 = bf16_to_f(w[oB3]);
+    if (threadIdx.x == 0) L.b3 = P.b3;
     __syncthreads();
 }
 
@@ -486,9 +563,10 @@ void k_mlp_net(int64_t n, MlpArgs p, const float *Gin, const uint16_t *__restric
                float *dEdG, double *__restrict__ part)
 {
     if (gated(p.gate)) return;
-    __shared__ WeightsLds L;
+    __shared__ __attribute__((aligned(16))) WeightsLds L;
+    __shared__ __attribute__((aligned(16))) ParamsLds P;
     __shared__ double red[kBlock / kWave];
-    stage_weights(L, w, p);
+    stage_weights<kBlock>(L, P, w, p);
 
     const uint32_t blk = xcd_block(blockIdx.x, gridDim.x);
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
@@ -721,88 +799,6 @@ __global__ __launch_bounds__(kBlock) void k_mlp_force(int64_t n, MlpArgs p, cons
 
 // ---- training ---------------------------------------------------------------
 
-// The parameters as they lie in memory, in LDS: a training block uses each
-// operand once or twice, so the reordered copy of WeightsLds would cost more
-// than it saves (22 x 512 two-byte gathers from memory per block).  Rows of
-// W2 are 4 values longer than their 64, which spreads the 16 rows that an
-// operand reads over the banks.
-struct GradW {
-    uint16_t w1[kHid * kIn];
-    uint16_t w2[kHid * (kHid + 4)];
-    float b1[kHid], b2[kHid], w3[kHid];
-    float mean[kIn], inv_std[kIn];
-    float b3;
-};
-
-// w with the block's threads: 16 bytes a load where the pointer allows it
-// (the entry points take any two-byte aligned one), else value by value.
-__device__ __forceinline__ void stage_params(GradW &L, const uint16_t *__restrict__ w, const MlpArgs &p)
-{
-    static_assert(oW1 % 8 == 0 && oB1 % 8 == 0 && oW2 % 8 == 0 && oB2 % 8 == 0 && oW3 % 8 == 0 && oB3 % 8 == 0,
-                  "16-byte groups of the parameters");
-    constexpr int S = kHid + 4;
-    auto vec = [&](int e) -> float * { return e < oW2 ? L.b1 + (e - oB1) : (e < oW3 ? L.b2 + (e - oB2) : L.w3 + (e - oW3)); };
-    if ((reinterpret_cast<uintptr_t>(w) & 15u) == 0) {
-#pragma unroll 6
-        for (int q = threadIdx.x; q < oB3 / 8; q += kGradBlock) {
-            const uint4 v = reinterpret_cast<const uint4 *>(w)[q];
-            const int e = 8 * q;
-            if (e < oB1) {
-                *reinterpret_cast<uint4 *>(L.w1 + e) = v;
-            } else if (e >= oW2 && e < oB2) {
-                const int k = e - oW2;
-                uint2 *d = reinterpret_cast<uint2 *>(L.w2 + (k >> 6) * S + (k & 63));
-                d[0] = make_uint2(v.x, v.y);
-                d[1] = make_uint2(v.z, v.w);
-            } else {
-                float *d = vec(e);
-                const uint32_t u[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    d[2 * j] = __uint_as_float(u[j] << 16);
-                    d[2 * j + 1] = __uint_as_float(u[j] & 0xffff0000u);
-                }
-            }
-        }
-    } else {
-        for (int e = threadIdx.x; e < oB3; e += kGradBlock) {
-            const uint16_t v = w[e];
-            if (e < oB1) L.w1[e] = v;
-            else if (e >= oW2 && e < oB2) L.w2[((e - oW2) >> 6) * S + ((e - oW2) & 63)] = v;
-            else *vec(e) = bf16_to_f(v);
-        }
-    }
-    if (threadIdx.x < kIn) {
-        L.mean[threadIdx.x] = p.mean[threadIdx.x];
-        L.inv_std[threadIdx.x] = p.inv_std[threadIdx.x];
-    }
-    if (threadIdx.x == 0) L.b3 = bf16_to_f(w[oB3]);
-    __syncthreads();
-}
-
-// Operand o of `lane`, the values stage_weights puts there (o is a constant
-// after unrolling; the 16 inputs of layer 1 fill half of its K slots).
-__device__ __forceinline__ bf16x8 op(const GradW &L, int o, int lane)
-{
-    constexpr int S = kHid + 4;
-    const int g = lane >> 4, li = lane & 15;
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (o < kOpL2) {
-        if (g < 2) v = *reinterpret_cast<const uint4 *>(L.w1 + (16 * o + li) * kIn + 8 * g);
-    } else if (o < kOpB2) {
-        const int t = (o - kOpL2) >> 1, s = (o - kOpL2) & 1;
-        const uint16_t *r = L.w2 + (16 * t + li) * S + 32 * s + 4 * g;
-        const uint2 a = *reinterpret_cast<const uint2 *>(r), b = *reinterpret_cast<const uint2 *>(r + 16);
-        v = make_uint4(a.x, a.y, b.x, b.y);
-    } else {
-        const int t = (o - kOpB2) >> 1, s = (o - kOpB2) & 1;
-        const uint16_t *r = L.w2 + (32 * s + 4 * g) * S + 16 * t + li;
-        const auto two = [&](int k) { return uint32_t(r[k * S]) | (uint32_t(r[(k + 1) * S]) << 16); };
-        v = make_uint4(two(0), two(2), two(16), two(18));
-    }
-    return __builtin_bit_cast(bf16x8, v);
-}
-
 constexpr int kGradCols = 2 * kTile + 8;   // a row's 32 atoms and padding (banks)
 
 struct GradLds {
@@ -836,7 +832,7 @@ __global__ __launch_bounds__(kGradBlock) void k_mlp_grad(int64_t batch, const in
                                                          const uint16_t *__restrict__ w, float *__restrict__ part,
                                                          double *__restrict__ lpart)
 {
-    __shared__ __attribute__((aligned(16))) GradW L;
+    __shared__ __attribute__((aligned(16))) ParamsLds L;
     __shared__ __attribute__((aligned(16))) GradLds T;
     const int h = threadIdx.x / kWave, lane = threadIdx.x % kWave;   // h: the half of a group, then of the tiles
     const int g = lane >> 4, m = lane & 15;
@@ -860,7 +856,7 @@ __global__ __launch_bounds__(kGradBlock) void k_mlp_grad(int64_t batch, const in
         }
     };
     if (q0 < q1) fetch(q0);
-    stage_params(L, w, p);
+    stage_params<kGradBlock>(L, w, p);
 
     f32x4 gW2[8], gW1[2];
 #pragma unroll

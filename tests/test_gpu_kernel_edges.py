@@ -262,3 +262,25 @@ def test_learned_pair_pass_over_ragged_rows(M, orc, dmu, width):
     fg = np.empty((n, 3))
     fg[ids] = f.cpu().numpy().T
     assert np.linalg.norm(fg - fo) <= 1e-5 * np.linalg.norm(fo)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 64 * 512, 64 * 512 + 1])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_network_at_block_edges(M, orc, n, shift):
+    """Atoms around one 64-atom chunk, one chunk per block of the persistent
+    grid and one more, with parameters at and off a 16-byte boundary, FP32
+    activations: each atom within 2e-5 of the FP64 network."""
+    from oracle import mlp as om
+    from paper_1611_00075_amd import mlp as P
+    rng = np.random.default_rng(n)
+    G = np.abs(rng.standard_normal((n, 16)) * 2.0 + 3.0).astype(np.float32)
+    bits = P.bf16_bits(P.init_params(12, e_mean=-3.4, w3_scale=0.3))
+    w = torch.zeros(M.MD_MLP_NPARAM + 8, dtype=torch.int16, device="cuda")[shift:shift + M.MD_MLP_NPARAM]
+    w.copy_(bits)
+    e = torch.full((n,), np.nan, dtype=torch.float32, device="cuda")
+    d = torch.full((n, 16), np.nan, dtype=torch.float32, device="cuda")
+    M.md_mlp_eval(n, torch.tensor(G, device="cuda"), P.spec(np.zeros(16), np.full(16, 0.25), fp32_activations=True), w, e,
+                  d)
+    eo, do = om.energy(G.astype(np.float64), om.Spec(mean=np.zeros(16), inv_std=np.full(16, 0.25)), P.bf16_values(bits))
+    assert np.abs(e.cpu().numpy() - eo).max() <= 2e-5 * np.abs(eo).max()
+    assert np.abs(d.cpu().numpy() - do).max() <= 2e-5 * np.abs(do).max()
