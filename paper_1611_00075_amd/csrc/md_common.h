@@ -42,18 +42,39 @@ constexpr uint32_t kXcdChunk = 512;
 __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t G) { return xcd_chunked(b, G, kXcdChunk); }
 
 // Device-side skip of a speculative launch: a gated kernel returns at once
-// when *flag == tag or *over > limit (words written earlier on the same
-// stream).
+// when *flag is tag or tag_before, or *over > limit (words written earlier on
+// the same stream).
 struct Gate {
     const int32_t *flag = nullptr;
-    int32_t tag = 0;
+    int32_t tag = 0, tag_before = 0;
     const int32_t *over = nullptr;
     int32_t limit = 0;
 };
 __device__ __forceinline__ bool gated(const Gate &g)
 {
-    return (g.flag && *g.flag == g.tag) || (g.over && *g.over > g.limit);
+    return (g.flag && (*g.flag == g.tag || *g.flag == g.tag_before)) || (g.over && *g.over > g.limit);
 }
+
+// A step's rebuild flag in one host word: the step's tag and two bits, so that
+// the word is complete whenever the host sees it.
+__host__ __device__ inline uint32_t flag_word(int32_t tag, bool moved, bool bad)
+{
+    return (uint32_t(tag) << 2) | (moved ? 1u : 0u) | (bad ? 2u : 0u);
+}
+__device__ __forceinline__ void post_flag_word(uint32_t *word, int32_t tag, bool moved, bool bad)
+{
+    __hip_atomic_store(word, flag_word(tag, moved, bad), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// What a kick-drift of the native driver does beyond md_integrate's: with
+// `word`, post the flag of the previous step (tag) there and do nothing if it
+// is set; driven: status[0] also tells of non-finite positions; first: of
+// those found before this run.
+struct FlagPost {
+    uint32_t *word = nullptr;
+    int32_t tag = 0;
+    bool driven = false, first = false;
+};
 
 // Orders the LDS accesses of one wavefront around this point (the lanes of a
 // wave exchange data through LDS without a block barrier).
@@ -213,6 +234,6 @@ int mlp_grad_update(int64_t, const int32_t *, const float *, const float *, cons
 int run(md_system_t *sys, int64_t steps, hipStream_t s);
 int kick_drift(const md_box_t *box, int64_t n, double *x, double *v, const void *f, bool f64, double kick, double dt,
                const double *xref, double half_skin_sq, int32_t *status, int32_t tag, uint32_t *xs, hipStream_t s,
-               bool keep_element = false);
+               bool keep_element = false, const FlagPost &post = {});
 
 }  // namespace md

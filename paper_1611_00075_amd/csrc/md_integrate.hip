@@ -11,6 +11,7 @@ struct DriftArgs {
     double k[3];           // 2^32 / L, scaled coordinates
     double half_skin_sq;
     int32_t tag;
+    FlagPost post;         // the previous step's flag (native driver)
 };
 
 __device__ __forceinline__ double minimg_d(double d, double L, double hL)
@@ -30,13 +31,31 @@ __global__ __launch_bounds__(kBlock) void k_kick_drift(int64_t n, double *__rest
 {
     const int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
     bool moved = false, bad = false;
+    const int32_t seen = a.post.word ? status[0] : 0;
+    double p[3] = {0, 0, 0}, u[3] = {0, 0, 0}, fc[3] = {0, 0, 0};
     if (i < n) {
-        double p[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            double vc = v[c * n + i] + a.hk * double(f[c * n + i]);
+            p[c] = x[c * n + i];
+            u[c] = v[c * n + i];
+            fc[c] = double(f[c * n + i]);
+        }
+    }
+    if (a.post.word) {
+        // Queued ahead of the host: the previous step's flag goes to the host
+        // from here, and when that step asks for a build (or met a non-finite
+        // position) its state stays as it is.  Blocks of this launch write
+        // status only if it is not so, and then another tag.
+        const bool stop = seen == a.post.tag;
+        if (blockIdx.x == 0 && threadIdx.x == 0) post_flag_word(a.post.word, a.post.tag, stop, stop && status[1] != 0);
+        if (stop) return;
+    }
+    if (i < n) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double vc = u[c] + a.hk * fc[c];
             v[c * n + i] = vc;
-            p[c] = x[c * n + i] + a.dt * vc;
+            p[c] = p[c] + a.dt * vc;
             x[c * n + i] = p[c];
             bad |= !isfinite(p[c]);
         }
@@ -51,7 +70,9 @@ __global__ __launch_bounds__(kBlock) void k_kick_drift(int64_t n, double *__rest
                                uint32_t(uint64_t(__double2ll_rn(p[1] * a.k[1]))),
                                uint32_t(uint64_t(__double2ll_rn(p[2] * a.k[2]))), KEEP ? xs[i].w & 1u : 0u);
     }
-    // one store per wave that saw the condition (idempotent values)
+    // one store per wave that saw the condition (idempotent values); under the
+    // driver a non-finite position, or one met before this run, stops like a build
+    if (a.post.driven) moved |= bad || (a.post.first && i == 0 && status[1] != 0);
     if (__ballot(moved) && (threadIdx.x % kWave) == 0) status[0] = a.tag;
     if (__ballot(bad) && (threadIdx.x % kWave) == 0) atomicOr(&status[1], 1);
 }
@@ -87,7 +108,7 @@ __global__ __launch_bounds__(kBlock) void k_kick(int64_t n, double *__restrict__
 // previous step is fused in (same forces).
 int kick_drift(const md_box_t *box, int64_t n, double *x, double *v, const void *f, bool f64, double kick, double dt,
                const double *xref, double half_skin_sq, int32_t *status, int32_t tag, uint32_t *xs, hipStream_t s,
-               bool keep_element)
+               bool keep_element, const FlagPost &post)
 {
     const uint32_t gb = uint32_t((n + kBlock - 1) / kBlock);
     if (n <= 0) return MD_OK;
@@ -101,6 +122,7 @@ int kick_drift(const md_box_t *box, int64_t n, double *x, double *v, const void 
     }
     a.half_skin_sq = half_skin_sq;
     a.tag = tag;
+    a.post = post;
     uint4 *q = reinterpret_cast<uint4 *>(xs);
     if (f64)
         hipLaunchKernelGGL((k_kick_drift<double, false>), dim3(gb), dim3(kBlock), 0, s, n, x, v,
