@@ -53,24 +53,35 @@ __global__ __launch_bounds__(kBlock) void k_bin_assign(int64_t n, double *x, Gri
     const int32_t r = lin2rank[lin];
     cell[i] = r;
     // one atomic per distinct cell of the wave (atoms arrive nearly sorted):
-    // the first remaining lane claims a run of slots for all lanes of its
-    // cell, which take consecutive slots in lane order
+    // the first lane of a cell claims a run of slots for all lanes of the cell,
+    // which take consecutive slots in lane order.  The lanes are grouped first
+    // and the claims of all groups made by one instruction: made one group after
+    // another, their round trips to the L2 (~6 a wave) were the kernel's time.
+    const int lane = threadIdx.x % kWave;
+    int leader = lane;
+    uint32_t before = 0;
+    int32_t members = 0;
     uint64_t todo = __ballot(true);
     while (todo) {
-        const int leader = __builtin_ctzll(todo);
-        const int32_t rc = __builtin_amdgcn_readlane(r, leader);
+        const int first = __builtin_ctzll(todo);
+        const int32_t rc = __builtin_amdgcn_readlane(r, first);
         const uint64_t same = __ballot(r == rc) & todo;
-        int32_t base = 0;
-        if ((threadIdx.x % kWave) == leader) base = atomicAdd(&cnt[rc], __popcll(same));
-        base = __builtin_amdgcn_readlane(base, leader);
-        if (r == rc && ((todo >> (threadIdx.x % kWave)) & 1u))
-            slot[i] = base + __builtin_amdgcn_mbcnt_hi(uint32_t(same >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(same), 0u));
+        if (r == rc && ((todo >> lane) & 1u)) {
+            leader = first;
+            members = __popcll(same);
+            before = __builtin_amdgcn_mbcnt_hi(uint32_t(same >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(same), 0u));
+        }
         todo &= ~same;
     }
+    int32_t base = 0;
+    if (leader == lane) base = atomicAdd(&cnt[r], members);
+    slot[i] = __shfl(base, leader, kWave) + int32_t(before);
 }
 
-__global__ __launch_bounds__(kBlock) void k_bin_scatter(int64_t n, const int32_t *cell, const int32_t *slot,
-                                                        const int32_t *cell_start, int32_t *tmp)
+__global__ __launch_bounds__(kBlock) void k_bin_scatter(int64_t n, const int32_t *__restrict__ cell,
+                                                        const int32_t *__restrict__ slot,
+                                                        const int32_t *__restrict__ cell_start,
+                                                        int32_t *__restrict__ tmp)
 {
     const int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
     if (i >= n) return;
@@ -79,8 +90,10 @@ __global__ __launch_bounds__(kBlock) void k_bin_scatter(int64_t n, const int32_t
 
 // The atomic slots give an arbitrary order inside each cell; restore input
 // order (stability) by ranking each atom among the members of its cell.
-__global__ __launch_bounds__(kBlock) void k_bin_stable(int64_t n, const int32_t *cell, const int32_t *tmp,
-                                                       const int32_t *cell_start, int32_t *perm)
+__global__ __launch_bounds__(kBlock) void k_bin_stable(int64_t n, const int32_t *__restrict__ cell,
+                                                       const int32_t *__restrict__ tmp,
+                                                       const int32_t *__restrict__ cell_start,
+                                                       int32_t *__restrict__ perm)
 {
     const int64_t p = int64_t(blockIdx.x) * kBlock + threadIdx.x;
     if (p >= n) return;
@@ -88,7 +101,13 @@ __global__ __launch_bounds__(kBlock) void k_bin_stable(int64_t n, const int32_t 
     const int32_t c = cell[i];
     const int32_t s0 = cell_start[c], s1 = cell_start[c + 1];
     int32_t rank = 0;
-    for (int32_t q = s0; q < s1; ++q) rank += tmp[q] < i;
+    for (int32_t q = s0; q < s1; q += 8) {   // eight loads in flight
+        int32_t m[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) m[k] = tmp[min(q + k, s1 - 1)];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) rank += q + k < s1 && m[k] < i;
+    }
     perm[s0 + rank] = i;
 }
 

@@ -284,3 +284,47 @@ def test_network_at_block_edges(M, orc, n, shift):
     eo, do = om.energy(G.astype(np.float64), om.Spec(mean=np.zeros(16), inv_std=np.full(16, 0.25)), P.bf16_values(bits))
     assert np.abs(e.cpu().numpy() - eo).max() <= 2e-5 * np.abs(eo).max()
     assert np.abs(d.cpu().numpy() - do).max() <= 2e-5 * np.abs(do).max()
+
+
+# ---- native driver ---------------------------------------------------------------------------
+
+@pytest.mark.parametrize("fp64", [False, True])
+def test_run_ahead_of_the_flag(M, fp64):
+    """With pinned memory the next step is queued before a step's flag is
+    read, without it the flag is copied first: same bits, builds and capacity
+    growth included, for runs of one, two and many steps."""
+    from paper_1611_00075_amd.sim import Simulation
+    s = inputs.lj_fcc(ncell=7, T=2.0)
+    out = []
+    for pinned in (True, False):
+        sim = Simulation(s.L, s.x, s.v, pair_fp64=fp64, row_cap=72, list_slack=1.0)
+        if not pinned:
+            sim._flag_host = None
+        for k in (1, 2, 1, 40, 7):
+            sim.run(k)
+        out.append((sim.builds, sim.row_cap, sim.positions(), sim.velocities(), sim.forces()))
+    assert out[0][:2] == out[1][:2] and out[0][0] > 4
+    assert all(np.array_equal(a, b) for a, b in zip(out[0][2:], out[1][2:]))
+
+
+@pytest.mark.parametrize("when", [0, 3])
+def test_run_ahead_stops_at_a_position_that_is_no_number(M, when):
+    """A non-finite position ends the run at its own step: the state is that of
+    the flow without pinned memory, not one step further."""
+    from paper_1611_00075_amd.sim import Simulation
+    s = inputs.lj_fcc(ncell=6)
+    out = []
+    for pinned in (True, False):
+        sim = Simulation(s.L, s.x, s.v)
+        if not pinned:
+            sim._flag_host = None
+        if when:
+            sim.run(when)
+        sim.v[1, 17] = float("inf")
+        with pytest.raises(M.MDError) as e:
+            sim.run(10)
+        assert e.value.code == M.MD_ERR_NONFINITE
+        assert sim._sys.step == when
+        out.append((sim.x.cpu().numpy(), sim.v.cpu().numpy()))
+    for a, b in zip(*out):
+        assert np.array_equal(a, b, equal_nan=True)
