@@ -516,8 +516,8 @@ typedef struct md_dd {
     int32_t *idx;                /* device [slot_cap * row_cap] */
     int64_t ghost_cap;           /* capacity of the ghost entry arrays */
     int32_t *gh_src, *gh_slot, *gh_code, *gh_src_slot;   /* device [ghost_cap] */
-    double *send, *recv;         /* device [3 * ghost_cap] */
-    uint32_t *send_w, *recv_w;   /* device [ghost_cap] */
+    double *send, *recv;         /* device [3 * ghost_cap]: message buffers of an exchange */
+    uint32_t *send_w, *recv_w;   /* device [ghost_cap]       between devices (unused on one) */
     void *vws;                   /* workspace of vgrid for slot_cap atoms (md_dd_workspace_init) */
     size_t vws_bytes;
     void *dws;                   /* scratch of md_dd_scratch_bytes */
@@ -562,10 +562,10 @@ int md_dd_workspace_init(md_dd_t *dd, void *stream);
 int md_dd_rebuild(md_dd_t *dd, void *stream);
 
 /* Forces of the current positions in the asynchronous order: local
- * coordinates scaled into the brick frames, ghost coordinates packed,
- * copied and unpacked on `comm` while the inner atoms' forces run on
- * `stream`, then the outer atoms' (FS: both passes so split, with the F'
- * of ghosts exchanged on `comm` between them).  f, rho, fprime are indexed
+ * coordinates scaled into the brick frames, ghost coordinates exchanged on
+ * `comm` (on one device straight from the atom to its ghosts) while the inner
+ * atoms' forces run on `stream`, then the outer atoms' (FS: both passes so
+ * split, with the F' of ghosts exchanged on `comm` between them).  f, rho, fprime are indexed
  * like x.  With MD_ENERGY in flags, ev[8] as md_forces_lj / md_forces_eam
  * over all atoms.  `comm` may equal `stream`. */
 int md_dd_forces(md_dd_t *dd, double *ev, int32_t flags, void *stream,
@@ -573,7 +573,8 @@ int md_dd_forces(md_dd_t *dd, double *ev, int32_t flags, void *stream,
 
 /* `steps` velocity-Verlet steps (dt, accel as md_integrate) with the
  * displacement rebuild rule (skin/2) checked after every drift (the flag
- * is read back each step), md_dd_rebuild when it fires, md_dd_forces.
+ * is read back each step, while the inner atoms' first pass runs),
+ * md_dd_rebuild when it fires, md_dd_forces.
  * A build that reports MD_ERR_CAPACITY returns at once with phase = 2:
  * grow the buffers and call again; the pending step is completed first. */
 int md_dd_run(md_dd_t *dd, int64_t steps, double dt, double accel,

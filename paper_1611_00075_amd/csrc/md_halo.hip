@@ -1,6 +1,5 @@
 // Domain decomposition on one device: bricks with ghost layers, the halo
-// exchange (pack, transfer, unpack) and the inner/outer split of the force
-// step (Sec. 2.1's hybrid algorithm; its steps pack boundary coordinates,
+// exchange and the inner/outer split of the force step (Sec. 2.1's hybrid algorithm; its steps pack boundary coordinates,
 // send, receive, compute forces inside the domain, wait, compute forces
 // across the boundary, wait).
 //
@@ -20,6 +19,7 @@
 namespace md {
 namespace {
 
+constexpr int kBuildFirst = 1;   // a force evaluation given up because its step asks for a build
 constexpr int kDirs = 27;
 constexpr int kSelf = 13;
 
@@ -211,16 +211,18 @@ __global__ __launch_bounds__(kBlock) void k_dd_assemble(int64_t m, int64_t nt, i
     }
 }
 
-// after a brick's sort: where its atoms came from (gperm) and where its
-// ghosts went (gh_slot)
+// after a brick's sort: where its atoms came from (gperm), where its ghosts
+// went (gh_slot) and how many atoms lie in inner cells
 // (the cell order puts a brick's own atoms first; an atom on the wrong side
 // of nt would be a broken invariant: it is flagged and not written)
 __global__ __launch_bounds__(kBlock) void k_dd_after_sort(int64_t m, int64_t nt, int64_t b0, int64_t g0,
                                                           int64_t slot0, const int32_t *perm, int32_t *gperm,
-                                                          int32_t *gh_slot, int32_t *bad)
+                                                          int32_t *gh_slot, int32_t *bad, const int32_t *inner_end,
+                                                          int32_t *n_inner)
 {
     const int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x;
     if (k >= m) return;
+    if (k == 0) *n_inner = *inner_end;
     const int32_t a = perm[k];
     if ((k < nt) != (a < nt) || a < 0 || a >= m) {
         atomicOr(bad, 1);
@@ -283,10 +285,11 @@ __global__ __launch_bounds__(kBlock) void k_dd_scale_local(int64_t n, const doub
 
 // velocity-Verlet kick (hk = the half kicks due, dt/2 or dt, times the
 // acceleration per unit force) and drift, the displacement rebuild check
-// against xref (status[0] = 1), and the new local coordinates written
+// against xref (status[0] = tag), and the new local coordinates written
 // straight into the brick frames (what k_dd_scale_local does)
 struct DdDrift {
     double hk, dt, hs2, L[3], hL[3];
+    int32_t tag;
 };
 
 __global__ __launch_bounds__(kBlock) void k_dd_kick_drift(int64_t n, double *x, double *v, const float *f,
@@ -316,43 +319,37 @@ __global__ __launch_bounds__(kBlock) void k_dd_kick_drift(int64_t n, double *x, 
         xs[slot0[b] + (i - bstart[b])] = make_uint4(to_fixed(p[0] + o[0], sc.k[0]), to_fixed(p[1] + o[1], sc.k[1]),
                                                     to_fixed(p[2] + o[2], sc.k[2]), 0u);
     }
-    if (__ballot(moved) && (threadIdx.x % kWave) == 0) status[0] = 1;
+    if (__ballot(moved) && (threadIdx.x % kWave) == 0) status[0] = a.tag;
     if (__ballot(bad) && (threadIdx.x % kWave) == 0) atomicOr(&status[1], 1);
 }
 
-__global__ __launch_bounds__(kBlock) void k_dd_pack(int64_t m, const double *x, int64_t n, const int32_t *src,
-                                                    double *send)
+// The halo exchange on one device: pack, transfer and unpack in one pass (a
+// ghost's position is read where its atom lies and written, shifted and
+// scaled, where the ghost lies).  As three steps through a message buffer the
+// two exchanges of a step were four kernels of 6 us and two copies of 4 us at
+// 500,000 atoms in 8 bricks.
+__global__ __launch_bounds__(kBlock) void k_dd_exchange(int64_t m, const double *__restrict__ x, int64_t n,
+                                                        const int32_t *__restrict__ src,
+                                                        const int32_t *__restrict__ slot,
+                                                        const int32_t *__restrict__ code,
+                                                        const double *__restrict__ off, Scale sc,
+                                                        uint4 *__restrict__ xs)
 {
     const int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x;
     if (k >= m) return;
-    const int32_t j = src[k];
-    send[k] = x[j];
-    send[m + k] = x[n + j];
-    send[2 * m + k] = x[2 * n + j];
-}
-
-__global__ __launch_bounds__(kBlock) void k_dd_unpack(int64_t m, const double *recv, const int32_t *slot,
-                                                      const int32_t *code, const double *off, Scale sc, uint4 *xs)
-{
-    const int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-    if (k >= m) return;
+    const int64_t j = src[k];
     const double *o = off + code[k] * 3;
-    xs[slot[k]] = make_uint4(to_fixed(recv[k] + o[0], sc.k[0]), to_fixed(recv[m + k] + o[1], sc.k[1]),
-                             to_fixed(recv[2 * m + k] + o[2], sc.k[2]), 0u);
+    xs[slot[k]] = make_uint4(to_fixed(x[j] + o[0], sc.k[0]), to_fixed(x[n + j] + o[1], sc.k[1]),
+                             to_fixed(x[2 * n + j] + o[2], sc.k[2]), 0u);
 }
 
-__global__ __launch_bounds__(kBlock) void k_dd_pack_w(int64_t m, const uint4 *xs, const int32_t *src_slot,
-                                                      uint32_t *send)
+// The fourth words (F') of the atoms that others hold as ghosts (source slots
+// hold atoms, target slots ghosts: no word is both read and written).
+__global__ __launch_bounds__(kBlock) void k_dd_exchange_w(int64_t m, const int32_t *__restrict__ src_slot,
+                                                          const int32_t *__restrict__ slot, uint4 *xs)
 {
     const int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-    if (k < m) send[k] = xs[src_slot[k]].w;
-}
-
-__global__ __launch_bounds__(kBlock) void k_dd_unpack_w(int64_t m, const uint32_t *recv, const int32_t *slot,
-                                                        uint4 *xs)
-{
-    const int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-    if (k < m) xs[slot[k]].w = recv[k];
+    if (k < m) xs[slot[k]].w = xs[src_slot[k]].w;
 }
 
 inline uint32_t blocks(int64_t n) { return uint32_t((n + kBlock - 1) / kBlock); }
@@ -419,7 +416,7 @@ DdScratch scratch_layout(const md_dd_t *dd)
     l.inv = take(size_t(n) * 4);
     l.part1 = take(size_t(l.rows) * 8 * 8);
     l.part2 = take(size_t(l.rows) * 8 * 8);
-    l.word = take(64);
+    l.word = take(size_t(2 * MD_DD_MAX_BRICKS + 1) * 4);
     l.tab_in = take(sizeof(BrickTab));
     l.tab_out = take(sizeof(BrickTab));
     l.total = o;
@@ -660,37 +657,37 @@ int md_dd_rebuild(md_dd_t *dd, void *stream)
     int32_t *cstart = ws_ptr<int32_t>(ws, l.cstart), *gperm = ws_ptr<int32_t>(ws, l.gperm);
     int32_t *word = ws_ptr<int32_t>(ws, l.word);
     const double *off = ws_ptr<double>(ws, l.off);
-    int32_t longest_all = 0;
-    int32_t *bad = word + 8;
-    if (int rc = launch_fill_i32(bad, 1, 0, s)) return rc;
+    // words of the bricks, read back once: longest row, atoms in inner cells;
+    // then the broken-invariant flag
+    int32_t *longest = word, *ninner = word + MD_DD_MAX_BRICKS, *bad = word + 2 * MD_DD_MAX_BRICKS;
+    std::vector<int32_t> hw(size_t(2 * MD_DD_MAX_BRICKS + 1));
+    if (int rc = launch_fill_i32(word, int64_t(hw.size()), 0, s)) return rc;
     for (int t = 0; t < P; ++t) {
         const int64_t nt = dd->brick_start[t + 1] - dd->brick_start[t];
         const int64_t gt = dd->ghost_start[t + 1] - dd->ghost_start[t];
         const int64_t m = nt + gt;
-        dd->n_inner[t] = 0;
         if (m == 0) continue;
         hipLaunchKernelGGL(k_dd_assemble, dim3(blocks(m)), dim3(kBlock), 0, s, m, nt, dd->brick_start[t],
                            dd->ghost_start[t], dd->x, n, dd->gh_src, dd->gh_code, off, t, g, xt, xb);
         MD_HIP_TRY(hipGetLastError());
         if (int rc = bin_cells(&dd->vgrid, m, xb, cell, permt, cstart, dd->vws, wl, s)) return rc;
         if (int rc = permute(m, 3, permt, xt, xsorted, 8, s)) return rc;
-        int32_t needed = 0;
-        const int rc = build_neighbors(&dd->vgrid, m, xsorted, cstart, dd->row_cap, dd->idx + dd->slot0[t] * dd->row_cap,
-                                       dd->count + dd->slot0[t], word, &needed, dd->vws, wl, s);
-        if (rc != MD_OK && rc != MD_ERR_CAPACITY) return rc;
-        longest_all = std::max(longest_all, needed);
-        int32_t ni = 0;
-        MD_HIP_TRY(hipMemcpyAsync(&ni, cstart + dd->inner_cells, 4, hipMemcpyDeviceToHost, s));
+        if (int rc = build_neighbors(&dd->vgrid, m, xsorted, cstart, dd->row_cap, dd->idx + dd->slot0[t] * dd->row_cap,
+                                     dd->count + dd->slot0[t], longest + t, nullptr, dd->vws, wl, s))
+            return rc;
         hipLaunchKernelGGL(k_dd_after_sort, dim3(blocks(m)), dim3(kBlock), 0, s, m, nt, dd->brick_start[t],
-                           dd->ghost_start[t], dd->slot0[t], permt, gperm, dd->gh_slot, bad);
+                           dd->ghost_start[t], dd->slot0[t], permt, gperm, dd->gh_slot, bad, cstart + dd->inner_cells,
+                           ninner + t);
         MD_HIP_TRY(hipGetLastError());
-        MD_HIP_TRY(hipStreamSynchronize(s));
-        dd->n_inner[t] = ni;
     }
-    int32_t broken = 0;
-    MD_HIP_TRY(hipMemcpyAsync(&broken, bad, 4, hipMemcpyDeviceToHost, s));
+    MD_HIP_TRY(hipMemcpyAsync(hw.data(), word, hw.size() * 4, hipMemcpyDeviceToHost, s));
     MD_HIP_TRY(hipStreamSynchronize(s));
-    if (broken) return MD_ERR_ARG;
+    int32_t longest_all = 0;
+    for (int t = 0; t < P; ++t) {
+        longest_all = std::max(longest_all, hw[size_t(t)]);
+        dd->n_inner[t] = hw[size_t(MD_DD_MAX_BRICKS + t)];
+    }
+    if (hw[size_t(2 * MD_DD_MAX_BRICKS)]) return MD_ERR_ARG;
     if (longest_all > dd->row_cap) {
         dd->row_cap_needed = longest_all;
         return MD_ERR_CAPACITY;
@@ -724,17 +721,16 @@ int md_dd_rebuild(md_dd_t *dd, void *stream)
     return MD_OK;
 }
 
+extern "C++" {
 namespace {
-int dd_forces(md_dd_t *dd, double *ev, int32_t flags, void *stream, void *comm, bool scale_local);
-}
 
-int md_dd_forces(md_dd_t *dd, double *ev, int32_t flags, void *stream, void *comm)
-{
-    return dd_forces(dd, ev, flags, stream, comm, true);
-}
-
-namespace {
-int dd_forces(md_dd_t *dd, double *ev, int32_t flags, void *stream, void *comm, bool scale_local)
+// `scale_local`: the local coordinates are not in the brick frames yet.  Once
+// the exchange and the first pass over the inner atoms are queued (that pass
+// behind `gate`), `check(comm)` is called, which may wait for the communication
+// stream; a non-zero result ends the evaluation there and is returned.
+template <class Check>
+int dd_forces(md_dd_t *dd, double *ev, int32_t flags, void *stream, void *comm, bool scale_local, Gate gate,
+              Check &&check)
 {
     if (!dd || dd->n < 1 || !dd->f || (dd->potential != MD_POT_LJ && dd->potential != MD_POT_EAM)) return MD_ERR_ARG;
     if (dd->potential == MD_POT_EAM && (!dd->rho || !dd->fprime)) return MD_ERR_ARG;
@@ -762,13 +758,11 @@ int dd_forces(md_dd_t *dd, double *ev, int32_t flags, void *stream, void *comm, 
         MD_HIP_TRY(hipGetLastError());
     }
     MD_HIP_TRY(hipEventRecord(eL, s));
-    // halo positions: pack, transfer, unpack on the communication stream
+    // halo positions on the communication stream
     MD_HIP_TRY(hipStreamWaitEvent(sc, eL, 0));
     if (G > 0) {
-        hipLaunchKernelGGL(k_dd_pack, dim3(blocks(G)), dim3(kBlock), 0, sc, G, dd->x, n, dd->gh_src, dd->send);
-        MD_HIP_TRY(hipMemcpyAsync(dd->recv, dd->send, size_t(3 * G) * 8, hipMemcpyDeviceToDevice, sc));
-        hipLaunchKernelGGL(k_dd_unpack, dim3(blocks(G)), dim3(kBlock), 0, sc, G, dd->recv, dd->gh_slot, dd->gh_code,
-                           off, scl, xs);
+        hipLaunchKernelGGL(k_dd_exchange, dim3(blocks(G)), dim3(kBlock), 0, sc, G, dd->x, n, dd->gh_src, dd->gh_slot,
+                           dd->gh_code, off, scl, xs);
         MD_HIP_TRY(hipGetLastError());
     }
     MD_HIP_TRY(hipEventRecord(eH, sc));
@@ -780,7 +774,7 @@ int dd_forces(md_dd_t *dd, double *ev, int32_t flags, void *stream, void *comm, 
     if (int64_t(gb_in) + gb_out > l.rows) return MD_ERR_WORKSPACE;
     const BrickTab *tab_in = ws_ptr<BrickTab>(ws, l.tab_in), *tab_out = ws_ptr<BrickTab>(ws, l.tab_out);
     // one phase (inner or outer atoms of every brick) of one pass, one launch
-    auto phase = [&](int pass, bool inner) -> int {
+    auto phase = [&](int pass, bool inner, Gate gate = {}) -> int {
         const BrickTab *tab = inner ? tab_in : tab_out;
         const uint32_t gb = inner ? gb_in : gb_out;
         int64_t &rows = pass == 2 ? rows2 : rows1;
@@ -788,15 +782,16 @@ int dd_forces(md_dd_t *dd, double *ev, int32_t flags, void *stream, void *comm, 
         int rc;
         if (dd->potential == MD_POT_LJ)
             rc = bricks_forces_lj(&dd->vbox, tab, gb, n, dd->xs, dd->row_cap, dd->idx, dd->count, &dd->lj, dd->f, fl,
-                                  part, s);
+                                  part, s, gate);
         else
             rc = bricks_forces_eam(pass, &dd->vbox, tab, gb, n, dd->xs, dd->row_cap, dd->idx, dd->count, &dd->fs,
-                                   dd->rho, dd->fprime, dd->f, fl, part, s);
+                                   dd->rho, dd->fprime, dd->f, fl, part, s, gate);
         rows += gb;
         return rc;
     };
     if (dd->potential == MD_POT_LJ) {
-        if (int rc = phase(1, true)) return rc;
+        if (int rc = phase(1, true, gate)) return rc;
+        if (int rc = check(sc)) return rc;
         MD_HIP_TRY(hipStreamWaitEvent(s, eH, 0));
         if (int rc = phase(1, false)) return rc;
         if (fl & MD_ENERGY) {
@@ -808,15 +803,14 @@ int dd_forces(md_dd_t *dd, double *ev, int32_t flags, void *stream, void *comm, 
     }
     // FS: densities (inner, then outer once the halo is in), F' of the atoms
     // others hold as ghosts exchanged while the inner pair forces run
-    if (int rc = phase(1, true)) return rc;
+    if (int rc = phase(1, true, gate)) return rc;
+    if (int rc = check(sc)) return rc;
     MD_HIP_TRY(hipStreamWaitEvent(s, eH, 0));
     if (int rc = phase(1, false)) return rc;
     MD_HIP_TRY(hipEventRecord(eR, s));
     MD_HIP_TRY(hipStreamWaitEvent(sc, eR, 0));
     if (G > 0) {
-        hipLaunchKernelGGL(k_dd_pack_w, dim3(blocks(G)), dim3(kBlock), 0, sc, G, xs, dd->gh_src_slot, dd->send_w);
-        MD_HIP_TRY(hipMemcpyAsync(dd->recv_w, dd->send_w, size_t(G) * 4, hipMemcpyDeviceToDevice, sc));
-        hipLaunchKernelGGL(k_dd_unpack_w, dim3(blocks(G)), dim3(kBlock), 0, sc, G, dd->recv_w, dd->gh_slot, xs);
+        hipLaunchKernelGGL(k_dd_exchange_w, dim3(blocks(G)), dim3(kBlock), 0, sc, G, dd->gh_src_slot, dd->gh_slot, xs);
         MD_HIP_TRY(hipGetLastError());
     }
     MD_HIP_TRY(hipEventRecord(eF, sc));
@@ -827,7 +821,18 @@ int dd_forces(md_dd_t *dd, double *ev, int32_t flags, void *stream, void *comm, 
     return MD_OK;
 }
 
+int dd_forces(md_dd_t *dd, double *ev, int32_t flags, void *stream, void *comm)
+{
+    return dd_forces(dd, ev, flags, stream, comm, true, Gate{}, [](hipStream_t) { return int(MD_OK); });
+}
+
 }  // namespace
+}  // extern "C++"
+
+int md_dd_forces(md_dd_t *dd, double *ev, int32_t flags, void *stream, void *comm)
+{
+    return dd_forces(dd, ev, flags, stream, comm);
+}
 
 // Steps with the closing half kick of a step fused into the next step's
 // kick-drift (one kick of dt), which also writes the brick-frame
@@ -838,7 +843,7 @@ int md_dd_run(md_dd_t *dd, int64_t steps, double dt, double accel, double skin, 
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (dd->builds < 1) {
         if (int rc = md_dd_rebuild(dd, stream)) return rc;
-        if (int rc = dd_forces(dd, nullptr, 0, stream, comm, true)) return rc;
+        if (int rc = dd_forces(dd, nullptr, 0, stream, comm)) return rc;
     }
     const DdScratch l = scratch_layout(dd);
     if (dd->dws_bytes < l.total) return MD_ERR_WORKSPACE;
@@ -851,29 +856,42 @@ int md_dd_run(md_dd_t *dd, int64_t steps, double dt, double accel, double skin, 
     }
     const double hk = 0.5 * dt * accel;
     bool pending = false;   // the closing half kick of the last completed step
+    // status[0] = k + 1: step k of this run asks for a build
+    if (int rc = launch_fill_i32(dd->status, 2, 0, s)) return rc;
     for (int64_t k = 0; k < steps; ++k) {
-        bool scaled = false;
         if (dd->phase == 0) {
-            if (int rc = launch_fill_i32(dd->status, 2, 0, s)) return rc;
             a.hk = pending ? 2.0 * hk : hk;
+            a.tag = int32_t(k + 1);
             hipLaunchKernelGGL(k_dd_kick_drift, dim3(blocks(dd->n)), dim3(kBlock), 0, s, dd->n, dd->x, dd->v, dd->f,
                                dd->xref, dd->status, ws_ptr<int64_t>(dd->dws, l.bstart),
                                ws_ptr<int64_t>(dd->dws, l.slot0), dd->n_bricks, ws_ptr<double>(dd->dws, l.off),
                                frame_scale(dd), a, reinterpret_cast<uint4 *>(dd->xs));
             MD_HIP_TRY(hipGetLastError());
             pending = false;
-            int32_t st[2] = {0, 0};
-            MD_HIP_TRY(hipMemcpyAsync(st, dd->status, 8, hipMemcpyDeviceToHost, s));
-            MD_HIP_TRY(hipStreamSynchronize(s));
-            if (st[1]) return MD_ERR_NONFINITE;
-            dd->phase = st[0] ? 2 : 1;
-            scaled = !st[0];
+            dd->phase = 1;
+            // the flag is read while the inner atoms' first pass runs (which
+            // does nothing on the device if the flag is set)
+            int rc = dd_forces(dd, nullptr, 0, stream, comm, false, Gate{dd->status, a.tag, a.tag},
+                               [&](hipStream_t sc) -> int {
+                                   int32_t st[2] = {0, 0};
+                                   MD_HIP_TRY(hipMemcpyAsync(st, dd->status, 8, hipMemcpyDeviceToHost, sc));
+                                   MD_HIP_TRY(hipStreamSynchronize(sc));
+                                   if (st[1]) return MD_ERR_NONFINITE;
+                                   return st[0] == a.tag ? kBuildFirst : int(MD_OK);
+                               });
+            if (rc == kBuildFirst) dd->phase = 2;
+            else if (rc) {
+                if (rc == MD_ERR_NONFINITE) dd->phase = 0;
+                return rc;
+            }
+        } else if (dd->phase == 1) {
+            if (int rc = dd_forces(dd, nullptr, 0, stream, comm)) return rc;
         }
         if (dd->phase == 2) {
             if (int rc = md_dd_rebuild(dd, stream)) return rc;
             dd->phase = 1;
+            if (int rc = dd_forces(dd, nullptr, 0, stream, comm)) return rc;
         }
-        if (int rc = dd_forces(dd, nullptr, 0, stream, comm, !scaled)) return rc;
         pending = true;
         dd->phase = 0;
         ++dd->steps;

@@ -286,6 +286,31 @@ def test_network_at_block_edges(M, orc, n, shift):
     assert np.abs(d.cpu().numpy() - do).max() <= 2e-5 * np.abs(do).max()
 
 
+# ---- decomposed run ---------------------------------------------------------------------
+
+@pytest.mark.parametrize("pot", ["lj", "eam"])
+def test_decomposed_run_on_one_and_two_streams(M, pot):
+    """The flag of a step is read beside the inner atoms' pass: with the
+    exchange on its own stream and on the compute stream the run takes the
+    same builds and gives the same bits, builds included."""
+    from paper_1611_00075_amd.dd import DomainSimulation
+    s = inputs.lj_fcc(ncell=12, T=1.4) if pot == "lj" else inputs.eam_cu(ncell=10, T=1500.0)
+    kw = dict(skin=0.3, dt=0.005) if pot == "lj" else dict(
+        potential="eam", fs=inputs.FS_CU, skin=0.4, dt=2.0, mass=inputs.CU_MASS_AMU,
+        force_to_accel=1.0 / inputs.AMU_A2_FS2_IN_EV)
+    out = []
+    for one in (False, True):
+        sim = DomainSimulation(s.L, s.x, s.v, p=(2, 2, 2) if pot == "eam" else (2, 1, 2), **kw)
+        if one:
+            sim.comm = torch.cuda.current_stream()
+        sim.run(25)
+        sim.run(15)
+        out.append((sim.dd.builds, sim.positions(), sim.forces()))
+        sim.close()
+    assert out[0][0] == out[1][0] > 2
+    assert np.array_equal(out[0][1], out[1][1]) and np.array_equal(out[0][2], out[1][2])
+
+
 # ---- native driver ---------------------------------------------------------------------------
 
 @pytest.mark.parametrize("fp64", [False, True])
