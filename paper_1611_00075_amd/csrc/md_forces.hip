@@ -67,7 +67,8 @@ __global__ __launch_bounds__(kBlock) void k_lj32(int64_t n, const uint4 *__restr
 
     const SliceBufs b = slice_bufs(xs, sp.n_xs, idx, cap, blk, sp.slice0);
     float fx = 0.f, fy = 0.f, fz = 0.f, cx = 0.f, cy = 0.f, cz = 0.f;
-    double e = 0.0, np = 0.0, w[6] = {0, 0, 0, 0, 0, 0};
+    double e = 0.0, w[6] = {0, 0, 0, 0, 0, 0};
+    int32_t np = 0;   // pairs counted
     if (i < n) {
         const uint4 pi = xs[i];
         const int32_t cnt = min(count[i], cap);
@@ -90,11 +91,10 @@ __global__ __launch_bounds__(kBlock) void k_lj32(int64_t n, const uint4 *__restr
                 bx = __builtin_fmaf(fs, dx, bx);
                 by = __builtin_fmaf(fs, dy, by);
                 bz = __builtin_fmaf(fs, dz, bz);
-                if (ENERGY && in) {
-                    e += double(p.eps4 * (s6 * s6 - s6));
-                    np += 1.0;
-                    w[0] += double(fs * dx * dx); w[1] += double(fs * dy * dy); w[2] += double(fs * dz * dz);
-                    w[3] += double(fs * dx * dy); w[4] += double(fs * dx * dz); w[5] += double(fs * dy * dz);
+                if (ENERGY) {
+                    e += double(in ? p.eps4 * (s6 * s6 - s6) : 0.f);
+                    np += in ? 1 : 0;
+                    add_virial(w, fs, dx, dy, dz);
                 }
             }
             acc_sum<COMP>(fx, cx, bx);
@@ -111,10 +111,8 @@ __global__ __launch_bounds__(kBlock) void k_lj32(int64_t n, const uint4 *__restr
     if (ENERGY) {
         __shared__ double lds[8 * (kBlock / kWave)];
         const double u = double(p.len);   // virial back to physical units
-        double v[8] = {e, np, w[0] * u, w[1] * u, w[2] * u, w[3] * u, w[4] * u, w[5] * u};
-        block_sum<8>(v, lds);
-        if (threadIdx.x == 0)
-            for (int c = 0; c < 8; ++c) part[int64_t(lblk) * 8 + c] = v[c];
+        const double v[8] = {e, double(np), w[0] * u, w[1] * u, w[2] * u, w[3] * u, w[4] * u, w[5] * u};
+        block_sum8<kBlock / kWave>(v, lds, part + int64_t(lblk) * 8);
     }
 }
 
@@ -192,12 +190,9 @@ __global__ __launch_bounds__(kBlock) void k_lj64(int64_t n, const double *__rest
             }
         }
     }
-#pragma unroll
-    for (int o = 1; o < kSlice; o <<= 1) {
-        fx += __shfl_xor(fx, o, kWave);
-        fy += __shfl_xor(fy, o, kWave);
-        fz += __shfl_xor(fz, o, kWave);
-    }
+    fx = sum8(fx);
+    fy = sum8(fy);
+    fz = sum8(fz);
     if (sub == 0 && i < n) {
         f[i] = fx;
         f[n + i] = fy;
@@ -205,10 +200,8 @@ __global__ __launch_bounds__(kBlock) void k_lj64(int64_t n, const double *__rest
     }
     if (ENERGY) {
         __shared__ double lds[8 * (kBlock / kWave)];
-        double v[8] = {e, np, w[0], w[1], w[2], w[3], w[4], w[5]};
-        block_sum<8>(v, lds);
-        if (threadIdx.x == 0)
-            for (int c = 0; c < 8; ++c) part[int64_t(blk) * 8 + c] = v[c];
+        const double v[8] = {e, np, w[0], w[1], w[2], w[3], w[4], w[5]};
+        block_sum8<kBlock / kWave>(v, lds, part + int64_t(blk) * 8);
     }
 }
 
@@ -279,7 +272,6 @@ struct TBM32 {
 
 struct PairOut {
     float g, v;
-    bool in;
 };
 
 // The form as the pairs of one atom see it (wi: the fourth word of its scaled
@@ -310,7 +302,7 @@ __device__ __forceinline__ PairOut force_term(const FS32 &p, float r2, bool vali
     const float dV = in_c ? t * __builtin_fmaf(t, dpoly, 2.f * poly) : 0.f;
     float g = -(dpsi + dV) * ir;
     g = in_d || in_c ? g : 0.f;
-    return {g, in_c ? t * t * poly : 0.f, in_d || in_c};
+    return {g, in_c ? t * t * poly : 0.f};
 }
 
 __device__ __forceinline__ uint32_t fprime_word(const FS32 &, float fp, uint32_t) { return __float_as_uint(fp); }
@@ -357,7 +349,7 @@ __device__ __forceinline__ PairOut force_term(const TB32 &p, float r2, bool vali
     const float ir = __builtin_amdgcn_rsqf(r2);
     const float2 o = tb_force(r2 * ir * p.len, ir, __uint_as_float(wi) + __uint_as_float(wj), p.rs, p.iw, p.kq,
                               p.cq, p.lq, p.kp, p.cp, p.lp);
-    return {in ? o.x : 0.f, in ? o.y : 0.f, in};
+    return {in ? o.x : 0.f, in ? o.y : 0.f};
 }
 
 __device__ __forceinline__ uint32_t fprime_word(const TB32 &, float fp, uint32_t) { return __float_as_uint(fp); }
@@ -421,7 +413,7 @@ __device__ __forceinline__ PairOut force_term(const TBMAtom<CC> &a, float r2, bo
     const float2 o = tb_force(r2 * ir * a.p.len, ir, fsum, cut_sel<CC>(a.p.rs, a.rs, one),
                               cut_sel<CC>(a.p.iw, a.iw, one), kq, one ? a.cq[1] : a.cq[0], kq * kLn2, kp,
                               one ? a.cp[1] : a.cp[0], kp * kLn2);
-    return {in ? o.x : 0.f, in ? o.y : 0.f, in};
+    return {in ? o.x : 0.f, in ? o.y : 0.f};
 }
 
 template <bool CC>
@@ -496,13 +488,9 @@ __global__ __launch_bounds__(kBlock) void k_eam_rho(int64_t n, uint4 *__restrict
         Fi = double(F);
     }
     if (ENERGY) {
-        __shared__ double lds[1 * (kBlock / kWave)];
-        double v[1] = {Fi};
-        block_sum<1>(v, lds);
-        if (threadIdx.x == 0) {
-            part[int64_t(lblk) * 8] = v[0];
-            for (int q = 1; q < 8; ++q) part[int64_t(lblk) * 8 + q] = 0.0;
-        }
+        __shared__ double lds[8 * (kBlock / kWave)];
+        const double v[8] = {Fi, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        block_sum8<kBlock / kWave>(v, lds, part + int64_t(lblk) * 8);
     }
 }
 
@@ -557,10 +545,9 @@ __global__ __launch_bounds__(kBlock) void k_eam_force(int64_t n, const uint4 *__
                 bx = __builtin_fmaf(g, dx, bx);
                 by = __builtin_fmaf(g, dy, by);
                 bz = __builtin_fmaf(g, dz, bz);
-                if (ENERGY && o.in) {
+                if (ENERGY) {
                     e += double(o.v);
-                    w[0] += double(g * dx * dx); w[1] += double(g * dy * dy); w[2] += double(g * dz * dz);
-                    w[3] += double(g * dx * dy); w[4] += double(g * dx * dz); w[5] += double(g * dy * dz);
+                    add_virial(w, g, dx, dy, dz);
                 }
             }
             acc_sum<COMP>(fx, cx, bx);
@@ -576,9 +563,7 @@ __global__ __launch_bounds__(kBlock) void k_eam_force(int64_t n, const uint4 *__
     }
     if (ENERGY && e_atom) {
         // site energy F(rho_i) + 1/2 sum_j V(r_ij); F as in the first pass
-        double ei = e;
-#pragma unroll
-        for (int o = 1; o < kSlice; o <<= 1) ei += __shfl_xor(ei, o, kWave);
+        const double ei = sum8(e);
         if (sub == 0 && i < n) {
             const float r = rho[i];
             const float F = r > 0.f ? -p.A * __builtin_amdgcn_sqrtf(r) : 0.f;
@@ -588,10 +573,8 @@ __global__ __launch_bounds__(kBlock) void k_eam_force(int64_t n, const uint4 *__
     if (ENERGY) {
         __shared__ double lds[8 * (kBlock / kWave)];
         const double u = double(p.len);
-        double v[8] = {e, 0.0, w[0] * u, w[1] * u, w[2] * u, w[3] * u, w[4] * u, w[5] * u};
-        block_sum<8>(v, lds);
-        if (threadIdx.x == 0)
-            for (int c = 0; c < 8; ++c) part[int64_t(lblk) * 8 + c] = v[c];
+        const double v[8] = {e, 0.0, w[0] * u, w[1] * u, w[2] * u, w[3] * u, w[4] * u, w[5] * u};
+        block_sum8<kBlock / kWave>(v, lds, part + int64_t(lblk) * 8);
     }
 }
 

@@ -775,10 +775,7 @@ __global__ __launch_bounds__(kBlock) void k_mlp_force(int64_t n, MlpArgs p, cons
             acc_add<COMP>(fx, cx, gs, dx);
             acc_add<COMP>(fy, cy, gs, dy);
             acc_add<COMP>(fz, cz, gs, dz);
-            if (ENERGY && in) {
-                w[0] += double(gs * dx * dx); w[1] += double(gs * dy * dy); w[2] += double(gs * dz * dz);
-                w[3] += double(gs * dx * dy); w[4] += double(gs * dx * dz); w[5] += double(gs * dy * dz);
-            }
+            if (ENERGY) add_virial(w, gs, dx, dy, dz);
         }
         asm volatile("" ::: "memory");   // this batch's rows are read before the next ones arrive
     }
@@ -790,10 +787,8 @@ __global__ __launch_bounds__(kBlock) void k_mlp_force(int64_t n, MlpArgs p, cons
     }
     if (ENERGY) {
         __shared__ double lds[8 * (kBlock / kWave)];
-        double v[8] = {0.0, 0.0, w[0], w[1], w[2], w[3], w[4], w[5]};
-        block_sum<8>(v, lds);
-        if (threadIdx.x == 0)
-            for (int c = 0; c < 8; ++c) part[int64_t(blk) * 8 + c] = v[c];
+        const double v[8] = {0.0, 0.0, w[0], w[1], w[2], w[3], w[4], w[5]};
+        block_sum8<kBlock / kWave>(v, lds, part + int64_t(blk) * 8);
     }
 }
 

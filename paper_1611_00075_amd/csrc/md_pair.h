@@ -263,7 +263,8 @@ __device__ __forceinline__ SliceBufs slice_bufs(const void *xs, int64_t n_xs, co
 
 // A double from the lane that data-parallel-primitive control CTRL names
 // (row and bank masks full): quad_perm 0xB1 = lane ^ 1, 0x4E = lane ^ 2,
-// row_half_mirror 0x141 = 7 - lane within each group of 8.
+// row_half_mirror 0x141 = 7 - lane within each group of 8, row_ror:8 0x128 =
+// lane ^ 8.
 template <int CTRL>
 __device__ __forceinline__ double dpp_double(double v)
 {
@@ -272,16 +273,66 @@ __device__ __forceinline__ double dpp_double(double v)
     return __hiloint2double(hi, lo);
 }
 
-// The 8 lanes of one atom are consecutive: combine over them in FP64, the
-// pairwise order ((g0 + g1) + (g2 + g3)) + ((g4 + g5) + (g6 + g7)) in every
-// lane.  All lanes of the wave must be active.
-__device__ __forceinline__ double combine(float s, float c)
+// The sum over the 8 lanes of an atom in every one of them, the pairwise order
+// ((g0 + g1) + (g2 + g3)) + ((g4 + g5) + (g6 + g7)).  All lanes of the wave must
+// be active.
+__device__ __forceinline__ double sum8(double g)
 {
-    double g = double(s) - double(c);
     g += dpp_double<0xb1>(g);
     g += dpp_double<0x4e>(g);
     g += dpp_double<0x141>(g);
     return g;
+}
+
+// The same of a compensated sum.
+__device__ __forceinline__ double combine(float s, float c) { return sum8(double(s) - double(c)); }
+
+// Sums of 8 doubles over a block of WAVES wavefronts, written to out[0..8) in a
+// fixed order.  A wave adds its lanes by halving the values instead of by eight
+// butterflies: lanes that differ in a bit of their number exchange one half of the
+// values and keep the other, so three exchanges inside 8 lanes (4 + 2 + 1 doubles,
+// on the vector unit) leave lane c with value c, and three more doubles finish
+// it.  (Eight butterflies are 96 passes through the LDS crossbar a wave, which
+// for a wave of 8 atoms is a good part of its life: force pass with MD_ENERGY of
+// 500,000 Cu atoms 80.4 us, now 64.5.)
+template <int WAVES>
+__device__ __forceinline__ void block_sum8(const double (&v)[8], double *lds /* 8 * WAVES */, double *out)
+{
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const bool h4 = lane & 4, h2 = lane & 2, h1 = lane & 1;
+    double a[4], b[2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) a[k] = (h4 ? v[k + 4] : v[k]) + dpp_double<0x141>(h4 ? v[k] : v[k + 4]);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) b[k] = (h2 ? a[k + 2] : a[k]) + dpp_double<0x4e>(h2 ? a[k] : a[k + 2]);
+    double t = (h1 ? b[1] : b[0]) + dpp_double<0xb1>(h1 ? b[0] : b[1]);
+    t += dpp_double<0x128>(t);   // row_ror:8 = lane ^ 8
+    t += __shfl_xor(t, 16, kWave);
+    t += __shfl_xor(t, 32, kWave);
+    if (lane < 8) lds[wave * 8 + lane] = t;
+    __syncthreads();
+    if (threadIdx.x < 8) {
+        double s = 0.0;
+        for (int w = 0; w < WAVES; ++w) s += lds[w * 8 + threadIdx.x];
+        out[threadIdx.x] = s;
+    }
+}
+
+// A lane's FP64 sum of the virials g d_a d_b of its pairs (order xx, yy, zz, xy,
+// xz, yz).  The products are FP64, which takes fewer conversions (4) and operations
+// than six FP32 products converted one by one, and there is no branch: pairs not
+// counted have g = 0 and a finite d.  (That form: 64.5 us where this takes 63.0,
+// force pass with MD_ENERGY of 500,000 Cu atoms.)
+__device__ __forceinline__ void add_virial(double (&w)[6], float g, float dx, float dy, float dz)
+{
+    const double x = double(dx), y = double(dy), z = double(dz);
+    const double gx = double(g) * x, gy = double(g) * y, gz = double(g) * z;
+    w[0] = __builtin_fma(gx, x, w[0]);
+    w[1] = __builtin_fma(gy, y, w[1]);
+    w[2] = __builtin_fma(gz, z, w[2]);
+    w[3] = __builtin_fma(gx, y, w[3]);
+    w[4] = __builtin_fma(gx, z, w[4]);
+    w[5] = __builtin_fma(gy, z, w[5]);
 }
 
 // Atom and lane-in-atom of this thread: a wave holds one slice of kSlice

@@ -98,26 +98,6 @@ __device__ __forceinline__ SliceRange wave_slices(uint32_t nslices)
     return {b0 + wave, min(b0 + run, hi), uint32_t(kTabWaves)};
 }
 
-// Sum of NV doubles over the block's waves, fixed order; valid in thread 0.
-template <int NV>
-__device__ __forceinline__ void tab_block_sum(double (&v)[NV], double *lds)
-{
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-#pragma unroll
-    for (int c = 0; c < NV; ++c) v[c] = group_sum(v[c], kWave);
-    if (lane == 0)
-#pragma unroll
-        for (int c = 0; c < NV; ++c) lds[wave * NV + c] = v[c];
-    __syncthreads();
-    if (threadIdx.x == 0)
-#pragma unroll
-        for (int c = 0; c < NV; ++c) {
-            double t = 0.0;
-            for (int w = 0; w < kTabWaves; ++w) t += lds[w * NV + c];
-            v[c] = t;
-        }
-}
-
 // pass 1: rho_i = sum psi(r_ij); F(rho_i), F'_i; F'_i into the fourth word
 template <int U, bool CUBIC, bool ENERGY, bool COMP>
 __global__ __launch_bounds__(kTabBlock) void k_tab_rho(int64_t n, uint4 *__restrict__ xs, int32_t cap,
@@ -171,13 +151,9 @@ __global__ __launch_bounds__(kTabBlock) void k_tab_rho(int64_t n, uint4 *__restr
         }
     }
     if (ENERGY) {
-        __shared__ double red[kTabWaves];
-        double v[1] = {Fsum};
-        tab_block_sum<1>(v, red);
-        if (threadIdx.x == 0) {
-            part[int64_t(blockIdx.x) * 8] = v[0];
-            for (int q = 1; q < 8; ++q) part[int64_t(blockIdx.x) * 8 + q] = 0.0;
-        }
+        __shared__ double red[8 * kTabWaves];
+        const double v[8] = {Fsum, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        block_sum8<kTabWaves>(v, red, part + int64_t(blockIdx.x) * 8);
     }
 }
 
@@ -230,10 +206,9 @@ __global__ __launch_bounds__(kTabBlock) void k_tab_force(int64_t n, const uint4 
                     bx = __builtin_fmaf(g, dx, bx);
                     by = __builtin_fmaf(g, dy, by);
                     bz = __builtin_fmaf(g, dz, bz);
-                    if (ENERGY && in) {
-                        ei += double(tab_val(cf, q));
-                        w[0] += double(g * dx * dx); w[1] += double(g * dy * dy); w[2] += double(g * dz * dz);
-                        w[3] += double(g * dx * dy); w[4] += double(g * dx * dz); w[5] += double(g * dy * dz);
+                    if (ENERGY) {
+                        ei += double(in ? tab_val(cf, q) : 0.f);
+                        add_virial(w, g, dx, dy, dz);
                     }
                 }
                 acc_sum<COMP>(fx, cx, bx);
@@ -251,9 +226,7 @@ __global__ __launch_bounds__(kTabBlock) void k_tab_force(int64_t n, const uint4 
             e += ei;
             if (e_atom) {
                 // site energy F(rho_i) + 1/2 sum_j Phi(r_ij)
-                double es = ei;
-#pragma unroll
-                for (int o = 1; o < kSlice; o <<= 1) es += __shfl_xor(es, o, kWave);
+                const double es = sum8(ei);
                 if (sub == 0 && i < n) {
                     float F, Fp;
                     tab_embed(p, Ftab, rho[i], F, Fp);
@@ -265,10 +238,8 @@ __global__ __launch_bounds__(kTabBlock) void k_tab_force(int64_t n, const uint4 
     if (ENERGY) {
         __shared__ double red[8 * kTabWaves];
         const double u = double(p.len);
-        double v[8] = {e, 0.0, w[0] * u, w[1] * u, w[2] * u, w[3] * u, w[4] * u, w[5] * u};
-        tab_block_sum<8>(v, red);
-        if (threadIdx.x == 0)
-            for (int c = 0; c < 8; ++c) part[int64_t(blockIdx.x) * 8 + c] = v[c];
+        const double v[8] = {e, 0.0, w[0] * u, w[1] * u, w[2] * u, w[3] * u, w[4] * u, w[5] * u};
+        block_sum8<kTabWaves>(v, red, part + int64_t(blockIdx.x) * 8);
     }
 }
 

@@ -56,6 +56,35 @@ def test_energy_rows_either_side_of_the_one_block_sum(M, pot):
     assert np.abs(ev[1] - ev[0]).max() <= (1e-11 if pot == "lj" else 2e-6) * scale, ev
 
 
+@pytest.mark.parametrize("pot", ["lj", "eam"])
+@pytest.mark.parametrize("n", [2, 9, 63, 65, 257])
+def test_energy_and_virial_of_partly_filled_wavefronts(orc, pot, n):
+    """A cluster of n atoms (8 a wavefront, 32 a block).  Each pair's energy and
+    force factor carries a few FP32 roundings (2^-24 each), at most 1e-5 of the
+    summed magnitudes; the sums themselves are FP64."""
+    from paper_1611_00075_amd.sim import Simulation
+    s = inputs.jitter(inputs.lj_fcc(ncell=8) if pot == "lj" else inputs.eam_cu(ncell=8), 0.04, n)
+    x = s.x[:n].copy()
+    rc, skin = (2.5, 0.3) if pot == "lj" else (4.4, 1.0)
+    kw = {} if pot == "lj" else dict(potential="eam", fs=inputs.FS_CU)
+    sim = Simulation(s.L, x, np.zeros_like(x), skin=skin, **kw)
+    sim.compute_forces(energy=True)
+    got = sim.ev.cpu().numpy()
+    xw = orc.wrap(x, s.L)
+    off, idx = orc.neighbors_brute(xw, s.L, rc + skin)
+    want = orc.forces_lj(xw, s.L, off, idx, rc=rc)[1] if pot == "lj" else orc.forces_eam(xw, s.L, off, idx, inputs.FS_CU)["ev"]
+    # magnitudes of the virial terms: every pair's |g| |d|^2 is at most |F_ij| r
+    i = np.repeat(np.arange(n), np.diff(off))
+    d = xw[idx] - xw[i]
+    d -= s.L * np.round(d / s.L)
+    r = np.sqrt((d * d).sum(1))
+    if pot == "lj":
+        scale = np.abs(24 * (2 * r ** -12 - r ** -6))[r < rc].sum() + abs(want[0])
+    else:
+        scale = 20.0 * n      # eV: |psi' F'| r + |V'| r, about 1 eV for each of 12 neighbours
+    assert np.abs(got - np.asarray(want)[: len(got)]).max() <= 1e-5 * scale, (got, want)
+
+
 # ---- training -------------------------------------------------------------------
 
 @pytest.mark.parametrize("batch,shift", [(1, 0), (17, 0), (32, 1), (33, 0), (4095, 1), (32 * 1024 + 5, 0)])
