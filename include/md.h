@@ -631,7 +631,7 @@ typedef struct md_system {
     int64_t step;               /* completed steps; step + 1 tags the rebuild check */
     int64_t builds;             /* list builds so far */
     double *x, *v, *xref;       /* [3n] FP64 */
-    double *scratch;            /* [3n] permutation scratch */
+    double *scratch;            /* [3n] scratch: permutations; md_run's second positions buffer */
     int32_t *ids, *ids_scratch; /* [n]: input index of each sorted atom */
     uint32_t *xs;               /* [4n] scaled coordinates (FP32 path) */
     void *f;                    /* float[3n], double[3n] with MD_PAIR_FP64 */
@@ -682,6 +682,9 @@ typedef struct md_system {
  * row), with host_status the next step as well; the kernels skip themselves
  * on the device when the flag is set or a row overflowed.
  * Returns MD_OK when all steps are done and the state is at a step boundary.
+ * Inside a run of a small system the kick and drift are part of the force
+ * kernels, with the same results bit for bit, and f is written by the last step
+ * only.
  * MD_ERR_CAPACITY: a list row exceeded row_cap; row_cap_needed holds the
  * longest row, a step is in flight (phase 1); grow idx, set row_cap and call
  * again with the remaining steps (target - step).  MD_ERR_NONFINITE: a

@@ -76,6 +76,38 @@ struct FlagPost {
     bool driven = false, first = false;
 };
 
+// The constants of a kick and drift: v += hk f, x += dt v.
+struct DriftArgs {
+    double hk, dt;         // hk = dt/2 * accel for a half kick
+    double L[3], hL[3];    // for the minimum image of x - xref
+    double k[3];           // 2^32 / L, scaled coordinates
+    double half_skin_sq;
+    int32_t tag;           // status[0] becomes this when an atom has moved too far
+    FlagPost post;         // the previous step's flag (native driver)
+};
+DriftArgs drift_args(const md_box_t *box, double kick, double dt, double half_skin_sq, int32_t tag);
+
+// A force kernel without and with the velocity update of its atoms (the native
+// driver's steps).  With it, the kernel posts its step's flag (a.post: tag of this
+// step), and the lanes that hold an atom's force apply the kick, and, with
+// `drift`, move the atom: its new scaled coordinates go to xs_out, not to the
+// array that other blocks are still reading (FP64: x_out, not x), and the rebuild
+// check sets status as the kick-drift kernel does.  f is written only where it is
+// asked for.
+struct NoAdvance {
+    static constexpr bool on = false;
+};
+struct Advance {
+    static constexpr bool on = true;
+    DriftArgs a;
+    const double *x;
+    double *x_out, *v;       // x_out may be x when other blocks read only xs
+    const double *xref;
+    int32_t *status;
+    uint32_t *xs_out;        // NULL in the FP64 path
+    bool drift, write_f;
+};
+
 // Orders the LDS accesses of one wavefront around this point (the lanes of a
 // wave exchange data through LDS without a block barrier).
 __device__ __forceinline__ void wave_sync()
@@ -183,24 +215,28 @@ int reorder_state(int64_t n, const int32_t *perm, double *x, double *v, int32_t 
 int build_neighbors(const md_grid_t *, int64_t, const double *, const int32_t *, int32_t, int32_t *, int32_t *,
                     int32_t *, int32_t *, void *, const WsLayout &, hipStream_t);
 int forces_lj(const md_box_t *, int64_t, const double *, const uint32_t *, int32_t, const int32_t *, const int32_t *,
-              const md_lj_t *, void *, double *, int32_t, void *, const WsLayout &, hipStream_t, Gate = {});
+              const md_lj_t *, void *, double *, int32_t, void *, const WsLayout &, hipStream_t, Gate = {},
+              const Advance * = nullptr);
 // forces_lj with its per-block energy partials (8 doubles per block of
 // kBlock / kSlice atoms, part_rows blocks at most) at `part`
 int forces_lj_part(const md_box_t *, int64_t, const double *, const uint32_t *, int32_t, const int32_t *,
                    const int32_t *, const md_lj_t *, void *, double *, int32_t, double *, int64_t, hipStream_t,
-                   Gate = {});
+                   Gate = {}, const Advance * = nullptr);
 // argument checks of md_forces_lj (everything but the workspace)
 int lj_args_check(const md_box_t *, int64_t, const double *, const uint32_t *, int32_t, const int32_t *,
                   const int32_t *, const md_lj_t *, const void *, const double *, int32_t);
 int forces_eam(const md_box_t *, int64_t, uint32_t *, int32_t, const int32_t *, const int32_t *, const md_fs_t *,
                float *, float *, float *, float *, double *, int32_t, void *, const WsLayout &, hipStream_t,
-               Gate = {});
+               Gate = {},
+              const Advance * = nullptr);
 int forces_tb(const md_box_t *, int64_t, uint32_t *, int32_t, const int32_t *, const int32_t *, const md_tb_t *,
               float *, float *, float *, float *, double *, int32_t, void *, const WsLayout &, hipStream_t,
-              Gate = {});
+              Gate = {},
+              const Advance * = nullptr);
 int forces_tbm(const md_box_t *, int64_t, uint32_t *, int32_t, const int32_t *, const int32_t *, const md_tbm_t *,
                float *, float *, float *, float *, double *, int32_t, void *, const WsLayout &, hipStream_t,
-               Gate = {});
+               Gate = {},
+              const Advance * = nullptr);
 int set_elements(int64_t, const int32_t *, uint32_t *, hipStream_t);
 int workspace_upload(const md_grid_t *, int64_t, const int32_t *, void *, size_t, hipStream_t);
 struct BrickTab;
@@ -215,7 +251,8 @@ int tab_pack(const md_tab_t *, const double *, const double *, const double *, c
              const double *, void *, hipStream_t);
 int forces_tab(const md_box_t *, int64_t, uint32_t *, int32_t, const int32_t *, const int32_t *, const md_tab_t *,
                const void *, float *, float *, float *, float *, double *, int32_t, void *, const WsLayout &,
-               hipStream_t, Gate = {});
+               hipStream_t, Gate = {},
+              const Advance * = nullptr);
 int integrate(int32_t, const md_box_t *, int64_t, double *, double *, const void *, double, double, double,
               const double *, double, int32_t *, int32_t, uint32_t *, double *, int32_t, void *, const WsLayout &,
               hipStream_t);
@@ -224,7 +261,8 @@ int mlp_descriptors(const md_box_t *, int64_t, const uint32_t *, int32_t, const 
 int mlp_eval(int64_t, const float *, const md_mlp_t *, const uint16_t *, float *, float *, hipStream_t);
 int forces_mlp(const md_box_t *, int64_t, const uint32_t *, int32_t, const int32_t *, const int32_t *,
                const md_mlp_t *, const uint16_t *, float *, int32_t *, int32_t *, float *, float *, double *, int32_t,
-               void *, const WsLayout &, hipStream_t, Gate = {});
+               void *, const WsLayout &, hipStream_t, Gate = {},
+              const Advance * = nullptr);
 size_t mlp_workspace_bytes(int64_t batch);
 int mlp_moments(int64_t, const float *, double *, void *, hipStream_t);
 // gradient of the batch loss (grad, loss may be NULL); with adam, an Adam
@@ -234,6 +272,6 @@ int mlp_grad_update(int64_t, const int32_t *, const float *, const float *, cons
 int run(md_system_t *sys, int64_t steps, hipStream_t s);
 int kick_drift(const md_box_t *box, int64_t n, double *x, double *v, const void *f, bool f64, double kick, double dt,
                const double *xref, double half_skin_sq, int32_t *status, int32_t tag, uint32_t *xs, hipStream_t s,
-               bool keep_element = false, const FlagPost &post = {});
+               bool keep_element = false, const FlagPost &post = {}, double *x_out = nullptr);
 
 }  // namespace md

@@ -1,18 +1,23 @@
 // Native velocity-Verlet driver (Sec. 3.3): runs whole steps of the path
 // without returning to the caller, so no interpreter sits between kernels.
 //
-// Per step: kick + drift with the rebuild check (the closing half kick of the
-// previous step is fused in when steps follow each other) and the force
-// evaluation of the new positions.  Both are queued one step ahead of the
-// host: the kick-drift of step k + 1 posts the flag of step k to pinned host
-// memory and, like the forces behind it, does nothing if that flag is set.
-// The host reads the flag of step k with step k + 1 already queued; when some
-// atom has moved more than half the skin it rebuilds the lists, evaluates the
-// forces of step k again and queues step k + 1 anew.  A step is two launches
-// (three with two-pass forces) and the GPU does not wait for the host.  (With
-// a one-thread kernel per step that posted the flag, and a step queued only
-// once the last flag was read: 20 steps of 4,000 FP64 LJ atoms 650 us, now 480;
-// of 2,000 copper atoms 390, now 342; of 20,000 LJ atoms 621, now 475.)
+// Per step: the force evaluation of the current positions, whose last kernel
+// also applies the kick (the closing half of this step and the opening half of
+// the next) and the drift to the next positions with the rebuild check.  The new
+// scaled coordinates (FP64: positions) go to a second buffer, md_system_t.scratch,
+// as other blocks still read the old ones; the two buffers swap each step, and the
+// first drift of a run chooses its side so that the run ends in the caller's.
+// Evaluations are queued one ahead of the host: that of step k + 1 does nothing if
+// the flag of step k or of step k + 1 asks for a build.  Each posts its step's
+// flag to pinned host memory; when some atom has moved more than half the skin the
+// host rebuilds the lists, evaluates step k again and queues step k + 1 anew.  A
+// step is one launch (two with two-pass forces) and the GPU does not wait for the
+// host.
+//
+// In large systems (kFuseAtoms), with timing (a force evaluation then has to be a
+// launch of its own), with plain FP32 sums or with a scratch buffer that is not aligned to 16 bytes, a kick-drift kernel
+// before each evaluation does the update in place, and posts the flag of the
+// step before it.
 #include <chrono>
 #include <thread>
 
@@ -143,32 +148,40 @@ int check_build(md_system_t *sys, int32_t *host_dev, hipStream_t s)
     return MD_OK;
 }
 
-// The force evaluation of the current positions; with a gate, the kernels
+// Where a step's positions are: what the force kernels read (x in the FP64 path,
+// xs in the other; the FP32 path updates x in place).
+struct Positions {
+    double *x;
+    uint32_t *xs;
+};
+
+// The force evaluation of the positions `at`; with a gate, the kernels
 // do nothing when the gate's flag is set on the device.
-int forces(md_system_t *sys, const WsLayout &w, hipStream_t s, Gate gate = {})
+int forces(md_system_t *sys, const WsLayout &w, hipStream_t s, const Positions &at, Gate gate = {},
+           const Advance *adv = nullptr)
 {
     if (sys->potential == MD_POT_LJ)
-        return forces_lj(&sys->box, sys->n, sys->x, sys->xs, sys->row_cap, sys->idx, sys->count, &sys->lj, sys->f,
-                         nullptr, sys->flags & (MD_PAIR_FP64 | MD_NO_COMPENSATE), sys->ws, w, s, gate);
+        return forces_lj(&sys->box, sys->n, at.x, at.xs, sys->row_cap, sys->idx, sys->count, &sys->lj, sys->f,
+                         nullptr, sys->flags & (MD_PAIR_FP64 | MD_NO_COMPENSATE), sys->ws, w, s, gate, adv);
     if (sys->potential == MD_POT_TBM)
-        return forces_tbm(&sys->box, sys->n, sys->xs, sys->row_cap, sys->idx, sys->count, &sys->tbm, sys->rho,
+        return forces_tbm(&sys->box, sys->n, at.xs, sys->row_cap, sys->idx, sys->count, &sys->tbm, sys->rho,
                           sys->fprime, static_cast<float *>(sys->f), nullptr, nullptr, sys->flags & MD_NO_COMPENSATE,
-                          sys->ws, w, s, gate);
+                          sys->ws, w, s, gate, adv);
     if (sys->potential == MD_POT_TAB)
-        return forces_tab(&sys->box, sys->n, sys->xs, sys->row_cap, sys->idx, sys->count, &sys->tab, sys->tab_table,
+        return forces_tab(&sys->box, sys->n, at.xs, sys->row_cap, sys->idx, sys->count, &sys->tab, sys->tab_table,
                           sys->rho, sys->fprime, static_cast<float *>(sys->f), nullptr, nullptr,
-                          sys->flags & MD_NO_COMPENSATE, sys->ws, w, s, gate);
+                          sys->flags & MD_NO_COMPENSATE, sys->ws, w, s, gate, adv);
     if (sys->potential == MD_POT_TB)
-        return forces_tb(&sys->box, sys->n, sys->xs, sys->row_cap, sys->idx, sys->count, &sys->tb, sys->rho,
+        return forces_tb(&sys->box, sys->n, at.xs, sys->row_cap, sys->idx, sys->count, &sys->tb, sys->rho,
                          sys->fprime, static_cast<float *>(sys->f), nullptr, nullptr, sys->flags & MD_NO_COMPENSATE,
-                         sys->ws, w, s, gate);
+                         sys->ws, w, s, gate, adv);
     if (sys->potential == MD_POT_MLP)
-        return forces_mlp(&sys->box, sys->n, sys->xs, sys->row_cap, sys->idx, sys->count, &sys->mlp, sys->mlp_w,
+        return forces_mlp(&sys->box, sys->n, at.xs, sys->row_cap, sys->idx, sys->count, &sys->mlp, sys->mlp_w,
                           sys->dEdG, sys->idx_in, sys->cnt_in, nullptr, static_cast<float *>(sys->f), nullptr,
-                          sys->flags & MD_NO_COMPENSATE, sys->ws, w, s, gate);
-    return forces_eam(&sys->box, sys->n, sys->xs, sys->row_cap, sys->idx, sys->count, &sys->fs, sys->rho,
+                          sys->flags & MD_NO_COMPENSATE, sys->ws, w, s, gate, adv);
+    return forces_eam(&sys->box, sys->n, at.xs, sys->row_cap, sys->idx, sys->count, &sys->fs, sys->rho,
                       sys->fprime, static_cast<float *>(sys->f), nullptr, nullptr, sys->flags & MD_NO_COMPENSATE,
-                      sys->ws, w, s, gate);
+                      sys->ws, w, s, gate, adv);
 }
 
 // Optional timing of the force evaluations: one event pair per evaluation,
@@ -234,14 +247,23 @@ struct ForceTimer {
 
 }  // namespace
 
+// Largest system whose force kernels apply the kick and drift.  A launch less per
+// step is what small systems gain; but the update's reads and writes, 64 bytes at
+// a time behind a row walk, run at half the rate of the kick-drift kernel's, and
+// from about 100,000 atoms on that costs more.  us per step without builds,
+// separate / fused: LJ of 4,000 atoms 13.9 / 8.6, of 42,592 14.9 / 12.6, of 70,304
+// 17.4 / 16.9, of 108,000 21.5 / 21.5, of 1.26 M 156 / 182; FS of 2,048 14.3 / 10.8, of 55,296
+// 19.7 / 19.2, of 108,000 29.4 / 29.4, of 500,000 79.8 / 89.0; FP64 LJ of 4,000 14.4 / 9.0.
+constexpr int64_t kFuseAtoms = 65536;
+
 int run(md_system_t *sys, int64_t steps, hipStream_t s)
 {
     const WsLayout w = ws_layout(sys->grid.n_cells, sys->n);
+    const int64_t n = sys->n;
     const bool f64 = sys->flags & MD_PAIR_FP64;
     const double hk = 0.5 * sys->dt * sys->accel;
-    uint32_t *xs = f64 ? nullptr : sys->xs;
     int32_t *host_dev = nullptr;
-    if (sys->host_status && sys->n > 0) {   // (with no atoms no kick-drift runs to post a flag)
+    if (sys->host_status && n > 0) {   // (with no atoms no kernel runs to post a flag)
         void *p = nullptr;
         if (hipHostGetDevicePointer(&p, sys->host_status, 0) == hipSuccess) host_dev = static_cast<int32_t *>(p);
         else (void)hipGetLastError();
@@ -250,21 +272,83 @@ int run(md_system_t *sys, int64_t steps, hipStream_t s)
     bool moved = false, bad = false;
     ForceTimer timer;
     if (!timer.init(sys->timing != 0)) return MD_ERR_HIP;
+    // the caller's buffers and the second one (side 0 and side 1)
+    const bool fuse = n > 0 && n <= kFuseAtoms && !sys->timing && !(sys->flags & MD_NO_COMPENSATE) && sys->scratch &&
+                      (f64 || (reinterpret_cast<uintptr_t>(sys->scratch) & 15u) == 0);
+    const Positions side[2] = {{sys->x, f64 ? nullptr : sys->xs},
+                               {f64 ? sys->scratch : sys->x,
+                                f64 ? nullptr : reinterpret_cast<uint32_t *>(sys->scratch)}};
+    // a step's positions back on side 0 (before a build, which reads x, and on an error)
+    const auto settle = [&](int b) -> int {
+        if (b == 0) return MD_OK;
+        if (f64)
+            MD_HIP_TRY(hipMemcpyAsync(sys->x, side[1].x, size_t(n) * 24, hipMemcpyDeviceToDevice, s));
+        else
+            MD_HIP_TRY(hipMemcpyAsync(sys->xs, side[1].xs, size_t(n) * 16, hipMemcpyDeviceToDevice, s));
+        return MD_OK;
+    };
     // forces of a fresh build, skipped on the device when a row overflowed
     const Gate fits{nullptr, 0, 0, sys->max_count, sys->row_cap};
     if (sys->phase == 0 && sys->need_build) {
         if ((rc = rebuild(sys, w, s, host_dev))) return rc;
-        if ((rc = forces(sys, w, s, fits))) return rc;
+        if ((rc = forces(sys, w, s, side[0], fits))) return rc;
         if ((rc = check_build(sys, host_dev, s))) return rc;
         sys->need_build = 0;
     }
     int64_t done = 0;
-    // Queues kick (h) and drift of step `tag` and, gated on the device by its
-    // flag, the forces of the new positions.  ahead: the flag of step tag - 1
-    // is not read yet; this kick-drift posts it, and both are gated by it too.
-    // last: no kick-drift follows in this run, so a kernel posts this flag.
-    bool first = true;
-    const auto queue_step = [&](double h, int32_t tag, bool ahead, bool last) -> int {
+    const int64_t last = sys->step + steps;
+    // What the evaluation of step k with its positions on side b does besides:
+    // the closing kick of the run; kick and drift to the other side, when as many
+    // drifts as are left end on side 0; else nothing, and a kick-drift in place
+    // follows.
+    enum { kNothing, kDrift, kClose };
+    const auto besides = [&](int64_t k, int b) -> int {
+        if (!fuse) return kNothing;
+        if (k == last) return kClose;
+        return ((last - k) & 1) == b ? kDrift : kNothing;
+    };
+    bool first = true;   // no drift queued in this run yet
+    // Queues the evaluation of step k (positions on side b).  post: it posts the
+    // flag of step k; where it cannot and no kick-drift follows, a kernel does.
+    const auto queue_forces = [&](int64_t k, int b, Gate gate, bool post) -> int {
+        const int what = besides(k, b);
+        const int32_t tag = int32_t(k);
+        Advance adv{};
+        if (what != kNothing) {
+            adv.a = drift_args(&sys->box, what == kClose ? hk : 2.0 * hk, sys->dt, sys->half_skin_sq, tag + 1);
+            adv.drift = what == kDrift;
+            if (adv.drift) {
+                adv.a.post.first = first;
+                first = false;
+            }
+            adv.write_f = what == kClose;
+            adv.x = side[b].x;
+            adv.x_out = side[what == kDrift ? !b : b].x;
+            adv.v = sys->v;
+            adv.xref = sys->xref;
+            adv.status = sys->status;
+            adv.xs_out = what == kDrift ? side[!b].xs : nullptr;
+        }
+        if (post && host_dev && (what != kNothing || k == last)) {
+            expect_flag(sys, tag);
+            if (what != kNothing) {
+                adv.a.post.word = flag_slot(host_dev, tag);
+                adv.a.post.tag = tag;
+            } else {
+                hipLaunchKernelGGL(k_publish, dim3(1), dim3(1), 0, s, sys->status, flag_slot(host_dev, tag), tag);
+                MD_HIP_TRY(hipGetLastError());
+            }
+        }
+        timer.start(s);
+        if (int r = forces(sys, w, s, side[b], gate, what != kNothing ? &adv : nullptr)) return r;
+        timer.stop(sys, s);
+        return MD_OK;
+    };
+    // Queues the kick (h) and drift of step k from side b to side to, for FP32
+    // from whatever scaled coordinates to those of side to.  ahead: the flag of
+    // step k - 1 is not read yet; the kernel posts it and is gated by it.
+    const auto queue_drift = [&](double h, int64_t k, int b, int to, bool ahead) -> int {
+        const int32_t tag = int32_t(k);
         FlagPost post;
         post.driven = true;
         post.first = first;
@@ -274,35 +358,41 @@ int run(md_system_t *sys, int64_t steps, hipStream_t s)
             post.word = flag_slot(host_dev, tag - 1);
             post.tag = tag - 1;
         }
-        int r = kick_drift(&sys->box, sys->n, sys->x, sys->v, sys->f, f64, h, sys->dt, sys->xref, sys->half_skin_sq,
-                           sys->status, tag, xs, s, sys->potential == MD_POT_TBM, post);
-        if (r) return r;
-        if (last && host_dev) {
-            expect_flag(sys, tag);
-            hipLaunchKernelGGL(k_publish, dim3(1), dim3(1), 0, s, sys->status, flag_slot(host_dev, tag), tag);
-            MD_HIP_TRY(hipGetLastError());
-        }
-        timer.start(s);
-        if ((r = forces(sys, w, s, Gate{sys->status, tag, ahead ? tag - 1 : tag}))) return r;
-        timer.stop(sys, s);
-        return MD_OK;
+        return kick_drift(&sys->box, n, side[b].x, sys->v, sys->f, f64, h, sys->dt, sys->xref, sys->half_skin_sq,
+                          sys->status, tag, side[to].xs, s, sys->potential == MD_POT_TBM, post, side[to].x);
     };
-    bool queued = false;   // kick-drift and forces of step + 1 queued, its flag unread
+    bool queued = false;   // evaluation of the step in flight queued, its flag unread
+    int b = 0;             // side of the positions of the step in flight
     for (;;) {
         if (sys->phase == 0) {
             if (done >= steps) break;
-            if ((rc = queue_step(hk, int32_t(sys->step + 1), false, done + 1 == steps))) return rc;
+            const int64_t k = sys->step + 1;
+            b = fuse && sys->potential != MD_POT_TBM ? int((last - k) & 1) : 0;   // (elements stay in the caller's xs)
+            if ((rc = queue_drift(hk, k, 0, b, false))) return rc;
             sys->phase = 1;
+            if ((rc = queue_forces(k, b, Gate{sys->status, int32_t(k), int32_t(k)}, true))) return rc;
             queued = true;
         }
         // a step is in flight: positions drifted, forces stale unless queued
-        const int32_t tag = int32_t(sys->step + 1);
+        const int64_t k = sys->step + 1;
+        const int32_t tag = int32_t(k);
+        // the step after it: its kick and drift unless step k's evaluation has made
+        // them, and its evaluation
+        const auto queue_next = [&](bool ahead) -> int {
+            int to = b;
+            if (besides(k, b) == kDrift) to = !b;
+            else if (int r = queue_drift(2.0 * hk, k + 1, b, b, ahead)) return r;
+            return queue_forces(k + 1, to, Gate{sys->status, tag + 1, ahead ? tag : tag + 1}, true);
+        };
         bool ready = false, ahead = false;
         if (queued) {
             ahead = host_dev && done + 1 < steps;
-            if (ahead && (rc = queue_step(2.0 * hk, tag + 1, true, done + 2 == steps))) return rc;
+            if (ahead && (rc = queue_next(true))) return rc;
             if ((rc = read_flag(sys, host_dev, tag, s, &moved, &bad))) return rc;
-            if (bad) return MD_ERR_NONFINITE;
+            if (bad) {
+                if ((rc = settle(b))) return rc;
+                return MD_ERR_NONFINITE;
+            }
             ready = !moved;
             if (!ready) {   // the device skipped this step's forces and the step queued ahead
                 timer.drop_last();
@@ -316,13 +406,11 @@ int run(md_system_t *sys, int64_t steps, hipStream_t s)
         const bool built = sys->need_build != 0;
         if (built) {
             ready = false;
+            if (f64 && (rc = settle(b))) return rc;
+            b = 0;
             if ((rc = rebuild(sys, w, s, host_dev))) return rc;
         }
-        if (!ready) {
-            timer.start(s);
-            if ((rc = forces(sys, w, s, built ? fits : Gate{}))) return rc;
-            timer.stop(sys, s);
-        }
+        if (!ready && (rc = queue_forces(k, b, built ? fits : Gate{}, false))) return rc;
         if (built) {
             if ((rc = check_build(sys, host_dev, s))) {
                 timer.drop_last();
@@ -334,14 +422,13 @@ int run(md_system_t *sys, int64_t steps, hipStream_t s)
         ++done;
         queued = ahead;
         if (done < steps) {
-            // closing half kick of this step fused with the opening one of the next
-            if (!queued) {
-                if ((rc = queue_step(2.0 * hk, int32_t(sys->step + 1), false, done + 1 == steps))) return rc;
-                queued = true;
-            }
+            if (!queued && (rc = queue_next(false))) return rc;
+            queued = true;
+            if (besides(k, b) == kDrift) b = !b;
         } else {
-            if ((rc = integrate(MD_KICK, &sys->box, sys->n, sys->x, sys->v, sys->f, sys->dt, sys->accel, 1.0, nullptr,
-                                0.0, nullptr, 0, nullptr, nullptr, sys->flags & MD_PAIR_FP64, sys->ws, w, s)))
+            if (besides(k, b) != kClose &&
+                (rc = integrate(MD_KICK, &sys->box, n, sys->x, sys->v, sys->f, sys->dt, sys->accel, 1.0, nullptr, 0.0,
+                                nullptr, 0, nullptr, nullptr, sys->flags & MD_PAIR_FP64, sys->ws, w, s)))
                 return rc;
             sys->phase = 0;
         }

@@ -40,12 +40,13 @@ struct LJ32 {
     Gate gate;
 };
 
-template <int TPA, int U, bool CUBIC, bool ENERGY, bool COMP>
+template <int TPA, int U, bool CUBIC, bool ENERGY, bool COMP, class A>
 __global__ __launch_bounds__(kBlock) void k_lj32(int64_t n, const uint4 *__restrict__ xs,
                                                  int32_t cap, const int32_t *__restrict__ idx,
                                                  const int32_t *__restrict__ count, LJ32 p, float *__restrict__ f,
-                                                 double *__restrict__ part, Span sp, const BrickTab *tab)
+                                                 double *__restrict__ part, Span sp, const BrickTab *tab, A adv)
 {
+    post_flag(adv);
     if (gated(p.gate)) return;
     static_assert(TPA == kSlice, "one slice per wave");
     const uint32_t lblk = xcd_block(blockIdx.x, gridDim.x);   // partial rows by the launch's block
@@ -103,11 +104,12 @@ __global__ __launch_bounds__(kBlock) void k_lj32(int64_t n, const uint4 *__restr
         });
     }
     const double gx = combine(fx, cx), gy = combine(fy, cy), gz = combine(fz, cz);
-    if (sub == 0 && i < n) {
+    if (sub == 0 && i < n && writes_f(adv)) {
         f[i] = float(gx);
         f[sp.fs + i] = float(gy);
         f[2 * sp.fs + i] = float(gz);
     }
+    if constexpr (A::on) advance_atoms(adv, n, i, sub, float(gx), float(gy), float(gz), 0u);
     if (ENERGY) {
         __shared__ double lds[8 * (kBlock / kWave)];
         const double u = double(p.len);   // virial back to physical units
@@ -139,12 +141,13 @@ __device__ __forceinline__ double minimg64(double d, double L, double hL)
 // at 4,000 atoms (500 waves, half of one per SIMD) their latency was the
 // launch: 11.4 us; five at a time 7.8 us.  Same pairs in the same order: the sums
 // are bit for bit the same.
-template <int TPA, int U, bool ENERGY>
+template <int TPA, int U, bool ENERGY, class A>
 __global__ __launch_bounds__(kBlock) void k_lj64(int64_t n, const double *__restrict__ x,
                                                  int32_t cap, const int32_t *__restrict__ idx,
                                                  const int32_t *__restrict__ count, LJ64 p, double *__restrict__ f,
-                                                 double *__restrict__ part)
+                                                 double *__restrict__ part, A adv)
 {
+    post_flag(adv);
     if (gated(p.gate)) return;
     static_assert(TPA == kSlice, "one slice per wave");
     const uint32_t blk = xcd_block(blockIdx.x, gridDim.x);
@@ -193,11 +196,12 @@ __global__ __launch_bounds__(kBlock) void k_lj64(int64_t n, const double *__rest
     fx = sum8(fx);
     fy = sum8(fy);
     fz = sum8(fz);
-    if (sub == 0 && i < n) {
+    if (sub == 0 && i < n && writes_f(adv)) {
         f[i] = fx;
         f[n + i] = fy;
         f[2 * n + i] = fz;
     }
+    if constexpr (A::on) advance_atoms(adv, n, i, sub, fx, fy, fz, 0u);
     if (ENERGY) {
         __shared__ double lds[8 * (kBlock / kWave)];
         const double v[8] = {e, np, w[0], w[1], w[2], w[3], w[4], w[5]};
@@ -422,6 +426,18 @@ __device__ __forceinline__ uint32_t fprime_word(const TBM32<CC> &, float fp, uin
     return (__float_as_uint(fp) & ~1u) | (wi & 1u);
 }
 
+// the fourth word of an atom's next scaled coordinates: its element where there are two
+template <class P>
+__device__ __forceinline__ uint32_t element_word(const P &, uint32_t)
+{
+    return 0u;
+}
+template <bool CC>
+__device__ __forceinline__ uint32_t element_word(const TBM32<CC> &, uint32_t wi)
+{
+    return wi & 1u;
+}
+
 // pass 1: rho_i = sum psi(r_ij), then F_i = -A sqrt(rho_i), F'_i; F'_i is
 // stored in the fourth word of the scaled coordinates for pass 2's gather.
 template <class P, int TPA, int U, bool CUBIC, bool ENERGY, bool COMP>
@@ -495,14 +511,15 @@ __global__ __launch_bounds__(kBlock) void k_eam_rho(int64_t n, uint4 *__restrict
 }
 
 // pass 2: F_i = -sum_j [(F'_i + F'_j) psi'(r) + V'(r)] (r_i - r_j) / r
-template <class P, int TPA, int U, bool CUBIC, bool ENERGY, bool COMP>
+template <class P, int TPA, int U, bool CUBIC, bool ENERGY, bool COMP, class A>
 __global__ __launch_bounds__(kBlock) void k_eam_force(int64_t n, const uint4 *__restrict__ xs,
                                                       int32_t cap, const int32_t *__restrict__ idx,
                                                       const int32_t *__restrict__ count, P p,
                                                       const float *__restrict__ rho, float *__restrict__ f,
                                                       float *__restrict__ e_atom, double *__restrict__ part, Span sp,
-                                                      const BrickTab *tab)
+                                                      const BrickTab *tab, A adv)
 {
+    post_flag(adv);
     if (gated(p.gate)) return;
     static_assert(TPA == kSlice, "one slice per wave");
     const uint32_t lblk = xcd_block(blockIdx.x, gridDim.x);
@@ -527,8 +544,10 @@ __global__ __launch_bounds__(kBlock) void k_eam_force(int64_t n, const uint4 *__
     const SliceBufs b = slice_bufs(xs, sp.n_xs, idx, cap, blk, sp.slice0);
     float fx = 0.f, fy = 0.f, fz = 0.f, cx = 0.f, cy = 0.f, cz = 0.f;
     double e = 0.0, w[6] = {0, 0, 0, 0, 0, 0};
+    uint32_t keep = 0u;
     if (i < n) {
         const uint4 pi = xs[i];
+        keep = element_word(p, pi.w);
         const auto &form = local_form(p, pi.w);
         const int32_t cnt = min(count[i], cap);
         walk_form<P::kSplit, U, 4>(b.xs, b.row, cnt, sub, [&](const auto &pj, int32_t t0, auto masked) {
@@ -556,11 +575,12 @@ __global__ __launch_bounds__(kBlock) void k_eam_force(int64_t n, const uint4 *__
         });
     }
     const double gx = combine(fx, cx), gy = combine(fy, cy), gz = combine(fz, cz);
-    if (sub == 0 && i < n) {
+    if (sub == 0 && i < n && writes_f(adv)) {
         f[i] = float(gx);
         f[sp.fs + i] = float(gy);
         f[2 * sp.fs + i] = float(gz);
     }
+    if constexpr (A::on) advance_atoms(adv, n, i, sub, float(gx), float(gy), float(gz), keep);
     if (ENERGY && e_atom) {
         // site energy F(rho_i) + 1/2 sum_j V(r_ij); F as in the first pass
         const double ei = sum8(e);
@@ -596,20 +616,28 @@ struct List {
 
 template <int TPA, bool CUBIC, bool E, bool C>
 static void launch_lj32(uint32_t gb, hipStream_t s, int64_t n, const uint4 *q, const List &l, const LJ32 &p,
-                        float *f, double *part, const Span &sp, const BrickTab *tab)
+                        float *f, double *part, const Span &sp, const BrickTab *tab, const Advance *adv)
 {
-    hipLaunchKernelGGL((k_lj32<TPA, kUnrollLJ, CUBIC, E, C>), dim3(gb), dim3(kBlock), 0, s, n, q, l.cap, l.idx, l.cnt,
-                       p, f, part, sp, tab);
+    if constexpr (!E && C) {
+        if (adv) {
+            hipLaunchKernelGGL((k_lj32<TPA, kUnrollLJ, CUBIC, E, C, Advance>), dim3(gb), dim3(kBlock), 0, s, n, q,
+                               l.cap, l.idx, l.cnt, p, f, part, sp, tab, *adv);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_lj32<TPA, kUnrollLJ, CUBIC, E, C, NoAdvance>), dim3(gb), dim3(kBlock), 0, s, n, q, l.cap,
+                       l.idx, l.cnt, p, f, part, sp, tab, NoAdvance{});
 }
 
 template <int TPA, bool CUBIC>
 static void dispatch_lj32(bool e, bool c, uint32_t gb, hipStream_t s, int64_t n, const uint4 *q, const List &l,
-                          const LJ32 &p, float *f, double *part, const Span &sp, const BrickTab *tab = nullptr)
+                          const LJ32 &p, float *f, double *part, const Span &sp, const BrickTab *tab = nullptr,
+                          const Advance *adv = nullptr)
 {
-    if (e && c) launch_lj32<TPA, CUBIC, true, true>(gb, s, n, q, l, p, f, part, sp, tab);
-    else if (e) launch_lj32<TPA, CUBIC, true, false>(gb, s, n, q, l, p, f, part, sp, tab);
-    else if (c) launch_lj32<TPA, CUBIC, false, true>(gb, s, n, q, l, p, f, part, sp, tab);
-    else launch_lj32<TPA, CUBIC, false, false>(gb, s, n, q, l, p, f, part, sp, tab);
+    if (e && c) launch_lj32<TPA, CUBIC, true, true>(gb, s, n, q, l, p, f, part, sp, tab, adv);
+    else if (e) launch_lj32<TPA, CUBIC, true, false>(gb, s, n, q, l, p, f, part, sp, tab, adv);
+    else if (c) launch_lj32<TPA, CUBIC, false, true>(gb, s, n, q, l, p, f, part, sp, tab, adv);
+    else launch_lj32<TPA, CUBIC, false, false>(gb, s, n, q, l, p, f, part, sp, tab, adv);
 }
 
 // blocks of a launch over the slices from sp.slice0 to the one holding atom n-1
@@ -639,15 +667,15 @@ static LJ32 lj_constants(const md_box_t *box, const md_lj_t *lj, Gate gate)
 
 int forces_lj(const md_box_t *box, int64_t n, const double *x, const uint32_t *xs, int32_t cap, const int32_t *idx,
               const int32_t *cnt, const md_lj_t *lj, void *f, double *ev, int32_t flags, void *ws, const WsLayout &w,
-              hipStream_t s, Gate gate)
+              hipStream_t s, Gate gate, const Advance *adv)
 {
     return forces_lj_part(box, n, x, xs, cap, idx, cnt, lj, f, ev, flags, ws_ptr<double>(ws, w.red1), w.red_blocks,
-                          s, gate);
+                          s, gate, adv);
 }
 
 int forces_lj_part(const md_box_t *box, int64_t n, const double *x, const uint32_t *xs, int32_t cap,
                    const int32_t *idx, const int32_t *cnt, const md_lj_t *lj, void *f, double *ev, int32_t flags,
-                   double *part, int64_t part_rows, hipStream_t s, Gate gate)
+                   double *part, int64_t part_rows, hipStream_t s, Gate gate, const Advance *adv)
 {
     const List l{cap, idx, cnt};
     const bool energy = flags & MD_ENERGY;
@@ -673,11 +701,14 @@ int forces_lj_part(const md_box_t *box, int64_t n, const double *x, const uint32
             p.gate = gate;
             double *fd = static_cast<double *>(f);
             if (energy)
-                hipLaunchKernelGGL((k_lj64<kTPA, kUnroll64, true>), dim3(gb), dim3(kBlock), 0, s, n, x, cap, idx, cnt, p, fd,
-                                   part);
+                hipLaunchKernelGGL((k_lj64<kTPA, kUnroll64, true, NoAdvance>), dim3(gb), dim3(kBlock), 0, s, n, x, cap,
+                                   idx, cnt, p, fd, part, NoAdvance{});
+            else if (adv)
+                hipLaunchKernelGGL((k_lj64<kTPA, kUnroll64, false, Advance>), dim3(gb), dim3(kBlock), 0, s, n, x, cap,
+                                   idx, cnt, p, fd, part, *adv);
             else
-                hipLaunchKernelGGL((k_lj64<kTPA, kUnroll64, false>), dim3(gb), dim3(kBlock), 0, s, n, x, cap, idx, cnt, p, fd,
-                                   part);
+                hipLaunchKernelGGL((k_lj64<kTPA, kUnroll64, false, NoAdvance>), dim3(gb), dim3(kBlock), 0, s, n, x, cap,
+                                   idx, cnt, p, fd, part, NoAdvance{});
         } else {
             const bool cubic = is_cubic(box);
             gb = blocks_for(n, kTPA);
@@ -686,8 +717,8 @@ int forces_lj_part(const md_box_t *box, int64_t n, const double *x, const uint32
             const uint4 *q = reinterpret_cast<const uint4 *>(xs);
             float *ff = static_cast<float *>(f);
             const bool comp = !(flags & MD_NO_COMPENSATE);
-            if (cubic) dispatch_lj32<kTPA, true>(energy, comp, gb, s, n, q, l, p, ff, part, whole(n));
-            else dispatch_lj32<kTPA, false>(energy, comp, gb, s, n, q, l, p, ff, part, whole(n));
+            if (cubic) dispatch_lj32<kTPA, true>(energy, comp, gb, s, n, q, l, p, ff, part, whole(n), nullptr, adv);
+            else dispatch_lj32<kTPA, false>(energy, comp, gb, s, n, q, l, p, ff, part, whole(n), nullptr, adv);
         }
         MD_HIP_TRY(hipGetLastError());
     }
@@ -698,32 +729,39 @@ int forces_lj_part(const md_box_t *box, int64_t n, const double *x, const uint32
 template <class P, int TPA, bool CUBIC, bool E, bool C>
 static void launch_eam(int passes, uint32_t gb, hipStream_t s, int64_t n, uint4 *q, const List &l, const P &p,
                        float *rho, float *fprime, float *f, float *ea, double *part1, double *part2, const Span &sp,
-                       const BrickTab *tab)
+                       const BrickTab *tab, const Advance *adv)
 {
     if (passes & 1)
         hipLaunchKernelGGL((k_eam_rho<P, TPA, P::kRhoUnroll, CUBIC, E, C>), dim3(gb), dim3(kBlock), 0, s, n, q, l.cap,
                            l.idx, l.cnt, p, rho, fprime, part1, sp, tab);
-    if (passes & 2)
-        hipLaunchKernelGGL((k_eam_force<P, TPA, P::kForceUnroll, CUBIC, E, C>), dim3(gb), dim3(kBlock), 0, s, n, q, l.cap,
-                           l.idx, l.cnt, p, rho, f, ea, part2, sp, tab);
+    if (!(passes & 2)) return;
+    if constexpr (!E && C) {
+        if (adv) {
+            hipLaunchKernelGGL((k_eam_force<P, TPA, P::kForceUnroll, CUBIC, E, C, Advance>), dim3(gb), dim3(kBlock), 0,
+                               s, n, q, l.cap, l.idx, l.cnt, p, rho, f, ea, part2, sp, tab, *adv);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_eam_force<P, TPA, P::kForceUnroll, CUBIC, E, C, NoAdvance>), dim3(gb), dim3(kBlock), 0, s, n,
+                       q, l.cap, l.idx, l.cnt, p, rho, f, ea, part2, sp, tab, NoAdvance{});
 }
 
 template <class P, int TPA, bool CUBIC>
 static void dispatch_eam(int passes, bool e, bool c, uint32_t gb, hipStream_t s, int64_t n, uint4 *q,
                          const List &l, const P &p, float *rho, float *fprime, float *f, float *ea, double *p1,
-                         double *p2, const Span &sp, const BrickTab *tab = nullptr)
+                         double *p2, const Span &sp, const BrickTab *tab = nullptr, const Advance *adv = nullptr)
 {
-    if (e && c) launch_eam<P, TPA, CUBIC, true, true>(passes, gb, s, n, q, l, p, rho, fprime, f, ea, p1, p2, sp, tab);
-    else if (e) launch_eam<P, TPA, CUBIC, true, false>(passes, gb, s, n, q, l, p, rho, fprime, f, ea, p1, p2, sp, tab);
-    else if (c) launch_eam<P, TPA, CUBIC, false, true>(passes, gb, s, n, q, l, p, rho, fprime, f, ea, p1, p2, sp, tab);
-    else launch_eam<P, TPA, CUBIC, false, false>(passes, gb, s, n, q, l, p, rho, fprime, f, ea, p1, p2, sp, tab);
+    if (e && c) launch_eam<P, TPA, CUBIC, true, true>(passes, gb, s, n, q, l, p, rho, fprime, f, ea, p1, p2, sp, tab, adv);
+    else if (e) launch_eam<P, TPA, CUBIC, true, false>(passes, gb, s, n, q, l, p, rho, fprime, f, ea, p1, p2, sp, tab, adv);
+    else if (c) launch_eam<P, TPA, CUBIC, false, true>(passes, gb, s, n, q, l, p, rho, fprime, f, ea, p1, p2, sp, tab, adv);
+    else launch_eam<P, TPA, CUBIC, false, false>(passes, gb, s, n, q, l, p, rho, fprime, f, ea, p1, p2, sp, tab, adv);
 }
 
 // Both passes of an embedded-atom form P (geometry fields set here).
 template <class P>
 static int forces_two_pass(const md_box_t *box, int64_t n, uint32_t *xs, const List &l, P p, float *rho,
                            float *fprime, float *f, float *e_atom, double *ev, int32_t flags, void *ws,
-                           const WsLayout &w, hipStream_t s)
+                           const WsLayout &w, hipStream_t s, const Advance *adv)
 {
     const bool energy = flags & MD_ENERGY;
     const bool comp = !(flags & MD_NO_COMPENSATE);
@@ -736,10 +774,10 @@ static int forces_two_pass(const md_box_t *box, int64_t n, uint32_t *xs, const L
     if (n > 0) {
         if (cubic)
             dispatch_eam<P, kTPA, true>(3, energy, comp, gb, s, n, q, l, p, rho, fprime, f, e_atom, part1, part2,
-                                        whole(n));
+                                        whole(n), nullptr, adv);
         else
             dispatch_eam<P, kTPA, false>(3, energy, comp, gb, s, n, q, l, p, rho, fprime, f, e_atom, part1, part2,
-                                         whole(n));
+                                         whole(n), nullptr, adv);
         MD_HIP_TRY(hipGetLastError());
     }
     if (energy) return launch_reduce_partials(part1, gb, part2, gb, ev, kReduceEAM, 0.0, s);
@@ -772,15 +810,15 @@ static FS32 fs_constants(const md_box_t *box, const md_fs_t *fs, Gate gate)
 
 int forces_eam(const md_box_t *box, int64_t n, uint32_t *xs, int32_t cap, const int32_t *idx, const int32_t *cnt,
                const md_fs_t *fs, float *rho, float *fprime, float *f, float *e_atom, double *ev, int32_t flags,
-               void *ws, const WsLayout &w, hipStream_t s, Gate gate)
+               void *ws, const WsLayout &w, hipStream_t s, Gate gate, const Advance *adv)
 {
     return forces_two_pass(box, n, xs, List{cap, idx, cnt}, fs_constants(box, fs, gate), rho, fprime, f, e_atom, ev,
-                           flags, ws, w, s);
+                           flags, ws, w, s, adv);
 }
 
 int forces_tb(const md_box_t *box, int64_t n, uint32_t *xs, int32_t cap, const int32_t *idx, const int32_t *cnt,
               const md_tb_t *tb, float *rho, float *fprime, float *f, float *e_atom, double *ev, int32_t flags,
-              void *ws, const WsLayout &w, hipStream_t s, Gate gate)
+              void *ws, const WsLayout &w, hipStream_t s, Gate gate, const Advance *adv)
 {
     const double two32 = 4294967296.0, log2e = 1.4426950408889634;
     const double u = disp_unit(box);
@@ -801,7 +839,7 @@ int forces_tb(const md_box_t *box, int64_t n, uint32_t *xs, int32_t cap, const i
     p.lp = float(tb->p / tb->r0);
     p.A = 1.f;
     p.gate = gate;
-    return forces_two_pass(box, n, xs, List{cap, idx, cnt}, p, rho, fprime, f, e_atom, ev, flags, ws, w, s);
+    return forces_two_pass(box, n, xs, List{cap, idx, cnt}, p, rho, fprime, f, e_atom, ev, flags, ws, w, s, adv);
 }
 
 template <bool CC>
@@ -832,16 +870,16 @@ static TBM32<CC> tbm_constants(const md_box_t *box, const md_tbm_t *tb, Gate gat
 
 int forces_tbm(const md_box_t *box, int64_t n, uint32_t *xs, int32_t cap, const int32_t *idx, const int32_t *cnt,
                const md_tbm_t *tb, float *rho, float *fprime, float *f, float *e_atom, double *ev, int32_t flags,
-               void *ws, const WsLayout &w, hipStream_t s, Gate gate)
+               void *ws, const WsLayout &w, hipStream_t s, Gate gate, const Advance *adv)
 {
     const md_tb_t *q = tb->pair;
     const bool common = q[0].rs == q[1].rs && q[0].rs == q[2].rs && q[0].rc == q[1].rc && q[0].rc == q[2].rc;
     const List l{cap, idx, cnt};
     if (common)
         return forces_two_pass(box, n, xs, l, tbm_constants<true>(box, tb, gate), rho, fprime, f, e_atom, ev, flags,
-                               ws, w, s);
+                               ws, w, s, adv);
     return forces_two_pass(box, n, xs, l, tbm_constants<false>(box, tb, gate), rho, fprime, f, e_atom, ev, flags, ws,
-                           w, s);
+                           w, s, adv);
 }
 
 // ---- ranges of the bricks of a domain decomposition, one launch ----

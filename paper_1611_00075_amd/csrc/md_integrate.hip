@@ -5,15 +5,6 @@
 
 namespace md {
 
-struct DriftArgs {
-    double hk, dt;         // hk = dt/2 * accel
-    double L[3], hL[3];    // for the minimum image of x - xref
-    double k[3];           // 2^32 / L, scaled coordinates
-    double half_skin_sq;
-    int32_t tag;
-    FlagPost post;         // the previous step's flag (native driver)
-};
-
 __device__ __forceinline__ double minimg_d(double d, double L, double hL)
 {
     if (d > hL)
@@ -24,8 +15,9 @@ __device__ __forceinline__ double minimg_d(double d, double L, double hL)
 }
 
 template <typename FT, bool KEEP>
-__global__ __launch_bounds__(kBlock) void k_kick_drift(int64_t n, double *__restrict__ x, double *__restrict__ v,
-                                                       const FT *__restrict__ f, const double *__restrict__ xref,
+__global__ __launch_bounds__(kBlock) void k_kick_drift(int64_t n, const double *x, double *x_out,
+                                                       double *__restrict__ v, const FT *__restrict__ f,
+                                                       const double *__restrict__ xref,
                                                        int32_t *__restrict__ status, uint4 *__restrict__ xs,
                                                        DriftArgs a)
 {
@@ -56,7 +48,7 @@ __global__ __launch_bounds__(kBlock) void k_kick_drift(int64_t n, double *__rest
             const double vc = u[c] + a.hk * fc[c];
             v[c * n + i] = vc;
             p[c] = p[c] + a.dt * vc;
-            x[c * n + i] = p[c];
+            x_out[c * n + i] = p[c];
             bad |= !isfinite(p[c]);
         }
         if (xref) {
@@ -103,15 +95,8 @@ __global__ __launch_bounds__(kBlock) void k_kick(int64_t n, double *__restrict__
     }
 }
 
-// v += kick * f; x += dt v; rebuild check; scaled coordinates.  kick is
-// dt/2 * accel for a half step, dt * accel when the closing half kick of the
-// previous step is fused in (same forces).
-int kick_drift(const md_box_t *box, int64_t n, double *x, double *v, const void *f, bool f64, double kick, double dt,
-               const double *xref, double half_skin_sq, int32_t *status, int32_t tag, uint32_t *xs, hipStream_t s,
-               bool keep_element, const FlagPost &post)
+DriftArgs drift_args(const md_box_t *box, double kick, double dt, double half_skin_sq, int32_t tag)
 {
-    const uint32_t gb = uint32_t((n + kBlock - 1) / kBlock);
-    if (n <= 0) return MD_OK;
     DriftArgs a;
     a.hk = kick;
     a.dt = dt;
@@ -122,16 +107,30 @@ int kick_drift(const md_box_t *box, int64_t n, double *x, double *v, const void 
     }
     a.half_skin_sq = half_skin_sq;
     a.tag = tag;
+    return a;
+}
+
+// v += kick * f; x += dt v (into x_out, or in place); rebuild check; scaled coordinates.  kick is
+// dt/2 * accel for a half step, dt * accel when the closing half kick of the
+// previous step is fused in (same forces).
+int kick_drift(const md_box_t *box, int64_t n, double *x, double *v, const void *f, bool f64, double kick, double dt,
+               const double *xref, double half_skin_sq, int32_t *status, int32_t tag, uint32_t *xs, hipStream_t s,
+               bool keep_element, const FlagPost &post, double *x_out)
+{
+    const uint32_t gb = uint32_t((n + kBlock - 1) / kBlock);
+    if (n <= 0) return MD_OK;
+    DriftArgs a = drift_args(box, kick, dt, half_skin_sq, tag);
     a.post = post;
+    if (!x_out) x_out = x;
     uint4 *q = reinterpret_cast<uint4 *>(xs);
     if (f64)
-        hipLaunchKernelGGL((k_kick_drift<double, false>), dim3(gb), dim3(kBlock), 0, s, n, x, v,
+        hipLaunchKernelGGL((k_kick_drift<double, false>), dim3(gb), dim3(kBlock), 0, s, n, x, x_out, v,
                            static_cast<const double *>(f), xref, status, q, a);
     else if (keep_element)
-        hipLaunchKernelGGL((k_kick_drift<float, true>), dim3(gb), dim3(kBlock), 0, s, n, x, v,
+        hipLaunchKernelGGL((k_kick_drift<float, true>), dim3(gb), dim3(kBlock), 0, s, n, x, x_out, v,
                            static_cast<const float *>(f), xref, status, q, a);
     else
-        hipLaunchKernelGGL((k_kick_drift<float, false>), dim3(gb), dim3(kBlock), 0, s, n, x, v,
+        hipLaunchKernelGGL((k_kick_drift<float, false>), dim3(gb), dim3(kBlock), 0, s, n, x, x_out, v,
                            static_cast<const float *>(f), xref, status, q, a);
     MD_HIP_TRY(hipGetLastError());
     return MD_OK;

@@ -684,13 +684,14 @@ __device__ __forceinline__ void basis_sums(const MlpArgs &p, float t, const floa
 // sums 1 M copper atoms (43 M pairs) went from 285 to 262 us (one pair a lane
 // at a time; two 268, three 318); the vector unit and the addressers are then
 // both busy 87 % of the time.
-template <int U, bool FOLD, bool ENERGY, bool COMP>
+template <int U, bool FOLD, bool ENERGY, bool COMP, class A>
 __global__ __launch_bounds__(kBlock) void k_mlp_force(int64_t n, MlpArgs p, const uint4 *__restrict__ xs,
                                                       int32_t cap, const int32_t *__restrict__ idx,
                                                       const int32_t *__restrict__ count,
                                                       const float4 *__restrict__ dEdG, float *__restrict__ f,
-                                                      double *__restrict__ part)
+                                                      double *__restrict__ part, A adv)
 {
+    post_flag(adv);
     if (gated(p.gate)) return;
     __shared__ float4 stage[kBlock / kWave][U][4 * kWave];
     const uint32_t blk = xcd_block(blockIdx.x, gridDim.x);
@@ -780,11 +781,12 @@ __global__ __launch_bounds__(kBlock) void k_mlp_force(int64_t n, MlpArgs p, cons
         asm volatile("" ::: "memory");   // this batch's rows are read before the next ones arrive
     }
     const double gx = combine(fx, cx), gy = combine(fy, cy), gz = combine(fz, cz);
-    if (sub == 0 && live) {
+    if (sub == 0 && live && writes_f(adv)) {
         f[i] = float(gx);
         f[n + i] = float(gy);
         f[2 * n + i] = float(gz);
     }
+    if constexpr (A::on) advance_atoms(adv, n, i, sub, float(gx), float(gy), float(gz), 0u);
     if (ENERGY) {
         __shared__ double lds[8 * (kBlock / kWave)];
         const double v[8] = {0.0, 0.0, w[0], w[1], w[2], w[3], w[4], w[5]};
@@ -1143,7 +1145,7 @@ int mlp_eval(int64_t n, const float *G, const md_mlp_t *mlp, const uint16_t *w, 
 int forces_mlp(const md_box_t *box, int64_t n, const uint32_t *xs, int32_t cap, const int32_t *idx,
                const int32_t *count, const md_mlp_t *mlp, const uint16_t *w, float *dEdG, int32_t *idx_in,
                int32_t *cnt_in, float *e_atom, float *f, double *ev, int32_t flags, void *ws, const WsLayout &wl,
-               hipStream_t s, Gate gate)
+               hipStream_t s, Gate gate, const Advance *adv)
 {
     const bool energy = flags & MD_ENERGY;
     const bool comp = !(flags & MD_NO_COMPENSATE);
@@ -1175,8 +1177,16 @@ int forces_mlp(const md_box_t *box, int64_t n, const uint32_t *xs, int32_t cap, 
         const int32_t *pidx = reuse ? idx : idx_in;
         const int32_t *pcnt = reuse ? count : cnt_in;
         auto force = [&](auto fold, auto en, auto co) {
-            hipLaunchKernelGGL((k_mlp_force<kForceUnroll, decltype(fold)::value, decltype(en)::value, decltype(co)::value>),
-                               dim3(g2), dim3(kBlock), 0, s, n, a, q, cap, pidx, pcnt, d4, f, part2);
+            constexpr bool FO = decltype(fold)::value, EN = decltype(en)::value, CO = decltype(co)::value;
+            if constexpr (!EN && CO) {
+                if (adv) {
+                    hipLaunchKernelGGL((k_mlp_force<kForceUnroll, FO, EN, CO, Advance>), dim3(g2), dim3(kBlock), 0, s,
+                                       n, a, q, cap, pidx, pcnt, d4, f, part2, *adv);
+                    return;
+                }
+            }
+            hipLaunchKernelGGL((k_mlp_force<kForceUnroll, FO, EN, CO, NoAdvance>), dim3(g2), dim3(kBlock), 0, s, n, a,
+                               q, cap, pidx, pcnt, d4, f, part2, NoAdvance{});
         };
         using T = std::true_type;
         using F = std::false_type;

@@ -264,7 +264,7 @@ __device__ __forceinline__ SliceBufs slice_bufs(const void *xs, int64_t n_xs, co
 // A double from the lane that data-parallel-primitive control CTRL names
 // (row and bank masks full): quad_perm 0xB1 = lane ^ 1, 0x4E = lane ^ 2,
 // row_half_mirror 0x141 = 7 - lane within each group of 8, row_ror:8 0x128 =
-// lane ^ 8.
+// lane ^ 8, quad_perm 0x00, 0x55, 0xaa = lane 0, 1, 2 of the quad.
 template <int CTRL>
 __device__ __forceinline__ double dpp_double(double v)
 {
@@ -346,6 +346,73 @@ __device__ __forceinline__ SliceLane slice_lane(uint32_t blk, uint32_t slice0 = 
 {
     return {int64_t(slice0) * kSlice + int64_t(blk) * (kBlock / kSlice) + threadIdx.x / kSlice,
             int(threadIdx.x % kSlice)};
+}
+
+// ---- velocity update behind the forces (Advance) ---------------------------
+template <class A>
+__device__ __forceinline__ bool writes_f(const A &adv)
+{
+    if constexpr (A::on) return adv.write_f;
+    else return true;
+}
+
+// The launch's first thread posts the flag of the step whose forces these are
+// (before the gate: the host waits for it in either case).
+template <class A>
+__device__ __forceinline__ void post_flag(const A &adv)
+{
+    if constexpr (A::on) {
+        if (adv.a.post.word && blockIdx.x == 0 && threadIdx.x == 0) {
+            const bool stop = adv.status[0] == adv.a.post.tag;
+            post_flag_word(adv.a.post.word, adv.a.post.tag, stop, stop && adv.status[1] != 0);
+        }
+    }
+}
+
+// Kick and, with drift, move of the wave's 8 atoms from their forces (gx, gy, gz
+// in every lane of an atom), operation by operation as k_kick_drift and k_kick do
+// it: lane sub = c < 3 of an atom takes component c.  keep: the fourth word of the
+// new scaled coordinates.  All lanes of the wave call it.  (The state read before
+// the row walk instead: the same to 0.3 us a step slower below 50,000 atoms.)
+__device__ __forceinline__ void advance_atoms(const Advance &adv, int64_t n, int64_t i, int sub, double gx, double gy,
+                                              double gz, uint32_t keep)
+{
+    const DriftArgs &a = adv.a;
+    const bool mine = i < n && sub < 3;
+    const int64_t at = sub * n + i;
+    double v = 0.0, x = 0.0, ref = 0.0;
+    if (mine) {
+        v = adv.v[at];
+        if (adv.drift) {
+            x = adv.x[at];
+            if (adv.xref) ref = adv.xref[at];
+        }
+    }
+    const double fc = sub == 0 ? gx : (sub == 1 ? gy : gz);
+    const double vc = v + a.hk * fc;
+    if (mine) adv.v[at] = vc;
+    if (!adv.drift) return;
+    const double p = x + a.dt * vc;
+    if (mine) adv.x_out[at] = p;
+    const bool bad = mine && !isfinite(p);
+    const double L = sub == 0 ? a.L[0] : (sub == 1 ? a.L[1] : a.L[2]);
+    const double hL = sub == 0 ? a.hL[0] : (sub == 1 ? a.hL[1] : a.hL[2]);
+    double d = p - ref;
+    if (d > hL)
+        d -= L;
+    else if (d < -hL)
+        d += L;
+    const double d2 = d * d;
+    const double x2 = dpp_double<0x00>(d2), y2 = dpp_double<0x55>(d2), z2 = dpp_double<0xaa>(d2);
+    bool moved = adv.xref && sub == 0 && i < n && ((x2 + y2) + z2) > a.half_skin_sq;
+    if (adv.xs_out) {
+        const double k = sub == 0 ? a.k[0] : (sub == 1 ? a.k[1] : a.k[2]);
+        const uint32_t u = sub == 3 ? keep : uint32_t(uint64_t(__double2ll_rn(p * k)));
+        if (i < n && sub < 4) adv.xs_out[4 * i + sub] = u;
+    }
+    moved |= bad || (a.post.first && i == 0 && sub == 0 && adv.status[1] != 0);
+    if (__ballot(moved) && (threadIdx.x % kWave) == 0) adv.status[0] = a.tag;
+    if (__ballot(bad) && (threadIdx.x % kWave) == 0) atomicOr(&adv.status[1], 1);
 }
 
 }  // namespace md

@@ -158,15 +158,16 @@ __global__ __launch_bounds__(kTabBlock) void k_tab_rho(int64_t n, uint4 *__restr
 }
 
 // pass 2: F_i = -sum_j [(F'_i + F'_j) psi'(r) + Phi'(r)] (r_i - r_j) / r
-template <int U, bool CUBIC, bool ENERGY, bool COMP>
+template <int U, bool CUBIC, bool ENERGY, bool COMP, class A>
 __global__ __launch_bounds__(kTabBlock) void k_tab_force(int64_t n, const uint4 *__restrict__ xs, int32_t cap,
                                                          const int32_t *__restrict__ idx,
                                                          const int32_t *__restrict__ count, TAB32 p,
                                                          const float4 *__restrict__ table,
                                                          const float *__restrict__ rho, float *__restrict__ f,
                                                          float *__restrict__ e_atom, double *__restrict__ part,
-                                                         uint32_t nslices)
+                                                         uint32_t nslices, A adv)
 {
+    post_flag(adv);
     if (gated(p.gate)) return;
     extern __shared__ float4 lds_tab[];   // psi intervals, then Phi intervals
     for (int k = threadIdx.x; k < 2 * p.m; k += kTabBlock) lds_tab[k] = table[k];
@@ -217,11 +218,12 @@ __global__ __launch_bounds__(kTabBlock) void k_tab_force(int64_t n, const uint4 
             });
         }
         const double gx = combine(fx, cx), gy = combine(fy, cy), gz = combine(fz, cz);
-        if (sub == 0 && i < n) {
+        if (sub == 0 && i < n && writes_f(adv)) {
             f[i] = float(gx);
             f[n + i] = float(gy);
             f[2 * n + i] = float(gz);
         }
+        if constexpr (A::on) advance_atoms(adv, n, i, sub, float(gx), float(gy), float(gz), 0u);
         if (ENERGY) {
             e += ei;
             if (e_atom) {
@@ -311,24 +313,33 @@ static uint32_t tab_grid(const void *kernel, size_t lds, uint32_t nslices)
 template <bool CUBIC, bool E, bool C>
 static int launch_tab(hipStream_t s, int64_t n, uint4 *q, int32_t cap, const int32_t *idx, const int32_t *cnt,
                       const TAB32 &p, const float4 *table, float *rho, float *fprime, float *f, float *ea,
-                      double *part1, double *part2, int64_t max_blocks, uint32_t &g1, uint32_t &g2)
+                      double *part1, double *part2, int64_t max_blocks, uint32_t &g1, uint32_t &g2,
+                      const Advance *adv)
 {
     const uint32_t nslices = uint32_t((n + kSlice - 1) / kSlice);
     const size_t lds1 = size_t(p.m) * 16, lds2 = size_t(p.m) * 32;
     g1 = tab_grid(reinterpret_cast<const void *>(&k_tab_rho<kTabUnroll, CUBIC, E, C>), lds1, nslices);
-    g2 = tab_grid(reinterpret_cast<const void *>(&k_tab_force<kTabUnroll, CUBIC, E, C>), lds2, nslices);
-    if (int64_t(g1) > max_blocks || int64_t(g2) > max_blocks) return MD_ERR_WORKSPACE;
-    hipLaunchKernelGGL((k_tab_rho<kTabUnroll, CUBIC, E, C>), dim3(g1), dim3(kTabBlock), lds1, s, n, q, cap, idx, cnt,
-                       p, table, rho, fprime, part1, nslices);
-    hipLaunchKernelGGL((k_tab_force<kTabUnroll, CUBIC, E, C>), dim3(g2), dim3(kTabBlock), lds2, s, n, q, cap, idx,
-                       cnt, p, table, rho, f, ea, part2, nslices);
+    auto pass2 = [&](const auto &ad) -> int {
+        using A = std::decay_t<decltype(ad)>;
+        g2 = tab_grid(reinterpret_cast<const void *>(&k_tab_force<kTabUnroll, CUBIC, E, C, A>), lds2, nslices);
+        if (int64_t(g1) > max_blocks || int64_t(g2) > max_blocks) return MD_ERR_WORKSPACE;
+        hipLaunchKernelGGL((k_tab_rho<kTabUnroll, CUBIC, E, C>), dim3(g1), dim3(kTabBlock), lds1, s, n, q, cap, idx,
+                           cnt, p, table, rho, fprime, part1, nslices);
+        hipLaunchKernelGGL((k_tab_force<kTabUnroll, CUBIC, E, C, A>), dim3(g2), dim3(kTabBlock), lds2, s, n, q, cap,
+                           idx, cnt, p, table, rho, f, ea, part2, nslices, ad);
+        return MD_OK;
+    };
+    int rc;
+    if constexpr (!E && C) rc = adv ? pass2(*adv) : pass2(NoAdvance{});
+    else rc = pass2(NoAdvance{});
+    if (rc) return rc;
     MD_HIP_TRY(hipGetLastError());
     return MD_OK;
 }
 
 int forces_tab(const md_box_t *box, int64_t n, uint32_t *xs, int32_t cap, const int32_t *idx, const int32_t *cnt,
                const md_tab_t *tab, const void *table, float *rho, float *fprime, float *f, float *e_atom,
-               double *ev, int32_t flags, void *ws, const WsLayout &w, hipStream_t s, Gate gate)
+               double *ev, int32_t flags, void *ws, const WsLayout &w, hipStream_t s, Gate gate, const Advance *adv)
 {
     const double two32 = 4294967296.0;
     const bool cubic = box->L[0] == box->L[1] && box->L[1] == box->L[2];
@@ -357,7 +368,7 @@ int forces_tab(const md_box_t *box, int64_t n, uint32_t *xs, int32_t cap, const 
     if (n > 0) {
         auto go = [&](auto cub, auto en, auto co) {
             return launch_tab<decltype(cub)::value, decltype(en)::value, decltype(co)::value>(
-                s, n, q, cap, idx, cnt, p, t, rho, fprime, f, e_atom, part1, part2, w.red_blocks, g1, g2);
+                s, n, q, cap, idx, cnt, p, t, rho, fprime, f, e_atom, part1, part2, w.red_blocks, g1, g2, adv);
         };
         using T = std::true_type;
         using F = std::false_type;

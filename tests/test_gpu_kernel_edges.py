@@ -342,6 +342,54 @@ def test_decomposed_run_on_one_and_two_streams(M, pot):
 
 # ---- native driver ---------------------------------------------------------------------------
 
+@pytest.mark.parametrize("polled", [True, False])
+@pytest.mark.parametrize("pot,cells", [("lj", (5, 5, 5)), ("lj", (5, 6, 7)), ("lj64", (5, 5, 5)), ("eam", (4, 4, 4)),
+                                       ("eam", (4, 5, 4)), ("tb", (4, 4, 4)), ("tbm", (5, 5, 5)), ("tbm", (5, 4, 5)),
+                                       ("tab", (4, 4, 4)), ("tab", (4, 4, 5)), ("mlp", (4, 4, 4))])
+def test_velocity_update_in_the_force_kernels(M, pot, cells, polled):
+    """Runs of 1 to 7 steps, with builds at different places among them, against
+    the same runs with a kick-drift launch per step (timing): all state bit for
+    bit."""
+    from paper_1611_00075_amd import mlp as P
+    from paper_1611_00075_amd.sim import Simulation
+    a = inputs.fcc_lattice_constant(0.8442) if pot.startswith("lj") else inputs.CU_A0 * (1.04 if pot == "tbm" else 1.0)
+    x = _fcc(cells, a)
+    n = len(x) - 3                      # not a whole number of wavefronts
+    rng = np.random.default_rng(n)
+    x = x[:n] + 0.02 * a * rng.standard_normal((n, 3))
+    L = np.array(cells) * a
+    if pot.startswith("lj"):
+        kw = dict(skin=0.12, dt=0.005, pair_fp64=pot == "lj64")
+        v = 1.5 * rng.standard_normal((n, 3))
+    else:
+        kw = dict(potential=pot, skin=0.2, dt=4.0, mass=inputs.CU_MASS_AMU,
+                  force_to_accel=1.0 / inputs.AMU_A2_FS2_IN_EV)
+        v = 0.004 * rng.standard_normal((n, 3))
+        kw.update({"eam": dict(fs=inputs.FS_CU), "tb": dict(tb=inputs.TB_CU), "tab": dict(tab=inputs.fs_table(inputs.FS_CU)),
+                   "tbm": dict(tbm=inputs.TB2_PAIRS, types=rng.integers(0, 2, n).astype(np.int32)),
+                   "mlp": dict(mlp=P.spec(np.full(16, 4.0), np.full(16, 0.2)),
+                               mlp_w=P.bf16_bits(P.init_params(5, e_mean=-3.5, w3_scale=0.3)).cuda())}[pot])
+    sims = [Simulation(L, x, v, **kw) for _ in range(2)]
+    if not polled:
+        for sim in sims:
+            sim._flag_host = None
+    for steps in (1, 2, 3, 4, 7):
+        sims[0].run(steps)
+        sims[1].run(steps, timing=True)
+        for name in ("x", "v", "f", "ids", "xref", "count") + (() if pot == "lj64" else ("xs",)):
+            t, u = (getattr(sim, name) for sim in sims)
+            if name == "xs":            # (after the rho pass the fourth word holds F')
+                t, u = t[:, :3], u[:, :3]
+            assert torch.equal(t, u), (steps, name)
+        assert sims[0].builds == sims[1].builds
+    assert sims[0].builds > 1
+
+
+def _fcc(cells, a):
+    g = np.stack(np.meshgrid(*[np.arange(c) for c in cells], indexing="ij"), -1).reshape(-1, 1, 3)
+    return ((g + np.array(inputs.FCC_BASIS)) * a).reshape(-1, 3)
+
+
 @pytest.mark.parametrize("fp64", [False, True])
 def test_run_ahead_of_the_flag(M, fp64):
     """With pinned memory the next step is queued before a step's flag is
