@@ -151,6 +151,7 @@ struct MlpArgs {
     float c8;               // mu_8 = mu0 + 8 dmu
     float ka;               // log2(e) / (2 w^2)
     float alpha;            // log2(e) dmu / w^2
+    float ylim;             // largest |alpha t| that the folded sums take
     float q[8];             // exp(-(m + 1/2) dmu^2 / w^2)
     float Q[9];             // exp(-m^2 dmu^2 / 2 w^2)
     float phi;              // pi / (2 rc)
@@ -173,6 +174,7 @@ MlpArgs make_args(const md_box_t *box, const md_mlp_t *m)
     a.c8 = float(m->mu0 + 8.0 * m->dmu);
     a.ka = float(l2e / (2.0 * w2));
     a.alpha = float(l2e * m->dmu / w2);
+    a.ylim = float(13.22 * l2e * std::fabs(m->dmu) / m->width);   // exp(-13.22^2 / 2) < 2^-126
     for (int k = 0; k < 8; ++k) a.q[k] = float(std::exp(-(k + 0.5) * m->dmu * m->dmu / w2));
     for (int k = 0; k < 9; ++k) a.Q[k] = float(std::exp(-0.5 * k * k * m->dmu * m->dmu / w2));
     a.phi = float(3.14159265358979323846 / (2.0 * m->rc));
@@ -632,12 +634,15 @@ void k_mlp_net(int64_t n, MlpArgs p, const float *Gin, const uint16_t *__restric
 // with Q folded into the coefficients (di holds c's first term times Q) both
 // sums are polynomials in u and in 1/u, taken with their derivatives by
 // Horner's rule: 16 + 30 operations where forming the Gaussians and both
-// sums took 94.
+// sums took 94.  Beyond 13.22 widths from c8 e_8 is zero in FP32, and with it
+// both sums, so u stops there: the powers of 1 / u and u then stay in range (at
+// most 1e35 times the coefficients with the rule for folding) for the closest pairs too.
 __device__ __forceinline__ void basis_sums_folded(const MlpArgs &p, float t, const float (&di)[kIn],
                                                   const float (&dj)[kIn], float &S0, float &S1)
 {
     const float e8 = __builtin_amdgcn_exp2f(-p.ka * t * t);
-    const float up = __builtin_amdgcn_exp2f(p.alpha * t), dn = __builtin_amdgcn_exp2f(-p.alpha * t);
+    const float y = __builtin_amdgcn_fmed3f(p.alpha * t, -p.ylim, p.ylim);
+    const float up = __builtin_amdgcn_exp2f(y), dn = __builtin_amdgcn_exp2f(-y);
     float c[kIn];
 #pragma unroll
     for (int k = 0; k < kIn; ++k) c[k] = __builtin_fmaf(dj[k], p.Q[k < 8 ? 8 - k : k - 8], di[k]);
@@ -1190,13 +1195,13 @@ int forces_mlp(const md_box_t *box, int64_t n, const uint32_t *xs, int32_t cap, 
         };
         using T = std::true_type;
         using F = std::false_type;
-        // Folded sums where Q_8 = exp(-32 (dmu / w)^2) is above 1e-28 (the
-        // default spacing, dmu = w: 1.3e-14), so that the coefficients keep
-        // the FP32 range; plain ones for wider spacings, and with MD_ENERGY,
+        // Folded sums where Q_8 = exp(-32 (dmu / w)^2) is above 1e-18 (the
+        // default spacing, dmu = w: 1.3e-14), so that the coefficients and the
+        // powers keep the FP32 range; plain ones for wider spacings, and with MD_ENERGY,
         // whose FP64 virial then has the value it always had (the two differ
         // in the last bits of a pair's force factor).
         if (energy) comp ? force(F{}, T{}, T{}) : force(F{}, T{}, F{});
-        else if (a.Q[8] > 1e-28f) comp ? force(T{}, F{}, T{}) : force(T{}, F{}, F{});
+        else if (a.Q[8] > 1e-18f) comp ? force(T{}, F{}, T{}) : force(T{}, F{}, F{});
         else comp ? force(F{}, F{}, T{}) : force(F{}, F{}, F{});
         MD_HIP_TRY(hipGetLastError());
     }

@@ -268,7 +268,7 @@ def test_list_with_a_position_that_is_no_number(M, orc):
 def test_learned_pair_pass_over_ragged_rows(M, orc, dmu, width):
     """Rows of every length (0 to 60 in range) in one slice, and Gaussian
     spacings on both sides of the rule that folds them into polynomials
-    (exp(-32 (dmu / width)^2) above 1e-28: ratios 1 and 1.9).  FP32 pair
+    (exp(-32 (dmu / width)^2) above 1e-18: ratios 1 and 1.9).  FP32 pair
     terms from the same dE/dG: 1e-5 normwise."""
     from oracle import mlp as om
     from paper_1611_00075_amd import mlp as P
@@ -291,6 +291,31 @@ def test_learned_pair_pass_over_ragged_rows(M, orc, dmu, width):
     fg = np.empty((n, 3))
     fg[ids] = f.cpu().numpy().T
     assert np.linalg.norm(fg - fo) <= 1e-5 * np.linalg.norm(fo)
+
+
+@pytest.mark.parametrize("r", [0.05, 0.4, 0.6, 0.9, 1.0, 1.2, 1.3, 2.0])
+def test_learned_pair_pass_of_close_pairs(M, r):
+    """Pairs so close that the Gaussian at the centre of the set underflows
+    (3.6 - r above 2.64) or nearly does: the folded sums give what the Gaussians
+    themselves give (the form with MD_ENERGY), finite and to the FP32 rounding of
+    16 terms that cancel (1e-5 of the summed magnitudes)."""
+    from paper_1611_00075_amd import mlp as P
+    from paper_1611_00075_amd.sim import Simulation
+    x = np.array([[5.0, 5.0, 5.0], [5.0 + 0.6 * r, 5.0 + 0.8 * r, 5.0], [9.0, 5.0, 5.5]])
+    sim = Simulation(np.full(3, 20.0), x, np.zeros_like(x), potential="mlp", mlp=P.spec(),
+                     mlp_w=P.bf16_bits(P.init_params(5)).cuda(), skin=1.0, dt=1.0)
+    D = np.random.default_rng(3).uniform(0.5, 1.0, (3, 16)).astype(np.float32)
+    out = []
+    for energy in (0, M.MD_ENERGY):
+        sim.dEdG[:3] = torch.tensor(D, device="cuda")
+        f = torch.full((3, 3), np.nan, dtype=torch.float32, device="cuda")
+        M.md_forces_mlp(sim.L, 3, sim.xs, sim.row_cap, sim.idx, sim.count, sim.mlp, None, sim.dEdG, None, None, None,
+                        f, sim.ev, M.MD_MLP_REUSE | energy, sim.ws)
+        out.append(f.cpu().numpy().astype(np.float64))
+    assert np.isfinite(out[0]).all()
+    t = r - (P.MU0 + P.DMU * np.arange(16))
+    scale = (2 * np.exp(-t * t / (2 * P.WIDTH ** 2)) * (np.abs(t) / P.WIDTH ** 2 + 1)).sum()
+    assert np.abs(out[0] - out[1]).max() <= 1e-5 * (scale + np.abs(out[1]).max()), out
 
 
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 64 * 512, 64 * 512 + 1])
