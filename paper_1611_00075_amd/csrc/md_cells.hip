@@ -18,8 +18,12 @@ struct GridArgs {
     int32_t nc[3], reach;
 };
 
+// Inside the box floor(x / L) is 0 (a quotient below 1 never rounds up to 1) and w
+// is x (0 for -0), so the FP64 division is left out: most atoms at a build are
+// where the last one put them.
 __device__ __forceinline__ double wrap1(double x, double L)
 {
+    if (x >= 0.0 && x < L) return x + 0.0;
     double w = x - L * floor(x / L);
     if (w >= L) w -= L;
     if (w < 0.0) w += L;
@@ -109,39 +113,6 @@ __global__ __launch_bounds__(kBlock) void k_bin_stable(int64_t n, const int32_t 
         for (int k = 0; k < 8; ++k) rank += q + k < s1 && m[k] < i;
     }
     perm[s0 + rank] = i;
-}
-
-int bin_cells(const md_grid_t *grid, int64_t n, double *x, int32_t *cell, int32_t *perm, int32_t *cell_start,
-              void *ws, const WsLayout &w, hipStream_t s)
-{
-    GridArgs g;
-    for (int a = 0; a < 3; ++a) {
-        g.L[a] = grid->L[a];
-        g.hL[a] = 0.5 * grid->L[a];
-        g.inv_cell[a] = grid->inv_cell[a];
-        g.nc[a] = grid->nc[a];
-    }
-    g.reach = grid->reach;
-    int32_t *cnt = ws_ptr<int32_t>(ws, w.cell_cnt);
-    int32_t *slot = ws_ptr<int32_t>(ws, w.slot);
-    int32_t *tmp = ws_ptr<int32_t>(ws, w.tmp);
-    int rc = launch_fill_i32(cnt, grid->n_cells + 1, 0, s);
-    if (rc) return rc;
-    if (n > 0) {
-        const uint32_t gb = uint32_t((n + kBlock - 1) / kBlock);
-        hipLaunchKernelGGL(k_bin_assign, dim3(gb), dim3(kBlock), 0, s, n, x, g, ws_ptr<int32_t>(ws, w.lin2rank), cell,
-                           cnt, slot);
-        MD_HIP_TRY(hipGetLastError());
-    }
-    rc = launch_scan_i32_to_i32(cnt, cell_start, grid->n_cells, ws_ptr<int64_t>(ws, w.scan), s);
-    if (rc) return rc;
-    if (n > 0) {
-        const uint32_t gb = uint32_t((n + kBlock - 1) / kBlock);
-        hipLaunchKernelGGL(k_bin_scatter, dim3(gb), dim3(kBlock), 0, s, n, cell, slot, cell_start, tmp);
-        hipLaunchKernelGGL(k_bin_stable, dim3(gb), dim3(kBlock), 0, s, n, cell, tmp, cell_start, perm);
-        MD_HIP_TRY(hipGetLastError());
-    }
-    return MD_OK;
 }
 
 // ---------------------------------------------------------------------------
@@ -246,7 +217,7 @@ __global__ __launch_bounds__(kBlock) void k_reorder_put(int64_t n, const double 
     if (xs) xs[k] = make_uint4(scale1(p[0], k0), scale1(p[1], k1), scale1(p[2], k2), 0u);
 }
 
-int reorder_state(int64_t n, const int32_t *perm, double *x, double *v, int32_t *ids, double *xref, double *vtmp,
+static int reorder_state(int64_t n, const int32_t *perm, double *x, double *v, int32_t *ids, double *xref, double *vtmp,
                   int32_t *itmp, const md_box_t *box, uint32_t *xs, hipStream_t s)
 {
     if (n <= 0) return MD_OK;
@@ -257,6 +228,220 @@ int reorder_state(int64_t n, const int32_t *perm, double *x, double *v, int32_t 
                        two32 / box->L[0], two32 / box->L[1], two32 / box->L[2], reinterpret_cast<uint4 *>(xs));
     MD_HIP_TRY(hipGetLastError());
     return MD_OK;
+}
+
+// ---------------------------------------------------------------------------
+// sorting a small system in one launch
+// ---------------------------------------------------------------------------
+
+// What a build of the native driver reorders besides: state into the sorted order,
+// the new reference positions and scaled coordinates (xs may be NULL).
+struct SortState {
+    double *v, *xref;
+    int32_t *ids;
+    double k[3];   // 2^32 / L
+    uint4 *xs;
+};
+
+// Small systems: one block does the whole counting sort in LDS and, with STATE,
+// the reordering: the same cells, order and permutation as the general path,
+// whose five launches (seven with the reordering) of a few microseconds each
+// are what such a sort costs there.  Each thread keeps its K atoms in registers
+// from the wrap to their new places.  One CU does it all, so the work takes over
+// from the launches at some size: with STATE beyond 4,096 atoms (a whole build in
+// md_run, sort / general: 4,000 LJ atoms 46.8 / 54 us, 6,912 51.3 / 45), without
+// beyond 8,192 (md_bin_cells and the rest of a rebuild by separate calls: 6,912 atoms
+// 109 us, 8,788 on the general path 116).
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallCells = 4096;
+constexpr int64_t kSmallAtoms = 8192, kSmallState = 4096;
+static_assert(kSmallCells % kSmallBlock == 0 && kSmallAtoms <= 65536, "a thread's run of cells; 16-bit indices");
+
+template <bool STATE, int K>
+__global__ __launch_bounds__(kSmallBlock) void k_sort_small(int32_t n, double *x, GridArgs g, int32_t n_cells,
+                                                            const int32_t *lin2rank, int32_t *cell, int32_t *perm,
+                                                            int32_t *cell_start, SortState st)
+{
+    __shared__ int32_t start[kSmallCells + 1];
+    __shared__ uint16_t member[kSmallBlock * K];
+    __shared__ int32_t wsum[kSmallBlock / kWave];
+    const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
+    constexpr int C = kSmallCells / kSmallBlock;
+    for (int c = t; c <= kSmallCells; c += kSmallBlock) start[c] = 0;
+    double p[K][3];
+    int32_t rank[K], at[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int32_t i = t + k * kSmallBlock;
+        if (i >= n) continue;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) p[k][a] = x[a * n + i];
+    }
+    __syncthreads();
+    // cell of each atom, a slot in it
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int32_t i = t + k * kSmallBlock;
+        if (i >= n) continue;
+        int32_t c[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            p[k][a] = wrap1(p[k][a], g.L[a]);
+            if (!STATE) x[a * n + i] = p[k][a];
+            c[a] = cell1(p[k][a], g.inv_cell[a], g.nc[a]);
+        }
+        rank[k] = lin2rank[c[0] + int64_t(g.nc[0]) * (c[1] + int64_t(g.nc[1]) * c[2])];
+        cell[i] = rank[k];
+        at[k] = atomicAdd(&start[rank[k]], 1);
+    }
+    __syncthreads();
+    // first atom of each cell
+    int32_t cnt[C], sum = 0;
+#pragma unroll
+    for (int q = 0; q < C; ++q) {
+        cnt[q] = start[t * C + q];
+        sum += cnt[q];
+    }
+    int32_t inc = sum;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int32_t u = __shfl_up(inc, o, kWave);
+        if (lane >= o) inc += u;
+    }
+    if (lane == kWave - 1) wsum[wave] = inc;
+    __syncthreads();
+    int32_t run = inc - sum;
+    for (int w = 0; w < wave; ++w) run += wsum[w];
+#pragma unroll
+    for (int q = 0; q < C; ++q) {
+        const int32_t c = t * C + q;
+        start[c] = run;
+        if (c <= n_cells) cell_start[c] = run;
+        run += cnt[q];
+    }
+    if (t == kSmallBlock - 1) {
+        start[kSmallCells] = run;
+        if (n_cells == kSmallCells) cell_start[n_cells] = run;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if (t + k * kSmallBlock < n) member[start[rank[k]] + at[k]] = uint16_t(t + k * kSmallBlock);
+    __syncthreads();
+    // stable order: the place among the members of the cell
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int32_t i = t + k * kSmallBlock;
+        if (i >= n) continue;
+        const int32_t s0 = start[rank[k]], s1 = start[rank[k] + 1];
+        int32_t d = s0;
+        for (int32_t q = s0; q < s1; q += 8) {   // eight reads in flight
+            int32_t m[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) m[u] = member[min(q + u, s1 - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) d += q + u < s1 && m[u] < i;
+        }
+        at[k] = d;
+        perm[d] = i;
+    }
+    if constexpr (STATE) {
+        // every thread has read its positions (before the first barrier)
+        double v[K][3];
+        int32_t id[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int32_t i = t + k * kSmallBlock;
+            if (i >= n) continue;
+            const int32_t d = at[k];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                x[a * n + d] = p[k][a];
+                st.xref[a * n + d] = p[k][a];
+                v[k][a] = st.v[a * n + i];
+            }
+            id[k] = st.ids[i];
+            if (st.xs)
+                st.xs[d] = make_uint4(scale1(p[k][0], st.k[0]), scale1(p[k][1], st.k[1]), scale1(p[k][2], st.k[2]), 0u);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (t + k * kSmallBlock >= n) continue;
+            const int32_t d = at[k];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) st.v[a * n + d] = v[k][a];
+            st.ids[d] = id[k];
+        }
+    }
+}
+
+static GridArgs grid_args(const md_grid_t *grid)
+{
+    GridArgs g;
+    for (int a = 0; a < 3; ++a) {
+        g.L[a] = grid->L[a];
+        g.hL[a] = 0.5 * grid->L[a];
+        g.inv_cell[a] = grid->inv_cell[a];
+        g.nc[a] = grid->nc[a];
+    }
+    g.reach = grid->reach;
+    return g;
+}
+
+static bool sorts_small(const md_grid_t *grid, int64_t n, int64_t most)
+{
+    return n > 0 && n <= most && grid->n_cells <= kSmallCells;
+}
+
+int bin_cells(const md_grid_t *grid, int64_t n, double *x, int32_t *cell, int32_t *perm, int32_t *cell_start,
+              void *ws, const WsLayout &w, hipStream_t s)
+{
+    const GridArgs g = grid_args(grid);
+    if (sorts_small(grid, n, kSmallAtoms)) {
+        hipLaunchKernelGGL((n <= 4 * kSmallBlock ? k_sort_small<false, 4> : k_sort_small<false, 8>), dim3(1), dim3(kSmallBlock), 0, s, int32_t(n), x, g,
+                           int32_t(grid->n_cells), ws_ptr<int32_t>(ws, w.lin2rank), cell, perm, cell_start, SortState{});
+        MD_HIP_TRY(hipGetLastError());
+        return MD_OK;
+    }
+    int32_t *cnt = ws_ptr<int32_t>(ws, w.cell_cnt);
+    int32_t *slot = ws_ptr<int32_t>(ws, w.slot);
+    int32_t *tmp = ws_ptr<int32_t>(ws, w.tmp);
+    int rc = launch_fill_i32(cnt, grid->n_cells + 1, 0, s);
+    if (rc) return rc;
+    if (n > 0) {
+        const uint32_t gb = uint32_t((n + kBlock - 1) / kBlock);
+        hipLaunchKernelGGL(k_bin_assign, dim3(gb), dim3(kBlock), 0, s, n, x, g, ws_ptr<int32_t>(ws, w.lin2rank), cell,
+                           cnt, slot);
+        MD_HIP_TRY(hipGetLastError());
+    }
+    rc = launch_scan_i32_to_i32(cnt, cell_start, grid->n_cells, ws_ptr<int64_t>(ws, w.scan), s);
+    if (rc) return rc;
+    if (n > 0) {
+        const uint32_t gb = uint32_t((n + kBlock - 1) / kBlock);
+        hipLaunchKernelGGL(k_bin_scatter, dim3(gb), dim3(kBlock), 0, s, n, cell, slot, cell_start, tmp);
+        hipLaunchKernelGGL(k_bin_stable, dim3(gb), dim3(kBlock), 0, s, n, cell, tmp, cell_start, perm);
+        MD_HIP_TRY(hipGetLastError());
+    }
+    return MD_OK;
+}
+
+// bin_cells and reorder_state of a build.
+int sort_state(const md_grid_t *grid, int64_t n, double *x, int32_t *cell, int32_t *perm, int32_t *cell_start,
+               void *ws, const WsLayout &w, double *v, int32_t *ids, double *xref, double *vtmp, int32_t *itmp,
+               const md_box_t *box, uint32_t *xs, hipStream_t s)
+{
+    if (sorts_small(grid, n, kSmallState)) {
+        const double two32 = 4294967296.0;
+        const SortState st{v, xref, ids, {two32 / box->L[0], two32 / box->L[1], two32 / box->L[2]},
+                           reinterpret_cast<uint4 *>(xs)};
+        hipLaunchKernelGGL((k_sort_small<true, kSmallState / kSmallBlock>), dim3(1), dim3(kSmallBlock), 0, s, int32_t(n), x, grid_args(grid),
+                           int32_t(grid->n_cells), ws_ptr<int32_t>(ws, w.lin2rank), cell, perm, cell_start, st);
+        MD_HIP_TRY(hipGetLastError());
+        return MD_OK;
+    }
+    if (int rc = bin_cells(grid, n, x, cell, perm, cell_start, ws, w, s)) return rc;
+    return reorder_state(n, perm, x, v, ids, xref, vtmp, itmp, box, xs, s);
 }
 
 // The element of each atom (0 or 1; only bit 0 is used) into the fourth word
@@ -660,18 +845,17 @@ void k_neighbors_small(int64_t n, const double *x, GridArgs g, double rl2, doubl
 }
 
 // ---- the matrix-core build ----
-constexpr int kNmStage = 2 * kWave;   // staged candidates: a rest plus what one chunk of 64 keeps
-
 typedef float nm_f32x4 __attribute__((ext_vector_type(4)));
 
-template <int R>
+template <int R, int D>
 struct NmLds {
     static constexpr int kCells = (2 * R + 1) * (2 * R + 1) * (2 * R + 1);
-    float4 stage[kNmStage];          // kept candidates: position from the batch's centre, its square
+    static constexpr int kStage = (D + 1) * kWave;   // staged candidates: a rest plus what D chunks of 64 keep
+    float4 stage[kStage];          // kept candidates: position from the batch's centre, its square
     float4 home[kWave];              // homes: -2 x, -2 y, -2 z, 1
     float hom2[kWave];               // |home|^2 - r_list^2
     int32_t run[kWave], off[kWave];  // homes: row length so far, byte offset of the row in the batch's rows
-    int32_t stage_j[kNmStage];
+    int32_t stage_j[kStage];
     int32_t shift[kCells];           // stencil cell: its first atom minus the candidates before it
     int32_t rbase[kCells + 1];       // candidates before it
     int8_t img[kCells][4];           // its periodic image
@@ -833,14 +1017,13 @@ __device__ __forceinline__ int32_t wave_prefix(int32_t v)
 }
 
 // The homes of cell `rank` (those of `part`) against its stencil's
-// candidates; returns the longest row.  Candidates are read 64 at a time, the
-// next ones while the last are worked on; one is kept if it lies within
-// r_list of the bounding box of the batch's homes, in its periodic image of
+// candidates; returns the longest row.  Candidates are read D chunks of 64 at a
+// time; one is kept if it lies within r_list of the bounding box of the batch's homes, in its periodic image of
 // the stencil (FP32 positions from the box's centre, margin 1e-5 of r_list^2,
 // far above their rounding), or is one of the homes itself, which keeps these
 // consecutive in the stage.
-template <int R>
-__device__ __forceinline__ int32_t nm_cell(NmLds<R> &L, int64_t rank, int32_t part, int64_t n, const double *x,
+template <int R, int D>
+__device__ __forceinline__ int32_t nm_cell(NmLds<R, D> &L, int64_t rank, int32_t part, int64_t n, const double *x,
                                            const GridArgs &g, double rl2, const NbSplit &sp,
                                            const int32_t *cell_start, const int32_t *rank_xyz,
                                            const int32_t *lin2rank, int32_t row_cap, int32_t *idx, int32_t *count)
@@ -930,10 +1113,11 @@ __device__ __forceinline__ int32_t nm_cell(NmLds<R> &L, int64_t rank, int32_t pa
         const int32_t ts = centre + (hb - h0);   // candidate number of the first home
         int32_t self = 1 << 28;                  // its place in the stage, once staged
 
-        int32_t j = 0;
-        uint32_t im = 0;
-        double cx = 0.0, cy = 0.0, cz = 0.0;
-        auto fetch = [&](int32_t gq) {
+        int32_t j[D];
+        uint32_t im[D];
+        double cx[D], cy[D], cz[D];
+        auto fetch = [&](int d, int32_t gq) {
+            j[d] = 0, im[d] = 0, cx[d] = cy[d] = cz[d] = 0.0;
             if (gq >= total) return;
             int k = 0;
             if (total <= kNbMap) {
@@ -945,35 +1129,39 @@ __device__ __forceinline__ int32_t nm_cell(NmLds<R> &L, int64_t rank, int32_t pa
                     k = L.rbase[t] <= gq ? t : k;
                 }
             }
-            j = gq + L.shift[k];
-            im = *reinterpret_cast<const uint32_t *>(L.img[k]);
-            cx = x[j], cy = x[n + j], cz = x[2 * n + j];
+            j[d] = gq + L.shift[k];
+            im[d] = *reinterpret_cast<const uint32_t *>(L.img[k]);
+            cx[d] = x[j[d]], cy[d] = x[n + j[d]], cz[d] = x[2 * n + j[d]];
         };
         int32_t fill = 0;
-        for (int32_t t0 = 0; t0 < total; t0 += kWave) {
-            fetch(t0 + lane);
-            if (!interior) {
-                cx += double(int8_t(im)) * g.L[0];
-                cy += double(int8_t(im >> 8)) * g.L[1];
-                cz += double(int8_t(im >> 16)) * g.L[2];
+        for (int32_t t0 = 0; t0 < total; t0 += D * kWave) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) fetch(d, t0 + d * kWave + lane);
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const int32_t td = t0 + d * kWave;
+                if (!interior) {
+                    cx[d] += double(int8_t(im[d])) * g.L[0];
+                    cy[d] += double(int8_t(im[d] >> 8)) * g.L[1];
+                    cz[d] += double(int8_t(im[d] >> 16)) * g.L[2];
+                }
+                const float qx = float(cx[d] - mx), qy = float(cy[d] - my), qz = float(cz[d] - mz);
+                const float dx = fmaxf(fabsf(qx) - bx, 0.f), dy = fmaxf(fabsf(qy) - by, 0.f),
+                            dz = fmaxf(fabsf(qz) - bz, 0.f);
+                const float d2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
+                const bool keep = td + lane < total && (d2 < keep2 || uint32_t(j[d] - hb) < uint32_t(hn));
+                const uint64_t mk = __builtin_amdgcn_ballot_w64(keep);
+                const int32_t tl = ts - td;
+                if (tl >= 0 && tl < kWave) self = fill + __popcll(mk & ((uint64_t(1) << tl) - 1));
+                if (keep) {
+                    const int32_t at = int32_t(__builtin_amdgcn_mbcnt_hi(
+                        uint32_t(mk >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mk), uint32_t(fill))));
+                    L.stage[at] = make_float4(qx, qy, qz, __builtin_fmaf(qz, qz, __builtin_fmaf(qy, qy, qx * qx)));
+                    L.stage_j[at] = j[d];
+                }
+                fill += __popcll(mk);
             }
-            const float qx = float(cx - mx), qy = float(cy - my), qz = float(cz - mz);
-            const int32_t jr = j;
-            const float dx = fmaxf(fabsf(qx) - bx, 0.f), dy = fmaxf(fabsf(qy) - by, 0.f),
-                        dz = fmaxf(fabsf(qz) - bz, 0.f);
-            const float d2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
-            const bool keep = t0 + lane < total && (d2 < keep2 || uint32_t(jr - hb) < uint32_t(hn));
-            const uint64_t mk = __builtin_amdgcn_ballot_w64(keep);
-            const int32_t tl = ts - t0;
-            if (tl >= 0 && tl < kWave) self = fill + __popcll(mk & ((uint64_t(1) << tl) - 1));
-            if (keep) {
-                const int32_t at = int32_t(__builtin_amdgcn_mbcnt_hi(
-                    uint32_t(mk >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mk), uint32_t(fill))));
-                L.stage[at] = make_float4(qx, qy, qz, __builtin_fmaf(qz, qz, __builtin_fmaf(qy, qy, qx * qx)));
-                L.stage_j[at] = jr;
-            }
-            fill += __popcll(mk);
-            const bool last = t0 + kWave >= total;
+            const bool last = t0 + D * kWave >= total;
             if (last && lane >= (fill & (kWave - 1)) && (fill & (kWave - 1))) {
                 // candidates that no home hits fill the last chunk
                 const int32_t at = (fill & ~(kWave - 1)) + lane;
@@ -1041,36 +1229,53 @@ void k_neighbors(int64_t n, const double *__restrict__ x, GridArgs g, double rl2
                  const int32_t *__restrict__ lin2rank, int32_t row_cap, int32_t *__restrict__ idx,
                  int32_t *__restrict__ count, int32_t *max_count)
 {
-    __shared__ NmLds<R> L;
+    __shared__ NmLds<R, 1> L;
     const uint32_t blk = xcd_chunked(blockIdx.x, gridDim.x, kNbXcdChunk);
     const uint32_t rank = blk / uint32_t(sp.parts), part = blk % uint32_t(sp.parts);
-    nb_longest(nm_cell<R>(L, rank, int32_t(part), n, x, g, rl2, sp, cell_start, rank_xyz, lin2rank, row_cap, idx, count),
+    nb_longest(nm_cell<R, 1>(L, rank, int32_t(part), n, x, g, rl2, sp, cell_start, rank_xyz, lin2rank, row_cap, idx,
+                             count),
+               max_count);
+}
+
+// The same with four chunks of candidates requested at once, for cells too few to
+// fill the chip: a wavefront is then alone on its SIMD, and the trips to memory of
+// its ~14 chunks, one after another, are its time.  (FEW_FIGURES)
+template <int R>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2)))
+void k_neighbors_few(int64_t n, const double *__restrict__ x, GridArgs g, double rl2, NbSplit sp,
+                     const int32_t *__restrict__ cell_start, const int32_t *__restrict__ rank_xyz,
+                     const int32_t *__restrict__ lin2rank, int32_t row_cap, int32_t *__restrict__ idx,
+                     int32_t *__restrict__ count, int32_t *max_count)
+{
+    __shared__ NmLds<R, 4> L;
+    const uint32_t rank = blockIdx.x / uint32_t(sp.parts), part = blockIdx.x % uint32_t(sp.parts);
+    nb_longest(nm_cell<R, 4>(L, rank, int32_t(part), n, x, g, rl2, sp, cell_start, rank_xyz, lin2rank, row_cap, idx,
+                             count),
                max_count);
 }
 
 // Wavefronts per cell: one, unless the cells are too few to fill the chip
 // (256 CUs x 4 SIMDs x 2); then batches of 16 homes (8 on the path without
-// matrix cores), as many parts as an average cell has batches.
+// matrix cores), as many parts as an average cell has batches, and smaller
+// batches, down to 4, while there is less than a wavefront a SIMD: the rows of
+// a batch are written one after another (k_neighbors_few, 4,000 LJ atoms: 31 us with
+// 16 homes a wavefront, 23 with 4).
+constexpr int64_t kNbFew = 2048;   // cells
+
 NbSplit nb_split(int64_t n, int64_t n_cells, bool small)
 {
-    if (n_cells >= 2048) return {1, kWave};
-    const int32_t batch = small ? 8 : 16;
-    const int64_t parts = (n + n_cells * batch - 1) / (n_cells * batch);
-    return {int32_t(parts < 1 ? 1 : (parts > 8 ? 8 : parts)), batch};
+    if (n_cells >= kNbFew) return {1, kWave};
+    int32_t batch = small ? 8 : 16;
+    const auto parts = [&] { return (n + n_cells * batch - 1) / (n_cells * batch); };
+    while (!small && batch > 4 && n_cells * parts() < kNbFew / 2) batch /= 2;
+    return {int32_t(std::min<int64_t>(std::max<int64_t>(parts(), 1), 8)), batch};
 }
 
 int build_neighbors(const md_grid_t *grid, int64_t n, const double *x, const int32_t *cell_start, int32_t row_cap,
                     int32_t *idx, int32_t *count, int32_t *max_count, int32_t *needed, void *ws, const WsLayout &w,
                     hipStream_t s)
 {
-    GridArgs g;
-    for (int a = 0; a < 3; ++a) {
-        g.L[a] = grid->L[a];
-        g.hL[a] = 0.5 * grid->L[a];
-        g.inv_cell[a] = grid->inv_cell[a];
-        g.nc[a] = grid->nc[a];
-    }
-    g.reach = grid->reach;
+    const GridArgs g = grid_args(grid);
     const double rl2 = grid->r_list * grid->r_list;
     int rc = launch_fill_i32(max_count, 1, 0, s);
     if (rc) return rc;
@@ -1084,12 +1289,13 @@ int build_neighbors(const md_grid_t *grid, int64_t n, const double *x, const int
         if (small)
             hipLaunchKernelGGL(k_neighbors_small, nb, dim3(kWave), 0, s, n, x, g, rl2, rl2 * (1.0 + 1e-9), sp,
                                cell_start, xyz, l2r, row_cap, idx, count, max_count);
-        else if (grid->reach == 1)
-            hipLaunchKernelGGL(k_neighbors<1>, nb, dim3(kWave), 0, s, n, x, g, rl2, sp, cell_start, xyz, l2r, row_cap,
-                               idx, count, max_count);
-        else
-            hipLaunchKernelGGL(k_neighbors<2>, nb, dim3(kWave), 0, s, n, x, g, rl2, sp, cell_start, xyz, l2r,
-                               row_cap, idx, count, max_count);
+        else {
+            const bool few = grid->n_cells < kNbFew;
+            const auto kernel = grid->reach == 1 ? (few ? k_neighbors_few<1> : k_neighbors<1>)
+                                                 : (few ? k_neighbors_few<2> : k_neighbors<2>);
+            hipLaunchKernelGGL(kernel, nb, dim3(kWave), 0, s, n, x, g, rl2, sp, cell_start, xyz, l2r, row_cap, idx,
+                               count, max_count);
+        }
         MD_HIP_TRY(hipGetLastError());
     }
     if (needed) {

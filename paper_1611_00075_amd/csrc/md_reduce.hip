@@ -73,11 +73,13 @@ __global__ __launch_bounds__(kBlock) void k_scan_tile_offsets(int64_t *bsum, int
     }
 }
 
-// phase 3: rescan each tile and write out[q+1] = inclusive prefix (out[0] = 0)
-template <typename OutT>
+// phase 3: rescan each tile and write out[q+1] = inclusive prefix (out[0] = 0).
+// SUMS: bsum holds the tiles' sums, and the block adds those before its own itself.
+template <typename OutT, bool SUMS>
 __global__ __launch_bounds__(kBlock) void k_scan_write(const int32_t *in, int64_t m, const int64_t *bsum, OutT *out)
 {
     __shared__ int64_t lds[kBlock / kWave];
+    __shared__ int64_t before;
     const int64_t base = int64_t(blockIdx.x) * kScanTile + int64_t(threadIdx.x) * kScanItems;
     int32_t v[kScanItems];
     int64_t s = 0;
@@ -87,8 +89,19 @@ __global__ __launch_bounds__(kBlock) void k_scan_write(const int32_t *in, int64_
         v[k] = q < m ? in[q] : 0;
         s += v[k];
     }
+    int64_t off;
+    if (SUMS) {
+        int64_t t = 0;
+        for (uint32_t q = threadIdx.x; q < blockIdx.x; q += kBlock) t += bsum[q];
+        t = block_incl_scan(t, lds);
+        if (threadIdx.x == kBlock - 1) before = t;
+        __syncthreads();
+        off = before;
+    } else {
+        off = bsum[blockIdx.x];
+    }
     const int64_t inc = block_incl_scan(s, lds);
-    int64_t run = bsum[blockIdx.x] + inc - s;
+    int64_t run = off + inc - s;
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
         const int64_t q = base + k;
@@ -98,19 +111,61 @@ __global__ __launch_bounds__(kBlock) void k_scan_write(const int32_t *in, int64_
     if (blockIdx.x == 0 && threadIdx.x == 0) out[0] = OutT(0);
 }
 
+// The whole scan by one block, kScanOneItems consecutive inputs a thread.
+constexpr int kScanOneBlock = 1024, kScanOneItems = 16;
+template <typename OutT>
+__global__ __launch_bounds__(kScanOneBlock) void k_scan_one(const int32_t *in, int32_t m, OutT *out)
+{
+    __shared__ int64_t lds[kScanOneBlock / kWave];
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int32_t base = int32_t(threadIdx.x) * kScanOneItems;
+    int32_t v[kScanOneItems];
+    int64_t s = 0;
+#pragma unroll
+    for (int k = 0; k < kScanOneItems; ++k) {
+        v[k] = base + k < m ? in[base + k] : 0;
+        s += v[k];
+    }
+    int64_t inc = s;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int64_t t = __shfl_up(inc, o, kWave);
+        if (lane >= o) inc += t;
+    }
+    if (lane == kWave - 1) lds[wave] = inc;
+    __syncthreads();
+    int64_t run = inc - s;
+    for (int w = 0; w < wave; ++w) run += lds[w];
+#pragma unroll
+    for (int k = 0; k < kScanOneItems; ++k) {
+        run += v[k];
+        if (base + k < m) out[base + k + 1] = OutT(run);
+    }
+    if (threadIdx.x == 0) out[0] = OutT(0);
+}
+
+// Launches are what a scan of cell counts costs (2 to 5 us each with the gap before
+// it): one up to 16,384 values (3.8 us; three launches of 7.5 us before); two
+// while a block can add the sums of the tiles before it in a few loads a thread
+// (4 M values; 74,000 take 7.9 us, three launches took 10.5); else three.
+constexpr int64_t kScanSelf = 2048;   // tiles
+
 template <typename OutT>
 static int scan_impl(const int32_t *in, OutT *out, int64_t m, int64_t *bsum, hipStream_t s)
 {
-    if (m <= 0) {
-        hipLaunchKernelGGL(k_scan_write<OutT>, dim3(1), dim3(kBlock), 0, s, in, int64_t(0), bsum, out);
+    if (m <= kScanOneBlock * kScanOneItems) {
+        hipLaunchKernelGGL(k_scan_one<OutT>, dim3(1), dim3(kScanOneBlock), 0, s, in, int32_t(m > 0 ? m : 0), out);
         MD_HIP_TRY(hipGetLastError());
-        // bsum[0] may be garbage but no item reads it except out[0] = 0
         return MD_OK;
     }
     const int64_t nb = (m + kScanTile - 1) / kScanTile;
     hipLaunchKernelGGL(k_scan_tile_sums, dim3(uint32_t(nb)), dim3(kBlock), 0, s, in, m, bsum);
-    hipLaunchKernelGGL(k_scan_tile_offsets, dim3(1), dim3(kBlock), 0, s, bsum, nb);
-    hipLaunchKernelGGL(k_scan_write<OutT>, dim3(uint32_t(nb)), dim3(kBlock), 0, s, in, m, bsum, out);
+    if (nb <= kScanSelf) {
+        hipLaunchKernelGGL((k_scan_write<OutT, true>), dim3(uint32_t(nb)), dim3(kBlock), 0, s, in, m, bsum, out);
+    } else {
+        hipLaunchKernelGGL(k_scan_tile_offsets, dim3(1), dim3(kBlock), 0, s, bsum, nb);
+        hipLaunchKernelGGL((k_scan_write<OutT, false>), dim3(uint32_t(nb)), dim3(kBlock), 0, s, in, m, bsum, out);
+    }
     MD_HIP_TRY(hipGetLastError());
     return MD_OK;
 }

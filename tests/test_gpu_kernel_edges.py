@@ -455,3 +455,34 @@ def test_run_ahead_stops_at_a_position_that_is_no_number(M, when):
         out.append((sim.x.cpu().numpy(), sim.v.cpu().numpy()))
     for a, b in zip(*out):
         assert np.array_equal(a, b, equal_nan=True)
+
+
+# ---- binning -------------------------------------------------------------------------
+
+@pytest.mark.parametrize("n,nc", [(1, (3, 3, 3)), (1023, (16, 16, 16)), (1025, (5, 30, 7)), (4096, (17, 16, 16)),
+                                  (8191, (4, 4, 4)), (8192, (16, 16, 16)), (8193, (16, 16, 16)), (8192, (25, 25, 26)),
+                                  (9000, (26, 26, 26)), (9000, (162, 162, 162))])
+def test_sort_at_the_sizes_of_its_launches(M, orc, n, nc):
+    """One launch up to 8,192 atoms and 4,096 cells; scans of up to 16,384
+    counts by one block, up to 2,048 tiles of 2,048 in two launches, three above:
+    wrapped positions, cells, stable order and offsets are those of the
+    definition, to the bit."""
+    rng = np.random.default_rng(n + nc[0])
+    L = np.array(nc) + 0.5
+    x = rng.uniform(-0.3, 1.3, (n, 3)) * L
+    x[rng.random(n) < 0.3] = 0.25 * L          # a crowded cell
+    g = M.md_grid_init(L, 1.0)
+    assert tuple(g.nc) == nc
+    ws = torch.empty(M.md_workspace_bytes(g, n), dtype=torch.uint8, device="cuda")
+    M.md_workspace_init(g, n, ws)
+    xd = torch.tensor(x.T.copy(), device="cuda")
+    cell, perm = (torch.full((n,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+    start = torch.full((g.n_cells + 1,), -1, dtype=torch.int32, device="cuda")
+    M.md_bin_cells(g, n, xd, cell, perm, start, ws)
+    w = orc.wrap(x, L)
+    c = orc.cell_coords(w, L, nc).astype(np.int64)
+    rank = M.md_grid_cell_ranks(g)[c[:, 0] + nc[0] * (c[:, 1] + nc[1] * c[:, 2])]
+    assert np.array_equal(xd.cpu().numpy().T, w)
+    assert np.array_equal(cell.cpu().numpy(), rank)
+    assert np.array_equal(perm.cpu().numpy(), np.argsort(rank, kind="stable"))
+    assert np.array_equal(start.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(rank, minlength=g.n_cells))]))
