@@ -16,9 +16,7 @@
 // per block only pays when a block covers many atoms, so the blocks are
 // large (16 waves sharing one copy of the table) and each covers a
 // contiguous run of slices of 8 atoms, the runs of one XCD forming one
-// contiguous Morton range.  The grid is a few times what is resident at
-// once: with exactly one resident round the slowest waves set the time;
-// with several, the dispatcher fills the CUs that finish first.
+// contiguous Morton range.
 #include <cmath>
 #include <type_traits>
 #include <vector>
@@ -28,7 +26,6 @@
 namespace md {
 
 constexpr int kTabBlock = 1024;
-constexpr uint32_t kTabRounds = 4;   // grid = this many times the resident blocks
 constexpr int kTabWaves = kTabBlock / kWave;
 
 struct TAB32 {
@@ -288,9 +285,15 @@ int tab_pack(const md_tab_t *t, const double *psi, const double *dpsi, const dou
     return MD_OK;
 }
 
-// Blocks of the grid: kTabRounds times as many as fit on the device at once
-// for this kernel and LDS size, a multiple of 8, no more than the slices
-// need.
+// Blocks of the grid: as many as fit on the device at once for this kernel and LDS
+// size, and twice that (the dispatcher then fills the CUs that finish first)
+// once their wavefronts would take kTabDeep slices each; a multiple of 8, no more
+// than the slices need.  A block stages its table before its first slice, and
+// further rounds of blocks with a slice or two a wavefront are mostly staging.
+// Passes 1 + 2 with one, two and four rounds: 133,000 Cu atoms (2 slices a wavefront)
+// 14.5 + 16.8, 15.4 + 19.5, 16.7 + 20.8 us; 256,000 22.1 + 29.4, 23.3 + 29.1, 24.0 + 33.8;
+// 1 M (16 slices) 79.5 + 100.8, 76.2 + 98.2, 79.1 + 102.
+constexpr uint32_t kTabDeep = 8;
 static uint32_t tab_grid(const void *kernel, size_t lds, uint32_t nslices)
 {
     static int cus[64] = {0};
@@ -304,7 +307,8 @@ static uint32_t tab_grid(const void *kernel, size_t lds, uint32_t nslices)
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kTabBlock, lds) != hipSuccess || per_cu < 1)
         per_cu = 1;
-    const uint32_t full = uint32_t(cus[dev]) * uint32_t(per_cu) * kTabRounds;
+    const uint32_t once = uint32_t(cus[dev]) * uint32_t(per_cu);
+    const uint32_t full = nslices >= once * kTabWaves * kTabDeep ? 2 * once : once;
     const uint32_t need = (nslices + kTabWaves - 1) / kTabWaves;
     const uint32_t g = need < full ? need : full;
     return (g + kXcds - 1) / kXcds * kXcds;

@@ -457,6 +457,26 @@ def test_run_ahead_stops_at_a_position_that_is_no_number(M, when):
         assert np.array_equal(a, b, equal_nan=True)
 
 
+# ---- tabulated functions -------------------------------------------------------------
+
+@pytest.mark.parametrize("cells", [(4, 4, 4), (13, 13, 13), (33, 32, 32), (51, 51, 51)])
+def test_tabulated_forces_at_every_grid(M, cells):
+    """Fewer slices than wavefronts, one round of blocks with one to a few
+    slices a wavefront, two rounds: the table samples the Finnis-Sinclair set, so
+    both forms give the same forces (each within 1e-5 normwise of the FP64 ones)."""
+    from paper_1611_00075_amd.sim import Simulation
+    x = _fcc(cells, inputs.CU_A0)
+    x = x[: len(x) - 5]
+    x = x + 0.1 * np.random.default_rng(len(x)).standard_normal(x.shape)
+    out = []
+    for kw in (dict(potential="tab", tab=inputs.fs_table(inputs.FS_CU)), dict(potential="eam", fs=inputs.FS_CU)):
+        sim = Simulation(np.array(cells) * inputs.CU_A0, x, np.zeros_like(x), skin=1.0, dt=1.0, **kw)
+        sim.f.fill_(float("nan"))
+        sim.compute_forces()
+        out.append(sim.f.double())
+    assert (out[0] - out[1]).norm().item() <= 2e-5 * out[1].norm().item()
+
+
 # ---- binning -------------------------------------------------------------------------
 
 @pytest.mark.parametrize("n,nc", [(1, (3, 3, 3)), (1023, (16, 16, 16)), (1025, (5, 30, 7)), (4096, (17, 16, 16)),
