@@ -675,11 +675,11 @@ typedef struct md_system {
  * them to input order.
  * The host waits once per step for the 4-byte rebuild flag, and once per
  * build for the longest list row: when host_status is pinned host memory
- * the device publishes them there (words 0 and 1 in turn: flag, word 3:
+ * the device publishes them there (words 0 to 2 in turn: flag, word 3:
  * longest row) and the host polls them, otherwise it copies them and
  * synchronises the stream.  Each step's force evaluation is queued before the
  * host has read the flag (and after a build, before it has read the longest
- * row), with host_status the next step as well; the kernels skip themselves
+ * row), with host_status the next one or two steps as well; the kernels skip themselves
  * on the device when the flag is set or a row overflowed.
  * Returns MD_OK when all steps are done and the state is at a step boundary.
  * Inside a run of a small system the kick and drift are part of the force

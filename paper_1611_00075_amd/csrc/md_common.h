@@ -42,8 +42,8 @@ constexpr uint32_t kXcdChunk = 512;
 __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t G) { return xcd_chunked(b, G, kXcdChunk); }
 
 // Device-side skip of a speculative launch: a gated kernel returns at once
-// when *flag is tag or tag_before, or *over > limit (words written earlier on
-// the same stream).
+// when *flag is one of the tags tag_before .. tag, or *over > limit (words written
+// earlier on the same stream).
 struct Gate {
     const int32_t *flag = nullptr;
     int32_t tag = 0, tag_before = 0;
@@ -52,7 +52,7 @@ struct Gate {
 };
 __device__ __forceinline__ bool gated(const Gate &g)
 {
-    return (g.flag && (*g.flag == g.tag || *g.flag == g.tag_before)) || (g.over && *g.over > g.limit);
+    return (g.flag && uint32_t(g.tag - *g.flag) <= uint32_t(g.tag - g.tag_before)) || (g.over && *g.over > g.limit);
 }
 
 // A step's rebuild flag in one host word: the step's tag and two bits, so that

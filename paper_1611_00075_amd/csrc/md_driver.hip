@@ -7,17 +7,18 @@
 // scaled coordinates (FP64: positions) go to a second buffer, md_system_t.scratch,
 // as other blocks still read the old ones; the two buffers swap each step, and the
 // first drift of a run chooses its side so that the run ends in the caller's.
-// Evaluations are queued one ahead of the host: that of step k + 1 does nothing if
-// the flag of step k or of step k + 1 asks for a build.  Each posts its step's
+// Evaluations are queued two ahead of the host: that of step k + 2 does nothing if
+// the flag of step k, k + 1 or k + 2 asks for a build.  Each posts its step's
 // flag to pinned host memory; when some atom has moved more than half the skin the
-// host rebuilds the lists, evaluates step k again and queues step k + 1 anew.  A
+// host rebuilds the lists, evaluates step k again and queues the next steps anew.  A
 // step is one launch (two with two-pass forces) and the GPU does not wait for the
-// host.
+// host.  (One ahead, a step waited for the host's round trip: LJ of 4,000 atoms
+// 7.9 us a step, now 6.3; FS of 2,048 10.9, now 9.5.)
 //
 // In large systems (kFuseAtoms), with timing (a force evaluation then has to be a
 // launch of its own), with plain FP32 sums or with a scratch buffer that is not aligned to 16 bytes, a kick-drift kernel
 // before each evaluation does the update in place, and posts the flag of the
-// step before it.
+// step before it; the host is then one step behind.
 #include <chrono>
 #include <thread>
 
@@ -44,10 +45,10 @@ __global__ void k_publish_longest(const int32_t *max_count, int32_t *host)
 
 namespace {
 
-// Host word of a step's flag: two words in turn, as the flag of step k + 1 can
-// be posted before the host has read that of step k.  `host_dev` is the
+// Host word of a step's flag: three words in turn, as the flags of steps k + 1 and
+// k + 2 can be posted before the host has read that of step k.  `host_dev` is the
 // device's address of md_system_t.host_status.
-inline uint32_t *flag_slot(int32_t *base, int32_t tag) { return reinterpret_cast<uint32_t *>(base) + (tag & 1); }
+inline uint32_t *flag_slot(int32_t *base, int32_t tag) { return reinterpret_cast<uint32_t *>(base) + uint32_t(tag) % 3u; }
 
 // Clears the word before the kernel that posts `tag` is queued.
 void expect_flag(md_system_t *sys, int32_t tag)
@@ -359,44 +360,49 @@ int run(md_system_t *sys, int64_t steps, hipStream_t s)
         return kick_drift(&sys->box, n, side[b].x, sys->v, sys->f, f64, h, sys->dt, sys->xref, sys->half_skin_sq,
                           sys->status, tag, side[to].xs, s, sys->potential == MD_POT_TBM, post, side[to].x);
     };
-    bool queued = false;   // evaluation of the step in flight queued, its flag unread
-    int b = 0;             // side of the positions of the step in flight
+    const int64_t depth = fuse ? 2 : 1;   // steps queued behind the one in flight
+    int b = 0;                    // side of the positions of the step in flight
+    int64_t known = sys->step;    // flags up to this step's are read
+    int64_t queued = sys->step;   // evaluations up to this step's are queued (none beyond `step`: none in flight)
+    int qb = 0;                   // side of the positions of the last queued one
+    // Queues the step after the last queued one: its kick and drift unless that
+    // one's evaluation makes them, and its evaluation.
+    const auto queue_after = [&]() -> int {
+        int to = qb;
+        if (besides(queued, qb) == kDrift) to = !qb;
+        else if (int r = queue_drift(2.0 * hk, queued + 1, qb, qb, queued > known)) return r;
+        if (int r = queue_forces(queued + 1, to, Gate{sys->status, int32_t(queued + 1), int32_t(known + 1)}, true))
+            return r;
+        ++queued;
+        qb = to;
+        return MD_OK;
+    };
     for (;;) {
+        const int64_t k = sys->step + 1;
+        const int32_t tag = int32_t(k);
         if (sys->phase == 0) {
             if (done >= steps) break;
-            const int64_t k = sys->step + 1;
             b = fuse && sys->potential != MD_POT_TBM ? int((last - k) & 1) : 0;   // (elements stay in the caller's xs)
             if ((rc = queue_drift(hk, k, 0, b, false))) return rc;
             sys->phase = 1;
-            if ((rc = queue_forces(k, b, Gate{sys->status, int32_t(k), int32_t(k)}, true))) return rc;
-            queued = true;
+            if ((rc = queue_forces(k, b, Gate{sys->status, tag, tag}, true))) return rc;
+            queued = k;
+            qb = b;
         }
         // a step is in flight: positions drifted, forces stale unless queued
-        const int64_t k = sys->step + 1;
-        const int32_t tag = int32_t(k);
-        // the step after it: its kick and drift unless step k's evaluation has made
-        // them, and its evaluation
-        const auto queue_next = [&](bool ahead) -> int {
-            int to = b;
-            if (besides(k, b) == kDrift) to = !b;
-            else if (int r = queue_drift(2.0 * hk, k + 1, b, b, ahead)) return r;
-            return queue_forces(k + 1, to, Gate{sys->status, tag + 1, ahead ? tag : tag + 1}, true);
-        };
-        bool ready = false, ahead = false;
-        if (queued) {
-            ahead = host_dev && done + 1 < steps;
-            if (ahead && (rc = queue_next(true))) return rc;
+        bool ready = false;
+        if (queued >= k) {
+            // (a kick-drift kernel is gated by the flag of the step before it alone)
+            while (host_dev && queued < last && queued - k < depth && (queued == k || besides(queued, qb) == kDrift))
+                if ((rc = queue_after())) return rc;
             if ((rc = read_flag(sys, host_dev, tag, s, &moved, &bad))) return rc;
             if (bad) {
                 if ((rc = settle(b))) return rc;
                 return MD_ERR_NONFINITE;
             }
             ready = !moved;
-            if (!ready) {   // the device skipped this step's forces and the step queued ahead
-                timer.drop_last();
-                if (ahead) timer.drop_last();
-                ahead = false;
-            }
+            if (!ready)   // the device skipped this step's forces and the steps queued ahead
+                for (; queued >= k; --queued) timer.drop_last();
             // the flag was posted behind every evaluation but the newest one
             timer.collect(sys, false, ready ? 1 : 0);
             sys->need_build |= moved ? 1 : 0;
@@ -408,7 +414,11 @@ int run(md_system_t *sys, int64_t steps, hipStream_t s)
             b = 0;
             if ((rc = rebuild(sys, w, s, host_dev))) return rc;
         }
-        if (!ready && (rc = queue_forces(k, b, built ? fits : Gate{}, false))) return rc;
+        if (!ready) {
+            if ((rc = queue_forces(k, b, built ? fits : Gate{}, false))) return rc;
+            queued = k;
+            qb = b;
+        }
         if (built) {
             if ((rc = check_build(sys, host_dev, s))) {
                 timer.drop_last();
@@ -416,15 +426,15 @@ int run(md_system_t *sys, int64_t steps, hipStream_t s)
             }
             sys->need_build = 0;
         }
+        known = k;
         ++sys->step;
         ++done;
-        queued = ahead;
+        const int what = besides(k, b);
         if (done < steps) {
-            if (!queued && (rc = queue_next(false))) return rc;
-            queued = true;
-            if (besides(k, b) == kDrift) b = !b;
+            if (queued == k && (rc = queue_after())) return rc;
+            if (what == kDrift) b = !b;
         } else {
-            if (besides(k, b) != kClose &&
+            if (what != kClose &&
                 (rc = integrate(MD_KICK, &sys->box, n, sys->x, sys->v, sys->f, sys->dt, sys->accel, 1.0, nullptr, 0.0,
                                 nullptr, 0, nullptr, nullptr, sys->flags & MD_PAIR_FP64, sys->ws, w, s)))
                 return rc;
