@@ -8,34 +8,10 @@
 // assignments and neighbour sets are reproducible bit for bit.
 #include <algorithm>
 
-#include "md_common.h"
+#include "md_bin.h"
 #include "md_pair.h"
 
 namespace md {
-
-struct GridArgs {
-    double L[3], hL[3], inv_cell[3];
-    int32_t nc[3], reach;
-};
-
-// Inside the box floor(x / L) is 0 (a quotient below 1 never rounds up to 1) and w
-// is x (0 for -0), so the FP64 division is left out: most atoms at a build are
-// where the last one put them.
-__device__ __forceinline__ double wrap1(double x, double L)
-{
-    if (x >= 0.0 && x < L) return x + 0.0;
-    double w = x - L * floor(x / L);
-    if (w >= L) w -= L;
-    if (w < 0.0) w += L;
-    return w;
-}
-
-__device__ __forceinline__ int32_t cell1(double w, double inv, int32_t nc)
-{
-    int32_t c = int32_t(w * inv);
-    c = c >= nc ? nc - 1 : c;
-    return c < 0 ? 0 : c;
-}
 
 // ---------------------------------------------------------------------------
 // binning
@@ -56,30 +32,7 @@ __global__ __launch_bounds__(kBlock) void k_bin_assign(int64_t n, double *x, Gri
     const int64_t lin = c[0] + int64_t(g.nc[0]) * (c[1] + int64_t(g.nc[1]) * c[2]);
     const int32_t r = lin2rank[lin];
     cell[i] = r;
-    // one atomic per distinct cell of the wave (atoms arrive nearly sorted):
-    // the first lane of a cell claims a run of slots for all lanes of the cell,
-    // which take consecutive slots in lane order.  The lanes are grouped first
-    // and the claims of all groups made by one instruction: made one group after
-    // another, their round trips to the L2 (~6 a wave) were the kernel's time.
-    const int lane = threadIdx.x % kWave;
-    int leader = lane;
-    uint32_t before = 0;
-    int32_t members = 0;
-    uint64_t todo = __ballot(true);
-    while (todo) {
-        const int first = __builtin_ctzll(todo);
-        const int32_t rc = __builtin_amdgcn_readlane(r, first);
-        const uint64_t same = __ballot(r == rc) & todo;
-        if (r == rc && ((todo >> lane) & 1u)) {
-            leader = first;
-            members = __popcll(same);
-            before = __builtin_amdgcn_mbcnt_hi(uint32_t(same >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(same), 0u));
-        }
-        todo &= ~same;
-    }
-    int32_t base = 0;
-    if (leader == lane) base = atomicAdd(&cnt[r], members);
-    slot[i] = __shfl(base, leader, kWave) + int32_t(before);
+    slot[i] = claim_slot(r, cnt);
 }
 
 __global__ __launch_bounds__(kBlock) void k_bin_scatter(int64_t n, const int32_t *__restrict__ cell,
@@ -104,15 +57,7 @@ __global__ __launch_bounds__(kBlock) void k_bin_stable(int64_t n, const int32_t 
     const int32_t i = tmp[p];
     const int32_t c = cell[i];
     const int32_t s0 = cell_start[c], s1 = cell_start[c + 1];
-    int32_t rank = 0;
-    for (int32_t q = s0; q < s1; q += 8) {   // eight loads in flight
-        int32_t m[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) m[k] = tmp[min(q + k, s1 - 1)];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) rank += q + k < s1 && m[k] < i;
-    }
-    perm[s0 + rank] = i;
+    perm[s0 + stable_rank(tmp, s0, s1, i)] = i;
 }
 
 // ---------------------------------------------------------------------------
@@ -217,7 +162,7 @@ __global__ __launch_bounds__(kBlock) void k_reorder_put(int64_t n, const double 
     if (xs) xs[k] = make_uint4(scale1(p[0], k0), scale1(p[1], k1), scale1(p[2], k2), 0u);
 }
 
-static int reorder_state(int64_t n, const int32_t *perm, double *x, double *v, int32_t *ids, double *xref, double *vtmp,
+int reorder_state(int64_t n, const int32_t *perm, double *x, double *v, int32_t *ids, double *xref, double *vtmp,
                   int32_t *itmp, const md_box_t *box, uint32_t *xs, hipStream_t s)
 {
     if (n <= 0) return MD_OK;
@@ -374,19 +319,6 @@ __global__ __launch_bounds__(kSmallBlock) void k_sort_small(int32_t n, double *x
             st.ids[d] = id[k];
         }
     }
-}
-
-static GridArgs grid_args(const md_grid_t *grid)
-{
-    GridArgs g;
-    for (int a = 0; a < 3; ++a) {
-        g.L[a] = grid->L[a];
-        g.hL[a] = 0.5 * grid->L[a];
-        g.inv_cell[a] = grid->inv_cell[a];
-        g.nc[a] = grid->nc[a];
-    }
-    g.reach = grid->reach;
-    return g;
 }
 
 static bool sorts_small(const md_grid_t *grid, int64_t n, int64_t most)
@@ -1002,20 +934,6 @@ __device__ __forceinline__ void nm_chunk(LDS &L, int32_t base, int64_t n, const 
     }
 }
 
-// Inclusive prefix sum over the wave.
-__device__ __forceinline__ int32_t wave_prefix(int32_t v)
-{
-#define MD_DPP(ctrl, rows) v += __builtin_amdgcn_update_dpp(0, v, ctrl, rows, 0xf, false)
-    MD_DPP(0x111, 0xf);   // from 1, 2, 4 and 8 lanes below in each row of 16
-    MD_DPP(0x112, 0xf);
-    MD_DPP(0x114, 0xf);
-    MD_DPP(0x118, 0xf);
-    MD_DPP(0x142, 0xa);   // rows 1 and 3 add row 0's and 2's last lane
-    MD_DPP(0x143, 0xc);   // rows 2 and 3 add lane 31
-#undef MD_DPP
-    return v;
-}
-
 // The homes of cell `rank` (those of `part`) against its stencil's
 // candidates; returns the longest row.  Candidates are read D chunks of 64 at a
 // time; one is kept if it lies within r_list of the bounding box of the batch's homes, in its periodic image of
@@ -1222,36 +1140,66 @@ __device__ __forceinline__ int32_t nm_cell(NmLds<R, D> &L, int64_t rank, int32_t
 // 515 and 581 us for the whole rebuild of the void system), the next 64
 // requested ahead (the registers cost more than the wait), 4, 5, 7 or 8 waves
 // per SIMD.
-template <int R>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(6)))
-void k_neighbors(int64_t n, const double *__restrict__ x, GridArgs g, double rl2, NbSplit sp,
-                 const int32_t *__restrict__ cell_start, const int32_t *__restrict__ rank_xyz,
-                 const int32_t *__restrict__ lin2rank, int32_t row_cap, int32_t *__restrict__ idx,
-                 int32_t *__restrict__ count, int32_t *max_count)
+// One system, or the bricks of a decomposition (Bricks) in one launch: the cells of
+// brick t follow those of brick t - 1, its atoms start at slot0[t] of the arrays, and
+// it has an offsets array and a longest row of its own.
+struct OneGrid {
+    static constexpr bool many = false;
+};
+struct Bricks {
+    static constexpr bool many = true;
+    uint32_t n_cells;
+    int32_t slot0[MD_DD_MAX_BRICKS];
+};
+
+template <int R, int D, class B>
+__device__ __forceinline__ void nm_kernel(NmLds<R, D> &L, uint32_t blk, int64_t n, const double *x, const GridArgs &g,
+                                          double rl2, const NbSplit &sp, const int32_t *cell_start,
+                                          const int32_t *rank_xyz, const int32_t *lin2rank, int32_t row_cap,
+                                          int32_t *idx, int32_t *count, int32_t *max_count, const B &bricks)
 {
-    __shared__ NmLds<R, 1> L;
-    const uint32_t blk = xcd_chunked(blockIdx.x, gridDim.x, kNbXcdChunk);
-    const uint32_t rank = blk / uint32_t(sp.parts), part = blk % uint32_t(sp.parts);
-    nb_longest(nm_cell<R, 1>(L, rank, int32_t(part), n, x, g, rl2, sp, cell_start, rank_xyz, lin2rank, row_cap, idx,
+    uint32_t rank = blk / uint32_t(sp.parts);
+    const uint32_t part = blk % uint32_t(sp.parts);
+    if constexpr (B::many) {
+        const uint32_t t = rank / bricks.n_cells;
+        const int64_t s0 = bricks.slot0[t];
+        rank -= t * bricks.n_cells;
+        x += s0;
+        cell_start += t * (bricks.n_cells + 1);
+        idx += s0 * row_cap;
+        count += s0;
+        max_count += t;
+    }
+    nb_longest(nm_cell<R, D>(L, rank, int32_t(part), n, x, g, rl2, sp, cell_start, rank_xyz, lin2rank, row_cap, idx,
                              count),
                max_count);
 }
 
+template <int R, class B>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(6)))
+void k_neighbors(int64_t n, const double *__restrict__ x, GridArgs g, double rl2, NbSplit sp,
+                 const int32_t *__restrict__ cell_start, const int32_t *__restrict__ rank_xyz,
+                 const int32_t *__restrict__ lin2rank, int32_t row_cap, int32_t *__restrict__ idx,
+                 int32_t *__restrict__ count, int32_t *max_count, B bricks)
+{
+    __shared__ NmLds<R, 1> L;
+    nm_kernel(L, xcd_chunked(blockIdx.x, gridDim.x, kNbXcdChunk), n, x, g, rl2, sp, cell_start, rank_xyz, lin2rank,
+              row_cap, idx, count, max_count, bricks);
+}
+
 // The same with four chunks of candidates requested at once, for cells too few to
 // fill the chip: a wavefront is then alone on its SIMD, and the trips to memory of
-// its ~14 chunks, one after another, are its time.  (FEW_FIGURES)
-template <int R>
+// its ~14 chunks, one after another, are a good part of its time (4,000 LJ atoms,
+// 16 homes a wavefront: 34 us by single chunks, 31 by four; with 4 homes 23).
+template <int R, class B>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2)))
 void k_neighbors_few(int64_t n, const double *__restrict__ x, GridArgs g, double rl2, NbSplit sp,
                      const int32_t *__restrict__ cell_start, const int32_t *__restrict__ rank_xyz,
                      const int32_t *__restrict__ lin2rank, int32_t row_cap, int32_t *__restrict__ idx,
-                     int32_t *__restrict__ count, int32_t *max_count)
+                     int32_t *__restrict__ count, int32_t *max_count, B bricks)
 {
     __shared__ NmLds<R, 4> L;
-    const uint32_t rank = blockIdx.x / uint32_t(sp.parts), part = blockIdx.x % uint32_t(sp.parts);
-    nb_longest(nm_cell<R, 4>(L, rank, int32_t(part), n, x, g, rl2, sp, cell_start, rank_xyz, lin2rank, row_cap, idx,
-                             count),
-               max_count);
+    nm_kernel(L, blockIdx.x, n, x, g, rl2, sp, cell_start, rank_xyz, lin2rank, row_cap, idx, count, max_count, bricks);
 }
 
 // Wavefronts per cell: one, unless the cells are too few to fill the chip
@@ -1291,10 +1239,10 @@ int build_neighbors(const md_grid_t *grid, int64_t n, const double *x, const int
                                cell_start, xyz, l2r, row_cap, idx, count, max_count);
         else {
             const bool few = grid->n_cells < kNbFew;
-            const auto kernel = grid->reach == 1 ? (few ? k_neighbors_few<1> : k_neighbors<1>)
-                                                 : (few ? k_neighbors_few<2> : k_neighbors<2>);
+            const auto kernel = grid->reach == 1 ? (few ? k_neighbors_few<1, OneGrid> : k_neighbors<1, OneGrid>)
+                                                 : (few ? k_neighbors_few<2, OneGrid> : k_neighbors<2, OneGrid>);
             hipLaunchKernelGGL(kernel, nb, dim3(kWave), 0, s, n, x, g, rl2, sp, cell_start, xyz, l2r, row_cap, idx,
-                               count, max_count);
+                               count, max_count, OneGrid{});
         }
         MD_HIP_TRY(hipGetLastError());
     }
@@ -1305,6 +1253,32 @@ int build_neighbors(const md_grid_t *grid, int64_t n, const double *x, const int
         *needed = mc;
         if (mc > row_cap) return MD_ERR_CAPACITY;
     }
+    return MD_OK;
+}
+
+// The lists of all bricks: sorted positions x of component stride `slots` and the
+// bricks' slots in it, (n_cells + 1) offsets per brick, longest[t] cleared before.
+int build_neighbors_bricks(const md_grid_t *grid, int n_bricks, const int64_t *slot0, int64_t slots, const double *x,
+                           const int32_t *cell_start, int32_t row_cap, int32_t *idx, int32_t *count, int32_t *longest,
+                           void *ws, const WsLayout &w, hipStream_t s)
+{
+    const int64_t cells = grid->n_cells * n_bricks;
+    if (row_cap > (1 << 20) || cells * 8 > INT32_MAX || grid->reach != 1) {   // one by one
+        for (int t = 0; t < n_bricks; ++t)
+            if (int rc = build_neighbors(grid, slots, x + slot0[t], cell_start + t * (grid->n_cells + 1), row_cap,
+                                         idx + slot0[t] * row_cap, count + slot0[t], longest + t, nullptr, ws, w, s))
+                return rc;
+        return MD_OK;
+    }
+    Bricks b;
+    b.n_cells = uint32_t(grid->n_cells);
+    for (int t = 0; t < n_bricks; ++t) b.slot0[t] = int32_t(slot0[t]);
+    const NbSplit sp = nb_split(slots, cells, false);
+    const auto kernel = cells < kNbFew ? k_neighbors_few<1, Bricks> : k_neighbors<1, Bricks>;
+    hipLaunchKernelGGL(kernel, dim3(uint32_t(cells * sp.parts)), dim3(kWave), 0, s, slots, x, grid_args(grid),
+                       grid->r_list * grid->r_list, sp, cell_start, ws_ptr<int32_t>(ws, w.rank2lin),
+                       ws_ptr<int32_t>(ws, w.lin2rank), row_cap, idx, count, longest, b);
+    MD_HIP_TRY(hipGetLastError());
     return MD_OK;
 }
 

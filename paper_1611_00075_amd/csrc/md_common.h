@@ -117,6 +117,20 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Inclusive prefix sum over the wave.
+__device__ __forceinline__ int32_t wave_prefix(int32_t v)
+{
+#define MD_DPP(ctrl, rows) v += __builtin_amdgcn_update_dpp(0, v, ctrl, rows, 0xf, false)
+    MD_DPP(0x111, 0xf);   // from 1, 2, 4 and 8 lanes below in each row of 16
+    MD_DPP(0x112, 0xf);
+    MD_DPP(0x114, 0xf);
+    MD_DPP(0x118, 0xf);
+    MD_DPP(0x142, 0xa);   // rows 1 and 3 add row 0's and 2's last lane
+    MD_DPP(0x143, 0xc);   // rows 2 and 3 add lane 31
+#undef MD_DPP
+    return v;
+}
+
 template <typename T>
 __device__ __forceinline__ T group_sum(T v, int width)
 {
@@ -198,6 +212,9 @@ inline T *ws_ptr(void *ws, size_t off) { return reinterpret_cast<T *>(static_cas
 int launch_fill_i32(int32_t *p, int64_t count, int32_t value, hipStream_t s);
 // out[0] = 0, out[k+1] = sum_{q<=k} in[q], k < m.  OutT = int32_t or int64_t.
 int launch_scan_i32_to_i32(const int32_t *in, int32_t *out, int64_t m, int64_t *bsum, hipStream_t s);
+// `sets` scans of m values each, set k at in + k stride, out + k stride (stride > m).
+int launch_scan_sets(const int32_t *in, int32_t *out, int64_t m, int sets, int64_t stride, int64_t *bsum,
+                     hipStream_t s);
 // out[c] = sum over nb partial rows of part[b*8 + c], fixed order; then the
 // combination selected by `mode` (see md_reduce.hip).
 int launch_reduce_partials(double *part1, int64_t nb1, double *part2, int64_t nb2, double *out, int mode, double a0,
@@ -213,6 +230,11 @@ int scale_positions(const md_box_t *, int64_t, const double *, uint32_t *, hipSt
 int sort_state(const md_grid_t *, int64_t n, double *x, int32_t *cell, int32_t *perm, int32_t *cell_start, void *ws,
                const WsLayout &w, double *v, int32_t *ids, double *xref, double *vtmp, int32_t *itmp,
                const md_box_t *box, uint32_t *xs, hipStream_t s);
+int reorder_state(int64_t n, const int32_t *perm, double *x, double *v, int32_t *ids, double *xref, double *vtmp,
+                  int32_t *itmp, const md_box_t *box, uint32_t *xs, hipStream_t s);
+int build_neighbors_bricks(const md_grid_t *, int n_bricks, const int64_t *slot0, int64_t slots, const double *x,
+                           const int32_t *cell_start, int32_t row_cap, int32_t *idx, int32_t *count, int32_t *longest,
+                           void *ws, const WsLayout &, hipStream_t);
 int build_neighbors(const md_grid_t *, int64_t, const double *, const int32_t *, int32_t, int32_t *, int32_t *,
                     int32_t *, int32_t *, void *, const WsLayout &, hipStream_t);
 int forces_lj(const md_box_t *, int64_t, const double *, const uint32_t *, int32_t, const int32_t *, const int32_t *,

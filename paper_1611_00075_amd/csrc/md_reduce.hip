@@ -75,8 +75,9 @@ __global__ __launch_bounds__(kBlock) void k_scan_tile_offsets(int64_t *bsum, int
 
 // phase 3: rescan each tile and write out[q+1] = inclusive prefix (out[0] = 0).
 // SUMS: bsum holds the tiles' sums, and the block adds those before its own itself.
-template <typename OutT, bool SUMS>
-__global__ __launch_bounds__(kBlock) void k_scan_write(const int32_t *in, int64_t m, const int64_t *bsum, OutT *out)
+template <bool SUMS>
+__global__ __launch_bounds__(kBlock) void k_scan_write(const int32_t *in, int64_t m, const int64_t *bsum,
+                                                       int32_t *out)
 {
     __shared__ int64_t lds[kBlock / kWave];
     __shared__ int64_t before;
@@ -106,42 +107,52 @@ __global__ __launch_bounds__(kBlock) void k_scan_write(const int32_t *in, int64_
     for (int k = 0; k < kScanItems; ++k) {
         const int64_t q = base + k;
         run += v[k];
-        if (q < m) out[q + 1] = OutT(run);
+        if (q < m) out[q + 1] = int32_t(run);
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) out[0] = OutT(0);
+    if (blockIdx.x == 0 && threadIdx.x == 0) out[0] = 0;
 }
 
-// The whole scan by one block, kScanOneItems consecutive inputs a thread.
-constexpr int kScanOneBlock = 1024, kScanOneItems = 16;
-template <typename OutT>
-__global__ __launch_bounds__(kScanOneBlock) void k_scan_one(const int32_t *in, int32_t m, OutT *out)
+// The whole scan by one block (of each of gridDim.x sets), in rows of 1,024 inputs:
+// a wavefront's runs of 64 first, then the runs' sums, 16 of each row.
+constexpr int kScanOneBlock = 1024, kScanOneRows = 16, kScanOne = kScanOneBlock * kScanOneRows;
+__global__ __launch_bounds__(kScanOneBlock) void k_scan_one(const int32_t *in, int32_t m, int32_t *out, int64_t stride)
 {
-    __shared__ int64_t lds[kScanOneBlock / kWave];
+    constexpr int kWaves = kScanOneBlock / kWave, kRuns = kScanOneRows * kWaves;
+    static_assert(kRuns == 4 * kWave, "four runs a lane of the first wavefront");
+    __shared__ int32_t run[kRuns];
+    in += blockIdx.x * stride;
+    out += blockIdx.x * stride;
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    const int32_t base = int32_t(threadIdx.x) * kScanOneItems;
-    int32_t v[kScanOneItems];
-    int64_t s = 0;
+    int32_t v[kScanOneRows];
 #pragma unroll
-    for (int k = 0; k < kScanOneItems; ++k) {
-        v[k] = base + k < m ? in[base + k] : 0;
-        s += v[k];
+    for (int k = 0; k < kScanOneRows; ++k) {
+        const int32_t q = k * kScanOneBlock + int32_t(threadIdx.x);
+        v[k] = q < m ? in[q] : 0;
     }
-    int64_t inc = s;
 #pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int64_t t = __shfl_up(inc, o, kWave);
-        if (lane >= o) inc += t;
+    for (int k = 0; k < kScanOneRows; ++k) {
+        v[k] = wave_prefix(v[k]);
+        if (lane == kWave - 1) run[k * kWaves + wave] = v[k];
     }
-    if (lane == kWave - 1) lds[wave] = inc;
     __syncthreads();
-    int64_t run = inc - s;
-    for (int w = 0; w < wave; ++w) run += lds[w];
+    if (wave == 0) {
+        int32_t r[4], s = 0;
 #pragma unroll
-    for (int k = 0; k < kScanOneItems; ++k) {
-        run += v[k];
-        if (base + k < m) out[base + k + 1] = OutT(run);
+        for (int q = 0; q < 4; ++q) {
+            r[q] = s;
+            s += run[4 * lane + q];
+        }
+        const int32_t before = wave_prefix(s) - s;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) run[4 * lane + q] = before + r[q];
     }
-    if (threadIdx.x == 0) out[0] = OutT(0);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kScanOneRows; ++k) {
+        const int32_t q = k * kScanOneBlock + int32_t(threadIdx.x);
+        if (q < m) out[q + 1] = run[k * kWaves + wave] + v[k];
+    }
+    if (threadIdx.x == 0) out[0] = 0;
 }
 
 // Launches are what a scan of cell counts costs (2 to 5 us each with the gap before
@@ -150,29 +161,31 @@ __global__ __launch_bounds__(kScanOneBlock) void k_scan_one(const int32_t *in, i
 // (4 M values; 74,000 take 7.9 us, three launches took 10.5); else three.
 constexpr int64_t kScanSelf = 2048;   // tiles
 
-template <typename OutT>
-static int scan_impl(const int32_t *in, OutT *out, int64_t m, int64_t *bsum, hipStream_t s)
+int launch_scan_i32_to_i32(const int32_t *in, int32_t *out, int64_t m, int64_t *bsum, hipStream_t s)
 {
-    if (m <= kScanOneBlock * kScanOneItems) {
-        hipLaunchKernelGGL(k_scan_one<OutT>, dim3(1), dim3(kScanOneBlock), 0, s, in, int32_t(m > 0 ? m : 0), out);
+    return launch_scan_sets(in, out, m, 1, 0, bsum, s);
+}
+
+int launch_scan_sets(const int32_t *in, int32_t *out, int64_t m, int sets, int64_t stride, int64_t *bsum, hipStream_t s)
+{
+    if (m <= kScanOne) {
+        hipLaunchKernelGGL(k_scan_one, dim3(uint32_t(sets)), dim3(kScanOneBlock), 0, s, in, int32_t(m > 0 ? m : 0), out,
+                           stride);
         MD_HIP_TRY(hipGetLastError());
         return MD_OK;
     }
     const int64_t nb = (m + kScanTile - 1) / kScanTile;
-    hipLaunchKernelGGL(k_scan_tile_sums, dim3(uint32_t(nb)), dim3(kBlock), 0, s, in, m, bsum);
-    if (nb <= kScanSelf) {
-        hipLaunchKernelGGL((k_scan_write<OutT, true>), dim3(uint32_t(nb)), dim3(kBlock), 0, s, in, m, bsum, out);
-    } else {
-        hipLaunchKernelGGL(k_scan_tile_offsets, dim3(1), dim3(kBlock), 0, s, bsum, nb);
-        hipLaunchKernelGGL((k_scan_write<OutT, false>), dim3(uint32_t(nb)), dim3(kBlock), 0, s, in, m, bsum, out);
+    for (int k = 0; k < sets; ++k, in += stride, out += stride) {
+        hipLaunchKernelGGL(k_scan_tile_sums, dim3(uint32_t(nb)), dim3(kBlock), 0, s, in, m, bsum);
+        if (nb <= kScanSelf) {
+            hipLaunchKernelGGL(k_scan_write<true>, dim3(uint32_t(nb)), dim3(kBlock), 0, s, in, m, bsum, out);
+        } else {
+            hipLaunchKernelGGL(k_scan_tile_offsets, dim3(1), dim3(kBlock), 0, s, bsum, nb);
+            hipLaunchKernelGGL(k_scan_write<false>, dim3(uint32_t(nb)), dim3(kBlock), 0, s, in, m, bsum, out);
+        }
+        MD_HIP_TRY(hipGetLastError());
     }
-    MD_HIP_TRY(hipGetLastError());
     return MD_OK;
-}
-
-int launch_scan_i32_to_i32(const int32_t *in, int32_t *out, int64_t m, int64_t *bsum, hipStream_t s)
-{
-    return scan_impl<int32_t>(in, out, m, bsum, s);
 }
 
 // Fixed-order sums of [rows][8] partials, `stride` rows apart.  Thread t adds

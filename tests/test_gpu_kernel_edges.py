@@ -506,3 +506,31 @@ def test_sort_at_the_sizes_of_its_launches(M, orc, n, nc):
     assert np.array_equal(cell.cpu().numpy(), rank)
     assert np.array_equal(perm.cpu().numpy(), np.argsort(rank, kind="stable"))
     assert np.array_equal(start.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(rank, minlength=g.n_cells))]))
+
+
+# ---- decomposed build ----------------------------------------------------------------
+
+@pytest.mark.parametrize("p,L", [((2, 1, 1), (140.5, 70.5, 70.5)), ((2, 2, 1), (40.0, 40.0, 20.0)),
+                                 ((3, 1, 2), (60.0, 20.0, 40.0))])
+def test_decomposed_build_of_uneven_bricks(M, p, L):
+    """A cluster of 4,000 atoms across brick faces and the box boundary, other
+    bricks empty or nearly so; bricks of more than 16,384 cells (their scans go
+    one by one) and of a few hundred (all in one launch).  Forces as without
+    decomposition: FP32 sums in another order, 1e-5 normwise."""
+    from paper_1611_00075_amd.dd import DomainSimulation
+    from paper_1611_00075_amd.sim import Simulation
+    L = np.array(L)
+    rng = np.random.default_rng(7)
+    x = _fcc((10, 10, 10), inputs.fcc_lattice_constant(0.8442)) + 0.04 * rng.standard_normal((4000, 3)) - 8.0
+    v = 0.5 * rng.standard_normal(x.shape)
+    dd = DomainSimulation(L, x, v, p=p, potential="lj", skin=0.3, dt=0.005)
+    sim = Simulation(L, x, v, skin=0.3, dt=0.005)
+    for _ in range(2):
+        f, g = dd.forces(), sim.forces()
+        assert np.linalg.norm(f - g) <= 1e-5 * np.linalg.norm(g)
+        dd.run(7)
+        sim.run(7)
+        d = dd.positions() - sim.positions()
+        assert np.abs(d - L * np.round(d / L)).max() < 1e-5
+    assert sum(b[0] for b in dd.bricks()) == 4000
+    dd.close()
