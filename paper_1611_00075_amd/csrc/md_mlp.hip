@@ -801,6 +801,19 @@ __global__ __launch_bounds__(kBlock) void k_mlp_force(int64_t n, MlpArgs p, cons
 
 // ---- training ---------------------------------------------------------------
 
+// Sum over each row of 16 lanes in all of them: pairs, quads, eights, all, as
+// exchanges with lane ^ 1, 2, 4, 8 add.
+__device__ __forceinline__ float row_sum(float v)
+{
+#define MD_DPP(ctrl) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, false))
+    MD_DPP(0xb1);    // lane ^ 1
+    MD_DPP(0x4e);    // lane ^ 2
+    MD_DPP(0x141);   // mirrored within 8
+    MD_DPP(0x140);   // mirrored within 16
+#undef MD_DPP
+    return v;
+}
+
 constexpr int kGradCols = 2 * kTile + 8;   // a row's 32 atoms and padding (banks)
 
 struct GradLds {
@@ -827,7 +840,7 @@ __device__ __forceinline__ bf16x8 lds8(const uint16_t *p)
 // atoms each up to dE/da1, then half of the weight-gradient tiles each.
 // Four groups a block with the two halves of a group in turn, and operands
 // reordered from memory, measured 61.5 us a step with k_mlp_update (one thread
-// a parameter); this form 16.9 us.
+// a parameter); this form 16.3 us.
 __global__ __launch_bounds__(kGradBlock) void k_mlp_grad(int64_t batch, const int32_t *__restrict__ sel,
                                                          const float *__restrict__ G,
                                                          const float *__restrict__ target, MlpArgs p,
@@ -931,20 +944,18 @@ __global__ __launch_bounds__(kGradBlock) void k_mlp_grad(int64_t batch, const in
         __syncthreads();
     }
 
-    // sums over the 16 atoms of a lane group, then over the two waves
+    // sums over the 16 atoms of a lane group (on the vector unit: through the LDS
+    // crossbar, 200 exchanges, the kernel took 11.6 us at a batch of 4,096, now 9.8),
+    // then over the two waves
 #pragma unroll
-    for (int k = 0; k < 16; ++k)
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) {
-            gb1[k] += __shfl_xor(gb1[k], o, kWave);
-            gb2[k] += __shfl_xor(gb2[k], o, kWave);
-            gw3[k] += __shfl_xor(gw3[k], o, kWave);
-        }
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) {
-        gb3 += __shfl_xor(gb3, o, kWave);
-        loss += __shfl_xor(loss, o, kWave);
+    for (int k = 0; k < 16; ++k) {
+        gb1[k] = row_sum(gb1[k]);
+        gb2[k] = row_sum(gb2[k]);
+        gw3[k] = row_sum(gw3[k]);
     }
+    gb3 = row_sum(gb3);
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) loss += __shfl_xor(loss, o, kWave);
     float *out = part + int64_t(blockIdx.x) * kRow;
 #pragma unroll
     for (int a = 0; a < 2; ++a)
@@ -991,7 +1002,7 @@ __global__ __launch_bounds__(kGradBlock) void k_mlp_grad(int64_t batch, const in
 // wavefronts every 16th row each: 128 rows (a batch of 4,096) are 8 loads in
 // flight per lane instead of 128 in turn, on 84 CUs instead of 21.  The last
 // block sums the loss.  One step (both kernels and the call) at a batch of
-// 4,096 went from 61.5 to 16.9 us (k_mlp_grad 11.9, k_mlp_update 3.8).
+// 4,096 went from 61.5 to 16.3 us (k_mlp_grad 9.8, k_mlp_update 3.3).
 __global__ __launch_bounds__(kUpdBlock) void k_mlp_update(int32_t rows, const float *__restrict__ part,
                                                           const double *__restrict__ lpart, double inv_batch,
                                                           float *__restrict__ grad, double *__restrict__ loss,
@@ -1198,7 +1209,7 @@ int forces_mlp(const md_box_t *box, int64_t n, const uint32_t *xs, int32_t cap, 
         // Folded sums where Q_8 = exp(-32 (dmu / w)^2) is above 1e-18 (the
         // default spacing, dmu = w: 1.3e-14), so that the coefficients and the
         // powers keep the FP32 range; plain ones for wider spacings, and with MD_ENERGY,
-        // whose FP64 virial then has the value it always had (the two differ
+        // whose pair forces then have the value they always had (the two differ
         // in the last bits of a pair's force factor).
         if (energy) comp ? force(F{}, T{}, T{}) : force(F{}, T{}, F{});
         else if (a.Q[8] > 1e-18f) comp ? force(T{}, F{}, T{}) : force(T{}, F{}, F{});
