@@ -95,10 +95,14 @@ DriftArgs drift_args(const md_box_t *box, double kick, double dt, double half_sk
 // check sets status as the kick-drift kernel does.  f is written only where it is
 // asked for.
 struct NoAdvance {
-    static constexpr bool on = false;
+    static constexpr bool on = false, stream = false;
+};
+// (no update, the list read past the caches)
+struct Streamed {
+    static constexpr bool on = false, stream = true;
 };
 struct Advance {
-    static constexpr bool on = true;
+    static constexpr bool on = true, stream = false;
     DriftArgs a;
     const double *x;
     double *x_out, *v;       // x_out may be x when other blocks read only xs

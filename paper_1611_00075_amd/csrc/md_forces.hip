@@ -24,6 +24,7 @@
 // vector of a pair does not depend on the unit.  Pair arithmetic is FP32;
 // per-lane sums are Kahan-compensated unless MD_NO_COMPENSATE.
 #include <cmath>
+#include <type_traits>
 
 #include "md_pair.h"
 
@@ -74,7 +75,7 @@ __global__ __launch_bounds__(kBlock) void k_lj32(int64_t n, const uint4 *__restr
         const uint4 pi = xs[i];
         const int32_t cnt = min(count[i], cap);
         // a batch's pair forces are summed plainly, the sum added compensated
-        walk_split<U, 3>(b.xs, b.row, cnt, sub, [&](const auto &pj, int32_t t, auto masked) {
+        walk_split<U, 3, A::stream>(b.xs, b.row, cnt, sub, [&](const auto &pj, int32_t t, auto masked) {
             constexpr int K = sizeof(pj) / sizeof(uint4);
             float bx = 0.f, by = 0.f, bz = 0.f;
 #pragma unroll
@@ -440,7 +441,7 @@ __device__ __forceinline__ uint32_t element_word(const TBM32<CC> &, uint32_t wi)
 
 // pass 1: rho_i = sum psi(r_ij), then F_i = -A sqrt(rho_i), F'_i; F'_i is
 // stored in the fourth word of the scaled coordinates for pass 2's gather.
-template <class P, int TPA, int U, bool CUBIC, bool ENERGY, bool COMP>
+template <class P, int TPA, int U, bool CUBIC, bool ENERGY, bool COMP, bool STREAM>
 __global__ __launch_bounds__(kBlock) void k_eam_rho(int64_t n, uint4 *__restrict__ xs,
                                                     int32_t cap, const int32_t *__restrict__ idx,
                                                     const int32_t *__restrict__ count, P p,
@@ -475,7 +476,7 @@ __global__ __launch_bounds__(kBlock) void k_eam_rho(int64_t n, uint4 *__restrict
         wi = pi.w;
         const auto &form = local_form(p, wi);
         const int32_t cnt = min(count[i], cap);
-        walk_form<P::kSplit, U, P::kRhoWords>(b.xs, b.row, cnt, sub, [&](const auto &pj, int32_t t0, auto masked) {
+        walk_form<P::kSplit, U, P::kRhoWords, STREAM>(b.xs, b.row, cnt, sub, [&](const auto &pj, int32_t t0, auto masked) {
             constexpr int K = sizeof(pj) / sizeof(uint4);
             float bs = 0.f;
 #pragma unroll
@@ -550,7 +551,7 @@ __global__ __launch_bounds__(kBlock) void k_eam_force(int64_t n, const uint4 *__
         keep = element_word(p, pi.w);
         const auto &form = local_form(p, pi.w);
         const int32_t cnt = min(count[i], cap);
-        walk_form<P::kSplit, U, 4>(b.xs, b.row, cnt, sub, [&](const auto &pj, int32_t t0, auto masked) {
+        walk_form<P::kSplit, U, 4, A::stream>(b.xs, b.row, cnt, sub, [&](const auto &pj, int32_t t0, auto masked) {
             constexpr int K = sizeof(pj) / sizeof(uint4);
             float bx = 0.f, by = 0.f, bz = 0.f;
 #pragma unroll
@@ -614,6 +615,9 @@ struct List {
     const int32_t *idx, *cnt;
 };
 
+// an evaluation of a run's step (gate.flag) over a list too large for the caches
+static bool in_run_streams(const Gate &gate, int64_t n, int32_t cap) { return gate.flag && streams(n, cap); }
+
 template <int TPA, bool CUBIC, bool E, bool C>
 static void launch_lj32(uint32_t gb, hipStream_t s, int64_t n, const uint4 *q, const List &l, const LJ32 &p,
                         float *f, double *part, const Span &sp, const BrickTab *tab, const Advance *adv)
@@ -622,6 +626,11 @@ static void launch_lj32(uint32_t gb, hipStream_t s, int64_t n, const uint4 *q, c
         if (adv) {
             hipLaunchKernelGGL((k_lj32<TPA, kUnrollLJ, CUBIC, E, C, Advance>), dim3(gb), dim3(kBlock), 0, s, n, q,
                                l.cap, l.idx, l.cnt, p, f, part, sp, tab, *adv);
+            return;
+        }
+        if (!tab && in_run_streams(p.gate, n, l.cap)) {
+            hipLaunchKernelGGL((k_lj32<TPA, kUnrollLJ, CUBIC, E, C, Streamed>), dim3(gb), dim3(kBlock), 0, s, n, q,
+                               l.cap, l.idx, l.cnt, p, f, part, sp, tab, Streamed{});
             return;
         }
     }
@@ -717,8 +726,9 @@ int forces_lj_part(const md_box_t *box, int64_t n, const double *x, const uint32
             const uint4 *q = reinterpret_cast<const uint4 *>(xs);
             float *ff = static_cast<float *>(f);
             const bool comp = !(flags & MD_NO_COMPENSATE);
-            if (cubic) dispatch_lj32<kTPA, true>(energy, comp, gb, s, n, q, l, p, ff, part, whole(n), nullptr, adv);
-            else dispatch_lj32<kTPA, false>(energy, comp, gb, s, n, q, l, p, ff, part, whole(n), nullptr, adv);
+            const Span sp = whole(n);
+            if (cubic) dispatch_lj32<kTPA, true>(energy, comp, gb, s, n, q, l, p, ff, part, sp, nullptr, adv);
+            else dispatch_lj32<kTPA, false>(energy, comp, gb, s, n, q, l, p, ff, part, sp, nullptr, adv);
         }
         MD_HIP_TRY(hipGetLastError());
     }
@@ -731,9 +741,19 @@ static void launch_eam(int passes, uint32_t gb, hipStream_t s, int64_t n, uint4 
                        float *rho, float *fprime, float *f, float *ea, double *part1, double *part2, const Span &sp,
                        const BrickTab *tab, const Advance *adv)
 {
-    if (passes & 1)
-        hipLaunchKernelGGL((k_eam_rho<P, TPA, P::kRhoUnroll, CUBIC, E, C>), dim3(gb), dim3(kBlock), 0, s, n, q, l.cap,
-                           l.idx, l.cnt, p, rho, fprime, part1, sp, tab);
+    auto rho_pass = [&](auto stream) {
+        hipLaunchKernelGGL((k_eam_rho<P, TPA, P::kRhoUnroll, CUBIC, E, C, decltype(stream)::value>), dim3(gb),
+                           dim3(kBlock), 0, s, n, q, l.cap, l.idx, l.cnt, p, rho, fprime, part1, sp, tab);
+    };
+    if constexpr (!E && C) {
+        if (!tab && !adv && in_run_streams(p.gate, n, l.cap)) {   // (both passes)
+            rho_pass(std::true_type{});
+            hipLaunchKernelGGL((k_eam_force<P, TPA, P::kForceUnroll, CUBIC, E, C, Streamed>), dim3(gb), dim3(kBlock),
+                               0, s, n, q, l.cap, l.idx, l.cnt, p, rho, f, ea, part2, sp, tab, Streamed{});
+            return;
+        }
+    }
+    if (passes & 1) rho_pass(std::false_type{});
     if (!(passes & 2)) return;
     if constexpr (!E && C) {
         if (adv) {

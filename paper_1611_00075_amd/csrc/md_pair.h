@@ -67,6 +67,24 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, ui
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, int(bytes), 0x00020000);
 }
 
+// A list entry, read once a pass: with STREAM, past the caches (non-temporal).
+// In a run's steps a list that the last-level cache (256 MB) cannot hold until the
+// next step drives positions and velocities out of it; past it, these stay for
+// the kick-drift and the gathers.  Us per step cached / streamed (bytes allocated
+// for the rows): LJ of 666,000 atoms (264 MB) 87 / 91, of 864,000 (342 MB) 116 / 113, of
+// 1.26 M (498 MB) 163 / 155, of 2 M 256 / 241; FS of 0.78 M Cu (190 MB) 129 / 149, of 1.15 M
+// (280 MB) 211 / 210, of 2 M (500 MB) 365 / 355, of 4 M 692 / 693.  Evaluations alone gain
+// nothing (FS of 4 M 650 / 651, LJ of 1.5 M 153 / 158) but the tabulated form's (2.9 M
+// 579 / 556).
+constexpr int64_t kStreamBytes = int64_t(300) << 20;
+inline bool streams(int64_t n, int32_t cap) { return n * cap * 4 > kStreamBytes; }
+
+template <bool STREAM>
+__device__ __forceinline__ uint32_t load_entry(const __amdgpu_buffer_rsrc_t &row_r, uint32_t off)
+{
+    return __builtin_amdgcn_raw_buffer_load_b32(row_r, off, 0, STREAM ? 2 : 0);
+}
+
 // Compile-time flag handed to a row walk's body: whether slots of the
 // batch may lie past the row's end (the body must then mask them).
 template <bool M>
@@ -91,7 +109,7 @@ struct Masked {
 // or returns zero; the body masks those slots as before.  Fewer vector
 // instructions for more gathered bytes: it pays for the forms whose pair
 // terms are longest (the two-element tight-binding form).
-template <int U, int WORDS, bool MASKED = true, typename Body>
+template <int U, int WORDS, bool MASKED, bool STREAM, typename Body>
 __device__ __forceinline__ void walk_buf(const __amdgpu_buffer_rsrc_t &xs_r, const __amdgpu_buffer_rsrc_t &row_r,
                                          int32_t cnt, int sub, Body &&body)
 {
@@ -103,7 +121,7 @@ __device__ __forceinline__ void walk_buf(const __amdgpu_buffer_rsrc_t &xs_r, con
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             ok[u] = !MASKED || t + u * kSlice < cnt;
-            j[u] = __builtin_amdgcn_raw_buffer_load_b32(row_r, ok[u] ? off + u * 256u : kOut, 0, 0);
+            j[u] = load_entry<STREAM>(row_r, ok[u] ? off + u * 256u : kOut);
         }
         uint4 pj[U];
 #pragma unroll
@@ -145,7 +163,7 @@ __device__ __forceinline__ void walk_buf(const __amdgpu_buffer_rsrc_t &xs_r, con
 // arithmetic; entries in 16-byte loads, four consecutive ones per lane, ran
 // LJ at 122-129 us: the lanes of a gather then spread over 32 entries of a
 // row instead of 8 adjacent ones.)
-template <int U, int WORDS, typename Body>
+template <int U, int WORDS, bool STREAM, typename Body>
 __device__ __forceinline__ void walk_split(const __amdgpu_buffer_rsrc_t &xs_r, const __amdgpu_buffer_rsrc_t &row_r,
                                            int32_t cnt, int sub, Body &&body)
 {
@@ -166,7 +184,7 @@ __device__ __forceinline__ void walk_split(const __amdgpu_buffer_rsrc_t &xs_r, c
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             j[u] = 0u;
-            if (t + u * kSlice < cnt) j[u] = __builtin_amdgcn_raw_buffer_load_b32(row_r, off + u * 256u, 0, 0);
+            if (t + u * kSlice < cnt) j[u] = load_entry<STREAM>(row_r, off + u * 256u);
         }
     };
     entries();
@@ -196,12 +214,12 @@ __device__ __forceinline__ void walk_split(const __amdgpu_buffer_rsrc_t &xs_r, c
 
 // The row walk of a pair form: split (SPLIT) or whole batches with no
 // selects (walk_buf without masking).
-template <bool SPLIT, int U, int WORDS, typename Body>
+template <bool SPLIT, int U, int WORDS, bool STREAM, typename Body>
 __device__ __forceinline__ void walk_form(const __amdgpu_buffer_rsrc_t &xs_r, const __amdgpu_buffer_rsrc_t &row_r,
                                           int32_t cnt, int sub, Body &&body)
 {
-    if constexpr (SPLIT) walk_split<U, WORDS>(xs_r, row_r, cnt, sub, body);
-    else walk_buf<U, WORDS, false>(xs_r, row_r, cnt, sub, body);
+    if constexpr (SPLIT) walk_split<U, WORDS, STREAM>(xs_r, row_r, cnt, sub, body);
+    else walk_buf<U, WORDS, false, STREAM>(xs_r, row_r, cnt, sub, body);
 }
 
 // The atoms a force launch covers: the slices from slice0 on, rows and

@@ -96,7 +96,7 @@ __device__ __forceinline__ SliceRange wave_slices(uint32_t nslices)
 }
 
 // pass 1: rho_i = sum psi(r_ij); F(rho_i), F'_i; F'_i into the fourth word
-template <int U, bool CUBIC, bool ENERGY, bool COMP>
+template <int U, bool CUBIC, bool ENERGY, bool COMP, bool STREAM>
 __global__ __launch_bounds__(kTabBlock) void k_tab_rho(int64_t n, uint4 *__restrict__ xs, int32_t cap,
                                                        const int32_t *__restrict__ idx,
                                                        const int32_t *__restrict__ count, TAB32 p,
@@ -120,7 +120,7 @@ __global__ __launch_bounds__(kTabBlock) void k_tab_rho(int64_t n, uint4 *__restr
         if (i < n) {
             const uint4 pi = xs[i];
             const int32_t cnt = min(count[i], cap);
-            walk_split<U, 3>(xs_r, row_r, cnt, sub, [&](const auto &pj, int32_t t0, auto masked) {
+            walk_split<U, 3, STREAM>(xs_r, row_r, cnt, sub, [&](const auto &pj, int32_t t0, auto masked) {
                 constexpr int K = sizeof(pj) / sizeof(uint4);
                 float bs = 0.f;
 #pragma unroll
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(kTabBlock) void k_tab_force(int64_t n, const uint4 
             const uint4 pi = xs[i];
             const float fpi = __uint_as_float(pi.w);
             const int32_t cnt = min(count[i], cap);
-            walk_split<U, 4>(xs_r, row_r, cnt, sub, [&](const auto &pj, int32_t t0, auto masked) {
+            walk_split<U, 4, A::stream>(xs_r, row_r, cnt, sub, [&](const auto &pj, int32_t t0, auto masked) {
                 constexpr int K = sizeof(pj) / sizeof(uint4);
                 float bx = 0.f, by = 0.f, bz = 0.f;
 #pragma unroll
@@ -322,20 +322,20 @@ static int launch_tab(hipStream_t s, int64_t n, uint4 *q, int32_t cap, const int
 {
     const uint32_t nslices = uint32_t((n + kSlice - 1) / kSlice);
     const size_t lds1 = size_t(p.m) * 16, lds2 = size_t(p.m) * 32;
-    g1 = tab_grid(reinterpret_cast<const void *>(&k_tab_rho<kTabUnroll, CUBIC, E, C>), lds1, nslices);
-    auto pass2 = [&](const auto &ad) -> int {
+    auto both = [&](const auto &ad) -> int {
         using A = std::decay_t<decltype(ad)>;
+        g1 = tab_grid(reinterpret_cast<const void *>(&k_tab_rho<kTabUnroll, CUBIC, E, C, A::stream>), lds1, nslices);
         g2 = tab_grid(reinterpret_cast<const void *>(&k_tab_force<kTabUnroll, CUBIC, E, C, A>), lds2, nslices);
         if (int64_t(g1) > max_blocks || int64_t(g2) > max_blocks) return MD_ERR_WORKSPACE;
-        hipLaunchKernelGGL((k_tab_rho<kTabUnroll, CUBIC, E, C>), dim3(g1), dim3(kTabBlock), lds1, s, n, q, cap, idx,
-                           cnt, p, table, rho, fprime, part1, nslices);
+        hipLaunchKernelGGL((k_tab_rho<kTabUnroll, CUBIC, E, C, A::stream>), dim3(g1), dim3(kTabBlock), lds1, s, n, q,
+                           cap, idx, cnt, p, table, rho, fprime, part1, nslices);
         hipLaunchKernelGGL((k_tab_force<kTabUnroll, CUBIC, E, C, A>), dim3(g2), dim3(kTabBlock), lds2, s, n, q, cap,
                            idx, cnt, p, table, rho, f, ea, part2, nslices, ad);
         return MD_OK;
     };
     int rc;
-    if constexpr (!E && C) rc = adv ? pass2(*adv) : pass2(NoAdvance{});
-    else rc = pass2(NoAdvance{});
+    if constexpr (!E && C) rc = adv ? both(*adv) : (streams(n, cap) ? both(Streamed{}) : both(NoAdvance{}));
+    else rc = both(NoAdvance{});
     if (rc) return rc;
     MD_HIP_TRY(hipGetLastError());
     return MD_OK;

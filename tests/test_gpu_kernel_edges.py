@@ -410,6 +410,29 @@ def test_velocity_update_in_the_force_kernels(M, pot, cells, polled):
     assert sims[0].builds > 1
 
 
+@pytest.mark.parametrize("pot", ["lj", "eam", "tb", "tbm", "tab"])
+@pytest.mark.parametrize("timing", [False, True])
+def test_lists_read_past_the_caches(M, pot, timing):
+    """Rows of 24,576 entries' room make the lists of 3,500 atoms larger than the
+    300 MB above which a run reads them past the caches: same trajectory, to the
+    bit, as with rows of 104."""
+    from paper_1611_00075_amd.sim import Simulation
+    cells, a = (10, 10, 9), inputs.fcc_lattice_constant(0.8442) if pot == "lj" else inputs.CU_A0
+    rng = np.random.default_rng(5)
+    x = _fcc(cells, a)[:3500]
+    x = x + 0.02 * a * rng.standard_normal(x.shape)
+    kw = dict(skin=0.3, dt=0.005) if pot == "lj" else dict(
+        potential=pot, skin=0.4, dt=2.0, mass=inputs.CU_MASS_AMU, force_to_accel=1.0 / inputs.AMU_A2_FS2_IN_EV,
+        **{"eam": dict(fs=inputs.FS_CU), "tb": dict(tb=inputs.TB_CU), "tab": dict(tab=inputs.fs_table(inputs.FS_CU)),
+           "tbm": dict(tbm=inputs.TB2_PAIRS, types=rng.integers(0, 2, 3500).astype(np.int32))}[pot])
+    v = (0.8 if pot == "lj" else 0.003) * rng.standard_normal(x.shape)
+    sims = [Simulation(np.array(cells) * a, x, v, row_cap=cap, **kw) for cap in (104, 24_576)]
+    for sim in sims:
+        sim.run(6, timing=timing)
+    for name in ("x", "v", "f", "ids"):
+        assert torch.equal(*(getattr(sim, name) for sim in sims)), name
+
+
 def _fcc(cells, a):
     g = np.stack(np.meshgrid(*[np.arange(c) for c in cells], indexing="ij"), -1).reshape(-1, 1, 3)
     return ((g + np.array(inputs.FCC_BASIS)) * a).reshape(-1, 3)
