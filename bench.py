@@ -708,16 +708,16 @@ TAB_SRC = ["paper_1611_00075_amd/csrc/md_tab.hip", "paper_1611_00075_amd/csrc/md
            "paper_1611_00075_amd/csrc/md_common.h"]
 MLP_SRC = ["paper_1611_00075_amd/csrc/md_mlp.hip", "paper_1611_00075_amd/csrc/md_pair.h",
            "paper_1611_00075_amd/csrc/md_common.h"]
-CELLS_SRC = ["paper_1611_00075_amd/csrc/md_cells.hip", "paper_1611_00075_amd/csrc/md_pair.h",
-             "paper_1611_00075_amd/csrc/md_common.h"]
+CELLS_SRC = ["paper_1611_00075_amd/csrc/md_cells.hip", "paper_1611_00075_amd/csrc/md_bin.h",
+             "paper_1611_00075_amd/csrc/md_pair.h", "paper_1611_00075_amd/csrc/md_common.h"]
 PROBE_SRC = ["paper_1611_00075_amd/csrc/md_probe.hip", "paper_1611_00075_amd/csrc/md_common.h"]
 
 # key: (sources, kernel-name pattern, grid size)  -- grid sizes of the
 # benchmark's systems: 1,228,798 (voids), 4,000,000 (Cu), 31,860,227 (slab)
 # atoms; 103,823 / 287,496 / 216,000 / 3,375,000 cells
 COUNTER_KERNELS = {
-    "k_lj32_lj_voids_1.23M": (FORCES_SRC, r"k_lj32<8, \d+, true, false, true>", 9830400),
-    "k_lj32_lj_slab_32M": (FORCES_SRC, r"k_lj32<8, \d+, true, false, true>", 254882048),
+    "k_lj32_lj_voids_1.23M": (FORCES_SRC, r"k_lj32<8, \d+, true, false, true[,>]", 9830400),
+    "k_lj32_lj_slab_32M": (FORCES_SRC, r"k_lj32<8, \d+, true, false, true[,>]", 254882048),
     "k_eam_rho_cu_4M": (FORCES_SRC, r"k_eam_rho<md::FS32,", 32000000),
     "k_eam_force_cu_4M": (FORCES_SRC, r"k_eam_force<md::FS32,", 32000000),
     "k_tb_rho_cu_4M": (FORCES_SRC, r"k_eam_rho<md::TB32,", 32000000),
@@ -726,12 +726,12 @@ COUNTER_KERNELS = {
     "k_tbm_force_cu_au_4M": (FORCES_SRC, r"k_eam_force<md::TBM32<", 32000000),
     "k_tab_rho_cu_4M": (TAB_SRC, r"k_tab_rho<", None),
     "k_tab_force_cu_4M": (TAB_SRC, r"k_tab_force<", None),
-    "k_mlp_desc_cu_4M": (MLP_SRC, r"k_mlp_desc\(", 32000000),
+    "k_mlp_desc_cu_4M": (MLP_SRC, r"k_mlp_desc(<true>)?\(", 32000000),
     "k_mlp_net_cu_4M": (MLP_SRC, r"k_mlp_net<1>", 524288),
-    "k_mlp_force_cu_4M": (MLP_SRC, r"k_mlp_force<2, false, true>", 32000000),
-    "k_neighbors_lj_voids_1.23M": (CELLS_SRC, r"k_neighbors(<1>)?\(", 103823 * 64),
-    "k_neighbors_cu_5.4A_4M": (CELLS_SRC, r"k_neighbors(<1>)?\(", 287496 * 64),
-    "k_neighbors_lj_slab_32M": (CELLS_SRC, r"k_neighbors(<1>)?\(", 3375000 * 64),
+    "k_mlp_force_cu_4M": (MLP_SRC, r"k_mlp_force<1, true, false, true[,>]", 32000000),
+    "k_neighbors_lj_voids_1.23M": (CELLS_SRC, r"k_neighbors(<1[^>]*>)?\(", 103823 * 64),
+    "k_neighbors_cu_5.4A_4M": (CELLS_SRC, r"k_neighbors(<1[^>]*>)?\(", 287496 * 64),
+    "k_neighbors_lj_slab_32M": (CELLS_SRC, r"k_neighbors(<1[^>]*>)?\(", 3375000 * 64),
     "k_probe_fma_f32": (PROBE_SRC, r"k_probe_fma<float>", None),
     "k_probe_fma_f64": (PROBE_SRC, r"k_probe_fma<double>", None),
     "k_probe_mfma": (PROBE_SRC, r"k_probe_mfma\(", None),
@@ -782,7 +782,7 @@ def summarize_dd_overlap(d):
     DomainSimulation.compute_forces calls: for each evaluation (it starts
     with k_dd_scale_local) the span, the inner and outer launches of the two
     passes (the inner one has the larger grid), and the position and F'
-    halos from the start of their pack to the end of their unpack, with
+    halos from the start of their exchange to its end, with
     whether each ends inside the inner launch it overlaps.  Prints means,
     minima and maxima over the evaluations after the first two."""
     import csv
@@ -809,7 +809,9 @@ def summarize_dd_overlap(d):
 
         rho = sorted(pick("k_eam_rho")[:2], key=lambda k: -k[3])
         frc = sorted(pick("k_eam_force")[:2], key=lambda k: -k[3])
-        pk, up, pkw, upw = pick("k_dd_pack"), pick("k_dd_unpack"), pick("k_dd_pack_w"), pick("k_dd_unpack_w")
+        # the halos: a pack and an unpack, or one kernel that does both
+        pk, up = (pick(k) or pick("k_dd_exchange") for k in ("k_dd_pack", "k_dd_unpack"))
+        pkw, upw = (pick(k) or pick("k_dd_exchange_w") for k in ("k_dd_pack_w", "k_dd_unpack_w"))
         if len(rho) < 2 or len(frc) < 2 or not (pk and up and pkw and upw):
             continue
         end = max(k[1] for k in ks if "k_eam" in k[2] or "k_dd" in k[2])
