@@ -148,9 +148,10 @@ __global__ __launch_bounds__(kBlock) void k_reorder_put(int64_t n, const double 
                                                         const double *__restrict__ vt,
                                                         const int32_t *__restrict__ it, double *__restrict__ x,
                                                         double *__restrict__ v, int32_t *__restrict__ ids, double k0,
-                                                        double k1, double k2, uint4 *__restrict__ xs)
+                                                        double k1, double k2, uint4 *__restrict__ xs, int32_t *clear)
 {
     const int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+    if (clear && k == 0) *clear = 0;
     if (k >= n) return;
     double p[3];
     for (int c = 0; c < 3; ++c) {
@@ -163,14 +164,14 @@ __global__ __launch_bounds__(kBlock) void k_reorder_put(int64_t n, const double 
 }
 
 int reorder_state(int64_t n, const int32_t *perm, double *x, double *v, int32_t *ids, double *xref, double *vtmp,
-                  int32_t *itmp, const md_box_t *box, uint32_t *xs, hipStream_t s)
+                  int32_t *itmp, const md_box_t *box, uint32_t *xs, hipStream_t s, int32_t *clear)
 {
     if (n <= 0) return MD_OK;
     const double two32 = 4294967296.0;
     const uint32_t gb = uint32_t((n + kBlock - 1) / kBlock);
     hipLaunchKernelGGL(k_reorder_gather, dim3(gb), dim3(kBlock), 0, s, n, perm, x, v, ids, xref, vtmp, itmp);
     hipLaunchKernelGGL(k_reorder_put, dim3(gb), dim3(kBlock), 0, s, n, xref, vtmp, itmp, x, v, ids,
-                       two32 / box->L[0], two32 / box->L[1], two32 / box->L[2], reinterpret_cast<uint4 *>(xs));
+                       two32 / box->L[0], two32 / box->L[1], two32 / box->L[2], reinterpret_cast<uint4 *>(xs), clear);
     MD_HIP_TRY(hipGetLastError());
     return MD_OK;
 }
@@ -186,6 +187,7 @@ struct SortState {
     int32_t *ids;
     double k[3];   // 2^32 / L
     uint4 *xs;
+    int32_t *clear;   // a word set to 0
 };
 
 // Small systems: one block does the whole counting sort in LDS and, with STATE,
@@ -292,6 +294,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_sort_small(int32_t n, double *x
     }
     if constexpr (STATE) {
         // every thread has read its positions (before the first barrier)
+        if (t == 0) *st.clear = 0;
         double v[K][3];
         int32_t id[K];
 #pragma unroll
@@ -358,22 +361,22 @@ int bin_cells(const md_grid_t *grid, int64_t n, double *x, int32_t *cell, int32_
     return MD_OK;
 }
 
-// bin_cells and reorder_state of a build.
+// bin_cells and reorder_state of a build; sets *max_count to 0 for its lists (n > 0).
 int sort_state(const md_grid_t *grid, int64_t n, double *x, int32_t *cell, int32_t *perm, int32_t *cell_start,
                void *ws, const WsLayout &w, double *v, int32_t *ids, double *xref, double *vtmp, int32_t *itmp,
-               const md_box_t *box, uint32_t *xs, hipStream_t s)
+               const md_box_t *box, uint32_t *xs, int32_t *max_count, hipStream_t s)
 {
     if (sorts_small(grid, n, kSmallState)) {
         const double two32 = 4294967296.0;
         const SortState st{v, xref, ids, {two32 / box->L[0], two32 / box->L[1], two32 / box->L[2]},
-                           reinterpret_cast<uint4 *>(xs)};
+                           reinterpret_cast<uint4 *>(xs), max_count};
         hipLaunchKernelGGL((k_sort_small<true, kSmallState / kSmallBlock>), dim3(1), dim3(kSmallBlock), 0, s, int32_t(n), x, grid_args(grid),
                            int32_t(grid->n_cells), ws_ptr<int32_t>(ws, w.lin2rank), cell, perm, cell_start, st);
         MD_HIP_TRY(hipGetLastError());
         return MD_OK;
     }
     if (int rc = bin_cells(grid, n, x, cell, perm, cell_start, ws, w, s)) return rc;
-    return reorder_state(n, perm, x, v, ids, xref, vtmp, itmp, box, xs, s);
+    return reorder_state(n, perm, x, v, ids, xref, vtmp, itmp, box, xs, s, max_count);
 }
 
 // The element of each atom (0 or 1; only bit 0 is used) into the fourth word
@@ -1221,12 +1224,12 @@ NbSplit nb_split(int64_t n, int64_t n_cells, bool small)
 
 int build_neighbors(const md_grid_t *grid, int64_t n, const double *x, const int32_t *cell_start, int32_t row_cap,
                     int32_t *idx, int32_t *count, int32_t *max_count, int32_t *needed, void *ws, const WsLayout &w,
-                    hipStream_t s)
+                    hipStream_t s, bool cleared)
 {
     const GridArgs g = grid_args(grid);
     const double rl2 = grid->r_list * grid->r_list;
-    int rc = launch_fill_i32(max_count, 1, 0, s);
-    if (rc) return rc;
+    if (!cleared)
+        if (int rc = launch_fill_i32(max_count, 1, 0, s)) return rc;
     if (n > 0) {
         const int32_t least = std::min(grid->nc[0], std::min(grid->nc[1], grid->nc[2]));
         // (rows of a million entries and more: nine slices of them pass a buffer's 32-bit range)

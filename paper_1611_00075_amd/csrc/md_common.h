@@ -110,6 +110,8 @@ struct Advance {
     int32_t *status;
     uint32_t *xs_out;        // NULL in the FP64 path
     bool drift, write_f;
+    const int32_t *longest;  // behind a build: its longest row, for the host word
+    int32_t *longest_host;   // (NULL otherwise)
 };
 
 // Orders the LDS accesses of one wavefront around this point (the lanes of a
@@ -233,14 +235,14 @@ int permute(int64_t, int32_t, const int32_t *, const void *, void *, int32_t, hi
 int scale_positions(const md_box_t *, int64_t, const double *, uint32_t *, hipStream_t);
 int sort_state(const md_grid_t *, int64_t n, double *x, int32_t *cell, int32_t *perm, int32_t *cell_start, void *ws,
                const WsLayout &w, double *v, int32_t *ids, double *xref, double *vtmp, int32_t *itmp,
-               const md_box_t *box, uint32_t *xs, hipStream_t s);
+               const md_box_t *box, uint32_t *xs, int32_t *max_count, hipStream_t s);
 int reorder_state(int64_t n, const int32_t *perm, double *x, double *v, int32_t *ids, double *xref, double *vtmp,
-                  int32_t *itmp, const md_box_t *box, uint32_t *xs, hipStream_t s);
+                  int32_t *itmp, const md_box_t *box, uint32_t *xs, hipStream_t s, int32_t *clear = nullptr);
 int build_neighbors_bricks(const md_grid_t *, int n_bricks, const int64_t *slot0, int64_t slots, const double *x,
                            const int32_t *cell_start, int32_t row_cap, int32_t *idx, int32_t *count, int32_t *longest,
                            void *ws, const WsLayout &, hipStream_t);
 int build_neighbors(const md_grid_t *, int64_t, const double *, const int32_t *, int32_t, int32_t *, int32_t *,
-                    int32_t *, int32_t *, void *, const WsLayout &, hipStream_t);
+                    int32_t *, int32_t *, void *, const WsLayout &, hipStream_t, bool cleared = false);
 int forces_lj(const md_box_t *, int64_t, const double *, const uint32_t *, int32_t, const int32_t *, const int32_t *,
               const md_lj_t *, void *, double *, int32_t, void *, const WsLayout &, hipStream_t, Gate = {},
               const Advance * = nullptr);

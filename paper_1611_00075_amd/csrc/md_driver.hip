@@ -90,13 +90,13 @@ int read_flag(md_system_t *sys, int32_t *host_dev, int32_t tag, hipStream_t s, b
 // Bins, sorts and builds the lists without waiting for the longest row:
 // check_build reads it once the force evaluation (gated on the device by the
 // same row length) is queued behind the build.
-int rebuild(md_system_t *sys, const WsLayout &w, hipStream_t s, int32_t *host_dev)
+int rebuild(md_system_t *sys, const WsLayout &w, hipStream_t s)
 {
     const int64_t n = sys->n;
     // state into the sorted order; xref = the sorted positions
     uint32_t *xs = (sys->flags & MD_PAIR_FP64) ? nullptr : sys->xs;
     int rc = sort_state(&sys->grid, n, sys->x, sys->cell, sys->perm, sys->cell_start, sys->ws, w, sys->v, sys->ids,
-                        sys->xref, sys->scratch, sys->ids_scratch, &sys->box, xs, s);
+                        sys->xref, sys->scratch, sys->ids_scratch, &sys->box, xs, sys->max_count, s);
     if (rc) return rc;
     if (n > 0) {
         if (sys->potential == MD_POT_TBM) {
@@ -106,14 +106,20 @@ int rebuild(md_system_t *sys, const WsLayout &w, hipStream_t s, int32_t *host_de
             if ((rc = set_elements(n, sys->types, sys->xs, s))) return rc;
         }
     }
-    rc = build_neighbors(&sys->grid, n, sys->x, sys->cell_start, sys->row_cap, sys->idx, sys->count, sys->max_count,
-                         nullptr, sys->ws, w, s);
-    if (rc) return rc;
-    if (host_dev) {
-        reinterpret_cast<volatile int32_t *>(sys->host_status)[3] = -1;
-        hipLaunchKernelGGL(k_publish_longest, dim3(1), dim3(1), 0, s, sys->max_count, host_dev);
-        MD_HIP_TRY(hipGetLastError());
-    }
+    return build_neighbors(&sys->grid, n, sys->x, sys->cell_start, sys->row_cap, sys->idx, sys->count, sys->max_count,
+                           nullptr, sys->ws, w, s, n > 0);
+}
+
+// The host word of the longest row, before the kernel that posts it is queued.
+void expect_longest(md_system_t *sys) { reinterpret_cast<volatile int32_t *>(sys->host_status)[3] = -1; }
+
+// Posts the longest row where the evaluation behind the build does not.
+int publish_longest(md_system_t *sys, hipStream_t s, int32_t *host_dev)
+{
+    if (!host_dev) return MD_OK;
+    expect_longest(sys);
+    hipLaunchKernelGGL(k_publish_longest, dim3(1), dim3(1), 0, s, sys->max_count, host_dev);
+    MD_HIP_TRY(hipGetLastError());
     return MD_OK;
 }
 
@@ -289,7 +295,8 @@ int run(md_system_t *sys, int64_t steps, hipStream_t s)
     // forces of a fresh build, skipped on the device when a row overflowed
     const Gate fits{nullptr, 0, 0, sys->max_count, sys->row_cap};
     if (sys->phase == 0 && sys->need_build) {
-        if ((rc = rebuild(sys, w, s, host_dev))) return rc;
+        if ((rc = rebuild(sys, w, s))) return rc;
+        if ((rc = publish_longest(sys, s, host_dev))) return rc;
         if ((rc = forces(sys, w, s, side[0], fits))) return rc;
         if ((rc = check_build(sys, host_dev, s))) return rc;
         sys->need_build = 0;
@@ -309,7 +316,8 @@ int run(md_system_t *sys, int64_t steps, hipStream_t s)
     bool first = true;   // no drift queued in this run yet
     // Queues the evaluation of step k (positions on side b).  post: it posts the
     // flag of step k; where it cannot and no kick-drift follows, a kernel does.
-    const auto queue_forces = [&](int64_t k, int b, Gate gate, bool post) -> int {
+    // built: behind a build, whose longest row is posted likewise.
+    const auto queue_forces = [&](int64_t k, int b, Gate gate, bool post, bool built = false) -> int {
         const int what = besides(k, b);
         const int32_t tag = int32_t(k);
         Advance adv{};
@@ -336,6 +344,15 @@ int run(md_system_t *sys, int64_t steps, hipStream_t s)
             } else {
                 hipLaunchKernelGGL(k_publish, dim3(1), dim3(1), 0, s, sys->status, flag_slot(host_dev, tag), tag);
                 MD_HIP_TRY(hipGetLastError());
+            }
+        }
+        if (built && host_dev) {
+            if (what != kNothing) {
+                expect_longest(sys);
+                adv.longest = sys->max_count;
+                adv.longest_host = host_dev + 3;
+            } else if (int r = publish_longest(sys, s, host_dev)) {
+                return r;
             }
         }
         timer.start(s);
@@ -412,10 +429,10 @@ int run(md_system_t *sys, int64_t steps, hipStream_t s)
             ready = false;
             if (f64 && (rc = settle(b))) return rc;
             b = 0;
-            if ((rc = rebuild(sys, w, s, host_dev))) return rc;
+            if ((rc = rebuild(sys, w, s))) return rc;
         }
         if (!ready) {
-            if ((rc = queue_forces(k, b, built ? fits : Gate{}, false))) return rc;
+            if ((rc = queue_forces(k, b, built ? fits : Gate{}, false, built))) return rc;
             queued = k;
             qb = b;
         }

@@ -615,8 +615,9 @@ struct List {
     const int32_t *idx, *cnt;
 };
 
-// an evaluation of a run's step (gate.flag) over a list too large for the caches
-static bool in_run_streams(const Gate &gate, int64_t n, int32_t cap) { return gate.flag && streams(n, cap); }
+// an evaluation of a run (its steps are gated by flags, those behind a build by the
+// longest row) over a list too large for the caches
+static bool in_run_streams(const Gate &gate, int64_t n, int32_t cap) { return (gate.flag || gate.over) && streams(n, cap); }
 
 template <int TPA, bool CUBIC, bool E, bool C>
 static void launch_lj32(uint32_t gb, hipStream_t s, int64_t n, const uint4 *q, const List &l, const LJ32 &p,

@@ -374,8 +374,9 @@ __device__ __forceinline__ bool writes_f(const A &adv)
     else return true;
 }
 
-// The launch's first thread posts the flag of the step whose forces these are
-// (before the gate: the host waits for it in either case).
+// The launch's first thread posts the flag of the step whose forces these are, or
+// the longest row of the build before it (before the gate: the host waits for
+// either in any case).
 template <class A>
 __device__ __forceinline__ void post_flag(const A &adv)
 {
@@ -384,6 +385,8 @@ __device__ __forceinline__ void post_flag(const A &adv)
             const bool stop = adv.status[0] == adv.a.post.tag;
             post_flag_word(adv.a.post.word, adv.a.post.tag, stop, stop && adv.status[1] != 0);
         }
+        if (adv.longest_host && blockIdx.x == 0 && threadIdx.x == 0)
+            __hip_atomic_store(adv.longest_host, *adv.longest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
