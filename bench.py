@@ -727,7 +727,7 @@ COUNTER_KERNELS = {
     "k_tab_rho_cu_4M": (TAB_SRC, r"k_tab_rho<", None),
     "k_tab_force_cu_4M": (TAB_SRC, r"k_tab_force<", None),
     "k_mlp_desc_cu_4M": (MLP_SRC, r"k_mlp_desc(<true>)?\(", 32000000),
-    "k_mlp_net_cu_4M": (MLP_SRC, r"k_mlp_net<1>", 524288),
+    "k_mlp_net_cu_4M": (MLP_SRC, r"k_mlp_net<1>", 131072),
     "k_mlp_force_cu_4M": (MLP_SRC, r"k_mlp_force<1, true, false, true[,>]", 32000000),
     "k_neighbors_lj_voids_1.23M": (CELLS_SRC, r"k_neighbors(<1[^>]*>)?\(", 103823 * 64),
     "k_neighbors_cu_5.4A_4M": (CELLS_SRC, r"k_neighbors(<1[^>]*>)?\(", 287496 * 64),
