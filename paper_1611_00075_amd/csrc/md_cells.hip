@@ -1009,13 +1009,19 @@ __device__ __forceinline__ int32_t nm_cell(NmLds<R, D> &L, int64_t rank, int32_t
         L.run[lane] = 0;
         L.off[lane] = int32_t(uint32_t((hl >> 3) - (hb >> 3)) * uint32_t(row_cap) * 32u + uint32_t(hl & 7) * 32u);
         // bounding box of the homes: its centre and half edges, through FP32
-        // offsets from the first home
+        // offsets from the first home.  Homes that are no number take no part: theirs is
+        // one row of the matrix products, which then has no hits, and the rest stay as
+        // they are without it.
+        const bool number = isfinite(xh) && isfinite(yh) && isfinite(zh);
+        const uint64_t numbers = __builtin_amdgcn_ballot_w64(number);
+        const int src = numbers ? __builtin_ctzll(numbers) : 0;
         auto first = [&](double v) {
-            return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
-                                    __builtin_amdgcn_readfirstlane(__double2loint(v)));
+            return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src),
+                                    __builtin_amdgcn_readlane(__double2loint(v), src));
         };
         const double ox = first(xh), oy = first(yh), oz = first(zh);
-        const float fx = float(xh - ox), fy = float(yh - oy), fz = float(zh - oz);
+        const float fx = number ? float(xh - ox) : 0.f, fy = number ? float(yh - oy) : 0.f,
+                    fz = number ? float(zh - oz) : 0.f;
         const float lx = wave_extreme<false>(fx), ly = wave_extreme<false>(fy), lz = wave_extreme<false>(fz);
         const float ux = wave_extreme<true>(fx), uy = wave_extreme<true>(fy), uz = wave_extreme<true>(fz);
         const double mx = ox + double(0.5f * (lx + ux)), my = oy + double(0.5f * (ly + uy)),

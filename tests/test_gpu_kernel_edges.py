@@ -262,6 +262,37 @@ def test_list_with_a_position_that_is_no_number(M, orc):
         assert np.array_equal(np.sort(_row(idx, i, 200)[:cnt[i]]), rest[ob[off[k]:off[k + 1]]])
 
 
+def _nan_systems():
+    # few cells (batches of 4 homes), many cells (a batch is a cell), 125-cell
+    # stencils, three cells on an axis (the path without matrix cores)
+    return [((11.3, 12.1, 13.0), 2.8, 1, 900), ((36.5, 36.6, 37.0), 2.8, 1, 33000), ((8.5, 9.0, 9.6), 2.8, 2, 700),
+            ((9.0, 12.0, 12.5), 2.9, 1, 800)]
+
+
+@pytest.mark.parametrize("where,axes", [("first", (0, 1, 2)), ("first", (2,)), ("middle", (0, 1, 2)), ("last", (0, 1, 2)),
+                                        ("two", (0, 1, 2))])
+@pytest.mark.parametrize("L,r_list,reach,n", _nan_systems())
+def test_list_with_no_number_anywhere_in_a_batch(M, orc, L, r_list, reach, n, where, axes):
+    """Atoms whose position (or one component) is no number at the start, in the
+    middle and at the end of their cell: they have no neighbours and are
+    nobody's, and every other row is that of the system without them."""
+    L = np.array(L)
+    x = orc.wrap(inputs.random_gas(n, L, 6), L)
+    for k in {"first": [0], "middle": [n // 2], "last": [n - 1], "two": [0, 1]}[where]:
+        x[k, list(axes)] = np.nan
+    cap = 400
+    _, _, xs, idx, cnt, _ = _lists(M, orc, x, L, r_list, reach, cap)
+    bad = np.isnan(xs).any(axis=1)
+    assert (cnt[bad] == 0).all()
+    rest = np.flatnonzero(~bad)
+    off, ob = orc.neighbors_brute(xs[rest], L, r_list) if n < 10_000 else orc.neighbors_cells(xs[rest], L, r_list)
+    assert np.array_equal(cnt[rest], np.diff(off))
+    some = np.random.default_rng(n).choice(len(rest), min(len(rest), 900), replace=False)
+    for k in np.union1d(some, np.arange(40)):
+        i = rest[k]
+        assert np.array_equal(np.sort(_row(idx, i, cap)[:cnt[i]]), rest[np.sort(ob[off[k]:off[k + 1]])])
+
+
 # ---- learned potential ----------------------------------------------------------------
 
 @pytest.mark.parametrize("dmu,width", [(0.2, 0.2), (0.3, 0.16)])
