@@ -628,40 +628,48 @@ void k_mlp_net(int64_t n, MlpArgs p, const float *Gin, const uint16_t *__restric
 
 // ---- pass 2: forces ---------------------------------------------------------
 
+// a0 + a1 z + a2 z^2 + a3 z^3 and its derivative
+__device__ __forceinline__ void cubic(float a0, float a1, float a2, float a3, float z, float &v, float &d)
+{
+    v = __builtin_fmaf(a3, z, a2);
+    d = __builtin_fmaf(a3, z, v);
+    v = __builtin_fmaf(v, z, a1);
+    d = __builtin_fmaf(d, z, v);
+    v = __builtin_fmaf(v, z, a0);
+}
+
 // S0 = sum_k c_k e_k and S1 = sum_k (k - 8) c_k e_k over the 16 Gaussians of a
 // pair, c_k = dE_i/dG_ik + dE_j/dG_jk, t = r - c8.  With u = exp(t dmu / w^2),
 // e_{8+m} = e_8 u^m Q_m and e_{8-m} = e_8 u^-m Q_m, Q_m = exp(-m^2 dmu^2 / 2w^2):
 // with Q folded into the coefficients (di holds c's first term times Q) both
 // sums are polynomials in u and in 1/u, taken with their derivatives by
-// Horner's rule: 16 + 30 operations where forming the Gaussians and both
+// Horner's rule: 16 + 42 operations where forming the Gaussians and both
 // sums took 94.  Beyond 13.22 widths from c8 e_8 is zero in FP32, and with it
-// both sums, so u stops there: the powers of 1 / u and u then stay in range (at
-// most 1e35 times the coefficients with the rule for folding) for the closest pairs too.
+// both sums, so u stops there.  Each polynomial is taken in two halves, the
+// outer one with u^4 (u^-5) already times e_8: whole, the powers of the closest
+// pairs reach 1e32 (dmu = w; 2e34 at the edge of the rule for folding) before e_8
+// brings them back, and leave FP32 where dE/dG is large (4e5; 2e3); in halves they
+// stay below 1e16.  (1 M copper atoms 485.5 us whole, 487 in halves.)
 __device__ __forceinline__ void basis_sums_folded(const MlpArgs &p, float t, const float (&di)[kIn],
                                                   const float (&dj)[kIn], float &S0, float &S1)
 {
     const float e8 = __builtin_amdgcn_exp2f(-p.ka * t * t);
     const float y = __builtin_amdgcn_fmed3f(p.alpha * t, -p.ylim, p.ylim);
-    const float up = __builtin_amdgcn_exp2f(y), dn = __builtin_amdgcn_exp2f(-y);
+    const float u = __builtin_amdgcn_exp2f(y), v = __builtin_amdgcn_exp2f(-y);
     float c[kIn];
 #pragma unroll
     for (int k = 0; k < kIn; ++k) c[k] = __builtin_fmaf(dj[k], p.Q[k < 8 ? 8 - k : k - 8], di[k]);
-    // A(u) = sum_{m=0..7} c_{8+m} u^m and A'(u)
-    float A = c[15], dA = 0.f;
-#pragma unroll
-    for (int m = 6; m >= 0; --m) {
-        dA = m == 6 ? A : __builtin_fmaf(dA, up, A);
-        A = __builtin_fmaf(A, up, c[8 + m]);
-    }
-    // v C(v) = sum_{m=1..8} c_{8-m} v^m, v = 1/u, and C'(v)
-    float C = c[0], dC = 0.f;
-#pragma unroll
-    for (int m = 7; m >= 1; --m) {
-        dC = m == 7 ? C : __builtin_fmaf(dC, dn, C);
-        C = __builtin_fmaf(C, dn, c[8 - m]);
-    }
-    S0 = e8 * __builtin_fmaf(C, dn, A);
-    S1 = e8 * __builtin_fmaf(up, dA, -dn * __builtin_fmaf(dn, dC, C));
+    float a, da, b, db, f, df, g, dg;
+    cubic(c[8], c[9], c[10], c[11], u, a, da);     // m = 0 .. 3: u^m
+    cubic(c[12], c[13], c[14], c[15], u, b, db);   // m = 4 .. 7: u^4 u^(m - 4)
+    cubic(c[7], c[6], c[5], c[4], v, f, df);       // m = 1 .. 4: v v^(m - 1)
+    cubic(c[3], c[2], c[1], c[0], v, g, dg);       // m = 5 .. 8: v^5 v^(m - 5)
+    const float u2 = u * u, v2 = v * v;
+    const float eb = e8 * (u2 * u2), ef = e8 * v, eg = ef * (v2 * v2);
+    S0 = __builtin_fmaf(e8, a, __builtin_fmaf(eb, b, __builtin_fmaf(ef, f, eg * g)));
+    const float up = __builtin_fmaf(e8 * u, da, eb * __builtin_fmaf(u, db, 4.f * b));
+    const float dn = __builtin_fmaf(ef, __builtin_fmaf(v, df, f), eg * __builtin_fmaf(v, dg, 5.f * g));
+    S1 = up - dn;
 }
 
 // The same sums from the Gaussians themselves (di: c's first term): for
@@ -1207,8 +1215,8 @@ int forces_mlp(const md_box_t *box, int64_t n, const uint32_t *xs, int32_t cap, 
         using T = std::true_type;
         using F = std::false_type;
         // Folded sums where Q_8 = exp(-32 (dmu / w)^2) is above 1e-18 (the
-        // default spacing, dmu = w: 1.3e-14), so that the coefficients and the
-        // powers keep the FP32 range; plain ones for wider spacings, and with MD_ENERGY,
+        // default spacing, dmu = w: 1.3e-14), so that the coefficients and the powers
+        // keep the FP32 range; plain ones for wider spacings, and with MD_ENERGY,
         // whose pair forces then have the value they always had (the two differ
         // in the last bits of a pair's force factor).
         if (energy) comp ? force(F{}, T{}, T{}) : force(F{}, T{}, F{});

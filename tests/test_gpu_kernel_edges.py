@@ -349,6 +349,38 @@ def test_learned_pair_pass_of_close_pairs(M, r):
     assert np.abs(out[0] - out[1]).max() <= 1e-5 * (scale + np.abs(out[1]).max()), out
 
 
+@pytest.mark.parametrize("size", [1.0, 1e4, 1e7, 1e12, 1e20])
+@pytest.mark.parametrize("dmu,r", [(0.2, 1.0), (0.2, 1.1), (0.2, 1.4), (0.2, 2.5), (0.225, 1.25), (0.225, 1.6), (0.1, 0.2),
+                                   (0.1, 1.0)])
+def test_learned_pair_pass_of_large_gradients(M, orc, dmu, r, size):
+    """dE/dG of any size (inputs of small spread are scaled up by as much) for
+    pairs down to where the central Gaussian leaves FP32 (13.2 widths of 0.2 below its
+    centre): finite and right wherever the 16 terms are.  The exponents reach 127 and are
+    rounded two or three times (2^-24 each, ln 2 of them relative), the ratio is
+    taken to the eighth power: 1e-4 of the summed magnitudes."""
+    from oracle import mlp as om
+    from paper_1611_00075_amd import mlp as P
+    from paper_1611_00075_amd.sim import Simulation
+    x = np.array([[5.0, 5.0, 5.0], [5.0 + 0.6 * r, 5.0 + 0.8 * r, 5.0]])
+    spec = dict(rc=P.RC, mu0=P.MU0, dmu=dmu, width=P.WIDTH)
+    sim = Simulation(np.full(3, 20.0), x, np.zeros_like(x), potential="mlp", mlp=M.mlp_spec(*spec.values()),
+                     mlp_w=P.bf16_bits(P.init_params(5)).cuda(), skin=1.0, dt=1.0)
+    D = (size * np.random.default_rng(3).uniform(0.5, 1.0, (2, 16))).astype(np.float32)
+    ids = sim.ids.cpu().numpy()
+    off, idx = orc.neighbors_brute(x, np.full(3, 20.0), P.RC)
+    want, _ = om.forces(x, np.full(3, 20.0), off, idx, om.Spec(**spec), D.astype(np.float64))
+    t = r - (P.MU0 + dmu * np.arange(16))
+    scale = (D.sum(0) * np.exp(-t * t / (2 * P.WIDTH ** 2)) * (np.abs(t) / P.WIDTH ** 2 + 1)).sum()
+    for energy in (0, M.MD_ENERGY):
+        sim.dEdG[:2] = torch.tensor(D[ids], device="cuda")
+        f = torch.full((3, 2), np.nan, dtype=torch.float32, device="cuda")
+        M.md_forces_mlp(sim.L, 2, sim.xs, sim.row_cap, sim.idx, sim.count, sim.mlp, None, sim.dEdG, None, None, None,
+                        f, sim.ev, M.MD_MLP_REUSE | energy, sim.ws)
+        got = np.empty((2, 3))
+        got[ids] = f.cpu().numpy().T
+        assert np.abs(got - want).max() <= 1e-4 * scale, (energy, got, want)
+
+
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 64 * 512, 64 * 512 + 1])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_network_at_block_edges(M, orc, n, shift):
