@@ -643,13 +643,14 @@ __device__ __forceinline__ void cubic(float a0, float a1, float a2, float a3, fl
 // e_{8+m} = e_8 u^m Q_m and e_{8-m} = e_8 u^-m Q_m, Q_m = exp(-m^2 dmu^2 / 2w^2):
 // with Q folded into the coefficients (di holds c's first term times Q) both
 // sums are polynomials in u and in 1/u, taken with their derivatives by
-// Horner's rule: 16 + 42 operations where forming the Gaussians and both
+// Horner's rule (RAW: di without Q, which is multiplied in here): 16 + 42 operations where forming the Gaussians and both
 // sums took 94.  Beyond 13.22 widths from c8 e_8 is zero in FP32, and with it
 // both sums, so u stops there.  Each polynomial is taken in two halves, the
 // outer one with u^4 (u^-5) already times e_8: whole, the powers of the closest
 // pairs reach 1e32 (dmu = w; 2e34 at the edge of the rule for folding) before e_8
 // brings them back, and leave FP32 where dE/dG is large (4e5; 2e3); in halves they
 // stay below 1e16.  (1 M copper atoms 485.5 us whole, 487 in halves.)
+template <bool RAW>
 __device__ __forceinline__ void basis_sums_folded(const MlpArgs &p, float t, const float (&di)[kIn],
                                                   const float (&dj)[kIn], float &S0, float &S1)
 {
@@ -658,7 +659,10 @@ __device__ __forceinline__ void basis_sums_folded(const MlpArgs &p, float t, con
     const float u = __builtin_amdgcn_exp2f(y), v = __builtin_amdgcn_exp2f(-y);
     float c[kIn];
 #pragma unroll
-    for (int k = 0; k < kIn; ++k) c[k] = __builtin_fmaf(dj[k], p.Q[k < 8 ? 8 - k : k - 8], di[k]);
+    for (int k = 0; k < kIn; ++k) {
+        const float Q = p.Q[k < 8 ? 8 - k : k - 8];
+        c[k] = __builtin_fmaf(dj[k], Q, RAW ? di[k] * Q : di[k]);
+    }
     float a, da, b, db, f, df, g, dg;
     cubic(c[8], c[9], c[10], c[11], u, a, da);     // m = 0 .. 3: u^m
     cubic(c[12], c[13], c[14], c[15], u, b, db);   // m = 4 .. 7: u^4 u^(m - 4)
@@ -697,12 +701,20 @@ __device__ __forceinline__ void basis_sums(const MlpArgs &p, float t, const floa
 // sums 1 M copper atoms (43 M pairs) went from 285 to 262 us (one pair a lane
 // at a time; two 268, three 318); the vector unit and the addressers are then
 // both busy 87 % of the time.
+//
+// MD_ENERGY writes the same forces, to the bit, and its virial sums the pair
+// factors of the Gaussians themselves: the two sets of sums differ by FP32 rounding,
+// some of it common to all pairs (the constants), which FP64 sums over a million
+// pairs show.  So where the forces are folded a pair's sums are taken both ways, its
+// neighbour's row read from LDS a second time between them (kept, the registers
+// leave four waves a SIMD, 315 us; five 304): energies of 500,000 atoms 277 -> 304 us,
+// the forces alone stay where they are (plain sums in both: 1 M atoms 509 us
+// against 491).
 template <int U, bool FOLD, bool ENERGY, bool COMP, class A>
-__global__ __launch_bounds__(kBlock) void k_mlp_force(int64_t n, MlpArgs p, const uint4 *__restrict__ xs,
-                                                      int32_t cap, const int32_t *__restrict__ idx,
-                                                      const int32_t *__restrict__ count,
-                                                      const float4 *__restrict__ dEdG, float *__restrict__ f,
-                                                      double *__restrict__ part, A adv)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FOLD && ENERGY ? 5 : 1)))
+void k_mlp_force(int64_t n, MlpArgs p, const uint4 *__restrict__ xs, int32_t cap, const int32_t *__restrict__ idx,
+                 const int32_t *__restrict__ count, const float4 *__restrict__ dEdG, float *__restrict__ f,
+                 double *__restrict__ part, A adv)
 {
     post_flag(adv);
     if (gated(p.gate)) return;
@@ -726,7 +738,7 @@ __global__ __launch_bounds__(kBlock) void k_mlp_force(int64_t n, MlpArgs p, cons
         di[4 * q + 2] = v.z;
         di[4 * q + 3] = v.w;
     }
-    if (FOLD)
+    if (FOLD && !ENERGY)
 #pragma unroll
         for (int k = 0; k < kIn; ++k) di[k] *= p.Q[k < 8 ? 8 - k : k - 8];
     const int32_t cnt = live ? min(count[i], cap) : 0;
@@ -762,14 +774,17 @@ __global__ __launch_bounds__(kBlock) void k_mlp_force(int64_t n, MlpArgs p, cons
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             float dj[kIn];
+            const auto neighbour_row = [&]() {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 v = rows[u][lane * 4 + (q ^ ((lane >> 1) & 3))];
-                dj[4 * q] = v.x;
-                dj[4 * q + 1] = v.y;
-                dj[4 * q + 2] = v.z;
-                dj[4 * q + 3] = v.w;
-            }
+                for (int q = 0; q < 4; ++q) {
+                    const float4 v = rows[u][lane * 4 + (q ^ ((lane >> 1) & 3))];
+                    dj[4 * q] = v.x;
+                    dj[4 * q + 1] = v.y;
+                    dj[4 * q + 2] = v.z;
+                    dj[4 * q + 3] = v.w;
+                }
+            };
+            neighbour_row();
             float dx, dy, dz;
             disp<false>(pi, pj[u], p.ax, p.ay, p.az, dx, dy, dz);
             const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
@@ -782,16 +797,26 @@ __global__ __launch_bounds__(kBlock) void k_mlp_force(int64_t n, MlpArgs p, cons
             const float fc = c * c, dfc = -2.f * p.phi * s * c;
             // s_ij = sum_k c_k e_k (dfc - fc (t - (k - 8) dmu) / w^2)
             float S0, S1;
-            if (FOLD) basis_sums_folded(p, t, di, dj, S0, S1);
+            const auto factor = [&]() {
+                const float sij = __builtin_fmaf(-fc * t, p.iw2, dfc) * S0 + fc * p.cw * S1;
+                return in ? -sij * ir : 0.f;
+            };
+            if (FOLD) basis_sums_folded<ENERGY>(p, t, di, dj, S0, S1);
             else basis_sums(p, t, di, dj, S0, S1);
-            const float sij = __builtin_fmaf(-fc * t, p.iw2, dfc) * S0 + fc * p.cw * S1;
-            const float gs = in ? -sij * ir : 0.f;
+            const float gs = factor();
             acc_add<COMP>(fx, cx, gs, dx);
             acc_add<COMP>(fy, cy, gs, dy);
             acc_add<COMP>(fz, cz, gs, dz);
-            if (ENERGY) add_virial(w, gs, dx, dy, dz);
+            if (ENERGY) {
+                if (FOLD) {
+                    asm volatile("" ::: "memory");   // (from LDS again, not from registers)
+                    neighbour_row();
+                    basis_sums(p, t, di, dj, S0, S1);
+                }
+                add_virial(w, FOLD ? factor() : gs, dx, dy, dz);
+            }
         }
-        asm volatile("" ::: "memory");   // this batch's rows are read before the next ones arrive
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this batch's rows are read before the next ones arrive
     }
     const double gx = combine(fx, cx), gy = combine(fy, cy), gz = combine(fz, cz);
     if (sub == 0 && live && writes_f(adv)) {
@@ -1215,13 +1240,15 @@ int forces_mlp(const md_box_t *box, int64_t n, const uint32_t *xs, int32_t cap, 
         using T = std::true_type;
         using F = std::false_type;
         // Folded sums where Q_8 = exp(-32 (dmu / w)^2) is above 1e-18 (the
-        // default spacing, dmu = w: 1.3e-14), so that the coefficients and the powers
-        // keep the FP32 range; plain ones for wider spacings, and with MD_ENERGY,
-        // whose pair forces then have the value they always had (the two differ
-        // in the last bits of a pair's force factor).
-        if (energy) comp ? force(F{}, T{}, T{}) : force(F{}, T{}, F{});
-        else if (a.Q[8] > 1e-18f) comp ? force(T{}, F{}, T{}) : force(T{}, F{}, F{});
-        else comp ? force(F{}, F{}, T{}) : force(F{}, F{}, F{});
+        // default spacing, dmu = w: 1.3e-14), so that the coefficients and the
+        // powers keep the FP32 range; plain ones for wider spacings.  (By the spacing
+        // alone: forces have the same bits with and without MD_ENERGY.)
+        auto pick = [&](auto fold) {
+            if (energy) comp ? force(fold, T{}, T{}) : force(fold, T{}, F{});
+            else comp ? force(fold, F{}, T{}) : force(fold, F{}, F{});
+        };
+        if (a.Q[8] > 1e-18f) pick(T{});
+        else pick(F{});
         MD_HIP_TRY(hipGetLastError());
     }
     if (energy) return launch_reduce_partials(part1, g1, part2, g2, ev, kReduceEAM, 0.0, s);

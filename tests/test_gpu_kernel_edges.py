@@ -543,6 +543,67 @@ def test_run_ahead_stops_at_a_position_that_is_no_number(M, when):
         assert np.array_equal(a, b, equal_nan=True)
 
 
+# ---- the energy flag ------------------------------------------------------------------------
+
+def _small(M, pot, rng, cells=(6, 5, 7)):
+    """(box, positions, keyword arguments): a displaced crystal of each form."""
+    from paper_1611_00075_amd import mlp as P
+    a = inputs.fcc_lattice_constant(0.8442) if pot.startswith("lj") else inputs.CU_A0 * (1.04 if pot == "tbm" else 1.0)
+    x = _fcc(cells, a)[:-3]
+    n = len(x)
+    x = x + 0.02 * a * rng.standard_normal((n, 3))
+    if pot.startswith("lj"):
+        return np.array(cells) * a, x, dict(skin=0.3, dt=0.005, pair_fp64=pot == "lj64")
+    kw = dict(potential=pot, skin=0.6, dt=2.0, mass=inputs.CU_MASS_AMU, force_to_accel=1.0 / inputs.AMU_A2_FS2_IN_EV)
+    if pot.startswith("mlp"):
+        # narrow Gaussians: exp(-32 (dmu / width)^2) below 1e-18, no folding
+        width = P.WIDTH if pot == "mlp" else 0.13
+        kw.update(potential="mlp", mlp=M.mlp_spec(P.RC, P.MU0, P.DMU, width, np.full(16, 4.0), np.full(16, 0.2)),
+                  mlp_w=P.bf16_bits(P.init_params(5, e_mean=-3.5, w3_scale=0.3)).cuda())
+    else:
+        kw.update({"eam": dict(fs=inputs.FS_CU), "tb": dict(tb=inputs.TB_CU),
+                   "tab": dict(tab=inputs.fs_table(inputs.FS_CU)),
+                   "tbm": dict(tbm=inputs.TB2_PAIRS, types=rng.integers(0, 2, n).astype(np.int32))}[pot])
+    return np.array(cells) * a, x, kw
+
+
+FORMS = ["lj", "lj64", "eam", "tb", "tbm", "tab", "mlp", "mlp-narrow"]
+
+
+@pytest.mark.parametrize("compensate", [True, False])
+@pytest.mark.parametrize("pot", FORMS)
+def test_forces_do_not_depend_on_the_energy_flag(M, pot, compensate):
+    """MD_ENERGY also writes energy and virial: the forces are the same bits."""
+    from paper_1611_00075_amd.sim import Simulation
+    rng = np.random.default_rng(9)
+    L, x, kw = _small(M, pot, rng)
+    if pot == "lj64" and not compensate:
+        pytest.skip("FP64 sums have no compensation")
+    sim = Simulation(L, x, np.zeros_like(x), compensate=compensate, **kw)
+    out = []
+    for energy in (False, True):
+        sim.f.fill_(float("nan"))
+        sim.compute_forces(energy=energy)
+        out.append(sim.f.clone())
+    assert torch.isfinite(out[0]).all() and torch.equal(*out)
+
+
+@pytest.mark.parametrize("pot", FORMS)
+def test_reading_the_energy_does_not_change_a_trajectory(M, pot):
+    from paper_1611_00075_amd.sim import Simulation
+    rng = np.random.default_rng(9)
+    L, x, kw = _small(M, pot, rng)
+    v = (0.8 if pot.startswith("lj") else 0.003) * rng.standard_normal(x.shape)
+    sims = [Simulation(L, x, v, **kw) for _ in range(2)]
+    for look in (False, True):
+        sims[look].run(5)
+        if look:
+            sims[look].energies()
+        sims[look].run(5)
+    for name in ("x", "v", "f", "ids"):
+        assert torch.equal(*(getattr(s, name) for s in sims)), name
+
+
 # ---- tabulated functions -------------------------------------------------------------
 
 @pytest.mark.parametrize("cells", [(4, 4, 4), (13, 13, 13), (33, 32, 32), (51, 51, 51)])
