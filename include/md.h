@@ -688,7 +688,8 @@ typedef struct md_system {
  * MD_ERR_CAPACITY: a list row exceeded row_cap; row_cap_needed holds the
  * longest row, a step is in flight (phase 1); grow idx, set row_cap and call
  * again with the remaining steps (target - step).  MD_ERR_NONFINITE: a
- * position became non-finite.  With timing set, each force evaluation is
+ * position became non-finite.  After an error return nothing queued by the call
+ * writes to host_status any more.  With timing set, each force evaluation is
  * bracketed by HIP events on `stream` and their elapsed times are added to
  * force_ms / force_calls. */
 int md_run(md_system_t *sys, int64_t steps, void *stream);

@@ -45,6 +45,8 @@ __global__ void k_publish_longest(const int32_t *max_count, int32_t *host)
 
 namespace {
 
+constexpr int kNoAnswer = 1;   // a wait for the device given up: MD_ERR_HIP, with no other wait behind it
+
 // Host word of a step's flag: three words in turn, as the flags of steps k + 1 and
 // k + 2 can be posted before the host has read that of step k.  `host_dev` is the
 // device's address of md_system_t.host_status.
@@ -69,8 +71,8 @@ int read_flag(md_system_t *sys, int32_t *host_dev, int32_t tag, hipStream_t s, b
         for (uint64_t spin = 0; (got & ~3u) != want; ++spin, got = *h) {
             if ((spin & 4095) == 4095) {
                 const hipError_t e = hipStreamQuery(s);
-                if (e != hipSuccess && e != hipErrorNotReady) return MD_ERR_HIP;
-                if (std::chrono::steady_clock::now() - t0 > std::chrono::seconds(120)) return MD_ERR_HIP;
+                if (e != hipSuccess && e != hipErrorNotReady) return kNoAnswer;
+                if (std::chrono::steady_clock::now() - t0 > std::chrono::seconds(120)) return kNoAnswer;
                 std::this_thread::yield();
             }
         }
@@ -134,8 +136,8 @@ int check_build(md_system_t *sys, int32_t *host_dev, hipStream_t s)
         for (uint64_t spin = 0; h[3] < 0; ++spin) {
             if ((spin & 4095) == 4095) {
                 const hipError_t e = hipStreamQuery(s);
-                if (e != hipSuccess && e != hipErrorNotReady) return MD_ERR_HIP;
-                if (std::chrono::steady_clock::now() - t0 > std::chrono::seconds(120)) return MD_ERR_HIP;
+                if (e != hipSuccess && e != hipErrorNotReady) return kNoAnswer;
+                if (std::chrono::steady_clock::now() - t0 > std::chrono::seconds(120)) return kNoAnswer;
                 std::this_thread::yield();
             }
         }
@@ -261,7 +263,7 @@ struct ForceTimer {
 // 19.7 / 19.2, of 108,000 29.4 / 29.4, of 500,000 79.8 / 89.0; FP64 LJ of 4,000 14.4 / 9.0.
 constexpr int64_t kFuseAtoms = 65536;
 
-int run(md_system_t *sys, int64_t steps, hipStream_t s)
+static int run_steps(md_system_t *sys, int64_t steps, hipStream_t s)
 {
     const WsLayout w = ws_layout(sys->grid.n_cells, sys->n);
     const int64_t n = sys->n;
@@ -460,6 +462,18 @@ int run(md_system_t *sys, int64_t steps, hipStream_t s)
     }
     timer.collect(sys, true, 0);
     return MD_OK;
+}
+
+// The evaluations queued ahead post their steps' flags to host_status whatever
+// became of the step in flight, so a run that ends early waits for them: once it
+// has returned nothing writes to the caller's words.  (MD_ERR_CAPACITY needs no
+// wait: the longest row was posted behind all of them.)
+int run(md_system_t *sys, int64_t steps, hipStream_t s)
+{
+    const int rc = run_steps(sys, steps, s);
+    if (rc == kNoAnswer) return MD_ERR_HIP;
+    if (rc != MD_OK && rc != MD_ERR_CAPACITY) (void)hipStreamSynchronize(s);
+    return rc;
 }
 
 }  // namespace md

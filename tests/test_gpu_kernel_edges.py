@@ -543,6 +543,31 @@ def test_run_ahead_stops_at_a_position_that_is_no_number(M, when):
         assert np.array_equal(a, b, equal_nan=True)
 
 
+@pytest.mark.parametrize("pot", ["lj", "tb"])
+@pytest.mark.parametrize("when", [0, 3])
+def test_nothing_is_left_on_the_stream_after_a_position_that_is_no_number(M, pot, when):
+    """The steps queued ahead post their flags to the caller's host words, so a run
+    that ends with an error waits for them: the stream is idle at the return."""
+    import ctypes as C
+    from paper_1611_00075_amd.sim import Simulation
+    cells = (25, 25, 26)                # just below the largest system that queues two steps ahead
+    a = inputs.fcc_lattice_constant(0.8442) if pot == "lj" else inputs.CU_A0
+    x = _fcc(cells, a)
+    kw = {} if pot == "lj" else dict(potential="tb", tb=inputs.TB_CU, skin=1.0, dt=1.0, mass=inputs.CU_MASS_AMU,
+                                     force_to_accel=1.0 / inputs.AMU_A2_FS2_IN_EV)
+    sim = Simulation(np.array(cells) * a, x, np.zeros_like(x), **kw)
+    if when:
+        sim.run(when)
+    sim.v[2, 40000] = float("nan")
+    S, stream = sim._system(), torch.cuda.current_stream()
+    torch.cuda.synchronize()
+    run, handle = M.lib().md_run, stream.cuda_stream
+    rc = run(C.byref(S), 10, handle)
+    idle = stream.query()
+    assert rc == M.MD_ERR_NONFINITE and S.step == when
+    assert idle
+
+
 # ---- the energy flag ------------------------------------------------------------------------
 
 def _small(M, pot, rng, cells=(6, 5, 7)):
