@@ -573,8 +573,9 @@ int md_dd_forces(md_dd_t *dd, double *ev, int32_t flags, void *stream,
 
 /* `steps` velocity-Verlet steps (dt, accel as md_integrate) with the
  * displacement rebuild rule (skin/2) checked after every drift (the flag
- * is read back each step, while the inner atoms' first pass runs),
- * md_dd_rebuild when it fires, md_dd_forces.
+ * is read back each step, while the inner atoms' last pass runs),
+ * md_dd_rebuild when it fires, md_dd_forces.  MD_ERR_NONFINITE: a position
+ * became non-finite; f stays that of the last completed step.
  * A build that reports MD_ERR_CAPACITY returns at once with phase = 2:
  * grow the buffers and call again; the pending step is completed first. */
 int md_dd_run(md_dd_t *dd, int64_t steps, double dt, double accel,

@@ -349,7 +349,9 @@ __global__ __launch_bounds__(kBlock) void k_dd_kick_drift(int64_t n, double *x, 
         xs[slot0[b] + (i - bstart[b])] = make_uint4(to_fixed(p[0] + o[0], sc.k[0]), to_fixed(p[1] + o[1], sc.k[1]),
                                                     to_fixed(p[2] + o[2], sc.k[2]), 0u);
     }
-    if (__ballot(moved) && (threadIdx.x % kWave) == 0) status[0] = a.tag;
+    // a position that is no number (no distance then) closes the gate of the step's
+    // passes like a build
+    if (__ballot(moved || bad) && (threadIdx.x % kWave) == 0) status[0] = a.tag;
     if (__ballot(bad) && (threadIdx.x % kWave) == 0) atomicOr(&status[1], 1);
 }
 

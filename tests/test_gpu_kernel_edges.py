@@ -428,6 +428,29 @@ def test_decomposed_run_on_one_and_two_streams(M, pot):
     assert np.array_equal(out[0][1], out[1][1]) and np.array_equal(out[0][2], out[1][2])
 
 
+@pytest.mark.parametrize("pot", ["lj", "eam"])
+@pytest.mark.parametrize("when", [0, 2])
+def test_decomposed_run_keeps_its_forces_at_a_position_that_is_no_number(M, pot, when):
+    """The run ends at the drift that met the position: no pass runs on the bad
+    coordinates and f stays that of the last completed step."""
+    from paper_1611_00075_amd.dd import DomainSimulation
+    s = inputs.lj_fcc(ncell=12) if pot == "lj" else inputs.eam_cu(ncell=10)
+    kw = dict(skin=0.3, dt=0.005) if pot == "lj" else dict(
+        potential="eam", fs=inputs.FS_CU, skin=0.4, dt=2.0, mass=inputs.CU_MASS_AMU,
+        force_to_accel=1.0 / inputs.AMU_A2_FS2_IN_EV)
+    sim = DomainSimulation(s.L, s.x, s.v, p=(2, 2, 2) if pot == "eam" else (2, 1, 2), **kw)
+    if when:
+        sim.run(when)
+    f = sim.f.clone()
+    sim.v[1, 17] = float("nan")
+    with pytest.raises(M.MDError) as e:
+        sim.run(5)
+    assert e.value.code == M.MD_ERR_NONFINITE and sim.dd.phase == 0 and sim.dd.steps == when
+    torch.cuda.synchronize()
+    assert torch.equal(sim.f, f)
+    sim.close()
+
+
 # ---- native driver ---------------------------------------------------------------------------
 
 @pytest.mark.parametrize("polled", [True, False])
