@@ -752,7 +752,7 @@ __device__ __forceinline__ int32_t nb_cell(NbWaveLds &L, int64_t n, const double
     return longest;
 }
 
-// ---- boxes of fewer than 2 reach + 2 cells on an axis ----
+// ---- boxes of fewer than 2 reach + 2 cells on an axis, lengths past FP32 ----
 // One wavefront per cell (Morton rank) and part in one-wave blocks, no
 // block-wide barriers.  The atoms of the up to 27 (125) neighbouring cells are
 // contiguous runs of the sorted arrays; the wave streams them, keeps those
@@ -1228,6 +1228,16 @@ NbSplit nb_split(int64_t n, int64_t n_cells, bool small)
     return {int32_t(std::min<int64_t>(std::max<int64_t>(parts(), 1), 8)), batch};
 }
 
+// The matrix cores take squares of lengths in FP32, beside 1e30 for places that
+// hold no atom: lengths between 1e-12 and 1e12 keep the squares below that and their
+// rounding error, 1e-6 of r_list^2, above the smallest FP32 number.
+static bool fp32_lengths(const md_grid_t *grid)
+{
+    bool ok = grid->r_list >= 1e-12;
+    for (int a = 0; a < 3; ++a) ok = ok && grid->r_list <= 1e12 && grid->L[a] / grid->nc[a] <= 1e12;
+    return ok;
+}
+
 int build_neighbors(const md_grid_t *grid, int64_t n, const double *x, const int32_t *cell_start, int32_t row_cap,
                     int32_t *idx, int32_t *count, int32_t *max_count, int32_t *needed, void *ws, const WsLayout &w,
                     hipStream_t s, bool cleared)
@@ -1239,7 +1249,7 @@ int build_neighbors(const md_grid_t *grid, int64_t n, const double *x, const int
     if (n > 0) {
         const int32_t least = std::min(grid->nc[0], std::min(grid->nc[1], grid->nc[2]));
         // (rows of a million entries and more: nine slices of them pass a buffer's 32-bit range)
-        const bool small = least < 2 * grid->reach + 2 || row_cap > (1 << 20);
+        const bool small = least < 2 * grid->reach + 2 || row_cap > (1 << 20) || !fp32_lengths(grid);
         const NbSplit sp = nb_split(n, grid->n_cells, small);
         const dim3 nb(uint32_t(grid->n_cells * sp.parts));
         const int32_t *xyz = ws_ptr<int32_t>(ws, w.rank2lin), *l2r = ws_ptr<int32_t>(ws, w.lin2rank);
@@ -1272,7 +1282,7 @@ int build_neighbors_bricks(const md_grid_t *grid, int n_bricks, const int64_t *s
                            void *ws, const WsLayout &w, hipStream_t s)
 {
     const int64_t cells = grid->n_cells * n_bricks;
-    if (row_cap > (1 << 20) || cells * 8 > INT32_MAX || grid->reach != 1) {   // one by one
+    if (row_cap > (1 << 20) || cells * 8 > INT32_MAX || grid->reach != 1 || !fp32_lengths(grid)) {   // one by one
         for (int t = 0; t < n_bricks; ++t)
             if (int rc = build_neighbors(grid, slots, x + slot0[t], cell_start + t * (grid->n_cells + 1), row_cap,
                                          idx + slot0[t] * row_cap, count + slot0[t], longest + t, nullptr, ws, w, s))

@@ -293,6 +293,22 @@ def test_list_with_no_number_anywhere_in_a_batch(M, orc, L, r_list, reach, n, wh
         assert np.array_equal(np.sort(_row(idx, i, cap)[:cnt[i]]), rest[np.sort(ob[off[k]:off[k + 1]])])
 
 
+@pytest.mark.parametrize("unit", [2.0 ** -75, 2.0 ** -41, 2.0 ** -40, 2.0 ** 38, 2.0 ** 39, 2.0 ** 75])
+@pytest.mark.parametrize("reach", [1, 2])
+def test_list_in_any_unit_of_length(M, orc, unit, reach):
+    """The same system in units of length a power of two apart (every FP64
+    operation of the definition scales exactly): the same rows in the same order,
+    also where squares of lengths leave the FP32 range of the matrix cores."""
+    L = np.array((14.2, 14.6, 15.0))
+    n, cap = 900, 128
+    x = orc.wrap(inputs.random_gas(n, L, 8), L)
+    a = _lists(M, orc, x, L, 2.4, reach, cap)
+    b = _lists(M, orc, x * unit, L * unit, 2.4 * unit, reach, cap)
+    assert a[5] == b[5] <= cap and np.array_equal(a[4], b[4]) and np.array_equal(a[2] * unit, b[2])
+    for i in range(n):
+        assert np.array_equal(_row(a[3], i, cap), _row(b[3], i, cap))
+
+
 # ---- learned potential ----------------------------------------------------------------
 
 @pytest.mark.parametrize("dmu,width", [(0.2, 0.2), (0.3, 0.16)])
