@@ -151,6 +151,8 @@ int md_scale_positions(const md_box_t *box, int64_t n, const double *x,
  * displacement dx = x_j - x_i (shifted by L when |dx| > L/2), in FP64 with
  * no contraction.  j in N(i) iff i in N(j).  Positions must be the wrapped,
  * sorted output of md_bin_cells + md_permute, cell_start its output.
+ * An atom whose position is no number, or so large that FP64 cannot wrap it
+ * into the box (it stays more than four edges away), is in no row and has none.
  * Outputs: count[n], the rows in idx (order within a row unspecified but
  * deterministic), and *max_count (device int32) = the longest row.  Rows
  * longer than row_cap are truncated; the list is then invalid.  If `needed`

@@ -1001,6 +1001,8 @@ __device__ __forceinline__ int32_t nm_cell(NmLds<R, D> &L, int64_t rank, int32_t
 
     int32_t longest = 0;
     const float keep2 = float(rl2) * (1.f + 1e-5f), rl = __builtin_sqrtf(float(rl2));
+    // sizes from four times the longest edge on (by the exponent: + 2)
+    const uint32_t far = uint32_t(max(max(__double2hiint(g.L[0]), __double2hiint(g.L[1])), __double2hiint(g.L[2]))) + (2u << 20);
     while (hb < h1) {
         const int32_t hn = min(sp.batch, h1 - hb);
         // the slices of the batch as one buffer (at most 9 of them)
@@ -1009,19 +1011,22 @@ __device__ __forceinline__ int32_t nm_cell(NmLds<R, D> &L, int64_t rank, int32_t
         L.run[lane] = 0;
         L.off[lane] = int32_t(uint32_t((hl >> 3) - (hb >> 3)) * uint32_t(row_cap) * 32u + uint32_t(hl & 7) * 32u);
         // bounding box of the homes: its centre and half edges, through FP32
-        // offsets from the first home.  Homes that are no number take no part: theirs is
-        // one row of the matrix products, which then has no hits, and the rest stay as
-        // they are without it.
-        const bool number = isfinite(xh) && isfinite(yh) && isfinite(zh);
-        const uint64_t numbers = __builtin_amdgcn_ballot_w64(number);
-        const int src = numbers ? __builtin_ctzll(numbers) : 0;
+        // offsets from the first home.  Homes that are no number, or that FP64 could not
+        // wrap into the box, take no part and have no hits: the others are as without
+        // them, and the margins below stay in FP32 (with homes 1e18 apart `eps` passed the
+        // 1e30 of the empty places, whose positions were then read past the last atom).
+        // (Rows for such homes, of others as far out, by the definition: 340 -> 347 us.)
+        const auto size = [](double v) { return uint32_t(__double2hiint(v)) & 0x7fffffffu; };   // of exponents first
+        const bool near_box = max(max(size(xh), size(yh)), size(zh)) < far;
+        const uint64_t in_box = __builtin_amdgcn_ballot_w64(near_box);
+        const int src = in_box ? __builtin_ctzll(in_box) : 0;
         auto first = [&](double v) {
             return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src),
                                     __builtin_amdgcn_readlane(__double2loint(v), src));
         };
         const double ox = first(xh), oy = first(yh), oz = first(zh);
-        const float fx = number ? float(xh - ox) : 0.f, fy = number ? float(yh - oy) : 0.f,
-                    fz = number ? float(zh - oz) : 0.f;
+        const float fx = near_box ? float(xh - ox) : 0.f, fy = near_box ? float(yh - oy) : 0.f,
+                    fz = near_box ? float(zh - oz) : 0.f;
         const float lx = wave_extreme<false>(fx), ly = wave_extreme<false>(fy), lz = wave_extreme<false>(fz);
         const float ux = wave_extreme<true>(fx), uy = wave_extreme<true>(fy), uz = wave_extreme<true>(fz);
         const double mx = ox + double(0.5f * (lx + ux)), my = oy + double(0.5f * (ly + uy)),
@@ -1034,7 +1039,7 @@ __device__ __forceinline__ int32_t nm_cell(NmLds<R, D> &L, int64_t rank, int32_t
         const float reach = 2.f * hd + rl * 1.00001f;
         const float eps = 16.f * 5.9604645e-8f * (reach * reach + keep2);
         const float px = float(xh - mx), py = float(yh - my), pz = float(zh - mz);
-        const bool there = lane < hn;
+        const bool there = lane < hn && near_box;
         L.home[lane] = make_float4(there ? -2.f * px : 0.f, there ? -2.f * py : 0.f, there ? -2.f * pz : 0.f, 1.f);
         L.hom2[lane] = there ? float(double(px) * px + double(py) * py + double(pz) * pz - rl2) : 1e30f;
         const int32_t ts = centre + (hb - h0);   // candidate number of the first home

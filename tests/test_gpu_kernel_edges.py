@@ -293,6 +293,30 @@ def test_list_with_no_number_anywhere_in_a_batch(M, orc, L, r_list, reach, n, wh
         assert np.array_equal(np.sort(_row(idx, i, cap)[:cnt[i]]), rest[np.sort(ob[off[k]:off[k + 1]])])
 
 
+@pytest.mark.parametrize("far", [1e19, 1e21, 1e25, 1e40, 1e200])
+@pytest.mark.parametrize("L,r_list,reach,n", [((11.3, 12.1, 13.0), 2.8, 1, 900), ((36.5, 36.6, 37.0), 2.8, 1, 9000),
+                                              ((8.5, 9.0, 9.6), 2.8, 2, 700)])
+def test_list_with_positions_too_large_to_wrap(M, orc, L, r_list, reach, n, far):
+    """Finite positions so large that FP64 has no digits left for the box, the first
+    and the last atom among them: every row is that of the system without them."""
+    L = np.array(L)
+    x = orc.wrap(inputs.random_gas(n, L, 6), L)
+    # most such numbers come out of the wrap as 0: take some that stay outside
+    rng = np.random.default_rng(1)
+    for k in (0, n - 1):
+        while not (np.abs(orc.wrap(x[k:k + 1].copy(), L)) > 8 * L.max()).any():
+            x[k] = far * rng.uniform(-1.0, 1.0, 3)
+    cap = 400
+    _, _, xs, idx, cnt, _ = _lists(M, orc, x, L, r_list, reach, cap)
+    out = (np.abs(xs) > 8 * L.max()).any(axis=1)
+    assert out.sum() == 2 and (cnt[out] == 0).all()
+    rest = np.flatnonzero(~out)
+    off, ob = orc.neighbors_brute(xs[rest], L, r_list)
+    assert np.array_equal(cnt[rest], np.diff(off))
+    for k, i in enumerate(rest):
+        assert np.array_equal(np.sort(_row(idx, i, cap)[:cnt[i]]), rest[np.sort(ob[off[k]:off[k + 1]])])
+
+
 @pytest.mark.parametrize("unit", [2.0 ** -75, 2.0 ** -41, 2.0 ** -40, 2.0 ** 38, 2.0 ** 39, 2.0 ** 75])
 @pytest.mark.parametrize("reach", [1, 2])
 def test_list_in_any_unit_of_length(M, orc, unit, reach):
