@@ -1287,7 +1287,10 @@ int build_neighbors_bricks(const md_grid_t *grid, int n_bricks, const int64_t *s
                            void *ws, const WsLayout &w, hipStream_t s)
 {
     const int64_t cells = grid->n_cells * n_bricks;
-    if (row_cap > (1 << 20) || cells * 8 > INT32_MAX || grid->reach != 1 || !fp32_lengths(grid)) {   // one by one
+    // one by one: what the kernel does not take, and more threads than a launch can have
+    // (2^32, beyond which cells are dropped without an error; a wavefront per cell, parts
+    // only where cells are few)
+    if (row_cap > (1 << 20) || cells * kWave > int64_t(UINT32_MAX) || grid->reach != 1 || !fp32_lengths(grid)) {
         for (int t = 0; t < n_bricks; ++t)
             if (int rc = build_neighbors(grid, slots, x + slot0[t], cell_start + t * (grid->n_cells + 1), row_cap,
                                          idx + slot0[t] * row_cap, count + slot0[t], longest + t, nullptr, ws, w, s))

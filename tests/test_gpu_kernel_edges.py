@@ -769,3 +769,22 @@ def test_decomposed_build_of_uneven_bricks(M, p, L):
         assert np.abs(d - L * np.round(d / L)).max() < 1e-5
     assert sum(b[0] for b in dd.bricks()) == 4000
     dd.close()
+
+
+def test_decomposed_build_of_more_cells_than_a_launch_takes(M):
+    """Eight bricks of 8.9 M cells each (207 per axis): one launch with a wavefront
+    per cell of all bricks would be 4.5e9 threads, past the 2^32 of a launch (which
+    drops what is beyond, without an error).  A cluster around the corner that all
+    bricks share; forces as without decomposition: FP32 sums in another order, 1e-5
+    normwise."""
+    from paper_1611_00075_amd.dd import DomainSimulation
+    from paper_1611_00075_amd.sim import Simulation
+    rng = np.random.default_rng(7)
+    x = _fcc((5, 5, 5), inputs.fcc_lattice_constant(0.8442)) + 0.04 * rng.standard_normal((500, 3)) - 4.0
+    L = np.full(3, 2 * 204.5 * 2.8)
+    dd = DomainSimulation(L, x, np.zeros_like(x), p=(2, 2, 2), potential="lj", skin=0.3, dt=0.005)
+    assert dd.dd.vgrid.n_cells * 8 * 64 >= 2 ** 32
+    f = dd.forces()
+    dd.close()
+    g = Simulation(np.full(3, 60.0), x, np.zeros_like(x), skin=0.3, dt=0.005).forces()
+    assert np.linalg.norm(f - g) <= 1e-5 * np.linalg.norm(g)
