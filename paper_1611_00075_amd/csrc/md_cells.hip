@@ -197,8 +197,7 @@ struct SortState {
 // from the wrap to their new places.  One CU does it all, so the work takes over
 // from the launches at some size: with STATE beyond 4,096 atoms (a whole build in
 // md_run, sort / general: 4,000 LJ atoms 46.8 / 54 us, 6,912 51.3 / 45), without
-// beyond 8,192 (md_bin_cells and the rest of a rebuild by separate calls: 6,912 atoms
-// 109 us, 8,788 on the general path 116).
+// beyond 8,192, and for both where cells are crowded (sorts_small).
 constexpr int kSmallBlock = 1024;
 constexpr int kSmallCells = 4096;
 constexpr int64_t kSmallAtoms = 8192, kSmallState = 4096;
@@ -324,9 +323,19 @@ __global__ __launch_bounds__(kSmallBlock) void k_sort_small(int32_t n, double *x
     }
 }
 
+// One CU handles each atom and compares it with the members of its cell: about
+// n (n / n_cells + 22) comparisons' worth of work where atoms are spread evenly, which
+// grows past the general path's launches where cells are crowded.  Us of calls in a row,
+// one launch / general: 8,192 atoms 16 to a cell 24 / 19, 66 to a cell 46 / 20, 303 to a cell
+// 138 / 26, 1,024 to a cell 416 / 52; 4,096 atoms 64 to a cell 22 / 19, 152 to a cell 43 / 21.
+// Among other calls the host is behind and four launches less are worth more: rebuilds of
+// 6,912 LJ atoms 20 to a cell 105 / 117, 55 to a cell 129 / 146, 108 to a cell 215 / 221, of
+// 4,000 148 to a cell 263 / 277.  The line, at about 50 us of the one launch (8,192 atoms
+// 74 to a cell, 4,096 170), lies where a call that is waited for takes the same.
 static bool sorts_small(const md_grid_t *grid, int64_t n, int64_t most)
 {
-    return n > 0 && n <= most && grid->n_cells <= kSmallCells;
+    return n > 0 && n <= most && grid->n_cells <= kSmallCells &&
+           n * (n + 22 * grid->n_cells) <= (3 * grid->n_cells << 18);
 }
 
 int bin_cells(const md_grid_t *grid, int64_t n, double *x, int32_t *cell, int32_t *perm, int32_t *cell_start,

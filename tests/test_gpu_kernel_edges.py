@@ -743,6 +743,13 @@ def test_sort_at_the_sizes_of_its_launches(M, orc, n, nc):
     assert np.array_equal(start.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(rank, minlength=g.n_cells))]))
 
 
+@pytest.mark.parametrize("n,nc", [(8192, (5, 5, 5)), (8192, (4, 4, 4)), (8192, (2, 2, 2)), (4096, (3, 3, 3)),
+                                  (4096, (3, 3, 2)), (1000, (2, 2, 2))])
+def test_sort_of_crowded_cells(M, orc, n, nc):
+    """Either side of the line from which crowded cells leave the one-launch sort."""
+    test_sort_at_the_sizes_of_its_launches(M, orc, n, nc)
+
+
 # ---- decomposed build ----------------------------------------------------------------
 
 @pytest.mark.parametrize("p,L", [((2, 1, 1), (140.5, 70.5, 70.5)), ((2, 2, 1), (40.0, 40.0, 20.0)),
