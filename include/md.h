@@ -519,7 +519,7 @@ typedef struct md_dd {
     int64_t ghost_cap;           /* capacity of the ghost entry arrays */
     int32_t *gh_src, *gh_slot, *gh_code, *gh_src_slot;   /* device [ghost_cap] */
     double *send, *recv;         /* device [3 * ghost_cap]: message buffers of an exchange */
-    uint32_t *send_w, *recv_w;   /* device [ghost_cap]       between devices (unused on one) */
+    uint32_t *send_w, *recv_w;   /* device [ghost_cap]       between devices (not read on one: may be NULL) */
     void *vws;                   /* workspace of vgrid for slot_cap atoms (md_dd_workspace_init) */
     size_t vws_bytes;
     void *dws;                   /* scratch of md_dd_scratch_bytes */

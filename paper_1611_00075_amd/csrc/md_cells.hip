@@ -472,7 +472,6 @@ constexpr uint32_t kNbXcdChunk = 256;          // consecutive blocks (cells) an 
 struct NbCell {
     int32_t h0, h1;      // sorted atoms of the cell
     int32_t m, total;    // stencil cells, candidates in them
-    bool interior;       // no stencil cell wraps around the box
     bool nodup;          // every stencil offset is a cell of its own
 };
 
@@ -488,15 +487,12 @@ __device__ __forceinline__ NbCell nb_stencil(LDS &L, int64_t rank, const GridArg
     c.h0 = uni(cell_start[rank]);
     c.h1 = uni(cell_start[rank + 1]);
     c.m = c.total = 0;
-    c.interior = c.nodup = true;
+    c.nodup = true;
     if (c.h0 == c.h1) return c;
 
     const int32_t pk = uni(rank_xyz[rank]);   // packed cell coordinates
     const int32_t c3[3] = {pk & 1023, (pk >> 10) & 1023, pk >> 20};
-    for (int a = 0; a < 3; ++a) {
-        c.interior &= (g.nc[a] >= 2 * g.reach + 2) && (c3[a] - g.reach >= 0) && (c3[a] + g.reach < g.nc[a]);
-        c.nodup &= g.nc[a] >= 2 * g.reach + 1;
-    }
+    for (int a = 0; a < 3; ++a) c.nodup &= g.nc[a] >= 2 * g.reach + 1;
     int32_t ax[5], ay[5], az[5], ix[5], iy[5], iz[5];
     const int mx = stencil_axis(c3[0], g.nc[0], g.reach, ax, ix);
     const int my = stencil_axis(c3[1], g.nc[1], g.reach, ay, iy);
@@ -1143,26 +1139,6 @@ __device__ __forceinline__ int32_t nm_cell(NmLds<R, D> &L, int64_t rank, int32_t
     return longest;
 }
 
-// One wavefront per cell and part in one-wave blocks, as k_neighbors_small,
-// for boxes of at least 2 reach + 2 cells on every axis: a stencil cell is
-// then one periodic image and no home is further than half a box from a
-// candidate in that image, so the minimum image of the definition is the
-// image of the stencil (it differs only for pairs beyond half a box, which
-// neither counts).  Same rows, same order, bit for bit.
-//
-// What bounds it: instruction issue.  The FP64 test of every home against 64
-// candidates took 8 FP64 operations, two compares and the broadcast of a home
-// from LDS, ~27 vector instructions with the compaction; the squares now come
-// from the matrix cores beside the vector unit (one compare per four homes
-// and 16 candidates, a quarter of an instruction each for the check against
-// rounding), ~10 vector and ~11 scalar instructions.  The build of 1.23 M
-// atoms with voids went from 452 to 315 us (stripped variants: set-up 40,
-// reading and box test 75, squares and rows 195, of which stores 30), of 1 M
-// copper atoms at 5.4 A from 334 to 231 us, of 4,000 atoms from 60 to 33 us.
-// Slower: 128 or 256 candidates read at once (LDS for fewer waves; 490 against
-// 515 and 581 us for the whole rebuild of the void system), the next 64
-// requested ahead (the registers cost more than the wait), 4, 5, 7 or 8 waves
-// per SIMD.
 // One system, or the bricks of a decomposition (Bricks) in one launch: the cells of
 // brick t follow those of brick t - 1, its atoms start at slot0[t] of the arrays, and
 // it has an offsets array and a longest row of its own.
@@ -1198,6 +1174,28 @@ __device__ __forceinline__ void nm_kernel(NmLds<R, D> &L, uint32_t blk, int64_t 
                max_count);
 }
 
+// One wavefront per cell and part in one-wave blocks, as k_neighbors_small,
+// for boxes of at least 2 reach + 2 cells on every axis: a stencil cell is
+// then one periodic image and no home is further than half a box from a
+// candidate in that image, so the minimum image of the definition is the
+// image of the stencil (it differs only for pairs beyond half a box, which
+// neither counts).  Same rows, same order, bit for bit.
+//
+// What bounds it: the addressers (busy 0.79 of the cycles on the porous system, 0.86 on
+// copper) and the vector unit (issue 0.62, 0.67) together, neither of them full, and a
+// chain of trips to memory per cell.  The FP64 test of every home against 64
+// candidates took 8 FP64 operations, two compares and the broadcast of a home
+// from LDS, ~27 vector instructions with the compaction; the squares now come
+// from the matrix cores beside the vector unit (one compare per four homes
+// and 16 candidates, a quarter of an instruction each for the check against
+// rounding), ~10 vector and ~11 scalar instructions.  The build of 1.23 M
+// atoms with voids went from 452 to 297 us (variants stripped at 315: set-up 40,
+// reading and box test 75, squares and rows 195, of which stores 30), of 1 M
+// copper atoms at 5.4 A from 334 to 223 us.
+// Slower: 128 or 256 candidates read at once (LDS for fewer waves; 490 against
+// 515 and 581 us for the whole rebuild of the void system), the next 64
+// requested ahead (the registers cost more than the wait), 4, 5, 7 or 8 waves
+// per SIMD.
 template <int R, class B>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(6)))
 void k_neighbors(int64_t n, const double *__restrict__ x, GridArgs g, double rl2, NbSplit sp,

@@ -216,7 +216,7 @@ inline T *ws_ptr(void *ws, size_t off) { return reinterpret_cast<T *>(static_cas
 
 // ---- launchers implemented in the kernel translation units ----
 int launch_fill_i32(int32_t *p, int64_t count, int32_t value, hipStream_t s);
-// out[0] = 0, out[k+1] = sum_{q<=k} in[q], k < m.  OutT = int32_t or int64_t.
+// out[0] = 0, out[k+1] = sum_{q<=k} in[q], k < m.
 int launch_scan_i32_to_i32(const int32_t *in, int32_t *out, int64_t m, int64_t *bsum, hipStream_t s);
 // `sets` scans of m values each, set k at in + k stride, out + k stride (stride > m).
 int launch_scan_sets(const int32_t *in, int32_t *out, int64_t m, int sets, int64_t stride, int64_t *bsum,

@@ -650,13 +650,6 @@ static void dispatch_lj32(bool e, bool c, uint32_t gb, hipStream_t s, int64_t n,
     else launch_lj32<TPA, CUBIC, false, false>(gb, s, n, q, l, p, f, part, sp, tab, adv);
 }
 
-// blocks of a launch over the slices from sp.slice0 to the one holding atom n-1
-static uint32_t blocks_span(int64_t n, const Span &sp)
-{
-    const int64_t slices = (n + kSlice - 1) / kSlice - int64_t(sp.slice0);
-    return slices > 0 ? uint32_t((slices + kBlock / kWave - 1) / (kBlock / kWave)) : 0u;
-}
-
 static LJ32 lj_constants(const md_box_t *box, const md_lj_t *lj, Gate gate)
 {
     const double two32 = 4294967296.0;

@@ -1,7 +1,7 @@
 // Domain decomposition on one device: bricks with ghost layers, the halo
-// exchange and the inner/outer split of the force step (Sec. 2.1's hybrid algorithm; its steps pack boundary coordinates,
-// send, receive, compute forces inside the domain, wait, compute forces
-// across the boundary, wait).
+// exchange and the inner/outer split of the force step (Sec. 2.1's hybrid
+// algorithm; its steps pack boundary coordinates, send, receive, compute forces
+// inside the domain, wait, compute forces across the boundary, wait).
 //
 // Directions: d = (ex + 1) + 3 (ey + 1) + 9 (ez + 1) for e in {-1, 0, 1}^3,
 // d = 13 the brick itself.  A ghost entry of target brick t with direction

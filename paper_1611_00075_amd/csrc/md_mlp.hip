@@ -142,9 +142,6 @@ __device__ __forceinline__ float sigm(float a)
     return __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-a * kLog2e));
 }
 
-// feature carried by K slot (g, j) of K-step s
-__device__ __forceinline__ int kslot(int s, int g, int j) { return 32 * s + (j < 4 ? 4 * g + j : 12 + 4 * g + j); }
-
 struct MlpArgs {
     float ax, ay, az;       // L_a / 2^32: displacement per scaled unit (A)
     float rc2;              // rc^2
@@ -699,8 +696,8 @@ __device__ __forceinline__ void basis_sums(const MlpArgs &p, float t, const floa
 // then reads its own row back; the quarters of row r lie permuted by r / 2,
 // so that 8 lanes reading the same quarter touch all 32 banks.  With the folded
 // sums 1 M copper atoms (43 M pairs) went from 285 to 262 us (one pair a lane
-// at a time; two 268, three 318); the vector unit and the addressers are then
-// both busy 87 % of the time.
+// at a time; two 268, three 318).  The addressers are then busy 0.91 of the cycles,
+// the vector unit issues in two thirds of them.
 //
 // MD_ENERGY writes the same forces, to the bit, and its virial sums the pair
 // factors of the Gaussians themselves: the two sets of sums differ by FP32 rounding,

@@ -70,10 +70,6 @@ class DomainSimulation:
         self.count = torch.zeros(self.slot_cap, dtype=torch.int32, device=d)
         self.idx = torch.empty(self.slot_cap * self.row_cap, dtype=torch.int32, device=d)
         self.gh = torch.zeros((4, gc), dtype=torch.int32, device=d)
-        self.send = torch.empty(3 * gc, dtype=torch.float64, device=d)
-        self.recv = torch.empty(3 * gc, dtype=torch.float64, device=d)
-        self.send_w = torch.empty(gc, dtype=torch.int32, device=d)
-        self.recv_w = torch.empty(gc, dtype=torch.int32, device=d)
         self.vws = torch.empty(M.md_workspace_bytes(dd.vgrid, self.slot_cap), dtype=torch.uint8, device=d)
         self._bind()
         self.dws = torch.empty(M.md_dd_scratch_bytes(dd), dtype=torch.uint8, device=d)
@@ -89,7 +85,7 @@ class DomainSimulation:
         dd.xs, dd.count, dd.idx = p(self.xs), p(self.count), p(self.idx)
         dd.gh_src, dd.gh_slot, dd.gh_code, dd.gh_src_slot = (p(self.gh[0]), p(self.gh[1]), p(self.gh[2]),
                                                              p(self.gh[3]))
-        dd.send, dd.recv, dd.send_w, dd.recv_w = p(self.send), p(self.recv), p(self.send_w), p(self.recv_w)
+        dd.send = dd.recv = dd.send_w = dd.recv_w = None    # (messages between devices)
         dd.vws, dd.vws_bytes = p(self.vws), self.vws.numel()
         dws = getattr(self, "dws", None)
         dd.dws, dd.dws_bytes = (p(dws), dws.numel()) if dws is not None else (None, 0)
