@@ -1181,8 +1181,8 @@ __device__ __forceinline__ void nm_kernel(NmLds<R, D> &L, uint32_t blk, int64_t 
 // image of the stencil (it differs only for pairs beyond half a box, which
 // neither counts).  Same rows, same order, bit for bit.
 //
-// What bounds it: the addressers (busy 0.79 of the cycles on the porous system, 0.86 on
-// copper) and the vector unit (issue 0.62, 0.67) together, neither of them full, and a
+// What bounds it: the addressers (busy 0.78 of the cycles on the porous system, 0.86 on
+// copper) and the vector unit (issue 0.62, 0.68) together, neither of them full, and a
 // chain of trips to memory per cell.  The FP64 test of every home against 64
 // candidates took 8 FP64 operations, two compares and the broadcast of a home
 // from LDS, ~27 vector instructions with the compaction; the squares now come

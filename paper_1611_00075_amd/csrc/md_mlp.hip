@@ -696,8 +696,8 @@ __device__ __forceinline__ void basis_sums(const MlpArgs &p, float t, const floa
 // then reads its own row back; the quarters of row r lie permuted by r / 2,
 // so that 8 lanes reading the same quarter touch all 32 banks.  With the folded
 // sums 1 M copper atoms (43 M pairs) went from 285 to 262 us (one pair a lane
-// at a time; two 268, three 318).  The addressers are then busy 0.91 of the cycles,
-// the vector unit issues in two thirds of them.
+// at a time; two 268, three 318).  The addressers are then busy 0.93 of the cycles,
+// the vector unit issues in 0.69 of them.
 //
 // MD_ENERGY writes the same forces, to the bit, and its virial sums the pair
 // factors of the Gaussians themselves: the two sets of sums differ by FP32 rounding,
