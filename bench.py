@@ -613,7 +613,7 @@ def main():
             leg = leg_stats(s8.n, 200, {"seconds": secs, "force_ms": [f8], "rebuilds": builds})
             leg.update({
                 "bricks": list(pdd), "ghosts": int(sim8.dd.n_ghost),
-                "note": "forces: local coordinates into the brick frames, halo pack/copy/unpack on a second "
+                "note": "forces: local coordinates into the brick frames, halo exchange on a second "
                         "stream beside the inner atoms' passes, outer atoms after; F' of ghosts exchanged "
                         "between the passes; the step loop reads the rebuild flag back every step; forces_ms "
                         "from 20 back-to-back force steps",
